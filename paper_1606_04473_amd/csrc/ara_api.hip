@@ -1005,6 +1005,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     // with the compact value array
     const bool use_xcd = use_parts && tu.pass_variant != 1;
     const SplitPass split(t, tu);
+    const bool use_stream = use_xcd && split.stream;
     // several layers run as one persistent rank-based launch with pass_variant
     // 1; with the streaming (default) or XCD-affine pass they run one launch
     // sequence per layer, which ARA_GRAPH captures and replays as a whole
@@ -1102,7 +1103,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             }
             hipError_t le = hipSuccess;
             for (int i = 0; i < n_layers && le == hipSuccess; ++i) {
-                le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, go, t->parts.P, gp, s);
+                le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, nullptr, t->parts.P, gp, !split.stream, s);
                 if (le == hipSuccess) le = split.pass(L[i], gp, gx, s);
                 if (le == hipSuccess) le = split.combine(L[i], dL + i, gx, out + L[i].out_offset, nullptr, s);
             }
@@ -1201,8 +1202,8 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
         if (!literal) {
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
-                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, static_cast<double*>(obuf.p), t->parts.P,
-                                               pbuf.p, s),
+                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, nullptr, t->parts.P, pbuf.p,
+                                               !use_stream || stride_buf != nullptr, s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[i], static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1336,7 +1337,8 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
         if (!literal) {
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
-                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[l], nullptr, o_buf, t->parts.P, p_buf, s),
+                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[l], nullptr, nullptr, t->parts.P, p_buf,
+                                               !(use_xcd && split.stream), s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[l], o_buf, tu, s), "fold");
@@ -1544,7 +1546,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
             free_graph(ge);
             return hip_fail(e, "graph capture");
         }
-        hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, go, t->parts.P, gp, s);
+        hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, nullptr, t->parts.P, gp, !split.stream, s);
         if (le == hipSuccess) le = split.pass(L, gp, gx, s);
         if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, s);
         if (le == hipSuccess)
@@ -1642,8 +1644,7 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
         HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
         if (t->sparse.chunk_off) {
             // the forward's fold from the sparse pool (o, images and superblock counts)
-            HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, static_cast<double*>(obuf.p), t->parts.P,
-                                           pbuf.p, s),
+            HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, t->parts.P, pbuf.p, false, s),
                     "fold");
         } else {
             HIP_TRY(ara::launch_fold(t->elts, t->C, L, static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1735,7 +1736,8 @@ ara_status ara_debug_read(ara_tables* t, const ara_layer* layer, int32_t what, v
         HIP_TRY(buf.alloc(o_bytes + p_bytes, s), "scratch for the fold");
         double* o = static_cast<double*>(buf.p);
         void* pbuf = static_cast<char*>(buf.p) + o_bytes;
-        HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, o, t->parts.P, pbuf, s), "fold and part images");
+        HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, o, t->parts.P, pbuf, true, s),
+                "fold and part images");
         if (what == ARA_DEBUG_OCCURRENCE) {
             src = o;
             bytes = sizeof(double) * t->C;
@@ -1806,7 +1808,7 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     char* base = static_cast<char*>(lease.b->p);
     uint64_t* probe = reinterpret_cast<uint64_t*>(base + o_bytes + p_bytes);
     double* out = dev ? nets : reinterpret_cast<double*>(base + o_bytes + p_bytes + w_bytes);
-    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, reinterpret_cast<double*>(base), P, base + o_bytes, s),
+    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base + o_bytes, true, s),
             "fold and part images");
     HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base + o_bytes, P, t->C, probe, L, out, t->n_cu, s),
             "net-loss kernel");

@@ -107,6 +107,7 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // host-side state
@@ -162,6 +163,8 @@ constexpr int kImgRank16 = (1 << kImgShift) / 128;
 constexpr int kImgBase32 = (1 << kImgShift) / 4096;
 constexpr int64_t kImgPartBytes = int64_t(kImgWords) * 8 + int64_t(kImgRank16) * 2 + int64_t(kImgBase32) * 4;
 double* part_compact_values(void* part_scratch, int P);
+// each superblock's nonzero o(E) packed in event order at the start of its 4096-value slot
+double* part_stage_values(void* part_scratch, int P);
 // nonzero o(E) per 4096-event superblock, P * 64 of them, after launch_fold_parts
 uint32_t* part_superblock_counts(void* part_scratch, int P);
 
@@ -449,10 +452,13 @@ void free_part_layout(PartLayout* L, hipStream_t s);
 int64_t part_scratch_bytes(int64_t C, int P);
 int part_count(int64_t C);   // catalogue parts of the part images
 hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hipStream_t s, bool with_ranks);
-// the fold fused with the part images, then ranks and the compact array; with
-// L_dev the terms are read from device memory (for graph replays), else from L
+// the fold fused with the part images and the superblocks' packed values; with
+// L_dev the terms are read from device memory (for graph replays), else from L.
+// The dense o is written when `o` is given; the global ranks and the compact
+// array only with `compact`: the streaming pass and the gradient histograms read
+// the packed superblocks
 hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L, const LayerArgs* L_dev, double* o,
-                             int P, void* scratch, hipStream_t s);
+                             int P, void* scratch, bool compact, hipStream_t s);
 // the XCD-affine pass writes per-part partial sums; the combine merges them
 hipError_t launch_xcd_pass(const PartLayout& lay, int64_t N, int64_t C, const LayerArgs& L, void* part_scratch,
                            double* partials, int n_cu, hipStream_t s);

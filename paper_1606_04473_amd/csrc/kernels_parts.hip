@@ -394,7 +394,7 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
         const int word = w * 16 + k;
         const int64_t E = eb + k * 64;
         const double v = apply_terms(ys[word * 64 + lane], L.occR, L.occL);
-        if (E < C) o[E] = v;
+        if (o && E < C) o[E] = v;
         const uint64_t bits = __ballot(E < C && v != 0.0);
         vk[k] = v;
         bk[k] = bits;
@@ -1567,6 +1567,7 @@ PartScratch carve_parts(void* scratch, int P) {
 }  // namespace
 
 double* part_compact_values(void* part_scratch, int P) { return carve_parts(part_scratch, P).compact; }
+double* part_stage_values(void* part_scratch, int P) { return carve_parts(part_scratch, P).stage; }
 uint32_t* part_superblock_counts(void* part_scratch, int P) { return carve_parts(part_scratch, P).sb_count; }
 
 // ---------------------------------------------------------------------------
@@ -1957,7 +1958,7 @@ hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hi
 }
 
 hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L, const LayerArgs* L_dev, double* o,
-                             int P, void* scratch, hipStream_t s) {
+                             int P, void* scratch, bool compact, hipStream_t s) {
     PartScratch ps = carve_parts(scratch, P);
     const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
     hipError_t e;
@@ -1967,7 +1968,7 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
     else
         hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L, o,
                            ps.img, ps.sb_count, ps.stage);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess || !compact) return e;
     hipLaunchKernelGGL(compact_stage_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, ps.stage,
                        ps.sb_count, ps.img, ps.compact);
     return hipGetLastError();

@@ -47,6 +47,8 @@ namespace {
 constexpr int kQSize = 1 << kStreamShift;       // catalogue events per stream part
 constexpr int kChunkIds = 8;                    // 16-bit IDs per 16-byte load
 constexpr int64_t kStreamPad = 512;             // readable 0xFFFF IDs after the stream
+constexpr int kSuperEvents = 4096;              // events per superblock of the part images
+constexpr int kPartSuper = kQSize / kSuperEvents;
 
 __device__ __forceinline__ uint64_t stream_lanemask_lt() {
     const int lane = threadIdx.x & 63;
@@ -271,8 +273,8 @@ struct StreamPassArgs {
     const uint32_t* gstart;
     const uint16_t* gend;
     const uint8_t* img;             // part images of the 2^18-event parts
-    const double* compact;          // nonzero o(E) in rank order
-    int64_t C;
+    const uint32_t* sb_count;       // nonzero o(E) of each 4096-event superblock
+    const double* stage;            // [superblock][4096]: its nonzero o(E), packed in event order
     int P;
     int G;
     int64_t NG;
@@ -347,14 +349,17 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
     // minus one, then the byte map (a byte's offset from the map's start is its
     // event's part-relative ID; that offset fits the LDS instructions' constant
     // field, so a lookup costs no address arithmetic), the 16 hit queues, and
-    // then the forward's copy of as many of the part's nonzero o(E) as fit,
-    // followed by one 0.0 that the drain's idle slots read, or the backward's
-    // counters
+    // then the forward's copy of the part's nonzero o(E), followed by one 0.0
+    // that the drain's idle slots read, or the backward's counters.  A part
+    // with more nonzero events than LDS holds keeps those of each superblock's
+    // first ones (kSbCap, kSbCnt); its ranks are positions in the superblocks'
+    // 4096-value slots of the stage, so the others are read there directly
     constexpr uint32_t kMapOff = (kQSize / 128) * 4;
     constexpr uint32_t kQueueOff = kMapOff + kQSize;
     constexpr uint32_t kValOff = kQueueOff + 16 * kQ * 2;
     constexpr int kCap = static_cast<int>((160 * 1024 - kValOff) / 8) - 1;
     constexpr int kCnt = static_cast<int>((160 * 1024 - kValOff) / 4);
+    constexpr uint32_t kSbCap = kCap / kPartSuper, kSbCnt = kCnt / kPartSuper;
     static_assert(kValOff % 16 == 0 && kCap > 0 && kMapOff < 65536, "LDS layout");
     constexpr uint32_t kLdsBytes = kAdj ? kValOff + kCnt * 4 : kValOff + (kCap + 1) * 8;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
@@ -383,14 +388,18 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
     // the backward's counters to W_mean once every wave is done with the part,
     // in the byte map's event order; the part before the first has none
     int prev_pq = -1;
+    bool prev_fits = true;
     auto flush_counts = [&]() {
         __syncthreads();
         const int64_t ebase = static_cast<int64_t>(prev_pq) << kStreamShift;
         for (int e = threadIdx.x; e < kQSize; e += blockDim.x) {
             const uint32_t b = map[e];
             if (!b) continue;
-            const uint32_t r = bases[e >> 7] + b;
-            if (r >= static_cast<uint32_t>(kCnt)) continue;
+            uint32_t r = bases[e >> 7] + b;
+            if (!prev_fits) {
+                if ((r & (kSuperEvents - 1)) >= kSbCnt) continue;
+                r = (r / kSuperEvents) * kSbCnt + (r & (kSuperEvents - 1));
+            }
             const uint32_t cv = cnt[r];
             if (cv) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e]),
                               static_cast<unsigned long long>(cv));
@@ -406,70 +415,99 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         const int64_t ga = a.g_lo + (it - static_cast<int64_t>(pq) * NGr);
         const int64_t gb = a.g_lo + (seg_end - static_cast<int64_t>(pq) * NGr);
         it = seg_end;
-        // ---- the LDS image of stream part pq, from the part image of the
-        // 2^18-event part that holds it
-        const int ip = pq >> 2, is = pq & 3;
-        const uint8_t* gimg = a.img + static_cast<int64_t>(ip) * kImgPartBytes;
-        const uint64_t* gbm = reinterpret_cast<const uint64_t*>(gimg) + is * (kImgWords / 4);
-        const uint16_t* gr16 = reinterpret_cast<const uint16_t*>(gimg + int64_t(kImgWords) * 8) + is * (kImgRank16 / 4);
-        const uint32_t* gb32 = reinterpret_cast<const uint32_t*>(gimg + int64_t(kImgWords) * 8 + int64_t(kImgRank16) * 2) +
-                               is * (kImgBase32 / 4);
-        const uint32_t g0 = gb32[0];                // global rank of the part's first nonzero event
-        // the part's nonzero count, from the rank of the next quarter's first
-        // superblock (the next image part's, after the last quarter; unknown
-        // after the catalogue's last image part): when every rank fits the LDS
-        // copy of the values (the counters) the drain skips the L2 fallback
-        // (the global atomics)
-        const int64_t n_img = (a.C + (int64_t(1) << kImgShift) - 1) >> kImgShift;
-        bool fits = false;
-        if (is < 3 || ip + 1 < n_img) {
-            const uint32_t g_next = is < 3 ? gb32[kImgBase32 / 4]
-                                           : *reinterpret_cast<const uint32_t*>(
-                                                 gimg + kImgPartBytes + int64_t(kImgWords) * 8 + int64_t(kImgRank16) * 2);
-            fits = g_next - g0 <= static_cast<uint32_t>(kAdj ? kCnt : kCap);
+        // ---- the LDS image of stream part pq, from its quarter of the part
+        // image of a 2^18-event part: bitmap, ranks of 128-event blocks inside
+        // their superblock, and the counts and packed losses of its 16
+        // superblocks.  Every global load of the bitmap, the ranks and the
+        // counts, and then eight losses per lane, are in flight together.
+        const uint8_t* gimg = a.img + static_cast<int64_t>(pq >> 2) * kImgPartBytes;
+        const u64x2* gbm = reinterpret_cast<const u64x2*>(gimg) + (pq & 3) * (kImgWords / 8);
+        const uint16_t* gr16 =
+            reinterpret_cast<const uint16_t*>(gimg + int64_t(kImgWords) * 8) + (pq & 3) * (kImgRank16 / 4);
+        const double* gstage = a.stage + static_cast<int64_t>(pq) * kQSize;
+        uint32_t sb_n = a.sb_count[static_cast<int64_t>(pq) * kPartSuper + (lane & (kPartSuper - 1))];
+        u64x2 words[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) words[k] = gbm[(k * 1024 + static_cast<int>(threadIdx.x)) >> 3];
+        const uint32_t r16 = threadIdx.x < kQSize / 128 ? gr16[threadIdx.x] : 0u;
+        // ranks of the superblocks' first nonzero events (lane i: superblock i % 16)
+        uint32_t sb_end = sb_n;
+#pragma unroll
+        for (int off = 1; off < kPartSuper; off <<= 1) {
+            const uint32_t v = static_cast<uint32_t>(__shfl_up(static_cast<int>(sb_end), off, kPartSuper));
+            if ((lane & (kPartSuper - 1)) >= off) sb_end += v;
         }
+        const uint32_t sb_start = sb_end - sb_n;
+        const uint32_t n_vals = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_end), kPartSuper - 1));
+        // when every rank fits the LDS copy of the losses (the counters) the
+        // drain skips the L2 fallback (the global atomics)
+        const bool fits = n_vals <= static_cast<uint32_t>(kAdj ? kCnt : kCap);
         __syncthreads();
-        {
-            // byte map: thread i covers events 64i .. 64i+63 (one bitmap word)
-            const int i = threadIdx.x;
-            const uint64_t w = gbm[i];
-            uint32_t run = (i & 1) ? static_cast<uint32_t>(__popcll(gbm[i - 1])) : 0u;
-            uint32_t* dst = reinterpret_cast<uint32_t*>(map + i * 64);
+        // byte map, 16 events per thread and round, one 16-byte store each: per
+        // four events the bits spread to bytes, their inclusive prefix sum, plus
+        // the count of the block's earlier events in every byte
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                uint32_t pk = 0;
+        for (int k = 0; k < 4; ++k) {
+            const int i = k * 1024 + static_cast<int>(threadIdx.x);
+            const uint32_t sh = (i & 3) * 16;
+            const uint64_t w = (i & 4) ? words[k].y : words[k].x;
+            uint32_t before = static_cast<uint32_t>(__popcll(w & ((1ull << sh) - 1ull)));
+            if (i & 4) before += static_cast<uint32_t>(__popcll(words[k].x));
+            const uint32_t bits = static_cast<uint32_t>(w >> sh) & 0xFFFFu;
+            uint32_t run = before * 0x01010101u;
+            u32x4 out;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t bit = static_cast<uint32_t>(w >> (4 * k + b)) & 1u;
-                    run += bit;
-                    pk |= (bit ? run : 0u) << (8 * b);
-                }
-                dst[k] = pk;
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t one = (((bits >> (4 * b)) & 15u) * 0x00204081u) & 0x01010101u;
+                const uint32_t two = one + (one << 8);
+                const uint32_t sum = two + (two << 16) + run;
+                out[b] = sum & ((one << 8) - one);
+                run = __builtin_amdgcn_perm(sum, sum, 0x03030303u);
             }
+            reinterpret_cast<u32x4*>(map)[i] = out;
         }
-        if (threadIdx.x < kQSize / 128) {
-            const int k = threadIdx.x;
-            bases[k] = gb32[k >> 5] + gr16[k] - g0 - 1u;
+        if (threadIdx.x < kQSize / 128) {           // two superblocks of 32 blocks per wave
+            const int sb = 2 * wv + (lane >> 5);
+            const uint32_t s0 = static_cast<uint32_t>(__shfl(static_cast<int>(sb_start), sb));
+            bases[threadIdx.x] = (fits ? s0 : static_cast<uint32_t>(sb) * kSuperEvents) + r16 - 1u;
         }
         if constexpr (kAdj) {
             for (int k = threadIdx.x; k < kCnt; k += blockDim.x) cnt[k] = 0u;
         } else {
-            for (int k = threadIdx.x; k <= kCap; k += blockDim.x) {
-                const int64_t gk = static_cast<int64_t>(g0) + k;
-                vals[k] = k < kCap && gk < a.C ? a.compact[gk] : 0.0;
+            // wave w copies superblock w's losses
+            const uint32_t n0 =
+                fits ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_start), wv)) : wv * kSbCap;
+            const uint32_t nw = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_n), wv));
+            const uint32_t take = fits || nw < kSbCap ? nw : kSbCap;
+            const double* src = gstage + wv * kSuperEvents;
+            for (uint32_t j0 = 0; j0 < take; j0 += 64 * 8) {
+                double v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const uint32_t j = j0 + k * 64 + lane;
+                    v[k] = src[j < take ? j : 0u];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const uint32_t j = j0 + k * 64 + lane;
+                    if (j < take) vals[n0 + j] = v[k];
+                }
             }
+            if (threadIdx.x == 0) vals[kCap] = 0.0;
         }
         __syncthreads();
 
         // ---- this wave's groups [wa, wb) of the part
         const int64_t n = gb - ga;
         const int64_t wa = ga + wv * n / 16, wb = ga + (wv + 1) * n / 16;
-        if constexpr (kAdj) prev_pq = pq;
+        if constexpr (kAdj) {
+            prev_pq = pq;
+            prev_fits = fits;
+        }
         if (wa >= wb) continue;
         const uint16_t* ids = a.ids + a.part_base[pq];
         const uint32_t* gs = gstart_all + static_cast<int64_t>(pq) * (a.NG + 1);
         const uint16_t* ge = a.gend + static_cast<int64_t>(pq) * a.NG * kStreamGroupSlots;
-        const double* gcompact = a.compact + g0;
         double* out_hi = a.part_hi + static_cast<int64_t>(pq) * count;
         float* out_lo = a.part_lo + static_cast<int64_t>(pq) * count;
         const int64_t ebase = static_cast<int64_t>(pq) << kStreamShift;   // catalogue ID of the part's event 0
@@ -528,6 +566,9 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
             // plus the byte, which is 1 + the rank inside the block
             return bases[e >> 7] + map[e];
         };
+        // !fits: an entry's index inside its superblock, and the LDS slot of index i < per
+        auto sb_index = [&](uint32_t rk) -> uint32_t { return rk & (kSuperEvents - 1); };
+        auto sb_slot = [&](uint32_t rk, uint32_t i, uint32_t per) -> uint32_t { return rk / kSuperEvents * per + i; };
         auto drain = [&]() {
             constexpr int kR = 4;
             int lo = __shfl(qs, lane), hi = __shfl(qs, (lane + 1) & 63);
@@ -571,8 +612,9 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2) {
                             if (j + r2 >= hi) continue;
-                            if (rk[r2] < static_cast<uint32_t>(kCnt))
-                                atomicAdd(&cnt[rk[r2]], 1u);
+                            const uint32_t i = sb_index(rk[r2]);
+                            if (i < kSbCnt)
+                                atomicAdd(&cnt[sb_slot(rk[r2], i, kSbCnt)], 1u);
                             else
                                 atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
                         }
@@ -625,18 +667,18 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
                     }
 #pragma unroll
                     for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
-                    // the LDS copy; ranks past it (parts with more nonzero losses
-                    // than LDS holds) then read the value from L2
+                    // the LDS copy; entries past it then read the value from L2
                     bool spill = false;
 #pragma unroll
                     for (int r2 = 0; r2 < kR; ++r2) {
-                        v[r2] = vals[valid[r2] ? min(rk[r2], static_cast<uint32_t>(kCap - 1)) : kCap];
-                        spill |= valid[r2] && rk[r2] >= static_cast<uint32_t>(kCap);
+                        const uint32_t i = sb_index(rk[r2]);
+                        v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                        spill |= valid[r2] && i >= kSbCap;
                     }
                     if (__ballot(spill)) {
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2)
-                            if (valid[r2] && rk[r2] >= static_cast<uint32_t>(kCap)) v[r2] = gcompact[rk[r2]];
+                            if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
                     }
 #pragma unroll
                     for (int r2 = 0; r2 < kR; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
@@ -966,15 +1008,15 @@ int64_t stream_partials_bytes(const StreamLayout& lay, int64_t trials) {
 
 namespace {
 
-StreamPassArgs pass_args(const StreamLayout& lay, int64_t C, const LayerArgs& L, void* part_scratch, int n_img_parts) {
+StreamPassArgs pass_args(const StreamLayout& lay, const LayerArgs& L, void* part_scratch, int n_img_parts) {
     StreamPassArgs a{};
     a.ids = lay.ids;
     a.part_base = lay.part_base;
     a.gstart = lay.gstart;
     a.gend = lay.gend;
     a.img = static_cast<const uint8_t*>(part_scratch);
-    a.compact = part_compact_values(part_scratch, n_img_parts);
-    a.C = C;
+    a.sb_count = part_superblock_counts(part_scratch, n_img_parts);
+    a.stage = part_stage_values(part_scratch, n_img_parts);
     a.P = lay.P;
     a.G = lay.G;
     a.NG = lay.NG;
@@ -1002,7 +1044,7 @@ hipError_t launch_stream_pass(const StreamLayout& lay, int64_t C, const LayerArg
                               int n_img_parts, void* partials, int n_cu, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    StreamPassArgs a = pass_args(lay, C, L, part_scratch, n_img_parts);
+    StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
     a.part_hi = static_cast<double*>(partials);
     a.part_lo = reinterpret_cast<float*>(a.part_hi + static_cast<int64_t>(lay.P) * L.trial_count);
     hipLaunchKernelGGL(stream_pass_kernel<false>, dim3(pass_grid(n_cu)), dim3(1024), 0, s, a, StreamAdjArgs{},
@@ -1021,7 +1063,7 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, int64_t C, const Layer
                                  hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    const StreamPassArgs a = pass_args(lay, C, L, part_scratch, n_img_parts);
+    const StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
     const int64_t n_slots = (a.g_hi - a.g_lo) * 64;
     if (n_slots > scratch_bytes) return hipErrorInvalidValue;
     StreamAdjArgs adj{};
