@@ -571,6 +571,13 @@ hipError_t upload_plan(ara::HostStage& st, const BatchPlan& b, const ara::Batche
     return hipEventRecord(st.done, s);
 }
 
+// estimated share of the catalogue with a loss in the layer, from its table
+// count and the pool's mean nonzero losses per table
+double layer_density(const ara_tables* t, const ara::LayerArgs& L) {
+    const double cells = static_cast<double>(t->n_pool) * static_cast<double>(t->C);
+    return cells > 0.0 ? -std::expm1(-L.J * static_cast<double>(t->sparse.nnz) / cells) : 0.0;
+}
+
 // The passes that write per-(part, trial) partial sums for a merge: the
 // streaming pass over the 16-bit part-major copy (default), or the XCD-affine
 // pass over the 32-bit partitioned copy (pass_variant 2, or tables without
@@ -585,7 +592,9 @@ struct SplitPass {
                       : sizeof(double) * 2 * static_cast<size_t>(t->parts.P) * n;
     }
     hipError_t pass(const ara::LayerArgs& L, void* part_scratch, void* partials, hipStream_t s) const {
-        if (stream) return ara::launch_stream_pass(t->stream, t->C, L, part_scratch, t->parts.P, partials, t->n_cu, s);
+        if (stream)
+            return ara::launch_stream_pass(t->stream, layer_density(t, L), L, part_scratch, t->parts.P, partials,
+                                           t->n_cu, s);
         return ara::launch_xcd_pass(t->parts, t->n_trials, t->C, L, part_scratch, static_cast<double*>(partials),
                                     t->n_cu, s);
     }
@@ -1654,7 +1663,8 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
     }
     HIP_TRY(ara::launch_adjoint(t->offsets, t->ids, t->elts, t->C, L, t->ck.S, t->ck.ylt, m, scratch.p, gm, gt,
                                 t->n_cu, s, use_parts ? &t->parts : nullptr, pbuf.p, t->n_trials,
-                                t->sparse.chunk_off ? &t->sparse : nullptr, use_stream ? &t->stream : nullptr),
+                                t->sparse.chunk_off ? &t->sparse : nullptr, use_stream ? &t->stream : nullptr,
+                                layer_density(t, L)),
             "adjoint kernels");
     if (!dev) {
         std::vector<double> h(2 * P);

@@ -197,7 +197,8 @@ int64_t stream_partials_bytes(const StreamLayout& lay, int64_t trials);
 // the streaming pass: reads the part images and compact values that
 // launch_fold_parts wrote to part_scratch (n_img_parts 2^18-event parts), writes
 // per-(stream part, trial) partial sums; the combine merges them in part order
-hipError_t launch_stream_pass(const StreamLayout& lay, int64_t C, const LayerArgs& L, void* part_scratch,
+// `density`: the layer's estimated share of catalogue events with a loss (chooses among variants only)
+hipError_t launch_stream_pass(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                               int n_img_parts, void* partials, int n_cu, hipStream_t s);
 hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, const LayerArgs* L_dev,
                                  const void* partials, double* ylt, double* S, hipStream_t s);
@@ -208,7 +209,7 @@ struct TailStats;
 // checkpointed forward's, tail its order statistics on the device.  scratch
 // holds stream_adjoint_scratch_bytes(L.trial_count) bytes.
 int64_t stream_adjoint_scratch_bytes(int64_t trials);
-hipError_t launch_stream_adjoint(const StreamLayout& lay, int64_t C, const LayerArgs& L, void* part_scratch,
+hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                                  int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
                                  void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
                                  hipStream_t s);
@@ -517,6 +518,6 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                           int64_t C, const LayerArgs& L, const double* S, const double* ylt,
                           int64_t m, void* scratch, double* d_grad_mean, double* d_grad_tvar,
                           int n_cu, hipStream_t s, const PartLayout* parts, void* part_scratch,
-                          int64_t n_trials_total, const SparsePool* sp, const StreamLayout* stream);
+                          int64_t n_trials_total, const SparsePool* sp, const StreamLayout* stream, double density);
 
 }  // namespace ara

@@ -425,7 +425,7 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                           const LayerArgs& L, const double* S, const double* ylt, int64_t m, void* scratch,
                           double* d_grad_mean, double* d_grad_tvar, int n_cu, hipStream_t s,
                           const PartLayout* parts, void* part_scratch, int64_t n_trials_total,
-                          const SparsePool* sp, const StreamLayout* stream) {
+                          const SparsePool* sp, const StreamLayout* stream, double density) {
     AdjScratch a = carve(scratch, C, L.trial_count);
     hipError_t err;
     const int64_t n = L.trial_count;
@@ -445,7 +445,7 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                            a.acc);
         if ((err = hipGetLastError()) != hipSuccess) return err;
         if (stream && stream->P > 0 && (stream->P - 1) / 4 < parts->P) {
-            if ((err = launch_stream_adjoint(*stream, C, L, part_scratch, parts->P, S, ylt, a.tail, a.cls,
+            if ((err = launch_stream_adjoint(*stream, density, L, part_scratch, parts->P, S, ylt, a.tail, a.cls,
                                              a.cls_bytes, a.w_mean, a.w_tvar, n_cu, s)) != hipSuccess)
                 return err;
         } else if ((err = launch_part_adjoint(*parts, n_trials_total, L, part_scratch, S, ylt, a.tail, a.w_mean,

@@ -286,6 +286,9 @@ struct StreamPassArgs {
     int n_xcd;
 };
 
+// The drain's lanes: one per trial, or several where that fills the wave
+enum class PassMode { plain, spread };
+
 // bit if the lane's condition holds, else 0: one select on the compare's lane
 // mask, so the compare that also guards the lane's queue append is not redone
 // in inverted form
@@ -334,9 +337,10 @@ struct StreamAdjArgs {
 // gstart_all is a.gstart again, as a restrict-qualified parameter: its loads at
 // wave-uniform addresses then go through the scalar unit, so a group's range
 // never waits on the vector loads in flight
-template <bool kAdj>
+template <bool kAdj, PassMode kMode>
 __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, StreamAdjArgs adj,
                                                            const uint32_t* __restrict__ gstart_all) {
+    constexpr bool kSpread = kMode != PassMode::plain;
     constexpr int kU = 2;                                     // 16-byte loads per lane per batch
     constexpr uint32_t kBatch = 64 * kChunkIds * kU;          // IDs per batch
     constexpr int kQ = 64 * kChunkIds;                        // 16-bit queue entries per wave: one load's IDs
@@ -569,6 +573,11 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         // !fits: an entry's index inside its superblock, and the LDS slot of index i < per
         auto sb_index = [&](uint32_t rk) -> uint32_t { return rk & (kSuperEvents - 1); };
         auto sb_slot = [&](uint32_t rk, uint32_t i, uint32_t per) -> uint32_t { return rk / kSuperEvents * per + i; };
+        // With many hits of few trials in the queue (long trials over few
+        // parts, dense layers) one lane per trial leaves most lanes idle: then
+        // 2^s lanes take a trial's entries in turn and their sums are merged,
+        // s as large as the 64 lanes allow with at least four entries a lane on
+        // average.  s depends on the data alone.
         auto drain = [&]() {
             constexpr int kR = 4;
             int lo = __shfl(qs, lane), hi = __shfl(qs, (lane + 1) & 63);
@@ -577,6 +586,86 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
             if (lane >= G) hi = lo;                 // lanes past the group's trials
             if constexpr (kAdj) {
                 if (!(cls & 1u)) hi = lo;           // outside the aggregate band: no weight
+            }
+            bool spread_done = false;
+            if constexpr (kSpread) {
+            const uint64_t act = __ballot(hi > lo);
+            const int i0 = act ? __builtin_ctzll(act) : 0;
+            const int n_act = act ? 64 - __builtin_clzll(act) - i0 : 1;
+            const int lg_act = n_act > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(n_act - 1)) : 0;
+            const int lg_qn = qn > 0 ? 31 - __builtin_clz(static_cast<uint32_t>(qn)) : 0;
+            const int s = (lg_qn - 2 < 6 ? lg_qn - 2 : 6) - lg_act;
+            if (s > 0) {
+                const int per = 1 << s, slot = lane >> s, sub = lane & (per - 1);
+                const int from = (i0 + slot) & 63;
+                const int mlo = __shfl(lo, from), mhi = __shfl(hi, from);
+                const int jend = slot < n_act ? mhi : mlo;
+                if constexpr (kAdj) {
+                    const uint32_t mcls = static_cast<uint32_t>(__shfl(static_cast<int>(cls), from));
+                    const unsigned long long wt = (mcls & 6u)
+                        ? static_cast<unsigned long long>((mcls & 2u) ? ts.c_eq : ts.m - ts.c_gt) : 0ull;
+                    for (int j = mlo + sub; j < jend; j += kR * per) {
+                        uint32_t e[kR], rk[kR];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2 * per];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) {
+                            if (j + r2 * per >= jend) continue;
+                            const uint32_t i = sb_index(rk[r2]);
+                            if (fits || i < kSbCnt)
+                                atomicAdd(&cnt[fits ? rk[r2] : sb_slot(rk[r2], i, kSbCnt)], 1u);
+                            else
+                                atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
+                            if (wt) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + e[r2]]), wt);
+                        }
+                    }
+                } else {
+                    double h = 0.0, l = 0.0;
+                    for (int j = mlo + sub; j < jend; j += kR * per) {
+                        // entries past the trial's last read whatever LDS follows
+                        // (inside the allocation), then the 0.0 slot
+                        uint32_t e[kR], rk[kR];
+                        bool valid[kR];
+                        double v[kR];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) {
+                            valid[r2] = j + r2 * per < jend;
+                            e[r2] = q[j + r2 * per];
+                        }
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                        if (fits) {
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) v[r2] = vals[valid[r2] ? rk[r2] : kCap];
+                        } else {
+                            bool spill = false;
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) {
+                                const uint32_t i = sb_index(rk[r2]);
+                                v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                                spill |= valid[r2] && i >= kSbCap;
+                            }
+                            if (__ballot(spill)) {
+#pragma unroll
+                                for (int r2 = 0; r2 < kR; ++r2)
+                                    if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
+                            }
+                        }
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) dd_add(h, l, v[r2]);
+                    }
+                    for (int off = per >> 1; off >= 1; off >>= 1) dd_merge(h, l, shfl_xor_f64(h, off), shfl_xor_f64(l, off));
+                    const int back = ((lane - i0) << s) & 63;
+                    const double th_hi = shfl_f64(h, back), th_lo = shfl_f64(l, back);
+                    if (lane >= i0 && lane < i0 + n_act) dd_merge(acc_hi, acc_lo, th_hi, th_lo);
+                }
+                spread_done = true;
+            }
+            }
+            if (spread_done) {
+            } else if constexpr (kAdj) {
                 if (fits) {
                     // every rank has its LDS counter: whole steps unchecked,
                     // then the last one to three entries (their queue reads,
@@ -1038,17 +1127,36 @@ uint32_t pass_grid(int n_cu) {
     return static_cast<uint32_t>(grid);
 }
 
+// Where a trial has many hits in a part the queue fills before its group's
+// end and holds few trials; the drain then spreads them over the lanes.  The
+// code for it costs the pass 2-3% where it finds nothing to do (its size: 0.594
+// against 0.58 ms per 1e9 events at 4.4 hits per trial and part), and at 17 and
+// 52 hits it takes the pass from 23 to 17 us (1e6 events) and from 357 to 150 us
+// (5e7), so the line lies at 12.
+constexpr double kSpreadHits = 12.0;
+
+template <bool kAdj>
+void launch_pass(const StreamLayout& lay, StreamPassArgs& a, const StreamAdjArgs& adj, double density, int n_cu,
+                 hipStream_t s) {
+    const uint32_t grid = pass_grid(n_cu);
+    const double hits = density * static_cast<double>(lay.length) / (static_cast<double>(lay.P) * lay.NG * lay.G);
+    const dim3 g(grid), t(1024);
+    if (hits > kSpreadHits)
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::spread>), g, t, 0, s, a, adj, a.gstart);
+    else
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::plain>), g, t, 0, s, a, adj, a.gstart);
+}
+
 }  // namespace
 
-hipError_t launch_stream_pass(const StreamLayout& lay, int64_t C, const LayerArgs& L, void* part_scratch,
+hipError_t launch_stream_pass(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                               int n_img_parts, void* partials, int n_cu, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
     StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
     a.part_hi = static_cast<double*>(partials);
     a.part_lo = reinterpret_cast<float*>(a.part_hi + static_cast<int64_t>(lay.P) * L.trial_count);
-    hipLaunchKernelGGL(stream_pass_kernel<false>, dim3(pass_grid(n_cu)), dim3(1024), 0, s, a, StreamAdjArgs{},
-                       a.gstart);
+    launch_pass<false>(lay, a, StreamAdjArgs{}, density, n_cu, s);
     return hipGetLastError();
 }
 
@@ -1057,13 +1165,13 @@ int64_t stream_adjoint_scratch_bytes(int64_t trials) {
     return 4 * (trials > 0 ? trials : 0) + 256;
 }
 
-hipError_t launch_stream_adjoint(const StreamLayout& lay, int64_t C, const LayerArgs& L, void* part_scratch,
+hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                                  int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
                                  void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
                                  hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    const StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
+    StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
     const int64_t n_slots = (a.g_hi - a.g_lo) * 64;
     if (n_slots > scratch_bytes) return hipErrorInvalidValue;
     StreamAdjArgs adj{};
@@ -1077,7 +1185,7 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, int64_t C, const Layer
                        L.aggL, a.t_lo, a.t_hi, a.G, a.g_lo, n_slots, static_cast<uint8_t*>(scratch));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(stream_pass_kernel<true>, dim3(pass_grid(n_cu)), dim3(1024), 0, s, a, adj, a.gstart);
+    launch_pass<true>(lay, a, adj, density, n_cu, s);
     return hipGetLastError();
 }
 
