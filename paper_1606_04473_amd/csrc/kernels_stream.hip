@@ -277,6 +277,7 @@ struct StreamPassArgs {
     const double* stage;            // [superblock][4096]: its nonzero o(E), packed in event order
     int P;
     int G;
+    int K;                          // kSplit: units per group
     int64_t NG;
     int64_t g_lo, g_hi;             // groups holding the layer's trials
     int64_t t_lo, t_hi;
@@ -286,8 +287,10 @@ struct StreamPassArgs {
     int n_xcd;
 };
 
-// The drain's lanes: one per trial, or several where that fills the wave
-enum class PassMode { plain, spread };
+// How a wave takes its work: whole groups with one lane per trial in the
+// drain, the same with several lanes per trial where that fills the wave, or
+// (with those) single units of a group's trials
+enum class PassMode { plain, spread, split };
 
 // bit if the lane's condition holds, else 0: one select on the compare's lane
 // mask, so the compare that also guards the lane's queue append is not redone
@@ -340,7 +343,7 @@ struct StreamAdjArgs {
 template <bool kAdj, PassMode kMode>
 __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, StreamAdjArgs adj,
                                                            const uint32_t* __restrict__ gstart_all) {
-    constexpr bool kSpread = kMode != PassMode::plain;
+    constexpr bool kSplit = kMode == PassMode::split, kSpread = kMode != PassMode::plain;
     constexpr int kU = 2;                                     // 16-byte loads per lane per batch
     constexpr uint32_t kBatch = 64 * kChunkIds * kU;          // IDs per batch
     constexpr int kQ = 64 * kChunkIds;                        // 16-bit queue entries per wave: one load's IDs
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
 
     // the (part, group) work list, part-major; workgroup b runs on XCD b % n_xcd,
     // and each XCD takes a contiguous share of the list
-    const int64_t NGr = a.g_hi - a.g_lo;
+    const int64_t NGr = (a.g_hi - a.g_lo) * (kSplit ? a.K : 1);
     const int64_t n_items = static_cast<int64_t>(a.P) * NGr;
     const int64_t n_wg = gridDim.x;
     const int64_t per_x = n_wg / a.n_xcd;
@@ -416,8 +419,9 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         }
         const int pq = static_cast<int>(it / NGr);
         const int64_t seg_end = min(it_end, static_cast<int64_t>(pq + 1) * NGr);
-        const int64_t ga = a.g_lo + (it - static_cast<int64_t>(pq) * NGr);
-        const int64_t gb = a.g_lo + (seg_end - static_cast<int64_t>(pq) * NGr);
+        // groups of the part, or with kSplit units: K per group from a.g_lo's first
+        const int64_t ga = (kSplit ? 0 : a.g_lo) + (it - static_cast<int64_t>(pq) * NGr);
+        const int64_t gb = (kSplit ? 0 : a.g_lo) + (seg_end - static_cast<int64_t>(pq) * NGr);
         it = seg_end;
         // ---- the LDS image of stream part pq, from its quarter of the part
         // image of a 2^18-event part: bitmap, ranks of 128-event blocks inside
@@ -527,7 +531,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         auto group_class = [&](int64_t gg) -> uint32_t { return adj.cls[(gg - a.g_lo) * 64 + lane]; };
         // a group's IDs run from its start to the next group's start (its end
         // rounded up to the 8-ID chunk: the same chunks)
-        int64_t g = wa;
+        int64_t g = kSplit ? a.g_lo + wa / a.K : wa;
         uint32_t rs = gs[g];
         uint32_t re = gs[g + 1];
         uint32_t B = starts(rs, group_ends(g));
@@ -535,6 +539,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         uint32_t cls = 0, next_cls = 0;
         if constexpr (kAdj) cls = group_class(g);
         uint32_t c = rs;                            // first ID of the batch (a multiple of 8)
+        int tl = 0, th = G;                         // the trials of the group (of the unit) that this wave sums
         int qs = kInf;                              // lane i: queue index of trial i's first hit
         int qn = 0;                                 // queue entries
         double acc_hi = 0.0, acc_lo = 0.0;
@@ -583,7 +588,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
             int lo = __shfl(qs, lane), hi = __shfl(qs, (lane + 1) & 63);
             lo = lo < 0 ? 0 : (lo > qn ? qn : lo);
             hi = hi < 0 ? 0 : (hi > qn ? qn : hi);
-            if (lane >= G) hi = lo;                 // lanes past the group's trials
+            if (lane >= th || (kSplit && lane < tl)) hi = lo;   // lanes without a trial here
             if constexpr (kAdj) {
                 if (!(cls & 1u)) hi = lo;           // outside the aggregate band: no weight
             }
@@ -907,6 +912,45 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         // two register buffers in turn, so the next batch's loads stay in
         // flight while this one is tested
         u32x4 bufA[kU], bufB[kU];
+        if constexpr (kSplit) {
+            // one unit after the other: trials [tl, th) of a group, from the
+            // 16-byte chunk that holds the first one's first ID
+            for (int64_t u = wa; u < wb; ++u) {
+                g = a.g_lo + u / a.K;
+                const int k = static_cast<int>(u % a.K);
+                tl = G * k / a.K;
+                th = G * (k + 1) / a.K;
+                if (u > wa && k == 0) {
+                    B = starts(gs[g], group_ends(g));
+                    if constexpr (kAdj) cls = group_class(g);
+                }
+                c = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), tl)) & ~7u;
+                re = (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), th)) + 7u) & ~7u;
+                qs = kInf;
+                load_batch(c, re, bufA);
+                while (c < re) {
+                    load_batch(c + kBatch, re, bufB);
+                    process(bufA);
+                    c += kBatch;
+                    if (c >= re) break;
+                    load_batch(c + kBatch, re, bufA);
+                    process(bufB);
+                    c += kBatch;
+                }
+                drain();
+                if constexpr (!kAdj) {
+                    const int64_t t = g * G + lane;
+                    if (lane >= tl && lane < th && t >= a.t_lo && t < a.t_hi) {
+                        const double hi = acc_hi + acc_lo;      // renormalised: |lo| <= ulp(hi) / 2
+                        out_hi[t - a.t_lo] = hi;
+                        out_lo[t - a.t_lo] = static_cast<float>(acc_lo - (hi - acc_hi));
+                    }
+                    acc_hi = 0.0;
+                    acc_lo = 0.0;
+                }
+            }
+            continue;
+        }
         load_batch(c, re, bufA);
         for (;;) {
             load_next(bufB);
@@ -1127,6 +1171,28 @@ uint32_t pass_grid(int n_cu) {
     return static_cast<uint32_t>(grid);
 }
 
+// Units per group.  One wave streams a whole group unless the request has so
+// few groups that most waves would have none: then each group's trials are
+// split into K units.  K minimises the batches that the busiest wave
+// processes, a unit of a split group counting half a batch more (it starts
+// with its own load of the trial ends and has no batch in flight before).
+// 1e6 events in 320 groups: the pass 17 -> 10 us with K = 6.
+int units_per_group(const StreamLayout& lay, int64_t groups, int64_t waves) {
+    const double ids = static_cast<double>(lay.length) / (static_cast<double>(lay.P) * lay.NG);
+    int best_k = 1;
+    double best = 1e300;
+    for (int k = 1; k <= lay.G && (k == 1 || ids >= 128.0 * k); ++k) {
+        const double units = std::ceil(static_cast<double>(groups) * lay.P * k / static_cast<double>(waves));
+        const double cost = units * (std::ceil(ids / (1024.0 * k) + 0.25) + (k > 1 ? 0.5 : 0.0));
+        if (cost < best - 1e-9) {
+            best = cost;
+            best_k = k;
+        }
+        if (units > 8.0) break;                     // enough groups for every wave
+    }
+    return best_k;
+}
+
 // Where a trial has many hits in a part the queue fills before its group's
 // end and holds few trials; the drain then spreads them over the lanes.  The
 // code for it costs the pass 2-3% where it finds nothing to do (its size: 0.594
@@ -1139,9 +1205,12 @@ template <bool kAdj>
 void launch_pass(const StreamLayout& lay, StreamPassArgs& a, const StreamAdjArgs& adj, double density, int n_cu,
                  hipStream_t s) {
     const uint32_t grid = pass_grid(n_cu);
+    a.K = units_per_group(lay, a.g_hi - a.g_lo, int64_t(grid) * 16);
     const double hits = density * static_cast<double>(lay.length) / (static_cast<double>(lay.P) * lay.NG * lay.G);
     const dim3 g(grid), t(1024);
-    if (hits > kSpreadHits)
+    if (a.K > 1)
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::split>), g, t, 0, s, a, adj, a.gstart);
+    else if (hits > kSpreadHits)
         hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::spread>), g, t, 0, s, a, adj, a.gstart);
     else
         hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::plain>), g, t, 0, s, a, adj, a.gstart);

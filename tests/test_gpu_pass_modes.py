@@ -39,8 +39,8 @@ def test_long_dense_trials(ara, n_trials, lam, C, J, nnz):
     idx = np.arange(J, dtype=np.int32)
     plain = Layer(idx, 3.0e3, 4.0e5, 0.0, np.inf, 0, n_trials)
     _, S = oracle.run_layer(yet, pool, plain)
-    mid = float(np.median(S)) * 0.999
-    layer = Layer(idx, 3.0e3, 4.0e5, mid, float(np.max(S)) * 0.95 - mid, 0, n_trials)
+    low = float(np.median(S)) * 0.9
+    layer = Layer(idx, 3.0e3, 4.0e5, low, float(np.max(S)) * 0.97 - low, 0, n_trials)
     ref, S = oracle.run_layer(yet, pool, layer)
     spec = ara.LayerSpec.from_layer(layer, pool, n_trials)
     tables = ara.create_tables(yet.offsets, yet.ids, pool.losses)
