@@ -32,6 +32,7 @@ def ara():
     (1_000, 300, (1 << 16) + 3, 5, 20_000),
     (97, 3_000, 420_000, 9, 30_000),
     (1, 5_000, 40_000, 4, 12_000),
+    (200, 1_500, 30_000, 4, 9_000),
 ])
 def test_long_dense_trials(ara, n_trials, lam, C, J, nnz):
     yet = make_yet(n_trials, lam, C, seed=n_trials + lam)
@@ -44,6 +45,7 @@ def test_long_dense_trials(ara, n_trials, lam, C, J, nnz):
     ref, S = oracle.run_layer(yet, pool, layer)
     spec = ara.LayerSpec.from_layer(layer, pool, n_trials)
     tables = ara.create_tables(yet.offsets, yet.ids, pool.losses)
+    assert tables.layout()["stream_parts"] > 0
     ylt = ara.run_layers(tables, [spec], flags=ara.ARA_CHECKPOINT_S)
     assert np.all(np.abs(ara.read_checkpoints(tables, 0) - S) <= 1e-12 * S)
     assert np.all(np.abs(ylt - ref) <= 1e-12 * S)
