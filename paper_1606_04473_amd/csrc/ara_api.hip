@@ -1045,6 +1045,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     } obuf{base}, pbuf{base ? base + o_bytes : nullptr}, xbuf{base ? base + o_bytes + p_bytes : nullptr};
     double* S_buf = nullptr;
     double* stride_buf = nullptr;
+    PoolBuffer probe;                   // the stride checkpoints' lookup tables
     std::unique_lock<std::mutex> ck_lock(t->mu, std::defer_lock);
     if (ckpt) {
         ck_lock.lock();
@@ -1066,6 +1067,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             HIP_TRY(ara::launch_fill(ck.stride, t->n_events / ara::kStride + 1, std::nan(""), s), "fill");
             stride_buf = ck.stride;
             ck.has_stride = true;
+            if (use_xcd) HIP_TRY(probe.alloc(static_cast<size_t>(ara::probe_table_bytes(t->C)), s), "scratch for probe words");
         }
         S_buf = ck.S;
     }
@@ -1112,7 +1114,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             }
             hipError_t le = hipSuccess;
             for (int i = 0; i < n_layers && le == hipSuccess; ++i) {
-                le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, nullptr, t->parts.P, gp, !split.stream, s);
+                le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
                 if (le == hipSuccess) le = split.pass(L[i], gp, gx, s);
                 if (le == hipSuccess) le = split.combine(L[i], dL + i, gx, out + L[i].out_offset, nullptr, s);
             }
@@ -1211,8 +1213,8 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
         if (!literal) {
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
-                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, nullptr, t->parts.P, pbuf.p,
-                                               !use_stream || stride_buf != nullptr, s),
+                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, nullptr, t->parts.P, pbuf.p, !use_stream,
+                                               static_cast<uint64_t*>(probe.p), s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[i], static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1226,8 +1228,6 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             HIP_TRY(split.combine(L[i], nullptr, xbuf.p, a.ylt, a.S, s), "partial sums merge");
             kc.done();
             if (stride_buf) {
-                PoolBuffer probe;
-                HIP_TRY(probe.alloc(static_cast<size_t>(ara::probe_table_bytes(t->C)), s), "scratch for probe words");
                 HIP_TRY(ara::launch_stride_checkpoints(t->offsets, t->ids, pbuf.p, t->parts.P, t->C,
                                                        static_cast<uint64_t*>(probe.p), L[i], stride_buf, t->n_cu, s),
                         "stride checkpoints");
@@ -1347,7 +1347,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
                 HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[l], nullptr, nullptr, t->parts.P, p_buf,
-                                               !(use_xcd && split.stream), s),
+                                               !(use_xcd && split.stream), nullptr, s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[l], o_buf, tu, s), "fold");
@@ -1555,7 +1555,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
             free_graph(ge);
             return hip_fail(e, "graph capture");
         }
-        hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, nullptr, t->parts.P, gp, !split.stream, s);
+        hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
         if (le == hipSuccess) le = split.pass(L, gp, gx, s);
         if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, s);
         if (le == hipSuccess)
@@ -1653,7 +1653,7 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
         HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
         if (t->sparse.chunk_off) {
             // the forward's fold from the sparse pool (o, images and superblock counts)
-            HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, t->parts.P, pbuf.p, false, s),
+            HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, t->parts.P, pbuf.p, false, nullptr, s),
                     "fold");
         } else {
             HIP_TRY(ara::launch_fold(t->elts, t->C, L, static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1746,7 +1746,7 @@ ara_status ara_debug_read(ara_tables* t, const ara_layer* layer, int32_t what, v
         HIP_TRY(buf.alloc(o_bytes + p_bytes, s), "scratch for the fold");
         double* o = static_cast<double*>(buf.p);
         void* pbuf = static_cast<char*>(buf.p) + o_bytes;
-        HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, o, t->parts.P, pbuf, true, s),
+        HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, o, t->parts.P, pbuf, true, nullptr, s),
                 "fold and part images");
         if (what == ARA_DEBUG_OCCURRENCE) {
             src = o;
@@ -1818,7 +1818,7 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     char* base = static_cast<char*>(lease.b->p);
     uint64_t* probe = reinterpret_cast<uint64_t*>(base + o_bytes + p_bytes);
     double* out = dev ? nets : reinterpret_cast<double*>(base + o_bytes + p_bytes + w_bytes);
-    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base + o_bytes, true, s),
+    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base + o_bytes, false, probe, s),
             "fold and part images");
     HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base + o_bytes, P, t->C, probe, L, out, t->n_cu, s),
             "net-loss kernel");

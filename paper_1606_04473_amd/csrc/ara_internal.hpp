@@ -430,17 +430,17 @@ struct PortfolioSumArgs {
 };
 hipError_t launch_portfolio_sum(const PortfolioSumArgs& a, int n_cu, hipStream_t s);
 // per-event net losses of a layer's trials, in time order, reading o(E)
-// through the part images and compact values that launch_fold_parts wrote to
-// part_scratch (P = catalogue parts)
-hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P,
-                             int64_t C, uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s);
+// through the probe tables and the superblocks' packed values that
+// launch_fold_parts wrote to `probe` and part_scratch (P = catalogue parts)
+hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P, int64_t C,
+                             uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s);
 // the forward's stride checkpoints in the same time-ordered pass: slot b of
 // `stride` receives the running total S of the trial that owns global event
 // 64b + 63, after that event (slots outside the layer's trials untouched)
 hipError_t launch_stride_checkpoints(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P,
                                      int64_t C, uint64_t* probe, const LayerArgs& L, double* stride, int n_cu,
                                      hipStream_t s);
-int64_t probe_table_bytes(int64_t C);   // scratch for launch_event_nets' probe words
+int64_t probe_table_bytes(int64_t C);   // scratch for the time-ordered passes' probe words and coarse map
 hipError_t launch_debug_lookups(const int64_t* offsets, const uint32_t* ids, const double* elts,
                                 int64_t C, const LayerArgs& L, int64_t trial, uint32_t* ids_out,
                                 double* losses_out, hipStream_t s);
@@ -457,9 +457,10 @@ hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hi
 // L_dev the terms are read from device memory (for graph replays), else from L.
 // The dense o is written when `o` is given; the global ranks and the compact
 // array only with `compact`: the streaming pass and the gradient histograms read
-// the packed superblocks
+// the packed superblocks; the time-ordered passes' probe tables with `probe`
+// (probe_table_bytes(C))
 hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L, const LayerArgs* L_dev, double* o,
-                             int P, void* scratch, bool compact, hipStream_t s);
+                             int P, void* scratch, bool compact, uint64_t* probe, hipStream_t s);
 // the XCD-affine pass writes per-part partial sums; the combine merges them
 hipError_t launch_xcd_pass(const PartLayout& lay, int64_t N, int64_t C, const LayerArgs& L, void* part_scratch,
                            double* partials, int n_cu, hipStream_t s);

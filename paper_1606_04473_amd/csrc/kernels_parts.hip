@@ -22,8 +22,6 @@
 //    result does not depend on scheduling.
 #include <vector>
 
-#include <type_traits>
-
 #include "ara_internal.hpp"
 
 namespace ara {
@@ -296,11 +294,38 @@ __global__ __launch_bounds__(256) void part_image_kernel(const double* __restric
 // superblock count are written, and the superblock's nonzero o, packed in
 // event order, go to its 4096-value slot of `stage` (compact_stage_kernel
 // moves them to their global ranks).
+struct FoldOut {
+    double* o;                      // dense o, or null
+    uint8_t* img;
+    uint32_t* sb_count;
+    double* stage;
+    // the time-ordered passes' lookup tables, or null: a probe word per 32
+    // events (bits of o != 0 in the low half, the stage index of the word's
+    // first nonzero event in the high half) and a coarse map of one bit per
+    // 2^cshift events (null also where one of its words spans superblocks)
+    uint64_t* probe;
+    uint32_t* coarse;
+    int cshift;
+};
+
+// OR of each pair of adjacent bits, packed into the low half
+__device__ __forceinline__ uint32_t or_pairs(uint32_t x) {
+    x = (x | (x >> 1)) & 0x55555555u;
+    x = (x | (x >> 1)) & 0x33333333u;
+    x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+    x = (x | (x >> 4)) & 0x00FF00FFu;
+    return (x | (x >> 8)) & 0x0000FFFFu;
+}
+
 __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C, const LayerArgs& L,
-                                                double* __restrict__ o, uint8_t* __restrict__ img,
-                                                uint32_t* __restrict__ sb_count, double* __restrict__ stage) {
+                                                const FoldOut& out) {
+    double* __restrict__ o = out.o;
+    uint8_t* __restrict__ img = out.img;
+    uint32_t* __restrict__ sb_count = out.sb_count;
+    double* __restrict__ stage = out.stage;
     constexpr int kStage = 2048;                    // entries staged in LDS
     __shared__ uint32_t wc[64];
+    __shared__ uint64_t wb[64];
     __shared__ double ys[kSuper];
     __shared__ double sval[kStage];
     __shared__ uint16_t sev[kStage];
@@ -400,10 +425,43 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
         bk[k] = bits;
         if (lane == 0) {
             bm[ls * 64 + word] = bits;
+            wb[word] = bits;
             wc[word] = __popcll(bits);
         }
     }
     __syncthreads();
+    if (out.probe && w == 1) {
+        uint32_t before = wc[lane];                 // nonzero events before this lane's word
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(before, off, kWave);
+            if (lane >= off) before += v;
+        }
+        before += static_cast<uint32_t>(e0) - wc[lane];
+        const uint64_t bits = wb[lane];
+        const int64_t i = (e0 >> 5) + 2 * lane;
+        const int64_t n_words = (C + 31) >> 5;
+        const uint32_t low = static_cast<uint32_t>(bits);
+        if (i < n_words) out.probe[i] = (static_cast<uint64_t>(before) << 32) | low;
+        if (i + 1 < n_words)
+            out.probe[i + 1] = (static_cast<uint64_t>(before + __popc(low)) << 32) | static_cast<uint32_t>(bits >> 32);
+    }
+    if (out.coarse && static_cast<int>(threadIdx.x) < (128 >> out.cshift)) {
+        // coarse word i of the superblock covers 2^cshift of its 32-event pieces
+        const int s = out.cshift;
+        const uint32_t* piece = reinterpret_cast<const uint32_t*>(wb) + (threadIdx.x << s);
+        uint32_t m = 0;
+        for (int j = 0; j < (1 << s); ++j) {
+            uint32_t x = piece[j];
+            if (s <= 5) {
+                for (int k = 0; k < s; ++k) x = or_pairs(x);
+                m |= x << (j * (32 >> s));
+            } else {
+                m |= (x ? 1u : 0u) << (j >> (s - 5));
+            }
+        }
+        const int64_t i = (e0 >> (5 + s)) + threadIdx.x;
+        if ((i << (5 + s)) < C) out.coarse[i] = m;
+    }
     {   // the nonzero o packed in event order: the wave's first word starts
         // after the counts of the words before it
         uint32_t at = 0;
@@ -429,16 +487,12 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
 
 // terms as kernel arguments (eager runs) or read from device memory (graph
 // replays, whose terms may change between replays)
-__global__ __launch_bounds__(256) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L,
-                                                         double* __restrict__ o, uint8_t* __restrict__ img,
-                                                         uint32_t* __restrict__ sb_count, double* __restrict__ stage) {
-    fold_image_body(sp, C, L, o, img, sb_count, stage);
+__global__ __launch_bounds__(256) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
+    fold_image_body(sp, C, L, out);
 }
 __global__ __launch_bounds__(256) void fold_image_dev_kernel(SparsePool sp, int64_t C,
-                                                             const LayerArgs* __restrict__ L, double* __restrict__ o,
-                                                             uint8_t* __restrict__ img, uint32_t* __restrict__ sb_count,
-                                                             double* __restrict__ stage) {
-    fold_image_body(sp, C, *L, o, img, sb_count, stage);
+                                                             const LayerArgs* __restrict__ L, FoldOut out) {
+    fold_image_body(sp, C, *L, out);
 }
 
 // After the fold: each superblock's global rank (the nonzero count of the
@@ -1578,7 +1632,7 @@ namespace {
 
 constexpr int kProbeShift = 5;                  // 32 catalogue events per probe word
 constexpr int kNetsThreads = 1024;              // one workgroup per CU: its waves share the coarse map
-constexpr int kNetsStageBytes = 37 * 1024;     // the waves' stage and flag rows
+constexpr int kNetsStageBytes = 37 * 1024;     // the waves' queues and flag rows
 constexpr int kCoarseBytes = 160 * 1024 - kNetsStageBytes;   // LDS left for the coarse map
 
 // value moved across lanes by a DPP control; lanes without a source get 0
@@ -1647,26 +1701,9 @@ __device__ int64_t first_trial_at(const int64_t* __restrict__ offsets, int64_t l
     return lo + __builtin_ctzll(m);
 }
 
-// probe word per 32 catalogue events: the bitmap bits (low half) and the
-// rank of the word's first event among the nonzero ones (high half), built
-// from the part images
-__global__ __launch_bounds__(256) void probe_table_kernel(const uint8_t* __restrict__ img, int64_t n_words,
-                                                          uint64_t* __restrict__ probe) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_words) return;
-    constexpr int kShift = kPartShift - kProbeShift;                    // probe words per part
-    const uint8_t* base = img + (i >> kShift) * kImgBytes;
-    const uint32_t j = static_cast<uint32_t>(i & ((int64_t(1) << kShift) - 1));
-    const uint32_t* bm32 = reinterpret_cast<const uint32_t*>(base);
-    const uint16_t* r16 = reinterpret_cast<const uint16_t*>(base + int64_t(kWords) * 8);
-    const uint32_t* b32 = reinterpret_cast<const uint32_t*>(base + int64_t(kWords) * 8 + int64_t(kRank16) * 2);
-    uint32_t rank = b32[j >> 7] + r16[j >> 2];       // superblock base, 128-event offset
-    for (uint32_t k = j & ~3u; k < j; ++k) rank += __builtin_popcount(bm32[k]);
-    probe[i] = (static_cast<uint64_t>(rank) << 32) | bm32[j];
-}
-
 // coarse map: bit i is set when any of events [i << cshift, (i + 1) << cshift)
 // has a nonzero loss; one thread per 32-bit word, from the probe words' bits
+// (for catalogues whose coarse words span superblocks; the fold writes the others)
 __global__ __launch_bounds__(256) void coarse_map_kernel(const uint64_t* __restrict__ probe, int64_t n_words,
                                                          int cshift, int64_t n_cw, uint32_t* __restrict__ coarse) {
     const int64_t cw = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1689,49 +1726,359 @@ __global__ __launch_bounds__(256) void coarse_map_kernel(const uint64_t* __restr
     coarse[cw] = out;
 }
 
-// The layer's trials are split into one contiguous run per wave (event
-// shares rounded to trial starts), and each wave streams its run's IDs in
-// steps of 64 kE positions in time order, kE consecutive positions per lane
-// (16-byte loads, the next step's issued before this step's work).  o(E) is
-// 0 unless E's bit is set in its probe word, else compact[rank + bits below]
-// -- an 8-byte probe and one more load per nonzero loss, both from tables
-// that stay in L2.  L2 serves these random requests at a bounded rate, so the
-// workgroup's 16 waves first test a coarse map in LDS (one bit per 2^cshift
-// events, set when any of them has a loss) and probe L2 only for events
-// whose bit is set.  Trial starts (held one per lane and marked in a
-// per-wave LDS bit row) reset a segmented double-double scan: each event's
-// running total S_d (the lane's own prefix, the scan of the lanes before it,
-// the carry of earlier steps) is rounded once; A_d = clamp(S_d; AggR, AggL)
-// and the net is A_d - A_{d-1}, with A_{d-1} = A_0 = clamp(0; AggR, AggL)
-// for a trial's first event, so a trial's nets telescope to its year loss
-// minus A_0.  A lane forms its kE nets in registers (A of the position before
-// its first one comes from the lane below); the nets go through a per-wave
-// LDS stage, half a step at a time, and out in non-temporal stores of 64
-// consecutive values.  With kStride the kernel writes, instead of nets, the
-// running total S_d of every position d = 64b + 63 to slot b of `nets` (the
-// stride checkpoints of the forward pass) and needs no stage.  Eight events
-// per lane spread the wave scan over twice the events of four.
-template <int kE, bool kStride = false>
+// Both time-ordered passes split the layer's trials into one contiguous run
+// per wave (event shares rounded to trial starts).  o(E) is 0 unless E's bit is
+// set in its probe word, else stage[index + bits below] -- an 8-byte probe and
+// one more load per nonzero loss, both from tables that stay in L2.  L2 serves
+// these random requests at a bounded rate, so the workgroup's 16 waves first
+// test a coarse map in LDS (one bit per 2^cshift events, set when any of them
+// has a loss) and probe L2 only for events whose bit is set.  Trial starts are
+// held one per lane and marked in a per-wave LDS bit row.
+
+// the coarse map to LDS (n_cw words, both sides 16-byte aligned and padded)
+__device__ __forceinline__ void load_coarse(const uint32_t* __restrict__ gcoarse, int64_t n_cw, uint32_t* coarse) {
+    const u32x4* src = reinterpret_cast<const u32x4*>(gcoarse);
+    u32x4* dst = reinterpret_cast<u32x4*>(coarse);
+    const int n = static_cast<int>((n_cw + 3) / 4);
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kNetsThreads) {
+        u32x4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = src[i0 + k * kNetsThreads < n ? i0 + k * kNetsThreads : i0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i0 + k * kNetsThreads < n) dst[i0 + k * kNetsThreads] = v[k];
+    }
+}
+
+// The per-event nets.  With S_d a trial's running total and A_d = clamp(S_d;
+// AggR, AggL), the net A_d - A_{d-1} is 0 wherever o is 0, so the sums run over
+// the events that pass the coarse map alone (the candidates, about a quarter
+// of the 1M-trial workload's events) and every other event's net is a stored
+// zero.  A wave takes steps of six chunks of 128 positions, two per lane:
+//  * each event tests the coarse map; ballots rank the candidates in time order
+//    and place (ID, number of trial starts so far in the step) in a per-wave
+//    LDS queue of 256;
+//  * each lane takes up to four consecutive candidates: probe words together,
+//    then losses together, the lane's own double-double prefix, a segmented
+//    scan over the lanes (a candidate whose count of trial starts differs from
+//    its predecessor's starts a segment), S_d rounded once, A_d and the net,
+//    which replaces the queue entry;
+//  * the event's lane reads its net back and stores its two positions as 16
+//    bytes, 64 lanes to 1 KB.
+// Steps with more candidates than the queue holds go through it in balanced
+// runs of chunks.
+//
+// The vector L1 returns data in the order of the requests of the whole CU, so
+// an ID load that goes to HBM holds back every probe behind it.  The 16 waves
+// therefore step together (one barrier) and issue their next IDs at the start
+// of a step, where none has a probe in flight: one wait per step for the CU
+// instead of one per wave (2.5e8 events: 0.94 -> 0.83 ms, the L1's address unit
+// 88 -> 64% busy).  What is left is L1 request rate (310 random requests per
+// wave and step at 0.44 per clock, the rate that independent gathers from a 2 MB
+// table reach) and the arithmetic (840 vector instructions), about half each,
+// which the barrier keeps from overlapping fully.  A segmented scan over every
+// event, eight per lane, took 1.12 ms.
+constexpr int kNetsQueue = 256;
+typedef double f64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kNetsChunks = 6;
+
 __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t* __restrict__ offsets,
                                                                   const uint32_t* __restrict__ ids,
                                                                   const uint64_t* __restrict__ probe,
                                                                   const uint32_t* __restrict__ gcoarse, int cshift,
-                                                                  int64_t n_cw, const double* __restrict__ compact,
+                                                                  int64_t n_cw, const double* __restrict__ losses,
                                                                   LayerArgs L, double* __restrict__ nets) {
+    constexpr int kCh = kNetsChunks;
+    constexpr int kW = 128 * kCh;                                      // positions per step
+    constexpr int kN = kNetsQueue / 64;
+    static_assert(kW <= kIdPad, "a step may read up to kW - 1 IDs past the table's end");
+    static_assert(kNetsStageBytes >= (kNetsThreads / 64) * (kNetsQueue * 8 + kW / 8), "rows fit their LDS share");
+    __shared__ uint64_t queues[kNetsThreads / 64][kNetsQueue];
+    __shared__ uint32_t flag_rows[kNetsThreads / 64][kW / 32];          // bit i: a trial starts at c + i
+    __shared__ int most_steps;
+    extern __shared__ __attribute__((aligned(16))) uint32_t coarse[];  // [n_cw]
+    if (threadIdx.x == 0) most_steps = 0;
+    load_coarse(gcoarse, n_cw, coarse);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    uint64_t* qu = queues[threadIdx.x >> 6];
+    uint32_t* fl = flag_rows[threadIdx.x >> 6];
+    const int64_t w = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+    const int64_t n_w = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
+    const int64_t t0 = L.trial_begin, t1 = L.trial_begin + L.trial_count;
+    const int64_t ev0 = offsets[t0];
+    const int64_t tot = offsets[t1] - ev0;
+    const int64_t k0 = first_trial_at(offsets, t0, t1, ev0 + tot * w / n_w, lane);
+    const int64_t k1 = first_trial_at(offsets, t0, t1, ev0 + tot * (w + 1) / n_w, lane);
+    const int64_t P0 = uniform_i64(offsets[k0]), P1 = k0 < k1 ? uniform_i64(offsets[k1]) : P0;
+    const double A0 = apply_terms(0.0, L.aggR, L.aggL);
+    if (lane < kW / 32) fl[lane] = 0;
+    int64_t kb = k0;                                                   // trial starts held: kb .. kb + 63
+    int64_t bnd = kb + lane < k1 ? offsets[kb + lane] : INT64_MAX;
+    const int64_t c0 = P0 & ~int64_t(1);                               // 8-byte aligned ID loads
+    u32x2 nxt[kCh];
+    auto load_ids = [&](int64_t at) {
+#pragma unroll
+        for (int u = 0; u < kCh; ++u)
+            nxt[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ids + at + u * 128 + lane * 2));
+    };
+    // the workgroup's waves step together (see the loop's barrier): as many
+    // steps for each as its longest run takes
+    if (P0 < P1) load_ids(c0);
+    if (lane == 0 && P0 < P1) atomicMax(&most_steps, static_cast<int>((P1 - c0 + kW - 1) / kW));
+    __syncthreads();
+    const int n_steps = most_steps;
+    double ch = 0.0, cl = 0.0;            // running total at the last candidate
+    double a_prev = A0;                   // its A
+    uint32_t prev_seg = ~0u;              // its trial starts in this step; ~0: a trial started after it
+    int64_t c = c0;
+    for (int step = 0; step < n_steps; ++step, c += kW) {
+        __syncthreads();
+        if (c >= P1) continue;
+        u32x2 cur[kCh];
+#pragma unroll
+        for (int u = 0; u < kCh; ++u) cur[u] = nxt[u];
+        load_ids(c + kW < P1 ? c + kW : c);
+        // mark the trial starts inside [c, c + kW)
+        bool any_start = false;
+        for (;;) {
+            const bool in = bnd >= c && bnd < c + kW;
+            if (in) {
+                const uint32_t i = static_cast<uint32_t>(bnd - c);
+                atomicOr(&fl[i >> 5], 1u << (i & 31u));
+            }
+            any_start |= __ballot(in) != 0;
+            if (static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(bnd), 63)) >= c + kW) break;
+            kb += 64;
+            bnd = kb + lane < k1 ? offsets[kb + lane] : INT64_MAX;
+        }
+        __builtin_amdgcn_wave_barrier();
+        // positions of the run in this step, relative to c
+        const int lo = P0 > c ? static_cast<int>(P0 - c) : 0;
+        const int hi = P1 - c < kW ? static_cast<int>(P1 - c) : kW;
+        const bool inside = lo == 0 && hi == kW;
+        // candidates: bits 2u and 2u + 1 of cm for the lane's positions of chunk u
+        uint32_t cm = 0;
+        uint32_t bits[kCh][2];
+#pragma unroll
+        for (int u = 0; u < kCh; ++u)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                // IDs past the run are other trials' or the table's zero padding
+                const uint32_t cb = cur[u][k] >> cshift;
+                bits[u][k] = coarse[cb >> 5] >> (cb & 31u);
+            }
+#pragma unroll
+        for (int u = 0; u < kCh; ++u)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) cm |= (bits[u][k] & 1u) << (2 * u + k);
+        if (!inside) {
+#pragma unroll
+            for (int u = 0; u < kCh; ++u)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int i = u * 128 + lane * 2 + k;
+                    if (i < lo || i >= hi) cm &= ~(1u << (2 * u + k));
+                }
+        }
+        int n_of[kCh];
+        int total = 0;
+#pragma unroll
+        for (int u = 0; u < kCh; ++u) {
+            n_of[u] = static_cast<int>(__popcll(__ballot((cm >> (2 * u)) & 1u)) +
+                                       __popcll(__ballot((cm >> (2 * u + 1)) & 1u)));
+            total += n_of[u];
+        }
+        uint32_t starts = 0;                                           // trial starts of the chunks before
+        uint32_t at[kCh];                                              // queue index of the lane's first candidate
+        // queue the candidates of chunk u from queue index `base` on
+        auto append = [&](int u, uint32_t base) {
+            const bool h0 = (cm >> (2 * u)) & 1u, h1 = (cm >> (2 * u + 1)) & 1u;
+            const uint64_t b0 = __ballot(h0), b1 = __ballot(h1);
+            uint32_t s0 = starts, s1 = starts;
+            if (any_start) {
+                const uint32_t fb = (fl[u * 4 + (lane >> 4)] >> ((lane & 15) * 2)) & 3u;
+                const uint64_t g0 = __ballot(fb & 1u), g1 = __ballot(fb & 2u);
+                uint32_t seg = starts;
+                seg = __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(g0), seg);
+                seg = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(g0 >> 32), seg);
+                seg = __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(g1), seg);
+                seg = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(g1 >> 32), seg);
+                starts += static_cast<uint32_t>(__popcll(g0) + __popcll(g1));
+                s0 = seg + (fb & 1u);
+                s1 = s0 + (fb >> 1);
+            }
+            uint32_t i = base;
+            i = __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b0), i);
+            i = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b0 >> 32), i);
+            i = __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b1), i);
+            i = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b1 >> 32), i);
+            at[u] = i;
+            if (h0) qu[i] = (static_cast<uint64_t>(s0) << 32) | cur[u][0];
+            if (h1) qu[i + (h0 ? 1u : 0u)] = (static_cast<uint64_t>(s1) << 32) | cur[u][1];
+        };
+        // the queue's n_c candidates: their nets replace them
+        auto nets_of = [&](int n_c) {
+            const int n = (n_c + 63) >> 6;                             // consecutive candidates per lane
+            const uint32_t last_seg = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(qu[n_c - 1] >> 32));
+            uint32_t E[kN], sg[kN];
+            bool in[kN];
+            uint32_t before_seg = prev_seg;
+            if (lane > 0 && lane * n - 1 < n_c) before_seg = static_cast<uint32_t>(qu[lane * n - 1] >> 32);
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                in[k] = false;
+                E[k] = 0;
+                sg[k] = 0;
+                if (k >= n) continue;
+                const int i = lane * n + k;
+                in[k] = i < n_c;
+                const uint64_t e = qu[in[k] ? i : 0];
+                E[k] = static_cast<uint32_t>(e);
+                sg[k] = static_cast<uint32_t>(e >> 32);
+            }
+            uint64_t pw[kN];
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                pw[k] = 0;
+                if (k < n && in[k]) pw[k] = probe[E[k] >> kProbeShift];
+            }
+            double oq[kN];
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                const uint32_t word = static_cast<uint32_t>(pw[k]), bi = E[k] & 31u;
+                oq[k] = 0.0;
+                if (k < n && ((word >> bi) & 1u))
+                    oq[k] = losses[static_cast<uint32_t>(pw[k] >> 32) + __popc(word & ((1u << bi) - 1u))];
+            }
+            // the lane's total since its last trial start (all of it if none)
+            bool f[kN];
+            uint32_t sf = 0;
+            double h = 0.0, l = 0.0;
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                f[k] = in[k] && sg[k] != (k == 0 ? before_seg : sg[k - 1]);
+                if (k >= n) continue;
+                if (f[k]) {
+                    h = 0.0;
+                    l = 0.0;
+                    sf = 1u;
+                }
+                dd_add(h, l, oq[k]);
+            }
+            if (lane == 0 && !sf) dd_merge(h, l, ch, cl);              // the open trial's total so far
+            double sh = h, sl = l;
+            wave_seg_scan_dd(sf, sh, sl);
+            // the open trial's total before this lane, then candidate by candidate
+            double rh = __shfl_up(sh, 1, 64), rl = __shfl_up(sl, 1, 64);
+            if (lane == 0) {
+                rh = ch;
+                rl = cl;
+            }
+            double A[kN];
+            double a_last = 0.0;
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                A[k] = a_last;
+                if (k >= n) continue;
+                if (f[k]) {
+                    rh = 0.0;
+                    rl = 0.0;
+                }
+                dd_add(rh, rl, oq[k]);
+                A[k] = apply_terms(rh + rl, L.aggR, L.aggL);
+                a_last = A[k];
+            }
+            double before = __shfl_up(a_last, 1, 64);
+            if (lane == 0) before = a_prev;
+#pragma unroll
+            for (int k = 0; k < kN; ++k) {
+                if (k >= n) continue;
+                const double net = A[k] - (f[k] ? A0 : (k == 0 ? before : A[k - 1]));
+                if (in[k]) qu[lane * n + k] = static_cast<uint64_t>(__double_as_longlong(net));
+            }
+            // lanes past the last candidate add zeros: lane 63 holds its totals
+            a_prev = readlane_f64(a_last, 63);
+            ch = readlane_f64(sh, 63);
+            cl = readlane_f64(sl, 63);
+            prev_seg = last_seg;
+        };
+        // the lane's two nets of chunk u (queue entries past a lane's own are read and dropped)
+        auto net_pair = [&](int u) -> f64x2_a8 {
+            const bool h0 = (cm >> (2 * u)) & 1u, h1 = (cm >> (2 * u + 1)) & 1u;
+            const uint32_t i0 = at[u] & (kNetsQueue - 1), i1 = (at[u] + (h0 ? 1u : 0u)) & (kNetsQueue - 1);
+            const uint64_t q0 = qu[i0], q1 = qu[i1];
+            f64x2_a8 v;
+            v.x = __longlong_as_double(static_cast<int64_t>(h0 ? q0 : 0ull));
+            v.y = __longlong_as_double(static_cast<int64_t>(h1 ? q1 : 0ull));
+            return v;
+        };
+        double* dst0 = nets + (c + lane * 2 - ev0);
+        {
+            // in runs of chunks [u0, u1) of at most `limit` candidates (one chunk at least)
+            const int runs = (total + kNetsQueue - 1) / kNetsQueue;
+            const int limit =
+                runs <= 1 ? kNetsQueue : (total / runs + 32 < kNetsQueue ? total / runs + 32 : kNetsQueue);
+            int u0 = 0;
+            while (u0 < kCh) {
+                int u1 = u0, n_c = 0;
+#pragma unroll
+                for (int u = 0; u < kCh; ++u)
+                    if (u == u1 && u >= u0 && (u == u0 || n_c + n_of[u] <= limit)) {
+                        append(u, static_cast<uint32_t>(n_c));
+                        n_c += n_of[u];
+                        u1 = u + 1;
+                    }
+                __builtin_amdgcn_wave_barrier();
+                if (n_c > 0) nets_of(n_c);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int u = 0; u < kCh; ++u) {
+                    if (u < u0 || u >= u1) continue;
+                    const f64x2_a8 v = net_pair(u);
+                    const int i = u * 128 + lane * 2;
+                    double* dst = dst0 + u * 128;
+                    if (inside || (i >= lo && i + 1 < hi)) {
+                        __builtin_nontemporal_store(v, reinterpret_cast<f64x2_a8*>(dst));
+                    } else {
+                        if (i >= lo && i < hi) dst[0] = v.x;
+                        if (i + 1 >= lo && i + 1 < hi) dst[1] = v.y;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                u0 = u1;
+            }
+        }
+        prev_seg = prev_seg == starts ? 0u : ~0u;
+        __builtin_amdgcn_wave_barrier();
+        if (any_start && lane < kW / 32) fl[lane] = 0;
+    }
+}
+
+// The stride checkpoints: the running total S_d of every position d = 64b + 63
+// to slot b.  Steps of 64 kE positions in time order, kE consecutive positions
+// per lane (16-byte loads, the next step's issued before this step's work); a
+// segmented double-double scan over the wave gives each lane's last running
+// total.  Eight events per lane spread the scan over twice the events of four.
+template <int kE>
+__global__ __launch_bounds__(kNetsThreads) void stride_checkpoint_kernel(const int64_t* __restrict__ offsets,
+                                                                  const uint32_t* __restrict__ ids,
+                                                                  const uint64_t* __restrict__ probe,
+                                                                  const uint32_t* __restrict__ gcoarse, int cshift,
+                                                                  int64_t n_cw, const double* __restrict__ losses,
+                                                                  LayerArgs L, double* __restrict__ slots) {
     static_assert(kE == 4 || kE == 8, "four or eight events per lane");
     static_assert(64 % kE == 0, "stride slots are lanes' last events when kE divides 64");
     constexpr int kW = 64 * kE;                                        // positions per step
     static_assert(kW <= kIdPad, "a step may read up to kW - 1 IDs past the table's end");
-    constexpr int kRow = 32 * (kE + 1);        // half a step's nets, one pad slot per lane
-    static_assert(kNetsStageBytes >= (kNetsThreads / 64) * (kRow * 8 + kW / 8), "stage rows fit their LDS share");
-    __shared__ double stage[kNetsThreads / 64][kStride ? 1 : kRow];
     __shared__ uint32_t flag_rows[kNetsThreads / 64][kW / 32];          // bit i: a trial starts at c + i
-    extern __shared__ uint32_t coarse[];                               // [n_cw]
+    extern __shared__ __attribute__((aligned(16))) uint32_t coarse[];  // [n_cw]
     // the coarse map, before any wave can leave (the only workgroup barrier)
-    for (int64_t i = threadIdx.x; i < n_cw; i += blockDim.x) coarse[i] = gcoarse[i];
+    load_coarse(gcoarse, n_cw, coarse);
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    double* st = stage[threadIdx.x >> 6];
     uint32_t* fl = flag_rows[threadIdx.x >> 6];
     const int64_t w = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
     const int64_t n_w = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
@@ -1743,7 +2090,6 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
     if (k0 >= k1) return;
     const int64_t P0 = offsets[k0], P1 = offsets[k1];
     if (P0 >= P1) return;
-    const double A0 = apply_terms(0.0, L.aggR, L.aggL);
     if (lane < kW / 32) fl[lane] = 0;
     int64_t kb = k0;                                                   // trial starts held: kb .. kb + 63
     int64_t bnd = kb + lane < k1 ? offsets[kb + lane] : INT64_MAX;
@@ -1753,7 +2099,6 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
     for (int u = 0; u < kE / 4; ++u)
         nxt[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ids + c0 + lane * kE + 4 * u));
     double ch = 0.0, cl = 0.0;       // running total of the segment open at the step's start
-    double a_prev = A0;              // A of the position before the step
     for (int64_t c = c0; c < P1; c += kW) {
         u32x4 cur[kE / 4];
 #pragma unroll
@@ -1805,7 +2150,7 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
             oq[q] = 0.0;
             if (ok[q] && ((bits >> bi) & 1u)) {
                 const uint32_t below = bi ? (~0u >> (32u - bi)) : 0u;
-                oq[q] = compact[static_cast<uint32_t>(pw[q] >> 32) + __builtin_popcount(bits & below)];
+                oq[q] = losses[static_cast<uint32_t>(pw[q] >> 32) + __builtin_popcount(bits & below)];
             }
         }
         // the lane's total since its last trial start (all of it if none)
@@ -1823,56 +2168,10 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
         if (lane == 0 && !sf) dd_merge(h, l, ch, cl);              // the open segment's carry
         double sh = h, sl = l;
         wave_seg_scan_dd(sf, sh, sl);
-        if constexpr (kStride) {
-            // a lane's first position is a multiple of kE, and kE divides 64, so
-            // each 64b + 63 is some lane's last event, where the running total is
-            // that lane's inclusive scan
-            if (ok[kE - 1] && ((pos + kE - 1) & 63) == 63) nets[(pos + kE - 1) >> 6] = sh + sl;
-        } else {
-            // the open segment's total before this lane's first event, then the
-            // running totals again, event by event, and A of each position
-            double rh = __shfl_up(sh, 1, 64), rl = __shfl_up(sl, 1, 64);
-            if (lane == 0) {
-                rh = ch;
-                rl = cl;
-            }
-            double A[kE];
-#pragma unroll
-            for (int q = 0; q < kE; ++q) {
-                if (fq[q]) {
-                    rh = 0.0;
-                    rl = 0.0;
-                }
-                dd_add(rh, rl, oq[q]);
-                A[q] = apply_terms(rh + rl, L.aggR, L.aggL);
-            }
-            // A of the position before each: A_0 before a trial's first event,
-            // the lane below's last A before this lane's first, a_prev before the step's
-            double before = __shfl_up(A[kE - 1], 1, 64);
-            if (lane == 0) before = a_prev;
-            double net[kE];
-#pragma unroll
-            for (int q = 0; q < kE; ++q) net[q] = A[q] - (fq[q] ? A0 : (q == 0 ? before : A[q - 1]));
-            a_prev = readlane_f64(A[kE - 1], 63);
-            // half a step at a time: lanes [32 hf, 32 hf + 32) hold positions
-            // [kW/2 hf, kW/2 (hf + 1)); position i of the half sits at i + i / kE
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                if ((lane >> 5) == hf) {
-#pragma unroll
-                    for (int q = 0; q < kE; ++q) st[(lane & 31) * (kE + 1) + q] = net[q];
-                }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int r = 0; r < kE / 2; ++r) {
-                    const int i = r * 64 + lane;
-                    const int64_t p = c + hf * (kW / 2) + i;
-                    const double v = st[i + i / kE];
-                    if (p >= P0 && p < P1) __builtin_nontemporal_store(v, nets + (p - ev0));
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
+        // a lane's first position is a multiple of kE, and kE divides 64, so
+        // each 64b + 63 is some lane's last event, where the running total is
+        // that lane's inclusive scan
+        if (ok[kE - 1] && ((pos + kE - 1) & 63) == 63) slots[(pos + kE - 1) >> 6] = sh + sl;
         ch = readlane_f64(sh, 63);
         cl = readlane_f64(sl, 63);
         __builtin_amdgcn_wave_barrier();
@@ -1884,62 +2183,84 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
 
 int part_count(int64_t C) { return static_cast<int>((C + kPartSize - 1) / kPartSize); }
 
-int64_t probe_table_bytes(int64_t C) {
-    // probe words, then the coarse map (at most kCoarseBytes)
-    return static_cast<int64_t>(sizeof(uint64_t)) * ((C + (1 << kProbeShift) - 1) >> kProbeShift) + 256 +
-           kCoarseBytes;
+namespace {
+
+// where the time-ordered passes' tables lie in their scratch: probe words, then
+// the coarse map, the finest (2^cshift events per bit) that fits its LDS share
+struct ProbeTables {
+    uint64_t* probe;
+    uint32_t* coarse;
+    int cshift;
+    int64_t n_words, n_cw;
+    int64_t bytes;
+};
+ProbeTables probe_tables(void* scratch, int64_t C) {
+    ProbeTables t;
+    t.n_words = (C + (1 << kProbeShift) - 1) >> kProbeShift;
+    t.cshift = 0;
+    while ((((C + (int64_t(1) << t.cshift) - 1) >> t.cshift) + 31) / 32 * 4 > kCoarseBytes) ++t.cshift;
+    t.n_cw = (((C + (int64_t(1) << t.cshift) - 1) >> t.cshift) + 31) / 32;
+    const int64_t words = (static_cast<int64_t>(sizeof(uint64_t)) * t.n_words + 255) & ~int64_t(255);
+    t.bytes = words + kCoarseBytes + 256;
+    t.probe = static_cast<uint64_t*>(scratch);
+    t.coarse = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + words);
+    return t;
 }
+// the fold writes coarse words that lie inside one superblock
+bool coarse_in_fold(const ProbeTables& t) { return (int64_t(32) << t.cshift) <= kSuper; }
+
+}  // namespace
+
+int64_t probe_table_bytes(int64_t C) { return probe_tables(nullptr, C).bytes; }
 
 namespace {
 
-hipError_t launch_nets_or_stride(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P,
-                                 int64_t C, uint64_t* probe, const LayerArgs& L, double* out, bool stride, int n_cu,
-                                 hipStream_t s) {
-    if (L.trial_count <= 0) return hipSuccess;
-    PartScratch ps = carve_parts(const_cast<void*>(part_scratch), P);
-    const int64_t n_words = (C + (1 << kProbeShift) - 1) >> kProbeShift;
-    hipLaunchKernelGGL(probe_table_kernel, dim3(static_cast<uint32_t>((n_words + 255) / 256)), dim3(256), 0, s,
-                       ps.img, n_words, probe);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // the finest coarse map that fits: 2^cshift events per bit
-    int cshift = 0;
-    while ((((C + (int64_t(1) << cshift) - 1) >> cshift) + 31) / 32 * 4 > kCoarseBytes) ++cshift;
-    const int64_t n_cw = (((C + (int64_t(1) << cshift) - 1) >> cshift) + 31) / 32;
-    uint32_t* coarse = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(probe) + sizeof(uint64_t) * n_words + 256);
-    hipLaunchKernelGGL(coarse_map_kernel, dim3(static_cast<uint32_t>((n_cw + 255) / 256)), dim3(256), 0, s, probe,
-                       n_words, cshift, n_cw, coarse);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const size_t lds = sizeof(uint32_t) * static_cast<size_t>(n_cw);
+// workgroups of the time-ordered passes: a wave per trial at most, all resident
+template <typename K>
+uint32_t nets_grid(K kernel, size_t lds, int64_t trials, int n_cu) {
     int per_cu = 0;
-    if ((stride ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, event_nets_kernel<8, true>, kNetsThreads, lds)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, event_nets_kernel<8, false>, kNetsThreads,
-                                                                lds)) != hipSuccess ||
-        per_cu < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kNetsThreads, lds) != hipSuccess || per_cu < 1)
         per_cu = 1;
-    int64_t blocks = (L.trial_count + kNetsThreads / 64 - 1) / (kNetsThreads / 64);
+    int64_t blocks = (trials + kNetsThreads / 64 - 1) / (kNetsThreads / 64);
     const int64_t cap = static_cast<int64_t>(n_cu) * per_cu;
-    if (blocks > cap) blocks = cap;
-    if (stride)
-        hipLaunchKernelGGL((event_nets_kernel<8, true>), dim3(static_cast<uint32_t>(blocks)), dim3(kNetsThreads), lds,
-                           s, offsets, ids, probe, coarse, cshift, n_cw, ps.compact, L, out);
-    else
-        hipLaunchKernelGGL((event_nets_kernel<8, false>), dim3(static_cast<uint32_t>(blocks)), dim3(kNetsThreads), lds,
-                           s, offsets, ids, probe, coarse, cshift, n_cw, ps.compact, L, out);
+    return static_cast<uint32_t>(blocks > cap ? cap : blocks);
+}
+
+hipError_t finish_tables(const ProbeTables& t, hipStream_t s) {
+    if (coarse_in_fold(t)) return hipSuccess;
+    hipLaunchKernelGGL(coarse_map_kernel, dim3(static_cast<uint32_t>((t.n_cw + 255) / 256)), dim3(256), 0, s, t.probe,
+                       t.n_words, t.cshift, t.n_cw, t.coarse);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P,
-                             int64_t C, uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s) {
-    return launch_nets_or_stride(offsets, ids, part_scratch, P, C, probe, L, nets, false, n_cu, s);
+hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P, int64_t C,
+                             uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s) {
+    if (L.trial_count <= 0) return hipSuccess;
+    const PartScratch ps = carve_parts(const_cast<void*>(part_scratch), P);
+    const ProbeTables t = probe_tables(probe, C);
+    hipError_t e = finish_tables(t, s);
+    if (e != hipSuccess) return e;
+    const size_t lds = (sizeof(uint32_t) * static_cast<size_t>(t.n_cw) + 15) & ~size_t(15);
+    hipLaunchKernelGGL(event_nets_kernel, dim3(nets_grid(event_nets_kernel, lds, L.trial_count, n_cu)),
+                       dim3(kNetsThreads), lds, s, offsets, ids, t.probe, t.coarse, t.cshift, t.n_cw, ps.stage, L, nets);
+    return hipGetLastError();
 }
 
 hipError_t launch_stride_checkpoints(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P,
                                      int64_t C, uint64_t* probe, const LayerArgs& L, double* stride, int n_cu,
                                      hipStream_t s) {
-    return launch_nets_or_stride(offsets, ids, part_scratch, P, C, probe, L, stride, true, n_cu, s);
+    if (L.trial_count <= 0) return hipSuccess;
+    const PartScratch ps = carve_parts(const_cast<void*>(part_scratch), P);
+    const ProbeTables t = probe_tables(probe, C);
+    hipError_t e = finish_tables(t, s);
+    if (e != hipSuccess) return e;
+    const size_t lds = (sizeof(uint32_t) * static_cast<size_t>(t.n_cw) + 15) & ~size_t(15);
+    hipLaunchKernelGGL(stride_checkpoint_kernel<8>,
+                       dim3(nets_grid(stride_checkpoint_kernel<8>, lds, L.trial_count, n_cu)), dim3(kNetsThreads), lds,
+                       s, offsets, ids, t.probe, t.coarse, t.cshift, t.n_cw, ps.stage, L, stride);
+    return hipGetLastError();
 }
 
 hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hipStream_t s, bool with_ranks) {
@@ -1958,16 +2279,22 @@ hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hi
 }
 
 hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L, const LayerArgs* L_dev, double* o,
-                             int P, void* scratch, bool compact, hipStream_t s) {
+                             int P, void* scratch, bool compact, uint64_t* probe, hipStream_t s) {
     PartScratch ps = carve_parts(scratch, P);
     const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
+    FoldOut out{o, ps.img, ps.sb_count, ps.stage, nullptr, nullptr, 0};
+    if (probe) {
+        const ProbeTables t = probe_tables(probe, C);
+        out.probe = t.probe;
+        out.coarse = coarse_in_fold(t) ? t.coarse : nullptr;
+        out.cshift = t.cshift;
+    }
     hipError_t e;
     if (L_dev)
         hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L_dev,
-                           o, ps.img, ps.sb_count, ps.stage);
+                           out);
     else
-        hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L, o,
-                           ps.img, ps.sb_count, ps.stage);
+        hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L, out);
     if ((e = hipGetLastError()) != hipSuccess || !compact) return e;
     hipLaunchKernelGGL(compact_stage_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, ps.stage,
                        ps.sb_count, ps.img, ps.compact);
