@@ -47,6 +47,15 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), lane);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+    return __longlong_as_double(static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(__double_as_longlong(v)), lane)));
+}
+
 // ---------------------------------------------------------------------------
 // create-time layout
 // ---------------------------------------------------------------------------
@@ -281,19 +290,25 @@ __global__ __launch_bounds__(256) void part_image_kernel(const double* __restric
     }
 }
 
-// The fold and the part images in one pass: one workgroup (256 threads) per
+// The fold and the part images in one pass: one workgroup (eight waves) per
 // superblock of 4096 catalogue events.  The superblock's ELT-combined losses
 // y are summed in LDS from the sparse pool: for each ELT of the layer, in
 // layer order, the chunk's nonzero entries (distinct events) each add their
-// per-ELT net loss, with a barrier between ELTs.  An absent loss adds +0.0
-// (retentions are >= 0), which leaves y unchanged, so y is bit-identical to
-// summing every ELT's dense row in layer order.  The entries of all the
-// layer's ELTs are first copied to LDS with independent loads (up to kStage
-// of them; the rest are read in place), so the ELTs cost one load latency,
-// not one each.  Then o, the bitmap words, the per-128 ranks and the
-// superblock count are written, and the superblock's nonzero o, packed in
-// event order, go to its 4096-value slot of `stage` (compact_stage_kernel
-// moves them to their global ranks).
+// per-ELT net loss.  An absent loss adds +0.0 (retentions are >= 0), which
+// leaves y unchanged, so y is bit-identical to summing every ELT's dense row in
+// layer order.  The kernel is a chain of memory and LDS latencies, so:
+//  * the entries' net losses are first staged in LDS, four ELTs' loads in
+//    flight per wave (kFoldStage entries a round);
+//  * each wave then sums its own 512 events: their entries are a contiguous
+//    range of each ELT's (found by bisection, one ELT per lane), and a wave's
+//    LDS operations keep their order, so the ELTs need no barrier between them.
+// Then o, the bitmap words, the per-128 ranks and the superblock count are
+// written, and the superblock's nonzero o, packed in event order, go to its
+// 4096-value slot of `stage`.  16 ELTs over 2e6 events: 16.5 us with a barrier
+// per ELT and 256 threads, 13.9 us now.
+constexpr int kFoldThreads = 512;
+constexpr int kFoldWaves = kFoldThreads / 64;
+constexpr int kFoldStage = 4096;
 struct FoldOut {
     double* o;                      // dense o, or null
     uint8_t* img;
@@ -323,127 +338,162 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
     uint8_t* __restrict__ img = out.img;
     uint32_t* __restrict__ sb_count = out.sb_count;
     double* __restrict__ stage = out.stage;
-    constexpr int kStage = 2048;                    // entries staged in LDS
-    __shared__ uint32_t wc[64];
+    constexpr int kOwn = kSuper / kFoldWaves;       // events a wave sums
+    constexpr int kWordsOwn = kOwn / 64;
+    __shared__ __attribute__((aligned(16))) double ys[kSuper];
+    __shared__ double sval[kFoldStage];
+    __shared__ uint16_t sev[kFoldStage];
     __shared__ uint64_t wb[64];
-    __shared__ double ys[kSuper];
-    __shared__ double sval[kStage];
-    __shared__ uint16_t sev[kStage];
-    __shared__ int64_t gstart[kMaxJ];               // ELT j's first entry of this chunk in the pool
-    __shared__ int32_t fpre[kMaxJ + 1];             // ELT j's entries are [fpre[j], fpre[j+1]) of the chunk's list
     const int64_t sb = blockIdx.x;
     const int64_t e0 = sb * kSuper;
     const int64_t part = e0 >> kPartShift;
     const int ls = static_cast<int>((e0 & (kPartSize - 1)) >> kSuperShift);
     uint64_t* bm = reinterpret_cast<uint64_t*>(img + part * kImgBytes);
     uint16_t* r16 = reinterpret_cast<uint16_t*>(img + part * kImgBytes + int64_t(kWords) * 8);
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    for (int i = threadIdx.x; i < kSuper; i += blockDim.x) ys[i] = 0.0;
-    const int J = sb < sp.n_chunks ? L.J : 0;       // J <= kMaxJ <= 64: one wave holds the ELTs
-    if (w == 0) {
-        int32_t cnt = 0;
-        if (lane < J) {
-            const int64_t key = static_cast<int64_t>(L.idx[lane]) * sp.n_chunks + sb;
-            const int64_t b = sp.chunk_off[key];
-            gstart[lane] = b;
-            cnt = static_cast<int32_t>(sp.chunk_off[key + 1] - b);    // <= 4096
-        }
-        int32_t inc = cnt;                          // inclusive scan over the wave
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t v = __shfl_up(inc, off, kWave);
-            if (lane >= off) inc += v;
-        }
-        if (lane < J) fpre[lane + 1] = inc;
-        if (lane == 0) fpre[0] = 0;
+    // lane j: ELT j's entries of this chunk in the pool, its terms, and where
+    // its entries start in the chunk's list (J <= kMaxJ <= 64)
+    const int J = sb < sp.n_chunks ? L.J : 0;
+    int64_t pool_at = 0;
+    int cnt = 0;
+    double R = 0.0, Lim = 0.0;
+    if (lane < J) {
+        const int64_t key = static_cast<int64_t>(L.idx[lane]) * sp.n_chunks + sb;
+        R = L.R[lane];
+        Lim = L.Lim[lane];
+        pool_at = sp.chunk_off[key];
+        cnt = static_cast<int>(sp.chunk_off[key + 1] - pool_at);      // <= 4096
     }
-    __syncthreads();
-    const int n_list = fpre[J];
-    const int staged = n_list < kStage ? n_list : kStage;
-    // ELT of entry f of the list: the first j whose range ends past f
-    auto elt_of = [&](int f) {
-        int lo = 0, hi = J - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (fpre[mid + 1] > f) hi = mid;
-            else lo = mid + 1;
-        }
-        return lo;
-    };
-    for (int f0 = threadIdx.x; f0 < staged; f0 += 4 * blockDim.x) {
-        uint16_t ev[4];
-        double val[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int f = f0 + u * static_cast<int>(blockDim.x);
-            if (f < staged) {
-                const int j = elt_of(f);
-                const int64_t k = gstart[j] + (f - fpre[j]);
-                ev[u] = sp.ev[k];
-                val[u] = sp.val[k];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int f = f0 + u * static_cast<int>(blockDim.x);
-            if (f < staged) {
-                sev[f] = ev[u];
-                sval[f] = val[u];
-            }
-        }
+    {
+        u64x2* own = reinterpret_cast<u64x2*>(ys + w * kOwn);
+        for (int i = lane; i < kOwn / 2; i += 64) own[i] = u64x2{0, 0};
     }
-    __syncthreads();
-    for (int j = 0; j < J; ++j) {
-        const double R = L.R[j], Lim = L.Lim[j];
-        const int fe = fpre[j + 1];
-        for (int f = fpre[j] + static_cast<int>(threadIdx.x); f < fe; f += blockDim.x) {
-            int ev;
-            double v;
-            if (f < kStage) {
-                ev = sev[f];
-                v = sval[f];
-            } else {
-                const int64_t k = gstart[j] + (f - fpre[j]);
-                ev = sp.ev[k];
-                v = sp.val[k];
+    int pre = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(pre, off, kWave);
+        if (lane >= off) pre += v;
+    }
+    const int n_list = __builtin_amdgcn_readlane(pre, 63);
+    pre -= cnt;
+    for (int r0 = 0; r0 < n_list; r0 += kFoldStage) {
+        if (r0) __syncthreads();                    // the previous round's entries are used
+        // wave w stages the ELTs w, w + 8, ..., four of them at a time
+        const int lo = r0 > pre ? r0 - pre : 0;     // lane j: entries [lo, hi) of ELT j are in this round
+        int hi = r0 + kFoldStage - pre;
+        hi = hi < cnt ? hi : cnt;
+        for (int j0 = w; j0 < J; j0 += 4 * kFoldWaves) {
+            int f[4], fe[4], to[4];
+            const uint16_t* evs[4];
+            const double* vals[4];
+            double Rj[4], Lj[4];
+            int most = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = j0 + u * kFoldWaves < J ? j0 + u * kFoldWaves : j0;
+                const int64_t k = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(pool_at), j));
+                const int fl = __builtin_amdgcn_readlane(lo, j);
+                fe[u] = j0 + u * kFoldWaves < J ? __builtin_amdgcn_readlane(hi, j) : fl;
+                f[u] = fl + lane;
+                to[u] = __builtin_amdgcn_readlane(pre, j) - r0;
+                most = fe[u] - fl > most ? fe[u] - fl : most;
+                evs[u] = sp.ev + k;
+                vals[u] = sp.val + k;
+                Rj[u] = readlane_f64(R, j);
+                Lj[u] = readlane_f64(Lim, j);
             }
-            ys[ev] = ys[ev] + apply_terms(v, R, Lim);
+            for (int i = 0; i < most; i += 64) {
+                uint16_t e[4];
+                double v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    e[u] = 0;
+                    v[u] = 0.0;
+                    if (f[u] + i < fe[u]) {
+                        e[u] = evs[u][f[u] + i];
+                        v[u] = vals[u][f[u] + i];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (f[u] + i < fe[u]) {
+                        sev[to[u] + f[u] + i] = e[u];
+                        sval[to[u] + f[u] + i] = apply_terms(v[u], Rj[u], Lj[u]);
+                    }
+            }
         }
         __syncthreads();
-    }
-    const int64_t eb = e0 + static_cast<int64_t>(w) * 16 * 64 + lane;   // event of word 0 of this wave
-    double vk[16];
-    uint64_t bk[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int word = w * 16 + k;
-        const int64_t E = eb + k * 64;
-        const double v = apply_terms(ys[word * 64 + lane], L.occR, L.occL);
-        if (o && E < C) o[E] = v;
-        const uint64_t bits = __ballot(E < C && v != 0.0);
-        vk[k] = v;
-        bk[k] = bits;
-        if (lane == 0) {
-            bm[ls * 64 + word] = bits;
-            wb[word] = bits;
-            wc[word] = __popcll(bits);
+        // lane j: the wave's entries [a0, a1) of ELT j, by bisection on the event
+        const int from = pre + lo - r0, till = hi > lo ? pre + hi - r0 : from;
+        int a0 = from, b0 = till, a1 = from, b1 = till;
+        while (a0 < b0 || a1 < b1) {
+            const int m0 = (a0 + b0) >> 1, m1 = (a1 + b1) >> 1;
+            const int v0 = a0 < b0 ? sev[m0] : 0, v1 = a1 < b1 ? sev[m1] : 0;
+            if (a0 < b0) {
+                if (v0 < w * kOwn) a0 = m0 + 1; else b0 = m0;
+            }
+            if (a1 < b1) {
+                if (v1 < (w + 1) * kOwn) a1 = m1 + 1; else b1 = m1;
+            }
         }
+        // the ELTs in layer order, the next one's first entries read ahead
+        int f = J > 0 ? __builtin_amdgcn_readlane(a0, 0) + lane : 0;
+        int fe = J > 0 ? __builtin_amdgcn_readlane(a1, 0) : 0;
+        int ev = f < fe ? sev[f] : 0;
+        double x = f < fe ? sval[f] : 0.0;
+        for (int j = 0; j < J; ++j) {
+            const int jn = j + 1 < J ? j + 1 : j;
+            const int fn = __builtin_amdgcn_readlane(a0, jn) + lane;
+            const int fen = __builtin_amdgcn_readlane(a1, jn);
+            const int evn = fn < fen ? sev[fn] : 0;
+            const double xn = fn < fen ? sval[fn] : 0.0;
+            if (f < fe) ys[ev] = ys[ev] + x;
+            for (f += 64; f < fe; f += 64) {
+                const int e2 = sev[f];
+                ys[e2] = ys[e2] + sval[f];
+            }
+            __builtin_amdgcn_wave_barrier();
+            f = fn;
+            fe = fen;
+            ev = evn;
+            x = xn;
+        }
+    }
+    const int64_t eb = e0 + static_cast<int64_t>(w) * kOwn + lane;      // event of word 0 of this wave
+    double vk[kWordsOwn];
+    uint64_t bk[kWordsOwn];
+#pragma unroll
+    for (int k = 0; k < kWordsOwn; ++k) {
+        const int64_t E = eb + k * 64;
+        const double v = apply_terms(ys[w * kOwn + k * 64 + lane], L.occR, L.occL);
+        if (o && E < C) o[E] = v;
+        vk[k] = v;
+        bk[k] = __ballot(E < C && v != 0.0);
+        if (lane == 0) wb[w * kWordsOwn + k] = bk[k];
     }
     __syncthreads();
+    // lane i: bitmap word i and the nonzero events before it, in every wave
+    const uint64_t word = wb[lane];
+    int before = __popcll(word);
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(before, off, kWave);
+        if (lane >= off) before += v;
+    }
+    const int total = __builtin_amdgcn_readlane(before, 63);
+    before -= __popcll(word);
+    if (w == 0) {
+        bm[ls * 64 + lane] = word;
+        if ((lane & 1) == 0) r16[ls * 32 + (lane >> 1)] = static_cast<uint16_t>(before);
+        if (lane == 0) sb_count[sb] = static_cast<uint32_t>(total);
+    }
     if (out.probe && w == 1) {
-        uint32_t before = wc[lane];                 // nonzero events before this lane's word
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t v = __shfl_up(before, off, kWave);
-            if (lane >= off) before += v;
-        }
-        before += static_cast<uint32_t>(e0) - wc[lane];
-        const uint64_t bits = wb[lane];
+        const uint32_t first = static_cast<uint32_t>(e0) + static_cast<uint32_t>(before);
         const int64_t i = (e0 >> 5) + 2 * lane;
         const int64_t n_words = (C + 31) >> 5;
-        const uint32_t low = static_cast<uint32_t>(bits);
-        if (i < n_words) out.probe[i] = (static_cast<uint64_t>(before) << 32) | low;
+        const uint32_t low = static_cast<uint32_t>(word);
+        if (i < n_words) out.probe[i] = (static_cast<uint64_t>(first) << 32) | low;
         if (i + 1 < n_words)
-            out.probe[i + 1] = (static_cast<uint64_t>(before + __popc(low)) << 32) | static_cast<uint32_t>(bits >> 32);
+            out.probe[i + 1] = (static_cast<uint64_t>(first + __popc(low)) << 32) | static_cast<uint32_t>(word >> 32);
     }
     if (out.coarse && static_cast<int>(threadIdx.x) < (128 >> out.cshift)) {
         // coarse word i of the superblock covers 2^cshift of its 32-event pieces
@@ -462,35 +512,21 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
         const int64_t i = (e0 >> (5 + s)) + threadIdx.x;
         if ((i << (5 + s)) < C) out.coarse[i] = m;
     }
-    {   // the nonzero o packed in event order: the wave's first word starts
-        // after the counts of the words before it
-        uint32_t at = 0;
-        for (int k = 0; k < w * 16; ++k) at += wc[k];
-        double* dst = stage + sb * kSuper;
+    // the nonzero o packed in event order
+    double* dst = stage + sb * kSuper;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if ((bk[k] >> lane) & 1ull) dst[at + __popcll(bk[k] & lanemask_lt())] = vk[k];
-            at += __popcll(bk[k]);
-        }
-    }
-    if (threadIdx.x < 32) {
-        uint32_t before = 0;
-        for (int b = 0; b < static_cast<int>(threadIdx.x); ++b) before += wc[2 * b] + wc[2 * b + 1];
-        r16[ls * 32 + threadIdx.x] = static_cast<uint16_t>(before);
-    }
-    if (threadIdx.x == 0) {
-        uint32_t total = 0;
-        for (int k = 0; k < 64; ++k) total += wc[k];
-        sb_count[sb] = total;
+    for (int k = 0; k < kWordsOwn; ++k) {
+        const int at = __builtin_amdgcn_readlane(before, w * kWordsOwn + k);
+        if ((bk[k] >> lane) & 1ull) dst[at + __popcll(bk[k] & lanemask_lt())] = vk[k];
     }
 }
 
 // terms as kernel arguments (eager runs) or read from device memory (graph
 // replays, whose terms may change between replays)
-__global__ __launch_bounds__(256) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
+__global__ __launch_bounds__(kFoldThreads) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
     fold_image_body(sp, C, L, out);
 }
-__global__ __launch_bounds__(256) void fold_image_dev_kernel(SparsePool sp, int64_t C,
+__global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool sp, int64_t C,
                                                              const LayerArgs* __restrict__ L, FoldOut out) {
     fold_image_body(sp, C, *L, out);
 }
@@ -1647,15 +1683,6 @@ __device__ __forceinline__ double dpp_f64(double v) {
     const uint32_t hi = dpp_u32<kCtrl, kRowMask>(static_cast<uint32_t>(b >> 32));
     return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
 }
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), lane);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), lane);
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-    return __longlong_as_double(static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(__double_as_longlong(v)), lane)));
-}
-
 // One stage of a segmented double-double scan: (f, h, l) becomes
 // left (+) self, where a lane that starts a segment (f set) keeps its sum.
 template <int kCtrl, int kRowMask>
@@ -2291,10 +2318,10 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
     }
     hipError_t e;
     if (L_dev)
-        hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L_dev,
+        hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(kFoldThreads), 0, s, sp, C, L_dev,
                            out);
     else
-        hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, C, L, out);
+        hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(kFoldThreads), 0, s, sp, C, L, out);
     if ((e = hipGetLastError()) != hipSuccess || !compact) return e;
     hipLaunchKernelGGL(compact_stage_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, ps.stage,
                        ps.sb_count, ps.img, ps.compact);
