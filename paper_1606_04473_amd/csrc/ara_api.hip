@@ -1425,7 +1425,6 @@ ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* p
     hipStream_t s = static_cast<hipStream_t>(stream);
     int device = 0;
     HIP_TRY(hipGetDevice(&device), "hipGetDevice");
-    const int n_cu = query_cu_count(device);
     const bool dev = (flags & ARA_DEVICE_PTR) != 0;
     PoolBuffer staged_in, results;
     // kept per device, like the tables' scratch (see ScratchBuffer)
@@ -1458,11 +1457,8 @@ ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* p
     // through the results buffer [mean, PML_0, TVaR_0, PML_1, ...]
     const ara::MetricsOut out = dev ? ara::MetricsOut{mean_out, pml_out, tvar_out, 1}
                                     : ara::MetricsOut{r, r + 1, r + 2, 2};
-    // the scratch counts as primed only once this whole sequence is enqueued
-    const bool primed = scratch.b->primed;
-    scratch.b->primed = false;
-    HIP_TRY(ara::launch_metrics(x, n_trials, m.data(), n_probs, scratch.b->p, primed, out, n_cu, s), "metrics kernels");
-    scratch.b->primed = true;
+    HIP_TRY(ara::launch_metrics(x, n_trials, m.data(), n_probs, scratch.b->p, &scratch.b->primed, out, s),
+            "metrics kernels");
     if (dev) return ARA_OK;
     std::vector<double> h(1 + 2 * n_probs);
     HIP_TRY(hipMemcpyAsync(h.data(), r, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s), "copy metrics");
@@ -1550,17 +1546,23 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
         void* gp = gb + la_bytes + o_bytes;
         void* gx = gb + la_bytes + o_bytes + p_bytes;
         void* gm = gb + la_bytes + o_bytes + p_bytes + xg_bytes;
-        if ((e = upload(ge)) != hipSuccess || (e = ara::launch_metrics_prime(gm, m.data(), n_probs, s)) != hipSuccess ||
+        if ((e = upload(ge)) != hipSuccess || (e = ara::launch_metrics_prime(gm, s)) != hipSuccess ||
             (e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
             free_graph(ge);
             return hip_fail(e, "graph capture");
         }
         hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
         if (le == hipSuccess) le = split.pass(L, gp, gx, s);
-        if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, s);
-        if (le == hipSuccess)
-            le = ara::launch_metrics(ylt, L.trial_count, m.data(), n_probs, gm, true,
-                                     ara::MetricsOut{metrics, metrics + 1, metrics + 1 + n_probs, 1}, t->n_cu, s);
+        const ara::MetricsOut mo{metrics, metrics + 1, metrics + 1 + n_probs, 1};
+        if (le == hipSuccess && split.stream && ara::combine_metrics_apply(L.trial_count)) {
+            le = ara::launch_combine_metrics(static_cast<const double*>(gx),
+                                             ara::stream_partials_lo(t->stream, gx, L.trial_count), t->stream.P,
+                                             L.trial_count, dL, ylt, m.data(), n_probs, gm, mo, s);
+        } else {
+            bool primed = true;
+            if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, s);
+            if (le == hipSuccess) le = ara::launch_metrics(ylt, L.trial_count, m.data(), n_probs, gm, &primed, mo, s);
+        }
         e = hipStreamEndCapture(s, &ge->graph);
         if (le != hipSuccess || e != hipSuccess ||
             (e = hipGraphInstantiate(&ge->exec, ge->graph, nullptr, nullptr, 0)) != hipSuccess) {
@@ -1602,13 +1604,11 @@ ara_status ara_risk_metrics_noalloc(const double* ylt, int64_t n_trials, const d
                     "(n_probs * n_trials <= %lld); use ara_risk_metrics",
                     (long long)n_trials, n_probs, (long long)need, (long long)capacity,
                     (long long)ARA_METRICS_NOALLOC_KEYS);
-    int device = 0;
-    HIP_TRY(hipGetDevice(&device), "hipGetDevice");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    // not primed: the first kernel clears the histograms, counters and flag
-    // that earlier calls on this device left in the shared array
-    HIP_TRY(ara::launch_metrics(ylt, n_trials, m, n_probs, scratch, false,
-                                ara::MetricsOut{mean_out, pml_out, tvar_out, 1}, query_cu_count(device), s),
+    // not primed: the counters that earlier calls on this device left in the
+    // shared array are cleared first
+    bool primed = false;
+    HIP_TRY(ara::launch_metrics(ylt, n_trials, m, n_probs, scratch, &primed,
+                                ara::MetricsOut{mean_out, pml_out, tvar_out, 1}, static_cast<hipStream_t>(stream)),
             "metrics kernels");
     return ARA_OK;
 }

@@ -100,6 +100,34 @@ __device__ __forceinline__ void group_reduce_dd(double& hi, double& lo, int widt
     }
 }
 
+// value moved across lanes by a DPP control; lanes without a source get 0
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kCtrl, kRowMask, 0xF, false));
+}
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+    const uint32_t lo = dpp_u32<kCtrl, kRowMask>(static_cast<uint32_t>(v));
+    const uint32_t hi = dpp_u32<kCtrl, kRowMask>(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ double dpp_f64(double v) {
+    return __longlong_as_double(static_cast<int64_t>(dpp_u64<kCtrl, kRowMask>(static_cast<uint64_t>(__double_as_longlong(v)))));
+}
+
+// Applies step<ctrl, row mask> for row shifts 1, 2, 4, 8 and then row broadcasts
+// 15 and 31: an inclusive scan over the wave, whose lane 63 holds the total
+#define ARA_WAVE_SCAN(step)   \
+    do {                      \
+        step(0x111, 0xF);     \
+        step(0x112, 0xF);     \
+        step(0x114, 0xF);     \
+        step(0x118, 0xF);     \
+        step(0x142, 0xA);     \
+        step(0x143, 0xC);     \
+    } while (0)
+
 __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
     uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
     uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
@@ -194,6 +222,8 @@ hipError_t build_stream_layout(const int64_t* offsets, const uint32_t* ids, int6
 void free_stream_layout(StreamLayout* L, hipStream_t s);
 // bytes of the per-(part, trial) partial sums of the streaming pass
 int64_t stream_partials_bytes(const StreamLayout& lay, int64_t trials);
+// where the low parts of the partial sums start
+const float* stream_partials_lo(const StreamLayout& lay, const void* partials, int64_t trials);
 // the streaming pass: reads the part images and compact values that
 // launch_fold_parts wrote to part_scratch (n_img_parts 2^18-event parts), writes
 // per-(stream part, trial) partial sums; the combine merges them in part order
@@ -484,13 +514,19 @@ struct MetricsOut {
 };
 // scratch of launch_metrics for n_probs probabilities over n year losses
 int64_t metrics_scratch_bytes(int n_probs, int64_t n);
-// `primed`: the scratch was last used by a launch_metrics sequence that was
-// enqueued whole, which leaves it ready for the next one (no init kernel)
-// readies a new scratch for launch_metrics(..., primed = true): the state the
-// previous sequence of a reused scratch leaves behind
-hipError_t launch_metrics_prime(void* scratch, const int64_t* m_host, int n_probs, hipStream_t s);
+// `primed`: the scratch is ready, by launch_metrics_prime or because the last
+// sequence that used it was enqueued whole; kept up to date by the call
+hipError_t launch_metrics_prime(void* scratch, hipStream_t s);
 hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs,
-                          void* scratch, bool primed, MetricsOut out, int n_cu, hipStream_t s);
+                          void* scratch, bool* primed, MetricsOut out, hipStream_t s);
+
+// the same on a primed scratch, with the merge of the streaming pass's partial
+// sums into `ylt` as its first launch (terms from L_dev); for YLTs of more values
+// than one workgroup takes (combine_metrics_apply)
+hipError_t launch_combine_metrics(const double* part_hi, const float* part_lo, int P, int64_t n, const LayerArgs* L_dev,
+                                  double* ylt, const int64_t* m_host, int n_probs, void* scratch, MetricsOut out,
+                                  hipStream_t s);
+bool combine_metrics_apply(int64_t n);
 
 // the static scratch of ara_risk_metrics_noalloc on the current device and
 // its size in bytes (launch_metrics needs metrics_scratch_bytes of it)
@@ -504,8 +540,7 @@ struct TailStats {
     int64_t m;
 };
 int64_t tail_stats_scratch_bytes(int64_t n);
-hipError_t launch_tail_stats(const double* ylt, int64_t n, int64_t m, void* scratch, TailStats* out,
-                             int n_cu, hipStream_t s);
+hipError_t launch_tail_stats(const double* ylt, int64_t n, int64_t m, void* scratch, TailStats* out, hipStream_t s);
 
 hipError_t launch_part_adjoint(const PartLayout& lay, int64_t N, const LayerArgs& L, void* part_scratch,
                                const double* S, const double* ylt, const TailStats* tail, uint64_t* w_mean,

@@ -429,7 +429,7 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
     AdjScratch a = carve(scratch, C, L.trial_count);
     hipError_t err;
     const int64_t n = L.trial_count;
-    if ((err = launch_tail_stats(ylt, n, m, a.tail_scratch, a.tail, n_cu, s)) != hipSuccess) return err;
+    if ((err = launch_tail_stats(ylt, n, m, a.tail_scratch, a.tail, s)) != hipSuccess) return err;
     hipLaunchKernelGGL(clear_acc_kernel, dim3(1), dim3(256), 0, s, a.acc);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const uint32_t cblocks = static_cast<uint32_t>((C + 255) / 256);

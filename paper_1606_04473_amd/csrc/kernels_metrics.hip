@@ -1,77 +1,80 @@
 // Risk metrics from a Year Loss Table: mean, PML_p, TVaR_p.
 //
-// Year losses are >= 0, so their IEEE-754 bit patterns order like their
-// values when read as uint64.  PML_p (the m-th largest) is found by a radix
-// select over those patterns with 12/12/12/12/12/4-bit digits, each pass a
-// privatised LDS histogram of the values that match the prefix chosen so
-// far.  The digit of a pass is chosen at the start of the next pass by every
-// workgroup from the previous histogram (the same data, so the same choice),
-// which saves a launch per pass; three histograms rotate so that the one
-// being cleared is never read or written in the same pass.  All requested
-// probabilities advance together.  For ara_risk_metrics (and the adjoint's
-// tail statistics) the first two passes run over all values; then one pass sums the values above each 24-bit
-// prefix and collects the keys inside it (a handful, unless many losses tie),
-// and a single workgroup finishes the selection over those candidates: up to
-// 256 of them are ranked directly against each other, more go through the
-// last four digit passes.  Each launch costs about 9 us here, whatever its data, so
-// that cuts nine launches to five.  The scratch is kept between calls and each
-// call leaves it ready for the next (its candidate pass clears the first
-// histogram, its last kernel the error flag), so a call on a reused scratch
-// skips the init kernel: four launches.  TVaR_p = (sum of the values above v +
-// (m - c_gt) v) / m, with v = PML_p and c_gt the count above it.  Sums are
-// double-double, reduced in a fixed order (deterministic), and the product
-// (m - c_gt) v is added exactly via fma.
+// Year losses are >= 0, so their IEEE-754 bit patterns (keys) order like their
+// values when read as uint64.  PML_p is the m-th largest.  It is found in one
+// histogram over all values and a selection among the few that share its bin:
+//  * the largest key gives the top bin; every octave below it is cut into 64
+//    bins (six mantissa bits), 4096 bins in all, the lowest one holding
+//    everything further down (zeros among it).  The map is monotone, so the
+//    histogram's counts from the top give each probability's bin, the rank left
+//    to find inside it and the count above it.  Values spread over many bins:
+//    a histogram of plain top bits (sign and exponent) crowds them into a
+//    few, where LDS and device atomics queue up on each other;
+//  * values above the bin are summed, the keys inside it collected;
+//  * one workgroup narrows those by further 4096-bin steps between their smallest
+//    and largest key (one step as a rule; none when all are equal, as at a
+//    limit or at zero), ranks the last 256 or fewer against each other, and
+//    forms TVaR_p = (sum of the values above v + (m - c_gt) v) / m, with v =
+//    PML_p and c_gt the count above it.
+// All probabilities advance together.  Up to kSmallMax values one workgroup
+// holds them in registers and does everything in one launch; beyond, four
+// launches: sums and the largest key, the histogram, the collection, and a
+// finishing workgroup per probability (the first launch is the partial sums'
+// merge itself where the year losses are formed in the same call).  What bounds
+// all of them is latency -- a launch and its dependent loads are 4 us here, the
+// data of 1M losses 8 MB -- so launches, barriers and queues on one address were
+// taken out: 1M losses and three probabilities 42 us where two 12-bit radix
+// passes took 57, 10,000 losses and one probability 14 us (26).
+// Sums are double-double.  The order of the values above a bin is fixed by the
+// launch, that of the few collected candidates by timing; the rounded results do
+// not depend on either beyond the sums' 2^-100 error.  The product (m - c_gt) v
+// is added exactly via fma.
 #include "ara_internal.hpp"
 
 namespace ara {
 
 namespace {
 
+constexpr int kThreads = 1024;
+constexpr int kWaves = kThreads / 64;
+constexpr int kPer = 8;                // values per thread of the multi-workgroup launches
 constexpr int kSumBlocks = 512;
-static_assert(kSumBlocks % 256 == 0, "the finishing workgroup holds kSumBlocks / 256 partials per thread");
 constexpr int kBins = 4096;
-constexpr int kPasses = 6;
-constexpr int kMaxProbs = 4;   // 4 x 16 KB histograms fit the 64 KB dynamic-LDS default
-constexpr int kDirect = 256;   // candidates ranked directly (all pairs) instead of by radix digits
-// Workgroup sizes of the two histogram passes.  Each workgroup adds its
-// nonzero bins to the global histogram with device atomics, and those on one
-// bin serialise (in the first pass the values crowd into the few bins of
-// their exponents), so fewer, larger workgroups wait less: 45.7 against
-// 51.5 us for 1M losses and two probabilities with 256 threads in both.
-constexpr int kHist0Threads = 1024;
-constexpr int kHist1Threads = 1024;
-__constant__ int kShift[kPasses] = {52, 40, 28, 16, 4, 0};
-__constant__ int kBits[kPasses] = {12, 12, 12, 12, 12, 4};
+constexpr int kBinShift = 46;          // a key's bits below its bin: 64 bins per octave
+constexpr int kMaxProbs = 4;
+constexpr int kDirect = 256;           // candidates ranked directly (all pairs)
+// One workgroup up to here: 16 values per thread in registers.
+constexpr int kSmallPer = 16;
+constexpr int64_t kSmallMax = int64_t(kThreads) * kSmallPer;
+constexpr uint64_t kBadKey = ~uint64_t(0);
 
-struct SelState {
-    uint64_t prefix;
-    uint64_t mask;
-    int64_t k;      // rank still to find inside the current prefix (1-based)
-    int64_t m;
+// one probability's state after the histogram
+struct Pick {
+    uint32_t bin;     // its m-th largest value's bin
+    uint32_t count;   // values in the bin
+    int64_t k;        // rank to find inside the bin (1-based, from the largest)
+    int64_t above;    // values in higher bins
 };
 
 struct Scratch {
-    double* part_hi;      // [kMaxProbs + 1][kSumBlocks]
+    double* part_hi;      // [kMaxProbs + 1][kSumBlocks]: mean partials, then the tails'
     double* part_lo;
-    int64_t* part_cnt;
-    uint32_t* hist;       // [3][kMaxProbs][kBins]: pass k fills hist[k % 3]
-    SelState* st;         // [2][kMaxProbs]: the state pass k uses is st[k & 1] (pass 0: st[0])
-    uint32_t* flag;
+    uint64_t* part_max;   // [kSumBlocks] largest key; kBadKey when a value is NaN or < 0
+    uint32_t* hist;       // [kBins]
+    Pick* pick;           // [kMaxProbs] each probability's bin
     uint32_t* ccount;     // [kMaxProbs] candidates collected per probability
-    uint64_t* cand;       // [n_probs][n] keys inside each probability's 24-bit prefix
+    uint64_t* cand;       // [n_probs][n]
 };
-
-constexpr int64_t kHistStride = int64_t(kMaxProbs) * kBins;   // one rotating histogram
 
 constexpr int64_t kCandAlign = 256;
 
 constexpr int64_t base_bytes() {
-    return static_cast<int64_t>(kMaxProbs + 1) * kSumBlocks * (2 * sizeof(double) + sizeof(int64_t)) +
-           3 * kHistStride * sizeof(uint32_t) + 2 * kMaxProbs * sizeof(SelState) + 64;
+    return static_cast<int64_t>(kMaxProbs + 1) * kSumBlocks * 2 * sizeof(double) + kSumBlocks * sizeof(uint64_t) +
+           kBins * sizeof(uint32_t) + kMaxProbs * sizeof(Pick) + 64;
 }
 
 // Scratch of the allocation-free entry point: the fixed block plus candidate
-// keys for up to kMaxProbs x kStaticTrials year losses (32.2 MiB).  A static
+// keys for up to kMaxProbs x kStaticTrials year losses (32.1 MiB).  A static
 // device array, so each device the library runs on holds its own copy until
 // the process ends; host code reaches it only through the address that
 // hipGetSymbolAddress returns on that device (metrics_noalloc_scratch).
@@ -80,8 +83,7 @@ constexpr int64_t kStaticBytes =
     (base_bytes() + kCandAlign - 1) / kCandAlign * kCandAlign + kMaxProbs * kStaticTrials * int64_t(sizeof(uint64_t));
 static __device__ __align__(256) uint8_t scratch[kStaticBytes];
 
-Scratch carve(void* base, int n_probs) {
-    (void)n_probs;
+Scratch carve(void* base) {
     char* p = static_cast<char*>(base);
     char* const start = p;
     Scratch s;
@@ -90,14 +92,13 @@ Scratch carve(void* base, int n_probs) {
     p += np * sizeof(double);
     s.part_lo = reinterpret_cast<double*>(p);
     p += np * sizeof(double);
-    s.part_cnt = reinterpret_cast<int64_t*>(p);
-    p += np * sizeof(int64_t);
+    s.part_max = reinterpret_cast<uint64_t*>(p);
+    p += kSumBlocks * sizeof(uint64_t);
     s.hist = reinterpret_cast<uint32_t*>(p);
-    p += 3 * kHistStride * sizeof(uint32_t);
-    s.st = reinterpret_cast<SelState*>(p);
-    p += 2 * kMaxProbs * sizeof(SelState);
-    s.flag = reinterpret_cast<uint32_t*>(p);
-    s.ccount = reinterpret_cast<uint32_t*>(p + 16);
+    p += kBins * sizeof(uint32_t);
+    s.pick = reinterpret_cast<Pick*>(p);
+    p += kMaxProbs * sizeof(Pick);
+    s.ccount = reinterpret_cast<uint32_t*>(p);
     s.cand = reinterpret_cast<uint64_t*>(start + (base_bytes() + kCandAlign - 1) / kCandAlign * kCandAlign);
     return s;
 }
@@ -107,452 +108,652 @@ __device__ __forceinline__ uint64_t key_of(double x) {
     return __double_as_longlong(x + 0.0);
 }
 
-// block-wide double-double reduction; result valid in thread 0
-__device__ __forceinline__ void block_reduce_dd(double& hi, double& lo, int64_t& cnt) {
-    __shared__ double sh[16], sl[16];              // up to 1024 threads
-    __shared__ int64_t sc[16];
-    group_reduce_dd(hi, lo, kWave);
-    for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        sh[w] = hi;
-        sl[w] = lo;
-        sc[w] = cnt;
+// a key's bin below `top`, the largest key's bin number
+__device__ __forceinline__ uint32_t bin_of(uint64_t key, uint64_t top) {
+    const uint64_t below = top - (key >> kBinShift);
+    return below < kBins ? kBins - 1 - static_cast<uint32_t>(below) : 0u;
+}
+
+__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
+
+__device__ __forceinline__ double read_lane(double v, int lane) { return __shfl(v, lane, kWave); }
+
+// totals over the wave (and over its first 16 lanes), in every lane
+__device__ __forceinline__ void wave_sum_dd(double& hi, double& lo) {
+#define ARA_STEP(ctrl, mask)                                    \
+    {                                                           \
+        const double h = dpp_f64<ctrl, mask>(hi), l = dpp_f64<ctrl, mask>(lo); \
+        dd_merge(hi, lo, h, l);                                 \
+    }
+    ARA_WAVE_SCAN(ARA_STEP);
+#undef ARA_STEP
+    hi = read_lane(hi, 63);
+    lo = read_lane(lo, 63);
+}
+__device__ __forceinline__ void row_sum_dd(double& hi, double& lo) {
+#define ARA_STEP(ctrl)                                          \
+    {                                                           \
+        const double h = dpp_f64<ctrl, 0xF>(hi), l = dpp_f64<ctrl, 0xF>(lo); \
+        dd_merge(hi, lo, h, l);                                 \
+    }
+    ARA_STEP(0x111);
+    ARA_STEP(0x112);
+    ARA_STEP(0x114);
+    ARA_STEP(0x118);
+#undef ARA_STEP
+    hi = read_lane(hi, 15);
+    lo = read_lane(lo, 15);
+}
+__device__ __forceinline__ uint64_t wave_max(uint64_t v) {
+#define ARA_STEP(ctrl, mask) v = max_u64(v, dpp_u64<ctrl, mask>(v))
+    ARA_WAVE_SCAN(ARA_STEP);
+#undef ARA_STEP
+    return __shfl(v, 63, kWave);
+}
+__device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
+#define ARA_STEP(ctrl, mask) v += dpp_u64<ctrl, mask>(v)
+    ARA_WAVE_SCAN(ARA_STEP);
+#undef ARA_STEP
+    return __shfl(v, 63, kWave);
+}
+// inclusive prefix sum over the wave
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+#define ARA_STEP(ctrl, mask) v += dpp_u32<ctrl, mask>(v)
+    ARA_WAVE_SCAN(ARA_STEP);
+#undef ARA_STEP
+    return v;
+}
+
+// Workgroup reductions over kThreads threads, valid in every thread: kN sums (n
+// of them used), or two largest keys, for two barriers.  `sh` is reused by the
+// next call, whose first barrier covers this one's reads.
+struct ReduceLds {
+    double hi[kMaxProbs + 1][kWaves], lo[kMaxProbs + 1][kWaves];
+    uint64_t u[2][kWaves];
+};
+template <int kN>
+__device__ __forceinline__ void block_sums(ReduceLds& sh, double (&hi)[kN], double (&lo)[kN], int n) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < kN; ++q)
+        if (q < n) wave_sum_dd(hi[q], lo[q]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kN; ++q)
+        if (q < n && lane == 0) {
+            sh.hi[q][w] = hi[q];
+            sh.lo[q][w] = lo[q];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kN; ++q)
+        if (q < n) {
+            hi[q] = sh.hi[q][lane & (kWaves - 1)];
+            lo[q] = sh.lo[q][lane & (kWaves - 1)];
+            row_sum_dd(hi[q], lo[q]);
+        }
+}
+__device__ __forceinline__ void block_max2(ReduceLds& sh, uint64_t& a, uint64_t& b) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    a = wave_max(a);
+    b = wave_max(b);
+    __syncthreads();
+    if (lane == 0) {
+        sh.u[0][w] = a;
+        sh.u[1][w] = b;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        hi = sh[0];
-        lo = sl[0];
-        cnt = sc[0];
-        const int nw = blockDim.x >> 6;
-        for (int i = 1; i < nw; ++i) {
-            dd_merge(hi, lo, sh[i], sl[i]);
-            cnt += sc[i];
-        }
-    }
+    a = wave_max(sh.u[0][lane & (kWaves - 1)]);
+    b = wave_max(sh.u[1][lane & (kWaves - 1)]);
+}
+__device__ __forceinline__ uint64_t block_max(ReduceLds& sh, uint64_t v) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    v = wave_max(v);
+    __syncthreads();
+    if (lane == 0) sh.u[0][w] = v;
+    __syncthreads();
+    return wave_max(sh.u[0][lane & (kWaves - 1)]);
+}
+__device__ __forceinline__ uint64_t block_count(ReduceLds& sh, uint64_t v) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    v = wave_sum(v);
+    __syncthreads();
+    if (lane == 0) sh.u[1][w] = v;
+    __syncthreads();
+    return wave_sum(lane < kWaves ? sh.u[1][lane] : 0ull);
 }
 
 struct MArgs {
     int64_t m[kMaxProbs];
 };
 
-// Choose the digit of `pass` for one probability from that pass's histogram
-// h, starting from the state st the pass used: the digit (from the top)
-// whose bin holds the k-th largest remaining value.  Every thread of the
-// 256-thread workgroup calls it and gets the new state.
-__device__ SelState choose_digit(const uint32_t* __restrict__ h, SelState st, int pass) {
-    __shared__ uint64_t scan[256];
-    __shared__ SelState out;
-    const int nb = 1 << kBits[pass];
-    const int per = (nb + 255) / 256;                    // 16 (12-bit digits) or 1 (the last, 4-bit)
-    // thread i owns bins [nb - per (i+1), nb - per i): thread 0 the largest digits
-    const int t = threadIdx.x;
-    const bool owner = t < 256;                           // larger workgroups: the rest wait at the barriers
-    const int hiBin = nb - per * (owner ? t : 0);
-    const int loBin = hiBin - per;
-    uint32_t cnt[16];
-    if (!owner) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) cnt[k] = 0;
-    } else if (per == 16) {                               // 16 aligned bins: four 16-byte loads
-        const u32x4* v = reinterpret_cast<const u32x4*>(h + loBin);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const u32x4 t = v[k];
-            cnt[4 * k] = t.x;
-            cnt[4 * k + 1] = t.y;
-            cnt[4 * k + 2] = t.z;
-            cnt[4 * k + 3] = t.w;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) cnt[k] = (k < per && loBin + k >= 0) ? h[loBin + k] : 0u;
-    }
-    uint64_t local = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) local += cnt[k];
-    if (t == 0) out = st;                 // unchanged unless a bin is chosen (k beyond the count)
-    if (owner) scan[t] = local;
+// The bins that hold the k[q]-th largest counted values of a histogram, from the
+// highest bin down; picks in LDS, valid after the call's last barrier.  Called
+// by the whole workgroup of kThreads; thread t brings its four bins' counts,
+// thread 0 the highest (own_bins).
+struct PickLds {
+    uint32_t wave_sum[kWaves];
+    Pick pick[kMaxProbs];
+};
+__device__ __forceinline__ u32x4 own_bins(const uint32_t* h) {
+    return reinterpret_cast<const u32x4*>(h)[kThreads - 1 - threadIdx.x];
+}
+__device__ __forceinline__ void pick_bins(PickLds& sh, u32x4 c, const int64_t* k, int n) {
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int lo_bin = kBins - 4 * (t + 1);
+    const uint32_t local = c.x + c.y + c.z + c.w;
+    const uint32_t incl = wave_scan(local);
+    if (lane == 63) sh.wave_sum[w] = incl;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint64_t add = owner && t >= off ? scan[t - off] : 0;
-        __syncthreads();
-        if (owner) scan[t] += add;
-        __syncthreads();
-    }
-    const uint64_t incl = owner ? scan[t] : 0;
-    const uint64_t excl = incl - local;
-    const uint64_t k = static_cast<uint64_t>(st.k);
-    if (owner && excl < k && k <= incl) {
-        uint64_t cum = excl;
-        for (int i = per - 1; i >= 0; --i) {              // from this thread's largest digit down
-            const uint64_t c = cnt[i];
-            if (cum + c >= k) {
-                const int b = loBin + i;
-                const int shift = kShift[pass];
-                const uint64_t dmask = (uint64_t(1) << kBits[pass]) - 1;
-                SelState r = st;
-                r.k = static_cast<int64_t>(k - cum);
-                r.prefix = st.prefix | (static_cast<uint64_t>(b) << shift);
-                r.mask = st.mask | (dmask << shift);
-                out = r;
-                break;
+    const uint32_t before = wave_scan(lane < w ? sh.wave_sum[lane & (kWaves - 1)] : 0u);   // w < 16
+    const int64_t excl = static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(before), 63)) + incl - local;
+    for (int q = 0; q < n; ++q) {
+        if (excl < k[q] && k[q] <= excl + local) {
+            int64_t cum = excl;
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                if (cum < k[q] && k[q] <= cum + c[i])
+                    sh.pick[q] = Pick{static_cast<uint32_t>(lo_bin + i), c[i], k[q] - cum, cum};
+                cum += c[i];
             }
-            cum += c;
         }
     }
     __syncthreads();
-    const SelState r = out;
-    __syncthreads();
+}
+
+// LDS of a workgroup that finishes a probability
+struct FinishLds {
+    __attribute__((aligned(16))) uint32_t hist[kBins];
+    PickLds sel;
+    ReduceLds red;
+    uint64_t keys[kDirect];
+    uint64_t found;
+    uint32_t n_keys;
+};
+
+// what the selection among a probability's candidates gives
+struct Chosen {
+    uint64_t v;             // the key of rank k
+    double hi, lo;          // sum of the values above it
+    int64_t above, equal;   // how many are above it, and equal to it
+};
+
+// The k-th largest of c candidates (1 <= k <= c): steps of 4096 bins between the
+// smallest and the largest key still possible until at most kDirect are left,
+// which are ranked against each other, four threads a key.  `each(f)` calls f for
+// every candidate the thread holds, `all(f)` for every value to be summed and
+// counted (the candidates, or all values).  Whole workgroup.
+template <typename Each, typename All>
+__device__ __forceinline__ Chosen select_candidate(FinishLds& sh, Each each, All all, uint32_t c, int64_t k) {
+    uint64_t lo = 0, hi = ~uint64_t(0);                    // the range that holds the k-th largest
+    uint32_t inside = c;
+    int64_t kk = k;
+    if (threadIdx.x == 0) sh.n_keys = 0;
+    if (c > kDirect) {
+        uint64_t mx = 0, mn = 0;                           // mn: the largest complement
+        each([&](uint64_t key) {
+            mx = max_u64(mx, key);
+            mn = max_u64(mn, ~key);
+        });
+        block_max2(sh.red, mx, mn);
+        hi = mx;
+        lo = ~mn;
+        while (inside > kDirect && lo != hi) {
+            const int bits = 64 - __builtin_clzll(hi - lo);        // hi - lo < 2^bits
+            const int shift = bits > 12 ? bits - 12 : 0;
+            reinterpret_cast<u32x4*>(sh.hist)[threadIdx.x] = u32x4{0, 0, 0, 0};
+            __syncthreads();
+            each([&](uint64_t key) {
+                if (key >= lo && key <= hi) atomicAdd(&sh.hist[(key - lo) >> shift], 1u);
+            });
+            __syncthreads();
+            pick_bins(sh.sel, own_bins(sh.hist), &kk, 1);
+            const Pick p = sh.sel.pick[0];
+            lo += static_cast<uint64_t>(p.bin) << shift;
+            const uint64_t last = lo + ((uint64_t(1) << shift) - 1);
+            hi = last < hi ? last : hi;
+            inside = p.count;
+            kk = p.k;
+            __syncthreads();
+        }
+    }
+    Chosen r;
+    if (lo == hi) {                                        // every candidate left is the same
+        r.v = lo;
+    } else {
+        // at most kDirect keys in [lo, hi]: the k-th largest has fewer than k
+        // keys above it and at least k at or above it
+        __syncthreads();
+        each([&](uint64_t key) {
+            if (key >= lo && key <= hi) sh.keys[atomicAdd(&sh.n_keys, 1u)] = key;
+        });
+        __syncthreads();
+        const int n = static_cast<int>(inside);
+        if (static_cast<int>(threadIdx.x) < 4 * n) {
+            const uint64_t kj = sh.keys[threadIdx.x >> 2];
+            int gt = 0, ge = 0;
+            for (int i = threadIdx.x & 3; i < n; i += 4) {
+                gt += sh.keys[i] > kj;
+                ge += sh.keys[i] >= kj;
+            }
+            gt += __shfl_xor(gt, 1);
+            ge += __shfl_xor(ge, 1);
+            gt += __shfl_xor(gt, 2);
+            ge += __shfl_xor(ge, 2);
+            if (gt < kk && kk <= ge) sh.found = kj;                // every such thread writes the same key
+        }
+        __syncthreads();
+        r.v = sh.found;
+    }
+    // The sum above it: collected candidates' places depend on timing, the
+    // double-double sum's rounded value does not, beyond its 2^-100 error
+    double h[1] = {0.0}, l[1] = {0.0};
+    uint64_t counts = 0;                                   // above in the high half, equal in the low
+    all([&](uint64_t key) {
+        if (key > r.v) {
+            dd_add(h[0], l[0], __longlong_as_double(static_cast<long long>(key)));
+            counts += uint64_t(1) << 32;
+        }
+        counts += key == r.v;
+    });
+    block_sums(sh.red, h, l, 1);
+    counts = block_count(sh.red, counts);
+    r.hi = h[0];
+    r.lo = l[0];
+    r.above = static_cast<int64_t>(counts >> 32);
+    r.equal = static_cast<int64_t>(counts & 0xFFFFFFFFu);
     return r;
 }
 
-// resets the selection state and clears the first histogram (every
-// probability's slot) with plain stores
-__global__ void select_init_kernel(Scratch s, MArgs ma, int n_probs) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid < n_probs) {
-        s.st[tid].prefix = 0;
-        s.st[tid].mask = 0;
-        s.st[tid].k = ma.m[tid];
-        s.st[tid].m = ma.m[tid];
-    }
-    if (tid == 0) *s.flag = 0;
-    if (tid < kMaxProbs) s.ccount[tid] = 0;
-    for (int64_t i = tid; i < kHistStride; i += gridDim.x * blockDim.x) s.hist[i] = 0;
-}
-
-// Pass `pass` of the radix select (and, in pass 0, the sum for the mean):
-// finish the previous pass's digit choice, clear the histogram the next pass
-// fills, and count this pass's digits of the values matching the prefix.
-template <int kT>
-__global__ __launch_bounds__(kT) void histogram_kernel(const double* __restrict__ x, int64_t n, Scratch s,
-                                                       MArgs ma, int n_probs, int pass, int with_mean) {
-    extern __shared__ uint32_t lds_hist[];   // [nq][kBins]
-    __shared__ SelState cur[kMaxProbs];
-    // pass 0 starts every probability from the empty prefix, so one histogram serves all
-    const int nq = pass == 0 ? (n_probs > 0 ? 1 : 0) : n_probs;
-    for (int i = threadIdx.x; i < nq * kBins; i += blockDim.x) lds_hist[i] = 0;
-    for (int q = 0; q < n_probs; ++q) {
-        // pass 0 starts from the empty prefix and records that state for pass 1
-        SelState st{0, 0, ma.m[q], ma.m[q]};
-        if (pass == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
-            s.st[q] = st;
-            s.ccount[q] = 0;
+// a probability's candidates in memory: up to kPer per thread are loaded once
+__device__ __forceinline__ Chosen select_in_memory(FinishLds& sh, const uint64_t* cand, uint32_t c, int64_t k) {
+    if (c <= kThreads * kPer) {
+        uint64_t key[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint32_t i = u * kThreads + threadIdx.x;
+            key[u] = i < c ? cand[i] : 0ull;
         }
-        if (pass > 0) {
-            st = s.st[((pass - 1) & 1) * kMaxProbs + q];
-            // pass 0 fills the first probability's slot only: its histogram serves all
-            st = choose_digit(s.hist + ((pass - 1) % 3) * kHistStride + int64_t(pass == 1 ? 0 : q) * kBins, st,
-                              pass - 1);
-            if (blockIdx.x == 0 && threadIdx.x == 0) s.st[(pass & 1) * kMaxProbs + q] = st;
-        }
-        if (threadIdx.x == 0) cur[q] = st;
+        auto each = [&](auto f) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (u * kThreads + threadIdx.x < c) f(key[u]);
+        };
+        return select_candidate(sh, each, each, c, k);
     }
-    {   // the histogram pass + 1 fills: last used two passes ago, so nobody touches it now
-        uint32_t* nxt = s.hist + ((pass + 1) % 3) * kHistStride;
-        const int64_t per = (int64_t(n_probs) * kBins + gridDim.x - 1) / gridDim.x;
-        const int64_t b0 = per * blockIdx.x;
-        for (int64_t i = b0 + threadIdx.x; i < b0 + per && i < int64_t(n_probs) * kBins; i += blockDim.x) nxt[i] = 0;
-    }
-    __syncthreads();
-    const int shift = kShift[pass];
-    const uint64_t dmask = (uint64_t(1) << kBits[pass]) - 1;
-    uint64_t pre[kMaxProbs], msk[kMaxProbs];
-    for (int q = 0; q < n_probs; ++q) {
-        pre[q] = cur[q].prefix;
-        msk[q] = cur[q].mask;
-    }
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    uint32_t bad = 0;
-    double mhi = 0.0, mlo = 0.0;
-    auto take = [&](double v) {
-        if (pass == 0 && !(v >= 0.0)) bad = 1;
-        if (with_mean) dd_add(mhi, mlo, v);
-        const uint64_t key = key_of(v);
-        const uint32_t d = static_cast<uint32_t>((key >> shift) & dmask);
-        for (int q = 0; q < nq; ++q)
-            if ((key & msk[q]) == pre[q]) atomicAdd(&lds_hist[q * kBins + d], 1u);
+    auto each = [&](auto f) {
+        for (uint32_t i = threadIdx.x; i < c; i += kThreads) f(cand[i]);
     };
-    // eight loads in flight per thread (all of a thread's values at the
-    // launch's usual 2048 values per workgroup)
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += 8 * stride) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i + u * stride < n ? x[i + u * stride] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i + u * stride < n) take(v[u]);
+    return select_candidate(sh, each, each, c, k);
+}
+
+// PML and TVaR of probability q, or the tail statistics, from what was chosen and
+// the `above` values, of sum (hi, lo), above the candidates
+__device__ __forceinline__ void write_one(const Chosen& r, int64_t above, int64_t m, double hi, double lo, int q,
+                                          const MetricsOut& out, TailStats* tail) {
+    const int64_t gt = above + r.above;
+    if (tail) {
+        *tail = TailStats{r.v, gt, r.equal, m};
+        return;
     }
-    if (bad) atomicOr(s.flag, 1u);
-    if (with_mean) {
-        int64_t zero = 0;
-        block_reduce_dd(mhi, mlo, zero);
-        if (threadIdx.x == 0) {
-            s.part_hi[blockIdx.x] = mhi;
-            s.part_lo[blockIdx.x] = mlo;
-            s.part_cnt[blockIdx.x] = 0;
-        }
+    dd_merge(hi, lo, r.hi, r.lo);
+    const double v = __longlong_as_double(static_cast<long long>(r.v));
+    const double copies = static_cast<double>(m - gt);     // copies of v in the top m
+    const double pr = copies * v;
+    const double pe = fma(copies, v, -pr);                 // exact product pr + pe
+    dd_merge(hi, lo, pr, pe);
+    out.pml[q * out.stride] = v;
+    out.tvar[q * out.stride] = (hi + lo) / static_cast<double>(m);
+}
+
+// results of a YLT with a NaN or a negative value
+__device__ __forceinline__ void write_bad(int n_probs, const MetricsOut& out, TailStats* tail, const MArgs& ma) {
+    if (threadIdx.x != 0) return;
+    const double nan = __longlong_as_double(0x7ff8000000000000LL);
+    if (tail) {
+        *tail = TailStats{0, 0, 1, ma.m[0]};
+        return;
     }
-    __syncthreads();
-    uint32_t* h = s.hist + (pass % 3) * kHistStride;
-    for (int k = threadIdx.x; k < nq * kBins; k += blockDim.x) {
-        const uint32_t c = lds_hist[k];
-        if (c) atomicAdd(&h[k], c);
+    *out.mean = nan;
+    for (int q = 0; q < n_probs; ++q) {
+        out.pml[q * out.stride] = nan;
+        out.tvar[q * out.stride] = nan;
     }
 }
 
-// After the two 12-bit passes: every workgroup chooses the second digit, so
-// each probability has a 24-bit prefix that holds its m-th largest value
-// (block 0 keeps the state in st[0]).  Values above the prefix's range are
-// summed and counted into the tail partials (slot 1 + q); the keys inside it
-// are appended to the probability's candidate list, one atomic per wave.
-__global__ __launch_bounds__(256) void collect_kernel(const double* __restrict__ x, int64_t n, Scratch s,
-                                                      int n_probs) {
-    __shared__ uint64_t pre_s[kMaxProbs], msk_s[kMaxProbs];
-    constexpr int done = 1;                         // the pass whose histogram is read
-    for (int q = 0; q < n_probs; ++q) {
-        SelState st = s.st[(done & 1) * kMaxProbs + q];
-        st = choose_digit(s.hist + (done % 3) * kHistStride + int64_t(q) * kBins, st, done);
-        if (threadIdx.x == 0) {
-            pre_s[q] = st.prefix;
-            msk_s[q] = st.mask;
-            if (blockIdx.x == 0) s.st[((done + 1) & 1) * kMaxProbs + q] = st;
+// a new scratch: nothing collected
+__global__ void select_init_kernel(Scratch s) {
+    if (threadIdx.x < kMaxProbs) s.ccount[threadIdx.x] = 0;
+}
+
+// A workgroup's part of the first launch: its sum and largest key, and its share
+// of the histogram cleared for the second.
+__device__ __forceinline__ void store_partials(ReduceLds& sh, const Scratch& s, double hi, double lo, uint64_t mx) {
+    double h[1] = {hi}, l[1] = {lo};
+    block_sums(sh, h, l, 1);
+    mx = block_max(sh, mx);
+    if (threadIdx.x == 0) {
+        s.part_hi[blockIdx.x] = h[0];
+        s.part_lo[blockIdx.x] = l[0];
+        s.part_max[blockIdx.x] = mx;
+    }
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < kBins; i += gridDim.x * kThreads) s.hist[i] = 0;
+}
+
+// launch 1 where the year losses are formed: the merge of the streaming pass's
+// per-(part, trial) partial sums (part by part in double-double, rounded once, the
+// aggregate terms applied) with the sums and largest keys on the way
+__global__ __launch_bounds__(kThreads) void combine_sum_max_kernel(const double* __restrict__ part_hi,
+                                                                   const float* __restrict__ part_lo, int P, int64_t n,
+                                                                   const LayerArgs* __restrict__ L,
+                                                                   double* __restrict__ ylt, Scratch s) {
+    __shared__ ReduceLds sh;
+    const double aggR = L->aggR, aggL = L->aggL;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+    double sum_hi = 0.0, sum_lo = 0.0;
+    uint64_t mx = 0;
+    bool bad = false;
+    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; k < n; k += stride) {
+        double hi = 0.0, lo = 0.0;
+        for (int p = 0; p < P; ++p) dd_merge(hi, lo, part_hi[p * n + k], static_cast<double>(part_lo[p * n + k]));
+        const double y = apply_terms(hi + lo, aggR, aggL);
+        ylt[k] = y;
+        bad |= !(y >= 0.0);
+        dd_add(sum_hi, sum_lo, y);
+        mx = max_u64(mx, key_of(y));
+    }
+    store_partials(sh, s, sum_hi, sum_lo, bad ? kBadKey : mx);
+}
+
+// launch 1: sums and largest keys
+__global__ __launch_bounds__(kThreads) void sum_max_kernel(const double* __restrict__ x, int64_t n, Scratch s) {
+    __shared__ ReduceLds sh;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+    double hi = 0.0, lo = 0.0;
+    uint64_t mx = 0;
+    bool bad = false;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n; i += kPer * stride) {
+        double v[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) v[u] = i + u * stride < n ? x[i + u * stride] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            bad |= !(v[u] >= 0.0);
+            dd_add(hi, lo, v[u]);
+            mx = max_u64(mx, key_of(v[u]));
         }
+    }
+    store_partials(sh, s, hi, lo, bad ? kBadKey : mx);
+}
+
+// the largest key over the first launch's workgroups
+__device__ __forceinline__ uint64_t top_key(ReduceLds& sh, const Scratch& s, int n_part) {
+    return block_max(sh, static_cast<int>(threadIdx.x) < n_part ? s.part_max[threadIdx.x] : 0ull);
+}
+
+// launch 2: the histogram
+__global__ __launch_bounds__(kThreads) void bin_kernel(const double* __restrict__ x, int64_t n, Scratch s, int n_part) {
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
+    __shared__ ReduceLds sh;
+    reinterpret_cast<u32x4*>(hist)[threadIdx.x] = u32x4{0, 0, 0, 0};
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    double v[kPer];                                        // in flight while the largest key is found
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) v[u] = first + u * stride < n ? x[first + u * stride] : 0.0;
+    const uint64_t mk = top_key(sh, s, n_part);
+    if (mk == kBadKey) return;
+    const uint64_t top = mk >> kBinShift;
+    for (int64_t i = first; i < n; i += kPer * stride) {
+        if (i != first) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) v[u] = i + u * stride < n ? x[i + u * stride] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (i + u * stride < n) atomicAdd(&hist[bin_of(key_of(v[u]), top)], 1u);
     }
     __syncthreads();
-    {   // the first pass's histogram, read for the last time by the second
-        // pass, is cleared for the next call (with the error flag, cleared
-        // by the last kernel, the scratch is then ready without an init)
-        const int64_t per = (kHistStride + gridDim.x - 1) / gridDim.x;
-        const int64_t b0 = per * blockIdx.x;
-        for (int64_t i = b0 + threadIdx.x; i < b0 + per && i < kHistStride; i += blockDim.x) s.hist[i] = 0;
+    for (int k = threadIdx.x; k < kBins; k += kThreads) {
+        const uint32_t c = hist[k];
+        if (c) atomicAdd(&s.hist[k], c);
     }
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    uint64_t pre[kMaxProbs], msk[kMaxProbs];
-    double hi[kMaxProbs], lo[kMaxProbs];
-    int64_t cnt[kMaxProbs];
+}
+
+// launch 3: tail sums above each probability's bin, the keys inside it
+__global__ __launch_bounds__(kThreads) void collect_kernel(const double* __restrict__ x, int64_t n, Scratch s, MArgs ma,
+                                                           int n_probs, int n_part) {
+    __shared__ PickLds sel;
+    __shared__ ReduceLds red;
+    __shared__ uint32_t wave_n[kMaxProbs][kWaves], wave_at[kMaxProbs][kWaves];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+    const int64_t begin = static_cast<int64_t>(blockIdx.x) * kThreads;
+    double v[kPer];
 #pragma unroll
-    for (int q = 0; q < kMaxProbs; ++q) {
-        pre[q] = q < n_probs ? pre_s[q] : 0;
-        msk[q] = q < n_probs ? msk_s[q] : 0;
-        hi[q] = 0.0;
-        lo[q] = 0.0;
-        cnt[q] = 0;
+    for (int u = 0; u < kPer; ++u) {
+        const int64_t i = begin + u * stride + threadIdx.x;
+        v[u] = i < n ? x[i] : 0.0;
     }
-    // each value is loaded once for every probability, eight loads in
-    // flight per thread; whole waves step together (the bound is per
-    // workgroup), so every lane takes part in the ballots
-    for (int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x; b < n; b += 8 * stride) {
-        double v[8];
-        bool ok[8];
+    const u32x4 counts = own_bins(s.hist);
+    const uint64_t mk = top_key(red, s, n_part);
+    if (mk == kBadKey) return;
+    const uint64_t top = mk >> kBinShift;
+    pick_bins(sel, counts, ma.m, n_probs);
+    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n_probs) s.pick[threadIdx.x] = sel.pick[threadIdx.x];
+    uint32_t bins[kMaxProbs];
+    double hi[kMaxProbs] = {}, lo[kMaxProbs] = {};
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t i = b + u * stride + threadIdx.x;
-            ok[u] = i < n;
-            v[u] = ok[u] ? x[i] : 0.0;
+    for (int q = 0; q < kMaxProbs; ++q) bins[q] = q < n_probs ? sel.pick[q].bin : 0u;
+    for (int64_t b = begin; b < n; b += kPer * stride) {
+        uint32_t in[kMaxProbs] = {};                       // bit u: value u is a candidate
+        if (b != begin) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int64_t i = b + u * stride + threadIdx.x;
+                v[u] = i < n ? x[i] : 0.0;
+            }
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint64_t key = key_of(v[u]);
+        for (int u = 0; u < kPer; ++u) {
+            const bool ok = b + u * stride + threadIdx.x < n;
+            const uint32_t bin = bin_of(key_of(v[u]), top);
 #pragma unroll
             for (int q = 0; q < kMaxProbs; ++q) {
                 if (q >= n_probs) break;
-                const uint64_t top = pre[q] | ~msk[q];      // the largest key with the prefix
-                if (ok[u] && key > top) {
-                    dd_add(hi[q], lo[q], v[u]);
-                    cnt[q] += 1;
-                }
-                const bool in = ok[u] && (key & msk[q]) == pre[q];
-                const uint64_t bal = __ballot(in);
-                if (bal) {
-                    const int leader = __builtin_ctzll(bal);
-                    uint32_t at = 0;
-                    if (lane == leader) at = atomicAdd(&s.ccount[q], static_cast<uint32_t>(__popcll(bal)));
-                    at = static_cast<uint32_t>(__shfl(static_cast<int>(at), leader, kWave));
-                    if (in) s.cand[static_cast<int64_t>(q) * n + at + __popcll(bal & ((uint64_t(1) << lane) - 1))] = key;
-                }
+                if (ok && bin > bins[q]) dd_add(hi[q], lo[q], v[u]);
+                in[q] |= ok && bin == bins[q] ? 1u << u : 0u;
             }
         }
-    }
+        // one device atomic per workgroup and probability: every workgroup adds
+        // to the same counters
+        uint32_t pre[kMaxProbs];
 #pragma unroll
-    for (int q = 0; q < kMaxProbs; ++q) {
-        if (q >= n_probs) break;
-        block_reduce_dd(hi[q], lo[q], cnt[q]);
-        if (threadIdx.x == 0) {
-            s.part_hi[(1 + q) * kSumBlocks + blockIdx.x] = hi[q];
-            s.part_lo[(1 + q) * kSumBlocks + blockIdx.x] = lo[q];
-            s.part_cnt[(1 + q) * kSumBlocks + blockIdx.x] = cnt[q];
+        for (int q = 0; q < kMaxProbs; ++q) {
+            if (q >= n_probs) break;
+            const uint32_t c = static_cast<uint32_t>(__popc(in[q]));
+            const uint32_t incl = wave_scan(c);
+            pre[q] = incl - c;
+            if (lane == 63) wave_n[q][w] = incl;
         }
         __syncthreads();
+        if (w < n_probs && lane < kWaves) {
+            const uint32_t c = wave_n[w][lane];
+            const uint32_t incl = wave_scan(c);
+            uint32_t at = 0;
+            if (lane == kWaves - 1 && incl) at = atomicAdd(&s.ccount[w], incl);
+            wave_at[w][lane] = __shfl(at, kWaves - 1, kWave) + incl - c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kMaxProbs; ++q) {
+            if (q >= n_probs) break;
+            uint64_t* dst = s.cand + static_cast<int64_t>(q) * n + wave_at[q][w] + pre[q];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if ((in[q] >> u) & 1u) *dst++ = key_of(v[u]);
+        }
+    }
+    block_sums(red, hi, lo, n_probs);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < kMaxProbs; ++q)
+            if (q < n_probs) {
+                s.part_hi[(1 + q) * kSumBlocks + blockIdx.x] = hi[q];
+                s.part_lo[(1 + q) * kSumBlocks + blockIdx.x] = lo[q];
+            }
     }
 }
 
-// One workgroup: the mean from the pass-0 partials; per probability, the
-// remaining digits chosen over its candidates (histograms in LDS), then PML
-// and TVaR from the tail partials plus the candidates above the threshold
-// (fixed reduction order).  Every load that depends on no other is issued
-// first (partials, states, candidate counts), then the candidates of each
-// probability with few of them go to LDS, so the work waits for two round
-// trips to memory instead of one or more per step.
-__global__ __launch_bounds__(256) void finish_kernel(Scratch s, int n_probs, int n_mean_part, int n_tail_part,
-                                                     int64_t n, MetricsOut out) {
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
-    __shared__ uint64_t keys[kMaxProbs][kDirect];
-    __shared__ uint64_t found;
-    constexpr int kPer = kSumBlocks / 256;                  // partials per thread
-    const bool bad = *s.flag != 0;
-    const double nan = __longlong_as_double(0x7ff8000000000000LL);
-    double mh[kPer], ml[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int i = threadIdx.x + u * 256;
-        mh[u] = i < n_mean_part ? s.part_hi[i] : 0.0;
-        ml[u] = i < n_mean_part ? s.part_lo[i] : 0.0;
+// launch 4: one workgroup per probability finishes it; another forms the mean
+__global__ __launch_bounds__(kThreads) void finish_kernel(int64_t n, Scratch s, MArgs ma, int n_probs, int n_part,
+                                                          int n_tail_part, MetricsOut out, TailStats* tail) {
+    __shared__ FinishLds sh;
+    const int q = static_cast<int>(blockIdx.x);            // n_probs: the mean
+    const bool mean = q == n_probs;
+    const int row = mean ? 0 : 1 + q;
+    const bool in = static_cast<int>(threadIdx.x) < (mean ? n_part : n_tail_part);
+    // everything the workgroup needs from memory but the candidates, in flight together
+    double h[1] = {in ? s.part_hi[row * kSumBlocks + threadIdx.x] : 0.0};
+    double l[1] = {in ? s.part_lo[row * kSumBlocks + threadIdx.x] : 0.0};
+    const Pick p = mean ? Pick{0, 0, 1, 0} : s.pick[q];
+    const bool bad = top_key(sh.red, s, n_part) == kBadKey;
+    if (!mean && threadIdx.x == 0) s.ccount[q] = 0;        // ready for the next call
+    if (bad) {
+        if (q == 0) write_bad(n_probs, out, tail, ma);
+        return;
     }
-    SelState sq[kMaxProbs];
-    int64_t cq[kMaxProbs];
-    double th[kMaxProbs][kPer], tl[kMaxProbs][kPer];
-    int64_t tc[kMaxProbs][kPer];
-#pragma unroll
-    for (int q = 0; q < kMaxProbs; ++q) {
-        if (q >= n_probs) break;
-        sq[q] = s.st[q];                            // written by the collect pass (st[0])
-        cq[q] = static_cast<int64_t>(s.ccount[q]);
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = threadIdx.x + u * 256;
-            const bool in = i < n_tail_part;
-            th[q][u] = in ? s.part_hi[(1 + q) * kSumBlocks + i] : 0.0;
-            tl[q][u] = in ? s.part_lo[(1 + q) * kSumBlocks + i] : 0.0;
-            tc[q][u] = in ? s.part_cnt[(1 + q) * kSumBlocks + i] : 0;
-        }
+    block_sums(sh.red, h, l, 1);
+    if (mean) {
+        if (!tail && threadIdx.x == 0) *out.mean = (h[0] + l[0]) / static_cast<double>(n);
+        return;
     }
+    const Chosen r = select_in_memory(sh, s.cand + static_cast<int64_t>(q) * n, p.count, p.k);
+    if (threadIdx.x == 0) write_one(r, p.above, ma.m[q], h[0], l[0], q, out, tail);
+}
+
+// the mean alone (no probabilities), from the first launch's partials
+__global__ __launch_bounds__(kThreads) void mean_kernel(int64_t n, Scratch s, int n_part, MetricsOut out) {
+    __shared__ ReduceLds sh;
+    const bool in = static_cast<int>(threadIdx.x) < n_part;
+    double h[1] = {in ? s.part_hi[threadIdx.x] : 0.0}, l[1] = {in ? s.part_lo[threadIdx.x] : 0.0};
+    const bool bad = top_key(sh, s, n_part) == kBadKey;
+    block_sums(sh, h, l, 1);
+    if (threadIdx.x == 0)
+        *out.mean = bad ? __longlong_as_double(0x7ff8000000000000LL) : (h[0] + l[0]) / static_cast<double>(n);
+}
+
+// Everything in one workgroup, the values in registers (kV per thread).  The
+// selection runs over the registers too: a candidate is a value in the bin.
+template <int kV>
+__global__ __launch_bounds__(kThreads) void small_metrics_kernel(const double* __restrict__ x, int n, MArgs ma,
+                                                                 int n_probs, MetricsOut out, TailStats* tail) {
+    __shared__ FinishLds sh;
+    __shared__ Pick picks[kMaxProbs];
+    double v[kV];
 #pragma unroll
-    for (int q = 0; q < kMaxProbs; ++q) {
-        if (q >= n_probs) break;
-        if (cq[q] <= kDirect) {
-            const uint64_t* cand = s.cand + static_cast<int64_t>(q) * n;
-            for (int64_t j = threadIdx.x; j < cq[q]; j += blockDim.x) keys[q][j] = cand[j];
-        }
+    for (int u = 0; u < kV; ++u) {
+        const int i = u * kThreads + static_cast<int>(threadIdx.x);
+        v[u] = i < n ? x[i] : 0.0;
     }
+    reinterpret_cast<u32x4*>(sh.hist)[threadIdx.x] = u32x4{0, 0, 0, 0};
+    double mh[1] = {0.0}, ml[1] = {0.0};
+    uint64_t mx = 0;
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < kV; ++u) {
+        bad |= !(v[u] >= 0.0);
+        dd_add(mh[0], ml[0], v[u]);
+        mx = max_u64(mx, key_of(v[u]));
+    }
+    mx = block_max(sh.red, bad ? kBadKey : mx);
+    if (mx == kBadKey) {
+        write_bad(n_probs, out, tail, ma);
+        return;
+    }
+    const uint64_t top = mx >> kBinShift;
+#pragma unroll
+    for (int u = 0; u < kV; ++u)
+        if (u * kThreads + static_cast<int>(threadIdx.x) < n) atomicAdd(&sh.hist[bin_of(key_of(v[u]), top)], 1u);
+    if (!tail) {
+        block_sums(sh.red, mh, ml, 1);
+        if (threadIdx.x == 0) *out.mean = (mh[0] + ml[0]) / static_cast<double>(n);
+    }
+    if (n_probs == 0) return;
     __syncthreads();
-    {
-        double hi = 0.0, lo = 0.0;
-        int64_t cnt = 0;
+    pick_bins(sh.sel, own_bins(sh.hist), ma.m, n_probs);
+    if (threadIdx.x < kMaxProbs) picks[threadIdx.x] = sh.sel.pick[threadIdx.x];
+    __syncthreads();
+    auto all = [&](auto f) {
 #pragma unroll
-        for (int u = 0; u < kPer; ++u)
-            if (threadIdx.x + u * 256 < n_mean_part) dd_merge(hi, lo, mh[u], ml[u]);
-        block_reduce_dd(hi, lo, cnt);
-        if (threadIdx.x == 0) *out.mean = bad ? nan : (hi + lo) / static_cast<double>(n);
-        __syncthreads();
+        for (int u = 0; u < kV; ++u)
+            if (u * kThreads + static_cast<int>(threadIdx.x) < n) f(key_of(v[u]));
+    };
+#pragma unroll 1
+    for (int q = 0; q < n_probs; ++q) {
+        const Pick p = picks[q];
+        auto each = [&](auto f) {
+            all([&](uint64_t key) {
+                if (bin_of(key, top) == p.bin) f(key);
+            });
+        };
+        const Chosen r = select_candidate(sh, each, all, p.count, p.k);
+        if (threadIdx.x == 0) write_one(r, 0, ma.m[q], 0.0, 0.0, q, out, tail);
     }
-#pragma unroll
-    for (int q = 0; q < kMaxProbs; ++q) {
-        if (q >= n_probs) break;
-        SelState st = sq[q];
-        const int64_t c = cq[q];
-        const uint64_t* cand = s.cand + static_cast<int64_t>(q) * n;
-        const uint64_t* kq = keys[q];
-        if (c <= kDirect) {
-            // few candidates: the k-th largest is the key with fewer than k
-            // keys above it and at least k at or above it
-            for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-                const uint64_t kj = kq[j];
-                int64_t gt = 0, ge = 0;
-                for (int64_t i = 0; i < c; ++i) {
-                    gt += kq[i] > kj;
-                    ge += kq[i] >= kj;
-                }
-                if (gt < st.k && st.k <= ge) found = kj;      // every such thread writes the same key
-            }
-            __syncthreads();
-            st.prefix = found;
-            st.mask = ~uint64_t(0);
-            __syncthreads();
-        }
-        for (int pass = 2; pass < kPasses && c > kDirect; ++pass) {
-            for (int i = threadIdx.x; i < kBins; i += blockDim.x) hist[i] = 0;
-            __syncthreads();
-            const int shift = kShift[pass];
-            const uint64_t dmask = (uint64_t(1) << kBits[pass]) - 1;
-            for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-                const uint64_t key = cand[j];
-                if ((key & st.mask) == st.prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
-            }
-            __syncthreads();
-            st = choose_digit(hist, st, pass);
-        }
-        const uint64_t vk = st.prefix;              // all 64 bits chosen: the m-th largest key
-        double hi = 0.0, lo = 0.0;
-        int64_t cnt = 0;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            if (threadIdx.x + u * 256 < n_tail_part) {
-                dd_merge(hi, lo, th[q][u], tl[q][u]);
-                cnt += tc[q][u];
-            }
-        }
-        for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-            const uint64_t key = c <= kDirect ? kq[j] : cand[j];
-            if (key > vk) {
-                dd_add(hi, lo, __longlong_as_double(static_cast<long long>(key)));
-                cnt += 1;
-            }
-        }
-        block_reduce_dd(hi, lo, cnt);
-        if (threadIdx.x == 0) {
-            const double v = __longlong_as_double(static_cast<long long>(vk));
-            const double r = static_cast<double>(st.m - cnt);   // copies of v in the top m
-            const double p = r * v;
-            const double pe = fma(r, v, -p);                   // exact product p + pe
-            dd_merge(hi, lo, p, pe);
-            out.pml[q * out.stride] = bad ? nan : v;
-            out.tvar[q * out.stride] = bad ? nan : (hi + lo) / static_cast<double>(st.m);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *s.flag = 0;              // read by every thread before the barriers above
 }
 
-// one workgroup: the mean from the pass-0 partials, then PML and TVaR per
-// probability from the tail partials (fixed reduction order)
-__global__ __launch_bounds__(256) void final_kernel(Scratch s, int n_probs, int n_mean_part, int n_tail_part,
-                                                    int64_t n, MetricsOut out) {
-    const bool bad = *s.flag != 0;
-    const double nan = __longlong_as_double(0x7ff8000000000000LL);
-    for (int slot = 0; slot <= n_probs; ++slot) {
-        const int np = slot == 0 ? n_mean_part : n_tail_part;
-        double hi = 0.0, lo = 0.0;
-        int64_t cnt = 0;
-        for (int i = threadIdx.x; i < np; i += blockDim.x) {
-            dd_merge(hi, lo, s.part_hi[slot * kSumBlocks + i], s.part_lo[slot * kSumBlocks + i]);
-            cnt += s.part_cnt[slot * kSumBlocks + i];
-        }
-        block_reduce_dd(hi, lo, cnt);
-        if (threadIdx.x == 0) {
-            if (slot == 0) {
-                *out.mean = bad ? nan : (hi + lo) / static_cast<double>(n);
-            } else {
-                const int q = slot - 1;
-                const SelState st = s.st[((kPasses) & 1) * kMaxProbs + q];
-                const double v = __longlong_as_double(static_cast<long long>(st.prefix));
-                const double r = static_cast<double>(st.m - cnt);   // copies of v in the top m
-                const double p = r * v;
-                const double pe = fma(r, v, -p);                   // exact product p + pe
-                dd_merge(hi, lo, p, pe);
-                out.pml[q * out.stride] = bad ? nan : v;
-                out.tvar[q * out.stride] = bad ? nan : (hi + lo) / static_cast<double>(st.m);
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *s.flag = 0;              // read by every thread before the barriers above
+// workgroups of the multi-workgroup launches: kPer values per thread, at most kSumBlocks
+int sum_blocks(int64_t n) {
+    const int64_t b = (n + kThreads * kPer - 1) / (kThreads * kPer);
+    return static_cast<int>(b > kSumBlocks ? kSumBlocks : (b < 1 ? 1 : b));
 }
 
-// one workgroup: the final digit for the single tail count, into `out`
+// the launches after the sums and largest keys (n_part workgroups)
+hipError_t launch_selection(const double* ylt, int64_t n, const MArgs& ma, int n_probs, const Scratch& s, int n_part,
+                            MetricsOut out, TailStats* tail, hipStream_t st) {
+    const dim3 g(sum_blocks(n)), t(kThreads);
+    if (n_probs == 0) {
+        hipLaunchKernelGGL(mean_kernel, dim3(1), t, 0, st, n, s, n_part, out);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(bin_kernel, g, t, 0, st, ylt, n, s, n_part);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(collect_kernel, g, t, 0, st, ylt, n, s, ma, n_probs, n_part);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(finish_kernel, dim3(n_probs + (tail ? 0 : 1)), t, 0, st, n, s, ma, n_probs, n_part,
+                       static_cast<int>(g.x), out, tail);
+    return hipGetLastError();
+}
 
+hipError_t launch_all(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch, bool* primed,
+                      MetricsOut out, TailStats* tail, hipStream_t st) {
+    if (n_probs > kMaxProbs || n < 1) return hipErrorInvalidValue;
+    const Scratch s = carve(scratch);
+    MArgs ma{};
+    for (int q = 0; q < n_probs; ++q) ma.m[q] = m_host[q];
+    if (n <= kSmallMax) {
+        const int small_n = static_cast<int>(n);
+        if (n <= 4 * kThreads)
+            hipLaunchKernelGGL(small_metrics_kernel<4>, dim3(1), dim3(kThreads), 0, st, ylt, small_n, ma, n_probs, out,
+                               tail);
+        else
+            hipLaunchKernelGGL(small_metrics_kernel<kSmallPer>, dim3(1), dim3(kThreads), 0, st, ylt, small_n, ma, n_probs,
+                               out, tail);
+        return hipGetLastError();
+    }
+    hipError_t err;
+    if (!*primed) {
+        if ((err = launch_metrics_prime(scratch, st)) != hipSuccess) return err;
+    }
+    *primed = false;
+    const int b = sum_blocks(n);
+    hipLaunchKernelGGL(sum_max_kernel, dim3(b), dim3(kThreads), 0, st, ylt, n, s);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    if ((err = launch_selection(ylt, n, ma, n_probs, s, b, out, tail, st)) != hipSuccess) return err;
+    *primed = true;
+    return hipSuccess;
+}
 
 }  // namespace
 
@@ -561,68 +762,42 @@ int64_t metrics_scratch_bytes(int n_probs, int64_t n) {
     return base + static_cast<int64_t>(n_probs) * n * static_cast<int64_t>(sizeof(uint64_t));
 }
 
-namespace {
-// workgroups of `threads` threads for eight values per thread, at most kSumBlocks
-int hist_blocks(int64_t n, int threads) {
-    const int64_t per = static_cast<int64_t>(threads) * 8;
-    int64_t b = (n + per - 1) / per;
-    if (b > kSumBlocks) b = kSumBlocks;
-    if (b < 1) b = 1;
-    return static_cast<int>(b);
-}
-}  // namespace
-
-hipError_t launch_metrics_prime(void* scratch, const int64_t* m_host, int n_probs, hipStream_t st) {
-    if (n_probs > kMaxProbs) return hipErrorInvalidValue;
-    Scratch s = carve(scratch, n_probs);
-    MArgs ma{};
-    for (int q = 0; q < n_probs; ++q) ma.m[q] = m_host[q];
-    hipLaunchKernelGGL(select_init_kernel, dim3(16), dim3(256), 0, st, s, ma, n_probs);
+hipError_t launch_metrics_prime(void* scratch, hipStream_t st) {
+    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(64), 0, st, carve(scratch));
     return hipGetLastError();
 }
 
-hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs,
-                          void* scratch, bool primed, MetricsOut out, int n_cu, hipStream_t st) {
-    if (n_probs > kMaxProbs) return hipErrorInvalidValue;
-    (void)n_cu;
-    Scratch s = carve(scratch, n_probs);
-    MArgs ma{};
-    for (int q = 0; q < n_probs; ++q) ma.m[q] = m_host[q];
-    hipError_t err;
-    // a scratch left by a completed call has a clear first histogram and a
-    // clear error flag; only a new one (or one after a failed launch) needs this
-    if (!primed) {
-        hipLaunchKernelGGL(select_init_kernel, dim3(16), dim3(256), 0, st, s, ma, n_probs);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    // two 12-bit passes (the first also sums for the mean), then one pass that
-    // sums the tail above each 24-bit prefix and collects the keys inside it,
-    // and one workgroup that finishes the selection over those candidates
-    const int h0 = hist_blocks(n, kHist0Threads), h1 = hist_blocks(n, kHist1Threads);
-    hipLaunchKernelGGL(histogram_kernel<kHist0Threads>, dim3(h0), dim3(kHist0Threads), sizeof(uint32_t) * kBins, st,
-                       ylt, n, s, ma, n_probs, 0, 1);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (n_probs == 0) {
-        hipLaunchKernelGGL(final_kernel, dim3(1), dim3(256), 0, st, s, 0, h0, 1, n, out);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(histogram_kernel<kHist1Threads>, dim3(h1), dim3(kHist1Threads),
-                       sizeof(uint32_t) * kBins * n_probs, st, ylt, n, s, ma, n_probs, 1, 0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    int tblocks = static_cast<int>((n + 1023) / 1024);
-    if (tblocks > kSumBlocks) tblocks = kSumBlocks;
-    if (tblocks < 1) tblocks = 1;
-    hipLaunchKernelGGL(collect_kernel, dim3(tblocks), dim3(256), 0, st, ylt, n, s, n_probs);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(256), 0, st, s, n_probs, h0, tblocks, n, out);
-    return hipGetLastError();
+hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch, bool* primed,
+                          MetricsOut out, hipStream_t st) {
+    return launch_all(ylt, n, m_host, n_probs, scratch, primed, out, nullptr, st);
 }
 
-}  // namespace ara
+hipError_t launch_combine_metrics(const double* part_hi, const float* part_lo, int P, int64_t n, const LayerArgs* L_dev,
+                                  double* ylt, const int64_t* m_host, int n_probs, void* scratch, MetricsOut out,
+                                  hipStream_t st) {
+    if (n_probs > kMaxProbs || n <= kSmallMax) return hipErrorInvalidValue;
+    const Scratch s = carve(scratch);
+    MArgs ma{};
+    for (int q = 0; q < n_probs; ++q) ma.m[q] = m_host[q];
+    // a workgroup per 1024 trials, up to kSumBlocks (two per CU)
+    const int64_t want = (n + kThreads - 1) / kThreads;
+    const int b = static_cast<int>(want < kSumBlocks ? want : kSumBlocks);
+    hipLaunchKernelGGL(combine_sum_max_kernel, dim3(b), dim3(kThreads), 0, st, part_hi, part_lo, P, n, L_dev, ylt, s);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    return launch_selection(ylt, n, ma, n_probs, s, b, out, nullptr, st);
+}
 
-namespace ara {
+bool combine_metrics_apply(int64_t n) { return n > kSmallMax; }
 
 int64_t tail_stats_scratch_bytes(int64_t n) { return metrics_scratch_bytes(1, n); }
+
+// the m-th largest year loss with the counts above and at it: the metrics'
+// launches, whose last workgroup writes the statistics instead
+hipError_t launch_tail_stats(const double* ylt, int64_t n, int64_t m, void* scratch, TailStats* out, hipStream_t st) {
+    bool primed = false;
+    return launch_all(ylt, n, &m, 1, scratch, &primed, MetricsOut{}, out, st);
+}
 
 // The device address of `scratch` on the current device, looked up once per
 // device (with that device current) and kept; later calls reuse it.  No
@@ -644,105 +819,6 @@ hipError_t metrics_noalloc_scratch(void** ptr, int64_t* capacity) {
     *ptr = addr[dev];
     *capacity = kStaticBytes;
     return hipSuccess;
-}
-
-namespace {
-
-// After collect_kernel for one tail count m: the m-th largest key, chosen
-// among the candidates inside its 24-bit prefix as finish_kernel does, the
-// count of year losses above it (those above the prefix, counted by
-// collect_kernel, plus the candidates above it) and the count equal to it
-// (all of them are candidates).  One workgroup.
-__global__ __launch_bounds__(256) void tail_select_kernel(Scratch s, int n_tail_part, TailStats* out) {
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
-    __shared__ uint64_t keys[kDirect];
-    __shared__ uint64_t found;
-    __shared__ unsigned long long red[2][4];
-    SelState st = s.st[0];                          // written by the collect pass
-    const int64_t c = static_cast<int64_t>(s.ccount[0]);
-    const uint64_t* cand = s.cand;
-    if (c <= kDirect) {
-        for (int64_t j = threadIdx.x; j < c; j += blockDim.x) keys[j] = cand[j];
-        __syncthreads();
-        for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-            const uint64_t kj = keys[j];
-            int64_t gt = 0, ge = 0;
-            for (int64_t i = 0; i < c; ++i) {
-                gt += keys[i] > kj;
-                ge += keys[i] >= kj;
-            }
-            if (gt < st.k && st.k <= ge) found = kj;          // every such thread writes the same key
-        }
-        __syncthreads();
-        st.prefix = found;
-        st.mask = ~uint64_t(0);
-        __syncthreads();
-    }
-    for (int pass = 2; pass < kPasses && c > kDirect; ++pass) {
-        for (int i = threadIdx.x; i < kBins; i += blockDim.x) hist[i] = 0;
-        __syncthreads();
-        const int shift = kShift[pass];
-        const uint64_t dmask = (uint64_t(1) << kBits[pass]) - 1;
-        for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-            const uint64_t key = cand[j];
-            if ((key & st.mask) == st.prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
-        }
-        __syncthreads();
-        st = choose_digit(hist, st, pass);
-    }
-    const uint64_t vk = st.prefix;
-    unsigned long long gt = 0, eq = 0;
-    for (int i = threadIdx.x; i < n_tail_part; i += blockDim.x)
-        gt += static_cast<unsigned long long>(s.part_cnt[kSumBlocks + i]);
-    for (int64_t j = threadIdx.x; j < c; j += blockDim.x) {
-        const uint64_t key = cand[j];
-        gt += key > vk;
-        eq += key == vk;
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-        gt += __shfl_xor(gt, off, kWave);
-        eq += __shfl_xor(eq, off, kWave);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = gt;
-        red[1][threadIdx.x >> 6] = eq;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        out->v_bits = vk;
-        out->m = st.m;
-        out->c_gt = static_cast<int64_t>(red[0][0] + red[0][1] + red[0][2] + red[0][3]);
-        out->c_eq = static_cast<int64_t>(red[1][0] + red[1][1] + red[1][2] + red[1][3]);
-    }
-}
-
-}  // namespace
-
-// the m-th largest year loss with the counts above and at it: the selection of
-// launch_metrics (two 12-bit passes, the candidates inside the 24-bit prefix,
-// one workgroup over them), five launches
-hipError_t launch_tail_stats(const double* ylt, int64_t n, int64_t m, void* scratch, TailStats* out,
-                             int n_cu, hipStream_t st) {
-    (void)n_cu;
-    Scratch s = carve(scratch, 1);
-    MArgs ma{};
-    ma.m[0] = m;
-    hipError_t err;
-    hipLaunchKernelGGL(select_init_kernel, dim3(16), dim3(256), 0, st, s, ma, 1);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(histogram_kernel<kHist0Threads>, dim3(hist_blocks(n, kHist0Threads)), dim3(kHist0Threads),
-                       sizeof(uint32_t) * kBins, st, ylt, n, s, ma, 1, 0, 0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(histogram_kernel<kHist1Threads>, dim3(hist_blocks(n, kHist1Threads)), dim3(kHist1Threads),
-                       sizeof(uint32_t) * kBins, st, ylt, n, s, ma, 1, 1, 0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    int tblocks = static_cast<int>((n + 1023) / 1024);
-    if (tblocks > kSumBlocks) tblocks = kSumBlocks;
-    if (tblocks < 1) tblocks = 1;
-    hipLaunchKernelGGL(collect_kernel, dim3(tblocks), dim3(256), 0, st, ylt, n, s, 1);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(tail_select_kernel, dim3(1), dim3(256), 0, st, s, tblocks, out);
-    return hipGetLastError();
 }
 
 }  // namespace ara

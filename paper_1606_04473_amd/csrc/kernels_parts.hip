@@ -1671,18 +1671,6 @@ constexpr int kNetsThreads = 1024;              // one workgroup per CU: its wav
 constexpr int kNetsStageBytes = 37 * 1024;     // the waves' queues and flag rows
 constexpr int kCoarseBytes = 160 * 1024 - kNetsStageBytes;   // LDS left for the coarse map
 
-// value moved across lanes by a DPP control; lanes without a source get 0
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kCtrl, kRowMask, 0xF, false));
-}
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const uint64_t b = __double_as_longlong(v);
-    const uint32_t lo = dpp_u32<kCtrl, kRowMask>(static_cast<uint32_t>(b));
-    const uint32_t hi = dpp_u32<kCtrl, kRowMask>(static_cast<uint32_t>(b >> 32));
-    return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
-}
 // One stage of a segmented double-double scan: (f, h, l) becomes
 // left (+) self, where a lane that starts a segment (f set) keeps its sum.
 template <int kCtrl, int kRowMask>

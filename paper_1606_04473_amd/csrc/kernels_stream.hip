@@ -1144,6 +1144,10 @@ int64_t stream_partials_bytes(const StreamLayout& lay, int64_t trials) {
     return static_cast<int64_t>(sizeof(double) + sizeof(float)) * n + 256;
 }
 
+const float* stream_partials_lo(const StreamLayout& lay, const void* partials, int64_t trials) {
+    return reinterpret_cast<const float*>(static_cast<const double*>(partials) + static_cast<int64_t>(lay.P) * trials);
+}
+
 namespace {
 
 StreamPassArgs pass_args(const StreamLayout& lay, const LayerArgs& L, void* part_scratch, int n_img_parts) {
@@ -1267,7 +1271,7 @@ hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, co
                                  const void* partials, double* ylt, double* S, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     const double* hi = static_cast<const double*>(partials);
-    const float* lo = reinterpret_cast<const float*>(hi + static_cast<int64_t>(lay.P) * L.trial_count);
+    const float* lo = stream_partials_lo(lay, partials, L.trial_count);
     const int64_t blocks = (L.trial_count + 255) / 256;
     hipLaunchKernelGGL(stream_combine_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, hi, lo, lay.P,
                        L.trial_count, L.aggR, L.aggL, L_dev, ylt, S);
