@@ -27,7 +27,7 @@
  *     Calls with device outputs are asynchronous on `stream`.
  *   - Tables are read-only after creation: several threads may run layers on
  *     the same tables concurrently, on different streams.  The scratch of
- *     ara_run_layers (per-layer sequences), ara_run_portfolio, ara_event_nets
+ *     ara_run_layers (pass_variant 0), ara_run_portfolio, ara_event_nets
  *     and ara_risk_metrics is device memory kept between calls (by the
  *     tables, or by the library per device for the metrics): a call reuses a
  *     buffer last used on its own stream at once, one last used on another
@@ -69,13 +69,15 @@ typedef int32_t ara_status;
 #define ARA_PER_LAYER    (1u << 3)  /* ara_run_layers with several layers and pass_variant 1: one
                                        launch sequence per layer instead of the batched launch (a
                                        fold per layer, then one persistent pass over a (layer, tile)
-                                       work list sorted by decreasing cost).  With pass_variant 0
-                                       (the default) or 2 layers always run one sequence each. */
+                                       work list sorted by decreasing cost).  No effect with
+                                       pass_variant 0 (the default; over the 16-bit stream copy
+                                       batches of layers share a fold, a pass and a combine
+                                       launch) or 2 (one sequence per layer). */
 #define ARA_GRAPH        (1u << 4)  /* ara_run_layers: replay a HIP graph of the whole call, captured
                                        on first use for this shape (layer count, trial ranges,
                                        output pointer; with pass_variant 1 also the ELT counts) --
-                                       the per-layer sequences, or with pass_variant 1 and several
-                                       layers the batched launch.  Terms and ELT choices may change
+                                       the launches of pass_variant 0 or 2, or with pass_variant 1
+                                       and several layers the batched launch.  Terms and ELT choices may change
                                        between replays (they are copied to the device only when
                                        they differ from the last replay's, so repeated replays
                                        queue without host waits).  Requires a
@@ -443,8 +445,9 @@ ara_status ara_debug_read(ara_tables* tables, const ara_layer* layer, int32_t wh
 /*
  * ara_run_portfolio -- Algorithm 1: for each program of the portfolio PF
  * (Section IV-A), for each of its layers, the YET split into n_splits
- * contiguous trial ranges YET_i, each analysed as its own launch sequence,
- * and the layer's YLT populated from the parts.  The paper gives no rule for
+ * contiguous trial ranges YET_i, each analysed by itself (over the 16-bit
+ * stream copy ranges of several layers share launches, and neighbouring
+ * ranges of a layer are one), and the layer's YLT populated from the parts.  The paper gives no rule for
  * combining layers; a program's year loss is read as the per-trial sum of
  * its layers' year losses, the portfolio's as the sum over all its layers
  * (no terms above the layer).  Both sums are accumulated in double-double

@@ -191,8 +191,6 @@ constexpr int kImgRank16 = (1 << kImgShift) / 128;
 constexpr int kImgBase32 = (1 << kImgShift) / 4096;
 constexpr int64_t kImgPartBytes = int64_t(kImgWords) * 8 + int64_t(kImgRank16) * 2 + int64_t(kImgBase32) * 4;
 double* part_compact_values(void* part_scratch, int P);
-// each superblock's nonzero o(E) packed in event order at the start of its 4096-value slot
-double* part_stage_values(void* part_scratch, int P);
 // nonzero o(E) per 4096-event superblock, P * 64 of them, after launch_fold_parts
 uint32_t* part_superblock_counts(void* part_scratch, int P);
 
@@ -224,7 +222,24 @@ void free_stream_layout(StreamLayout* L, hipStream_t s);
 int64_t stream_partials_bytes(const StreamLayout& lay, int64_t trials);
 // where the low parts of the partial sums start
 const float* stream_partials_lo(const StreamLayout& lay, const void* partials, int64_t trials);
-// the streaming pass: reads the part images and compact values that
+// where a fold's outputs for one or more layers lie: part images, superblock
+// counts, packed values, with the strides from layer to layer (bytes, superblocks)
+struct FoldViews {
+    uint8_t* img;
+    uint32_t* sb_count;
+    double* stage;
+    int64_t img_stride, sb_stride;
+};
+FoldViews fold_views(void* part_scratch, int P);        // launch_fold_parts' one layer
+// the folds of n_layers layers in one launch, terms from L_dev[0..n_layers)
+int64_t fold_batch_bytes(int n_layers, int P);
+FoldViews fold_batch_views(void* scratch, int n_layers, int P);
+hipError_t launch_fold_batch(const SparsePool& sp, int64_t C, const LayerArgs* L_dev, int n_layers, int P, void* scratch,
+                             hipStream_t s);
+// layer arguments to device memory through kernel arguments (no staging to wait for)
+hipError_t launch_store_terms(const LayerArgs* L, int n, LayerArgs* dst, hipStream_t s);
+
+// the streaming pass: reads the part images and packed values that
 // launch_fold_parts wrote to part_scratch (n_img_parts 2^18-event parts), writes
 // per-(stream part, trial) partial sums; the combine merges them in part order
 // `density`: the layer's estimated share of catalogue events with a loss (chooses among variants only)
@@ -232,6 +247,21 @@ hipError_t launch_stream_pass(const StreamLayout& lay, double density, const Lay
                               int n_img_parts, void* partials, int n_cu, hipStream_t s);
 hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, const LayerArgs* L_dev,
                                  const void* partials, double* ylt, double* S, hipStream_t s);
+// the same for several layers or trial ranges in one launch each (at most
+// stream_batch_max() units): `layer` indexes the fold's views and L_dev, the
+// unit's year losses go to ylt + out_at.  Partials of stream_partials_bytes(all
+// units' trials).
+struct StreamUnit {
+    int32_t layer;
+    int64_t t_lo, count;
+    int64_t out_at;
+    double density;
+};
+int stream_batch_max();
+hipError_t launch_stream_pass_units(const StreamLayout& lay, const StreamUnit* units, int n, const FoldViews& fold,
+                                    int n_img_parts, void* partials, int n_cu, hipStream_t s);
+hipError_t launch_stream_combine_units(const StreamLayout& lay, const StreamUnit* units, int n, const LayerArgs* L_dev,
+                                       const void* partials, double* ylt, hipStream_t s);
 struct TailStats;
 // the backward histogram over the same stream: for the trials inside the
 // aggregate band, occurrences of each nonzero-o(E) event added to w_mean and

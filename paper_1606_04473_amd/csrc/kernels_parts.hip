@@ -20,6 +20,8 @@
 //    adds the part's partial sum (double-double) into the trial's LDS
 //    accumulator; the trial's owner and the part order are fixed, so the
 //    result does not depend on scheduling.
+#include <cstddef>
+#include <cstring>
 #include <vector>
 
 #include "ara_internal.hpp"
@@ -526,9 +528,41 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
 __global__ __launch_bounds__(kFoldThreads) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
     fold_image_body(sp, C, L, out);
 }
+// layer blockIdx.y of several
 __global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool sp, int64_t C,
-                                                             const LayerArgs* __restrict__ L, FoldOut out) {
-    fold_image_body(sp, C, *L, out);
+                                                                      const LayerArgs* __restrict__ L, FoldOut out,
+                                                                      int64_t img_stride, int64_t sb_stride) {
+    out.img += blockIdx.y * img_stride;
+    out.sb_count += blockIdx.y * sb_stride;
+    out.stage += blockIdx.y * sb_stride * kSuper;
+    fold_image_body(sp, C, L[blockIdx.y], out);
+}
+
+// Layer arguments packed into kernel arguments (which take 4 KB): per layer the
+// fixed fields, then its J indices (padded to whole doubles), retentions and limits
+constexpr int kTermsHead = static_cast<int>(offsetof(LayerArgs, idx) / 4);
+constexpr int kTermsLayers = 16;
+struct TermsPack {
+    uint32_t words[864];
+    int32_t start[kTermsLayers];
+};
+static_assert(sizeof(TermsPack) <= 3600 && kTermsHead + 5 * kMaxJ <= 864, "layer arguments as kernel arguments");
+__host__ __device__ constexpr int terms_words(int J) { return kTermsHead + ((J + 1) & ~1) + 4 * J; }
+
+// one workgroup per layer of the pack
+__global__ __launch_bounds__(256) void store_terms_kernel(TermsPack p, LayerArgs* __restrict__ dst) {
+    const uint32_t* src = p.words + p.start[blockIdx.x];
+    uint32_t* d = reinterpret_cast<uint32_t*>(dst + blockIdx.x);
+    const int J = static_cast<int>(src[0]), Je = (J + 1) & ~1;
+    for (int i = threadIdx.x; i < terms_words(J); i += blockDim.x) {
+        int at = i;                                     // head and indices lie as in LayerArgs
+        if (i >= kTermsHead + Je) {
+            const int k = i - kTermsHead - Je;
+            at = k < 2 * J ? static_cast<int>(offsetof(LayerArgs, R) / 4) + k
+                           : static_cast<int>(offsetof(LayerArgs, Lim) / 4) + k - 2 * J;
+        }
+        d[at] = src[i];
+    }
 }
 
 // After the fold: each superblock's global rank (the nonzero count of the
@@ -1657,7 +1691,29 @@ PartScratch carve_parts(void* scratch, int P) {
 }  // namespace
 
 double* part_compact_values(void* part_scratch, int P) { return carve_parts(part_scratch, P).compact; }
-double* part_stage_values(void* part_scratch, int P) { return carve_parts(part_scratch, P).stage; }
+FoldViews fold_views(void* part_scratch, int P) {
+    const PartScratch ps = carve_parts(part_scratch, P);
+    return FoldViews{ps.img, ps.sb_count, ps.stage, 0, 0};
+}
+// [layer] images, [layer] superblock counts, [layer] packed values
+FoldViews fold_batch_views(void* scratch, int n_layers, int P) {
+    const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
+    char* p = static_cast<char*>(scratch);
+    FoldViews v;
+    v.img = reinterpret_cast<uint8_t*>(p);
+    v.img_stride = part_image_bytes(P);
+    p += (v.img_stride * n_layers + 255) & ~int64_t(255);
+    v.sb_count = reinterpret_cast<uint32_t*>(p);
+    v.sb_stride = n_sb;
+    p += (static_cast<int64_t>(sizeof(uint32_t)) * n_sb * n_layers + 255) & ~int64_t(255);
+    v.stage = reinterpret_cast<double*>(p);
+    return v;
+}
+int64_t fold_batch_bytes(int n_layers, int P) {
+    const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
+    return n_layers * (part_image_bytes(P) + static_cast<int64_t>(sizeof(uint32_t)) * n_sb +
+                       static_cast<int64_t>(sizeof(double)) * n_sb * kSuper) + 512;
+}
 uint32_t* part_superblock_counts(void* part_scratch, int P) { return carve_parts(part_scratch, P).sb_count; }
 
 // ---------------------------------------------------------------------------
@@ -2307,13 +2363,46 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
     hipError_t e;
     if (L_dev)
         hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(kFoldThreads), 0, s, sp, C, L_dev,
-                           out);
+                           out, int64_t(0), int64_t(0));
     else
         hipLaunchKernelGGL(fold_image_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(kFoldThreads), 0, s, sp, C, L, out);
     if ((e = hipGetLastError()) != hipSuccess || !compact) return e;
     hipLaunchKernelGGL(compact_stage_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, ps.stage,
                        ps.sb_count, ps.img, ps.compact);
     return hipGetLastError();
+}
+
+hipError_t launch_fold_batch(const SparsePool& sp, int64_t C, const LayerArgs* L_dev, int n_layers, int P, void* scratch,
+                             hipStream_t s) {
+    const FoldViews v = fold_batch_views(scratch, n_layers, P);
+    const FoldOut out{nullptr, v.img, v.sb_count, v.stage, nullptr, nullptr, 0};
+    hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(v.sb_stride), static_cast<uint32_t>(n_layers)),
+                       dim3(kFoldThreads), 0, s, sp, C, L_dev, out, v.img_stride, v.sb_stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_store_terms(const LayerArgs* L, int n, LayerArgs* dst, hipStream_t s) {
+    static_assert(offsetof(LayerArgs, J) == 0 && offsetof(LayerArgs, idx) % 8 == 0, "packed layer arguments");
+    for (int i = 0; i < n;) {
+        TermsPack p{};
+        int k = 0, at = 0;
+        for (; i + k < n && k < kTermsLayers && at + terms_words(L[i + k].J) <= 864; ++k) {
+            const LayerArgs& a = L[i + k];
+            const int Je = (a.J + 1) & ~1;
+            uint32_t* w = p.words + at;
+            p.start[k] = at;
+            std::memcpy(w, &a, 4 * kTermsHead);
+            std::memcpy(w + kTermsHead, a.idx, 4 * static_cast<size_t>(a.J));
+            std::memcpy(w + kTermsHead + Je, a.R, 8 * static_cast<size_t>(a.J));
+            std::memcpy(w + kTermsHead + Je + 2 * a.J, a.Lim, 8 * static_cast<size_t>(a.J));
+            at += terms_words(a.J);
+        }
+        hipLaunchKernelGGL(store_terms_kernel, dim3(static_cast<uint32_t>(k)), dim3(256), 0, s, p, dst + i);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        i += k;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_part_pass(const PartLayout& lay, int64_t N, const LayerArgs& L, void* scratch, double* ylt,

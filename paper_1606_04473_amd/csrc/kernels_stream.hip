@@ -35,6 +35,7 @@
 //    the trials inside the aggregate band, and the TVaR weights of the tail
 //    trials) is the same kernel instantiated with kAdj: the same test and
 //    queue, a drain that counts occurrences in LDS instead of summing losses.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -272,16 +273,17 @@ struct StreamPassArgs {
     const int64_t* part_base;
     const uint32_t* gstart;
     const uint16_t* gend;
-    const uint8_t* img;             // part images of the 2^18-event parts
-    const uint32_t* sb_count;       // nonzero o(E) of each 4096-event superblock
-    const double* stage;            // [superblock][4096]: its nonzero o(E), packed in event order
+    const uint8_t* img;             // [layer] part images of the 2^18-event parts
+    const uint32_t* sb_count;       // [layer] nonzero o(E) of each 4096-event superblock
+    const double* stage;            // [layer][superblock][4096]: its nonzero o(E), packed in event order
+    int64_t img_stride, sb_stride;  // from layer to layer, bytes and superblocks
     int P;
     int G;
     int K;                          // kSplit: units per group
+    int n_seg;
     int64_t NG;
-    int64_t g_lo, g_hi;             // groups holding the layer's trials
-    int64_t t_lo, t_hi;
-    double* part_hi;                // [P][t_hi - t_lo]
+    int64_t work;                   // of all segments (Seg::w0 and weight)
+    double* part_hi;                // per segment [P][trials]
     float* part_lo;
     const uint16_t* pad;            // 16 readable bytes of 0xFFFF
     int n_xcd;
@@ -291,6 +293,22 @@ struct StreamPassArgs {
 // drain, the same with several lanes per trial where that fills the wave, or
 // (with those) single units of a group's trials
 enum class PassMode { plain, spread, split };
+
+// One layer over one range of trials: its (part, group) items follow the earlier
+// segments' in the work list, each counting `weight`.
+struct Seg {
+    int64_t t_lo, t_hi;
+    int64_t g_lo;                   // first group that holds its trials
+    int64_t units;                  // groups (kSplit: units) per part
+    int64_t w0;                     // work before it
+    int64_t part_at;                // its partial sums' place
+    int32_t weight;
+    int32_t layer;
+};
+constexpr int kMaxSegs = 32;
+struct SegList {
+    Seg seg[kMaxSegs];
+};
 
 // bit if the lane's condition holds, else 0: one select on the compare's lane
 // mask, so the compare that also guards the lane's queue append is not redone
@@ -337,11 +355,15 @@ struct StreamAdjArgs {
 // counters, and the TVaR weights of the few tail trials, use global atomics).
 // All weights are integers, so the order of the additions does not matter.
 //
+// The work list covers one or more segments (layers over trial ranges): many
+// layers share a launch, so its start and its end and the images are paid once
+// per workgroup's share and not once per layer.
+//
 // gstart_all is a.gstart again, as a restrict-qualified parameter: its loads at
 // wave-uniform addresses then go through the scalar unit, so a group's range
 // never waits on the vector loads in flight
 template <bool kAdj, PassMode kMode>
-__global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, StreamAdjArgs adj,
+__global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, SegList segs, StreamAdjArgs adj,
                                                            const uint32_t* __restrict__ gstart_all) {
     constexpr bool kSplit = kMode == PassMode::split, kSpread = kMode != PassMode::plain;
     constexpr int kU = 2;                                     // 16-byte loads per lane per batch
@@ -378,19 +400,16 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     uint16_t* q = reinterpret_cast<uint16_t*>(lds + kQueueOff) + wv * kQ;
     const int G = a.G;
-    const int64_t count = a.t_hi - a.t_lo;
     TailStats ts{};
     if constexpr (kAdj) ts = *adj.tail;
 
-    // the (part, group) work list, part-major; workgroup b runs on XCD b % n_xcd,
-    // and each XCD takes a contiguous share of the list
-    const int64_t NGr = (a.g_hi - a.g_lo) * (kSplit ? a.K : 1);
-    const int64_t n_items = static_cast<int64_t>(a.P) * NGr;
+    // the work list, segment after segment, in a segment the (part, group) items
+    // part-major; workgroup b runs on XCD b % n_xcd, and each XCD takes a
+    // contiguous share of the work
     const int64_t n_wg = gridDim.x;
     const int64_t per_x = n_wg / a.n_xcd;
     const int64_t l = static_cast<int64_t>(blockIdx.x % a.n_xcd) * per_x + blockIdx.x / a.n_xcd;
-    int64_t it = l * n_items / n_wg;
-    const int64_t it_end = (l + 1) * n_items / n_wg;
+    const int64_t w_begin = l * a.work / n_wg, w_end = (l + 1) * a.work / n_wg;
 
     // the backward's counters to W_mean once every wave is done with the part,
     // in the byte map's event order; the part before the first has none
@@ -413,552 +432,565 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Str
         }
     };
 
-    while (it < it_end) {
-        if constexpr (kAdj) {
-            if (prev_pq >= 0) flush_counts();
-        }
-        const int pq = static_cast<int>(it / NGr);
-        const int64_t seg_end = min(it_end, static_cast<int64_t>(pq + 1) * NGr);
-        // groups of the part, or with kSplit units: K per group from a.g_lo's first
-        const int64_t ga = (kSplit ? 0 : a.g_lo) + (it - static_cast<int64_t>(pq) * NGr);
-        const int64_t gb = (kSplit ? 0 : a.g_lo) + (seg_end - static_cast<int64_t>(pq) * NGr);
-        it = seg_end;
-        // ---- the LDS image of stream part pq, from its quarter of the part
-        // image of a 2^18-event part: bitmap, ranks of 128-event blocks inside
-        // their superblock, and the counts and packed losses of its 16
-        // superblocks.  Every global load of the bitmap, the ranks and the
-        // counts, and then eight losses per lane, are in flight together.
-        const uint8_t* gimg = a.img + static_cast<int64_t>(pq >> 2) * kImgPartBytes;
-        const u64x2* gbm = reinterpret_cast<const u64x2*>(gimg) + (pq & 3) * (kImgWords / 8);
-        const uint16_t* gr16 =
-            reinterpret_cast<const uint16_t*>(gimg + int64_t(kImgWords) * 8) + (pq & 3) * (kImgRank16 / 4);
-        const double* gstage = a.stage + static_cast<int64_t>(pq) * kQSize;
-        uint32_t sb_n = a.sb_count[static_cast<int64_t>(pq) * kPartSuper + (lane & (kPartSuper - 1))];
-        u64x2 words[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) words[k] = gbm[(k * 1024 + static_cast<int>(threadIdx.x)) >> 3];
-        const uint32_t r16 = threadIdx.x < kQSize / 128 ? gr16[threadIdx.x] : 0u;
-        // ranks of the superblocks' first nonzero events (lane i: superblock i % 16)
-        uint32_t sb_end = sb_n;
-#pragma unroll
-        for (int off = 1; off < kPartSuper; off <<= 1) {
-            const uint32_t v = static_cast<uint32_t>(__shfl_up(static_cast<int>(sb_end), off, kPartSuper));
-            if ((lane & (kPartSuper - 1)) >= off) sb_end += v;
-        }
-        const uint32_t sb_start = sb_end - sb_n;
-        const uint32_t n_vals = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_end), kPartSuper - 1));
-        // when every rank fits the LDS copy of the losses (the counters) the
-        // drain skips the L2 fallback (the global atomics)
-        const bool fits = n_vals <= static_cast<uint32_t>(kAdj ? kCnt : kCap);
-        __syncthreads();
-        // byte map, 16 events per thread and round, one 16-byte store each: per
-        // four events the bits spread to bytes, their inclusive prefix sum, plus
-        // the count of the block's earlier events in every byte
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = k * 1024 + static_cast<int>(threadIdx.x);
-            const uint32_t sh = (i & 3) * 16;
-            const uint64_t w = (i & 4) ? words[k].y : words[k].x;
-            uint32_t before = static_cast<uint32_t>(__popcll(w & ((1ull << sh) - 1ull)));
-            if (i & 4) before += static_cast<uint32_t>(__popcll(words[k].x));
-            const uint32_t bits = static_cast<uint32_t>(w >> sh) & 0xFFFFu;
-            uint32_t run = before * 0x01010101u;
-            u32x4 out;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const uint32_t one = (((bits >> (4 * b)) & 15u) * 0x00204081u) & 0x01010101u;
-                const uint32_t two = one + (one << 8);
-                const uint32_t sum = two + (two << 16) + run;
-                out[b] = sum & ((one << 8) - one);
-                run = __builtin_amdgcn_perm(sum, sum, 0x03030303u);
-            }
-            reinterpret_cast<u32x4*>(map)[i] = out;
-        }
-        if (threadIdx.x < kQSize / 128) {           // two superblocks of 32 blocks per wave
-            const int sb = 2 * wv + (lane >> 5);
-            const uint32_t s0 = static_cast<uint32_t>(__shfl(static_cast<int>(sb_start), sb));
-            bases[threadIdx.x] = (fits ? s0 : static_cast<uint32_t>(sb) * kSuperEvents) + r16 - 1u;
-        }
-        if constexpr (kAdj) {
-            for (int k = threadIdx.x; k < kCnt; k += blockDim.x) cnt[k] = 0u;
-        } else {
-            // wave w copies superblock w's losses
-            const uint32_t n0 =
-                fits ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_start), wv)) : wv * kSbCap;
-            const uint32_t nw = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_n), wv));
-            const uint32_t take = fits || nw < kSbCap ? nw : kSbCap;
-            const double* src = gstage + wv * kSuperEvents;
-            for (uint32_t j0 = 0; j0 < take; j0 += 64 * 8) {
-                double v[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t j = j0 + k * 64 + lane;
-                    v[k] = src[j < take ? j : 0u];
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t j = j0 + k * 64 + lane;
-                    if (j < take) vals[n0 + j] = v[k];
-                }
-            }
-            if (threadIdx.x == 0) vals[kCap] = 0.0;
-        }
-        __syncthreads();
-
-        // ---- this wave's groups [wa, wb) of the part
-        const int64_t n = gb - ga;
-        const int64_t wa = ga + wv * n / 16, wb = ga + (wv + 1) * n / 16;
-        if constexpr (kAdj) {
-            prev_pq = pq;
-            prev_fits = fits;
-        }
-        if (wa >= wb) continue;
-        const uint16_t* ids = a.ids + a.part_base[pq];
-        const uint32_t* gs = gstart_all + static_cast<int64_t>(pq) * (a.NG + 1);
-        const uint16_t* ge = a.gend + static_cast<int64_t>(pq) * a.NG * kStreamGroupSlots;
-        double* out_hi = a.part_hi + static_cast<int64_t>(pq) * count;
-        float* out_lo = a.part_lo + static_cast<int64_t>(pq) * count;
-        const int64_t ebase = static_cast<int64_t>(pq) << kStreamShift;   // catalogue ID of the part's event 0
-        // B, lane i: where trial i of group g starts; lanes >= G: the group's
-        // end.  The next group's trial ends are loaded with every batch (every
-        // lane loads, lane 0 then drops its value; no value is carried over, so
-        // no copy waits on the load) and added to its start when it begins.
-        // The backward loads the next group's trial classes alongside.
-        auto group_ends = [&](int64_t gg) -> uint32_t {
-            return ge[gg * kStreamGroupSlots + (lane == 0 ? 0 : lane - 1)];
+    for (int sg = 0; sg < (kAdj ? 1 : a.n_seg); ++sg) {       // the backward takes one segment
+        const Seg sgm = segs.seg[sg];
+        const int64_t NGr = sgm.units;
+        // a work position's item in this segment (shared ends of neighbouring shares agree)
+        auto item_at = [&](int64_t w) -> int64_t {
+            const int64_t d = w - sgm.w0, n = static_cast<int64_t>(a.P) * NGr;
+            return d <= 0 ? 0 : (d >= n * sgm.weight ? n : d / sgm.weight);
         };
-        auto starts = [&](uint32_t s0, uint32_t ends) -> uint32_t { return lane == 0 ? s0 : s0 + ends; };
-        auto group_class = [&](int64_t gg) -> uint32_t { return adj.cls[(gg - a.g_lo) * 64 + lane]; };
-        // a group's IDs run from its start to the next group's start (its end
-        // rounded up to the 8-ID chunk: the same chunks)
-        int64_t g = kSplit ? a.g_lo + wa / a.K : wa;
-        uint32_t rs = gs[g];
-        uint32_t re = gs[g + 1];
-        uint32_t B = starts(rs, group_ends(g));
-        uint32_t next_ends = 0;
-        uint32_t cls = 0, next_cls = 0;
-        if constexpr (kAdj) cls = group_class(g);
-        uint32_t c = rs;                            // first ID of the batch (a multiple of 8)
-        int tl = 0, th = G;                         // the trials of the group (of the unit) that this wave sums
-        int qs = kInf;                              // lane i: queue index of trial i's first hit
-        int qn = 0;                                 // queue entries
-        double acc_hi = 0.0, acc_lo = 0.0;
-        double held_hi[kHeld];
-        float held_lo[kHeld];
-        int n_held = 0;
-
-        auto load_batch = [&](uint32_t cb, uint32_t end, u32x4* v) {
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const uint32_t cu = cb + u * 64 * kChunkIds + lane * kChunkIds;
-                const uint16_t* src = cu < end ? ids + cu : a.pad;
-                v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src));
-            }
-        };
-        // the batch after the one at c: the rest of this group, else the next group's first
-        auto load_next = [&](u32x4* v) {
-            next_ends = group_ends(g + 1 < wb ? g + 1 : g);
-            if constexpr (kAdj) next_cls = group_class(g + 1 < wb ? g + 1 : g);
-            if (c + kBatch < re) {
-                load_batch(c + kBatch, re, v);
-            } else {
-                const bool more = g + 1 < wb;
-                const uint32_t n_rs = more ? gs[g + 1] : 0u;
-                const uint32_t n_re = more ? gs[g + 2] : 0u;
-                load_batch(n_rs, n_re, v);
-            }
-        };
-        // the queued hits: lane t takes trial t's entries, four at a time.
-        // The loads of a step are issued together.
-        auto rank = [&](uint32_t e) -> uint32_t {
-            // rank among the part's nonzero events: the block's base (minus one)
-            // plus the byte, which is 1 + the rank inside the block
-            return bases[e >> 7] + map[e];
-        };
-        // !fits: an entry's index inside its superblock, and the LDS slot of index i < per
-        auto sb_index = [&](uint32_t rk) -> uint32_t { return rk & (kSuperEvents - 1); };
-        auto sb_slot = [&](uint32_t rk, uint32_t i, uint32_t per) -> uint32_t { return rk / kSuperEvents * per + i; };
-        // With many hits of few trials in the queue (long trials over few
-        // parts, dense layers) one lane per trial leaves most lanes idle: then
-        // 2^s lanes take a trial's entries in turn and their sums are merged,
-        // s as large as the 64 lanes allow with at least four entries a lane on
-        // average.  s depends on the data alone.
-        auto drain = [&]() {
-            constexpr int kR = 4;
-            int lo = __shfl(qs, lane), hi = __shfl(qs, (lane + 1) & 63);
-            lo = lo < 0 ? 0 : (lo > qn ? qn : lo);
-            hi = hi < 0 ? 0 : (hi > qn ? qn : hi);
-            if (lane >= th || (kSplit && lane < tl)) hi = lo;   // lanes without a trial here
+        int64_t it = item_at(w_begin);
+        const int64_t it_end = item_at(w_end);
+        const int64_t t_lo = sgm.t_lo, t_hi = sgm.t_hi, g_lo = sgm.g_lo, count = t_hi - t_lo;
+        while (it < it_end) {
             if constexpr (kAdj) {
-                if (!(cls & 1u)) hi = lo;           // outside the aggregate band: no weight
+                if (prev_pq >= 0) flush_counts();
             }
-            bool spread_done = false;
-            if constexpr (kSpread) {
-            const uint64_t act = __ballot(hi > lo);
-            const int i0 = act ? __builtin_ctzll(act) : 0;
-            const int n_act = act ? 64 - __builtin_clzll(act) - i0 : 1;
-            const int lg_act = n_act > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(n_act - 1)) : 0;
-            const int lg_qn = qn > 0 ? 31 - __builtin_clz(static_cast<uint32_t>(qn)) : 0;
-            const int s = (lg_qn - 2 < 6 ? lg_qn - 2 : 6) - lg_act;
-            if (s > 0) {
-                const int per = 1 << s, slot = lane >> s, sub = lane & (per - 1);
-                const int from = (i0 + slot) & 63;
-                const int mlo = __shfl(lo, from), mhi = __shfl(hi, from);
-                const int jend = slot < n_act ? mhi : mlo;
+            const int pq = static_cast<int>(it / NGr);
+            const int64_t seg_end = min(it_end, static_cast<int64_t>(pq + 1) * NGr);
+            // groups of the part, or with kSplit units: K per group from g_lo's first
+            const int64_t ga = (kSplit ? 0 : g_lo) + (it - static_cast<int64_t>(pq) * NGr);
+            const int64_t gb = (kSplit ? 0 : g_lo) + (seg_end - static_cast<int64_t>(pq) * NGr);
+            it = seg_end;
+            // ---- the LDS image of stream part pq, from its quarter of the part
+            // image of a 2^18-event part: bitmap, ranks of 128-event blocks inside
+            // their superblock, and the counts and packed losses of its 16
+            // superblocks.  Every global load of the bitmap, the ranks and the
+            // counts, and then eight losses per lane, are in flight together.
+            const uint8_t* gimg = a.img + sgm.layer * a.img_stride + static_cast<int64_t>(pq >> 2) * kImgPartBytes;
+            const u64x2* gbm = reinterpret_cast<const u64x2*>(gimg) + (pq & 3) * (kImgWords / 8);
+            const uint16_t* gr16 =
+                reinterpret_cast<const uint16_t*>(gimg + int64_t(kImgWords) * 8) + (pq & 3) * (kImgRank16 / 4);
+            const double* gstage = a.stage + sgm.layer * a.sb_stride * kSuperEvents + static_cast<int64_t>(pq) * kQSize;
+            const uint32_t sb_n =
+                a.sb_count[sgm.layer * a.sb_stride + static_cast<int64_t>(pq) * kPartSuper + (lane & (kPartSuper - 1))];
+            u64x2 words[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) words[k] = gbm[(k * 1024 + static_cast<int>(threadIdx.x)) >> 3];
+            const uint32_t r16 = threadIdx.x < kQSize / 128 ? gr16[threadIdx.x] : 0u;
+            // ranks of the superblocks' first nonzero events (lane i: superblock i % 16)
+            uint32_t sb_end = sb_n;
+#pragma unroll
+            for (int off = 1; off < kPartSuper; off <<= 1) {
+                const uint32_t v = static_cast<uint32_t>(__shfl_up(static_cast<int>(sb_end), off, kPartSuper));
+                if ((lane & (kPartSuper - 1)) >= off) sb_end += v;
+            }
+            const uint32_t sb_start = sb_end - sb_n;
+            const uint32_t n_vals = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_end), kPartSuper - 1));
+            // when every rank fits the LDS copy of the losses (the counters) the
+            // drain skips the L2 fallback (the global atomics)
+            const bool fits = n_vals <= static_cast<uint32_t>(kAdj ? kCnt : kCap);
+            __syncthreads();
+            // byte map, 16 events per thread and round, one 16-byte store each: per
+            // four events the bits spread to bytes, their inclusive prefix sum, plus
+            // the count of the block's earlier events in every byte
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = k * 1024 + static_cast<int>(threadIdx.x);
+                const uint32_t sh = (i & 3) * 16;
+                const uint64_t w = (i & 4) ? words[k].y : words[k].x;
+                uint32_t before = static_cast<uint32_t>(__popcll(w & ((1ull << sh) - 1ull)));
+                if (i & 4) before += static_cast<uint32_t>(__popcll(words[k].x));
+                const uint32_t bits = static_cast<uint32_t>(w >> sh) & 0xFFFFu;
+                uint32_t run = before * 0x01010101u;
+                u32x4 out;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const uint32_t one = (((bits >> (4 * b)) & 15u) * 0x00204081u) & 0x01010101u;
+                    const uint32_t two = one + (one << 8);
+                    const uint32_t sum = two + (two << 16) + run;
+                    out[b] = sum & ((one << 8) - one);
+                    run = __builtin_amdgcn_perm(sum, sum, 0x03030303u);
+                }
+                reinterpret_cast<u32x4*>(map)[i] = out;
+            }
+            if (threadIdx.x < kQSize / 128) {           // two superblocks of 32 blocks per wave
+                const int sb = 2 * wv + (lane >> 5);
+                const uint32_t s0 = static_cast<uint32_t>(__shfl(static_cast<int>(sb_start), sb));
+                bases[threadIdx.x] = (fits ? s0 : static_cast<uint32_t>(sb) * kSuperEvents) + r16 - 1u;
+            }
+            if constexpr (kAdj) {
+                for (int k = threadIdx.x; k < kCnt; k += blockDim.x) cnt[k] = 0u;
+            } else {
+                // wave w copies superblock w's losses
+                const uint32_t n0 =
+                    fits ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_start), wv)) : wv * kSbCap;
+                const uint32_t nw = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sb_n), wv));
+                const uint32_t take = fits || nw < kSbCap ? nw : kSbCap;
+                const double* src = gstage + wv * kSuperEvents;
+                for (uint32_t j0 = 0; j0 < take; j0 += 64 * 8) {
+                    double v[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const uint32_t j = j0 + k * 64 + lane;
+                        v[k] = src[j < take ? j : 0u];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const uint32_t j = j0 + k * 64 + lane;
+                        if (j < take) vals[n0 + j] = v[k];
+                    }
+                }
+                if (threadIdx.x == 0) vals[kCap] = 0.0;
+            }
+            __syncthreads();
+
+            // ---- this wave's groups [wa, wb) of the part
+            const int64_t n = gb - ga;
+            const int64_t wa = ga + wv * n / 16, wb = ga + (wv + 1) * n / 16;
+            if constexpr (kAdj) {
+                prev_pq = pq;
+                prev_fits = fits;
+            }
+            if (wa >= wb) continue;
+            const uint16_t* ids = a.ids + a.part_base[pq];
+            const uint32_t* gs = gstart_all + static_cast<int64_t>(pq) * (a.NG + 1);
+            const uint16_t* ge = a.gend + static_cast<int64_t>(pq) * a.NG * kStreamGroupSlots;
+            double* out_hi = a.part_hi + sgm.part_at + static_cast<int64_t>(pq) * count;
+            float* out_lo = a.part_lo + sgm.part_at + static_cast<int64_t>(pq) * count;
+            const int64_t ebase = static_cast<int64_t>(pq) << kStreamShift;   // catalogue ID of the part's event 0
+            // B, lane i: where trial i of group g starts; lanes >= G: the group's
+            // end.  The next group's trial ends are loaded with every batch (every
+            // lane loads, lane 0 then drops its value; no value is carried over, so
+            // no copy waits on the load) and added to its start when it begins.
+            // The backward loads the next group's trial classes alongside.
+            auto group_ends = [&](int64_t gg) -> uint32_t {
+                return ge[gg * kStreamGroupSlots + (lane == 0 ? 0 : lane - 1)];
+            };
+            auto starts = [&](uint32_t s0, uint32_t ends) -> uint32_t { return lane == 0 ? s0 : s0 + ends; };
+            auto group_class = [&](int64_t gg) -> uint32_t { return adj.cls[(gg - g_lo) * 64 + lane]; };
+            // a group's IDs run from its start to the next group's start (its end
+            // rounded up to the 8-ID chunk: the same chunks)
+            int64_t g = kSplit ? g_lo + wa / a.K : wa;
+            uint32_t rs = gs[g];
+            uint32_t re = gs[g + 1];
+            uint32_t B = starts(rs, group_ends(g));
+            uint32_t next_ends = 0;
+            uint32_t cls = 0, next_cls = 0;
+            if constexpr (kAdj) cls = group_class(g);
+            uint32_t c = rs;                            // first ID of the batch (a multiple of 8)
+            int tl = 0, th = G;                         // the trials of the group (of the unit) that this wave sums
+            int qs = kInf;                              // lane i: queue index of trial i's first hit
+            int qn = 0;                                 // queue entries
+            double acc_hi = 0.0, acc_lo = 0.0;
+            double held_hi[kHeld];
+            float held_lo[kHeld];
+            int n_held = 0;
+
+            auto load_batch = [&](uint32_t cb, uint32_t end, u32x4* v) {
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const uint32_t cu = cb + u * 64 * kChunkIds + lane * kChunkIds;
+                    const uint16_t* src = cu < end ? ids + cu : a.pad;
+                    v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src));
+                }
+            };
+            // the batch after the one at c: the rest of this group, else the next group's first
+            auto load_next = [&](u32x4* v) {
+                next_ends = group_ends(g + 1 < wb ? g + 1 : g);
+                if constexpr (kAdj) next_cls = group_class(g + 1 < wb ? g + 1 : g);
+                if (c + kBatch < re) {
+                    load_batch(c + kBatch, re, v);
+                } else {
+                    const bool more = g + 1 < wb;
+                    const uint32_t n_rs = more ? gs[g + 1] : 0u;
+                    const uint32_t n_re = more ? gs[g + 2] : 0u;
+                    load_batch(n_rs, n_re, v);
+                }
+            };
+            // the queued hits: lane t takes trial t's entries, four at a time.
+            // The loads of a step are issued together.
+            auto rank = [&](uint32_t e) -> uint32_t {
+                // rank among the part's nonzero events: the block's base (minus one)
+                // plus the byte, which is 1 + the rank inside the block
+                return bases[e >> 7] + map[e];
+            };
+            // !fits: an entry's index inside its superblock, and the LDS slot of index i < per
+            auto sb_index = [&](uint32_t rk) -> uint32_t { return rk & (kSuperEvents - 1); };
+            auto sb_slot = [&](uint32_t rk, uint32_t i, uint32_t per) -> uint32_t { return rk / kSuperEvents * per + i; };
+            // With many hits of few trials in the queue (long trials over few
+            // parts, dense layers) one lane per trial leaves most lanes idle: then
+            // 2^s lanes take a trial's entries in turn and their sums are merged,
+            // s as large as the 64 lanes allow with at least four entries a lane on
+            // average.  s depends on the data alone.
+            auto drain = [&]() {
+                constexpr int kR = 4;
+                int lo = __shfl(qs, lane), hi = __shfl(qs, (lane + 1) & 63);
+                lo = lo < 0 ? 0 : (lo > qn ? qn : lo);
+                hi = hi < 0 ? 0 : (hi > qn ? qn : hi);
+                if (lane >= th || (kSplit && lane < tl)) hi = lo;   // lanes without a trial here
                 if constexpr (kAdj) {
-                    const uint32_t mcls = static_cast<uint32_t>(__shfl(static_cast<int>(cls), from));
-                    const unsigned long long wt = (mcls & 6u)
-                        ? static_cast<unsigned long long>((mcls & 2u) ? ts.c_eq : ts.m - ts.c_gt) : 0ull;
-                    for (int j = mlo + sub; j < jend; j += kR * per) {
-                        uint32_t e[kR], rk[kR];
+                    if (!(cls & 1u)) hi = lo;           // outside the aggregate band: no weight
+                }
+                bool spread_done = false;
+                if constexpr (kSpread) {
+                const uint64_t act = __ballot(hi > lo);
+                const int i0 = act ? __builtin_ctzll(act) : 0;
+                const int n_act = act ? 64 - __builtin_clzll(act) - i0 : 1;
+                const int lg_act = n_act > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(n_act - 1)) : 0;
+                const int lg_qn = qn > 0 ? 31 - __builtin_clz(static_cast<uint32_t>(qn)) : 0;
+                const int s = (lg_qn - 2 < 6 ? lg_qn - 2 : 6) - lg_act;
+                if (s > 0) {
+                    const int per = 1 << s, slot = lane >> s, sub = lane & (per - 1);
+                    const int from = (i0 + slot) & 63;
+                    const int mlo = __shfl(lo, from), mhi = __shfl(hi, from);
+                    const int jend = slot < n_act ? mhi : mlo;
+                    if constexpr (kAdj) {
+                        const uint32_t mcls = static_cast<uint32_t>(__shfl(static_cast<int>(cls), from));
+                        const unsigned long long wt = (mcls & 6u)
+                            ? static_cast<unsigned long long>((mcls & 2u) ? ts.c_eq : ts.m - ts.c_gt) : 0ull;
+                        for (int j = mlo + sub; j < jend; j += kR * per) {
+                            uint32_t e[kR], rk[kR];
 #pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2 * per];
+                            for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2 * per];
 #pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                            for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
 #pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) {
-                            if (j + r2 * per >= jend) continue;
-                            const uint32_t i = sb_index(rk[r2]);
-                            if (fits || i < kSbCnt)
-                                atomicAdd(&cnt[fits ? rk[r2] : sb_slot(rk[r2], i, kSbCnt)], 1u);
-                            else
-                                atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
-                            if (wt) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + e[r2]]), wt);
+                            for (int r2 = 0; r2 < kR; ++r2) {
+                                if (j + r2 * per >= jend) continue;
+                                const uint32_t i = sb_index(rk[r2]);
+                                if (fits || i < kSbCnt)
+                                    atomicAdd(&cnt[fits ? rk[r2] : sb_slot(rk[r2], i, kSbCnt)], 1u);
+                                else
+                                    atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
+                                if (wt) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + e[r2]]), wt);
+                            }
+                        }
+                    } else {
+                        double h = 0.0, l = 0.0;
+                        for (int j = mlo + sub; j < jend; j += kR * per) {
+                            // entries past the trial's last read whatever LDS follows
+                            // (inside the allocation), then the 0.0 slot
+                            uint32_t e[kR], rk[kR];
+                            bool valid[kR];
+                            double v[kR];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) {
+                                valid[r2] = j + r2 * per < jend;
+                                e[r2] = q[j + r2 * per];
+                            }
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                            if (fits) {
+#pragma unroll
+                                for (int r2 = 0; r2 < kR; ++r2) v[r2] = vals[valid[r2] ? rk[r2] : kCap];
+                            } else {
+                                bool spill = false;
+#pragma unroll
+                                for (int r2 = 0; r2 < kR; ++r2) {
+                                    const uint32_t i = sb_index(rk[r2]);
+                                    v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                                    spill |= valid[r2] && i >= kSbCap;
+                                }
+                                if (__ballot(spill)) {
+#pragma unroll
+                                    for (int r2 = 0; r2 < kR; ++r2)
+                                        if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
+                                }
+                            }
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) dd_add(h, l, v[r2]);
+                        }
+                        for (int off = per >> 1; off >= 1; off >>= 1) dd_merge(h, l, shfl_xor_f64(h, off), shfl_xor_f64(l, off));
+                        const int back = ((lane - i0) << s) & 63;
+                        const double th_hi = shfl_f64(h, back), th_lo = shfl_f64(l, back);
+                        if (lane >= i0 && lane < i0 + n_act) dd_merge(acc_hi, acc_lo, th_hi, th_lo);
+                    }
+                    spread_done = true;
+                }
+                }
+                if (spread_done) {
+                } else if constexpr (kAdj) {
+                    if (fits) {
+                        // every rank has its LDS counter: whole steps unchecked,
+                        // then the last one to three entries (their queue reads,
+                        // at most two entries past a full queue, stay inside the
+                        // allocation)
+                        int j = lo;
+                        for (; j + kR <= hi; j += kR) {
+                            uint32_t e[kR], rk[kR];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) atomicAdd(&cnt[rk[r2]], 1u);
+                        }
+                        if (j < hi) {
+                            uint32_t e[kR - 1], rk[kR - 1];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR - 1; ++r2) e[r2] = q[j + r2];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR - 1; ++r2) rk[r2] = rank(e[r2]);
+#pragma unroll
+                            for (int r2 = 0; r2 < kR - 1; ++r2)
+                                if (j + r2 < hi) atomicAdd(&cnt[rk[r2]], 1u);
+                        }
+                    } else {
+                        for (int j = lo; j < hi; j += kR) {
+                            uint32_t e[kR], rk[kR];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2) {
+                                if (j + r2 >= hi) continue;
+                                const uint32_t i = sb_index(rk[r2]);
+                                if (i < kSbCnt)
+                                    atomicAdd(&cnt[sb_slot(rk[r2], i, kSbCnt)], 1u);
+                                else
+                                    atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
+                            }
                         }
                     }
+                    if (cls & 6u) {
+                        // a tail trial: its TVaR weight on each of its occurrences
+                        const unsigned long long wt = static_cast<unsigned long long>((cls & 2u) ? ts.c_eq : ts.m - ts.c_gt);
+                        for (int j = lo; j < hi; ++j)
+                            atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + q[j]]), wt);
+                    }
+                } else if (fits) {
+                    // every rank has its value in LDS: whole steps unchecked, then
+                    // the last one to three entries, whose idle slots read the 0.0
+                    // after the copied losses (their queue reads, at most two entries
+                    // past a full queue, stay inside the allocation)
+                    int j = lo;
+                    for (; j + kR <= hi; j += kR) {
+                        uint32_t e[kR];
+                        double v[kR];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) v[r2] = vals[rank(e[r2])];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
+                    }
+                    if (j < hi) {
+                        uint32_t e[kR - 1];
+                        double v[kR - 1];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR - 1; ++r2) e[r2] = q[j + r2];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR - 1; ++r2) v[r2] = vals[j + r2 < hi ? rank(e[r2]) : kCap];
+#pragma unroll
+                        for (int r2 = 0; r2 < kR - 1; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
+                    }
                 } else {
-                    double h = 0.0, l = 0.0;
-                    for (int j = mlo + sub; j < jend; j += kR * per) {
-                        // entries past the trial's last read whatever LDS follows
-                        // (inside the allocation), then the 0.0 slot
+                    for (int j = lo; j < hi; j += kR) {
+                        // slots past the trial's last entry read whatever LDS follows
+                        // (still inside the allocation), then the 0.0 after the copied
+                        // losses, whose sum is exact
                         uint32_t e[kR], rk[kR];
                         bool valid[kR];
                         double v[kR];
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2) {
-                            valid[r2] = j + r2 * per < jend;
-                            e[r2] = q[j + r2 * per];
+                            valid[r2] = j + r2 < hi;
+                            e[r2] = q[j + r2];
                         }
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
-                        if (fits) {
-#pragma unroll
-                            for (int r2 = 0; r2 < kR; ++r2) v[r2] = vals[valid[r2] ? rk[r2] : kCap];
-                        } else {
-                            bool spill = false;
-#pragma unroll
-                            for (int r2 = 0; r2 < kR; ++r2) {
-                                const uint32_t i = sb_index(rk[r2]);
-                                v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
-                                spill |= valid[r2] && i >= kSbCap;
-                            }
-                            if (__ballot(spill)) {
-#pragma unroll
-                                for (int r2 = 0; r2 < kR; ++r2)
-                                    if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
-                            }
-                        }
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) dd_add(h, l, v[r2]);
-                    }
-                    for (int off = per >> 1; off >= 1; off >>= 1) dd_merge(h, l, shfl_xor_f64(h, off), shfl_xor_f64(l, off));
-                    const int back = ((lane - i0) << s) & 63;
-                    const double th_hi = shfl_f64(h, back), th_lo = shfl_f64(l, back);
-                    if (lane >= i0 && lane < i0 + n_act) dd_merge(acc_hi, acc_lo, th_hi, th_lo);
-                }
-                spread_done = true;
-            }
-            }
-            if (spread_done) {
-            } else if constexpr (kAdj) {
-                if (fits) {
-                    // every rank has its LDS counter: whole steps unchecked,
-                    // then the last one to three entries (their queue reads,
-                    // at most two entries past a full queue, stay inside the
-                    // allocation)
-                    int j = lo;
-                    for (; j + kR <= hi; j += kR) {
-                        uint32_t e[kR], rk[kR];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) atomicAdd(&cnt[rk[r2]], 1u);
-                    }
-                    if (j < hi) {
-                        uint32_t e[kR - 1], rk[kR - 1];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR - 1; ++r2) e[r2] = q[j + r2];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR - 1; ++r2) rk[r2] = rank(e[r2]);
-#pragma unroll
-                        for (int r2 = 0; r2 < kR - 1; ++r2)
-                            if (j + r2 < hi) atomicAdd(&cnt[rk[r2]], 1u);
-                    }
-                } else {
-                    for (int j = lo; j < hi; j += kR) {
-                        uint32_t e[kR], rk[kR];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                        // the LDS copy; entries past it then read the value from L2
+                        bool spill = false;
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2) {
-                            if (j + r2 >= hi) continue;
                             const uint32_t i = sb_index(rk[r2]);
-                            if (i < kSbCnt)
-                                atomicAdd(&cnt[sb_slot(rk[r2], i, kSbCnt)], 1u);
-                            else
-                                atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
+                            v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                            spill |= valid[r2] && i >= kSbCap;
                         }
+                        if (__ballot(spill)) {
+#pragma unroll
+                            for (int r2 = 0; r2 < kR; ++r2)
+                                if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
+                        }
+#pragma unroll
+                        for (int r2 = 0; r2 < kR; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
                     }
                 }
-                if (cls & 6u) {
-                    // a tail trial: its TVaR weight on each of its occurrences
-                    const unsigned long long wt = static_cast<unsigned long long>((cls & 2u) ? ts.c_eq : ts.m - ts.c_gt);
-                    for (int j = lo; j < hi; ++j)
-                        atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + q[j]]), wt);
-                }
-            } else if (fits) {
-                // every rank has its value in LDS: whole steps unchecked, then
-                // the last one to three entries, whose idle slots read the 0.0
-                // after the copied losses (their queue reads, at most two entries
-                // past a full queue, stay inside the allocation)
-                int j = lo;
-                for (; j + kR <= hi; j += kR) {
-                    uint32_t e[kR];
-                    double v[kR];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) v[r2] = vals[rank(e[r2])];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
-                }
-                if (j < hi) {
-                    uint32_t e[kR - 1];
-                    double v[kR - 1];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR - 1; ++r2) e[r2] = q[j + r2];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR - 1; ++r2) v[r2] = vals[j + r2 < hi ? rank(e[r2]) : kCap];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR - 1; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
-                }
-            } else {
-                for (int j = lo; j < hi; j += kR) {
-                    // slots past the trial's last entry read whatever LDS follows
-                    // (still inside the allocation), then the 0.0 after the copied
-                    // losses, whose sum is exact
-                    uint32_t e[kR], rk[kR];
-                    bool valid[kR];
-                    double v[kR];
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) {
-                        valid[r2] = j + r2 < hi;
-                        e[r2] = q[j + r2];
-                    }
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
-                    // the LDS copy; entries past it then read the value from L2
-                    bool spill = false;
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) {
-                        const uint32_t i = sb_index(rk[r2]);
-                        v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
-                        spill |= valid[r2] && i >= kSbCap;
-                    }
-                    if (__ballot(spill)) {
-#pragma unroll
-                        for (int r2 = 0; r2 < kR; ++r2)
-                            if (valid[r2] && sb_index(rk[r2]) >= kSbCap) v[r2] = gstage[rk[r2]];
-                    }
-#pragma unroll
-                    for (int r2 = 0; r2 < kR; ++r2) dd_add(acc_hi, acc_lo, v[r2]);
-                }
-            }
-            qs = qs == kInf ? kInf : qs - qn;
-            qn = 0;
-            __builtin_amdgcn_wave_barrier();
-        };
-        // test a batch against the byte map, append its hits to the queue in
-        // stream order, and note where each trial's hits start
-        auto process = [&](const u32x4* v) {
-            // Chunks past the group's end read padding or the next group's IDs;
-            // their hits are queued after the group's end boundary (lanes >= G
-            // note where it falls), so no trial takes them.
-            uint32_t m[kU];                         // bit w: ID w of the lane's chunk is a hit
-            bool hit[kU][8];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                uint32_t b[8];
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    b[2 * d] = map[v[u][d] & 0xFFFFu];
-                    b[2 * d + 1] = map[v[u][d] >> 16];
-                }
-#pragma unroll
-                for (int w = 0; w < 8; ++w) hit[u][w] = b[w] != 0;
-                m[u] = lane_select<1>(hit[u][0]) | lane_select<2>(hit[u][1]) | lane_select<4>(hit[u][2]) |
-                       lane_select<8>(hit[u][3]) | lane_select<16>(hit[u][4]) | lane_select<32>(hit[u][5]) |
-                       lane_select<64>(hit[u][6]) | lane_select<128>(hit[u][7]);
-            }
-            // hit counts per chunk, prefix-summed over the wave two chunks at a time
-            // (16-bit halves: at most 8 x 64 hits per load)
-            uint32_t pre[kU], tot = 0, tot0 = 0;
-            {
-                const uint32_t ca = static_cast<uint32_t>(__popc(m[0]));
-                const uint32_t cb = static_cast<uint32_t>(__popc(m[1]));
-                const uint32_t sc = stream_wave_scan(ca | (cb << 16));
-                const uint32_t tt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sc), 63));
-                pre[0] = (sc & 0xFFFFu) - ca;
-                pre[1] = (tt & 0xFFFFu) + (sc >> 16) - cb;
-                tot0 = tt & 0xFFFFu;
-                tot = tot0 + (tt >> 16);
-            }
-            // append the hits of load u; `skip` hits of the batch precede the queue's end
-            auto append = [&](int u, uint32_t skip) {
-                uint8_t* at = reinterpret_cast<uint8_t*>(q + qn + (pre[u] - skip));   // LDS byte address
-#pragma unroll
-                for (int w = 0; w < 8; ++w) {
-                    if (hit[u][w]) *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(v[u][w >> 1] >> (16 * (w & 1)));
-                    at += hit[u][w] ? 2 : 0;
-                }
+                qs = qs == kInf ? kInf : qs - qn;
+                qn = 0;
+                __builtin_amdgcn_wave_barrier();
             };
-            // trial starts at batch positions [from, to): the hits of the chunk
-            // before the start's position, plus the chunk's queue offset
-            const uint32_t rel = B - c;
-            const uint32_t k = rel >> 3;
-            const int src = static_cast<int>(k & 63u);
-            const uint32_t p0 = static_cast<uint32_t>(__shfl(static_cast<int>((pre[0] << 8) | m[0]), src));
-            const uint32_t p1 = static_cast<uint32_t>(__shfl(static_cast<int>((pre[1] << 8) | m[1]), src));
-            const uint32_t pk = (k >> 6) == 0 ? p0 : p1;
-            const int before = static_cast<int>(pk >> 8) + __popc((pk & 0xFFu) & ((1u << (rel & 7u)) - 1u));
-            auto record = [&](uint32_t from, uint32_t to, int skip) {
-                if (B >= c && rel >= from && rel < to) qs = qn + before - skip;
+            // test a batch against the byte map, append its hits to the queue in
+            // stream order, and note where each trial's hits start
+            auto process = [&](const u32x4* v) {
+                // Chunks past the group's end read padding or the next group's IDs;
+                // their hits are queued after the group's end boundary (lanes >= G
+                // note where it falls), so no trial takes them.
+                uint32_t m[kU];                         // bit w: ID w of the lane's chunk is a hit
+                bool hit[kU][8];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    uint32_t b[8];
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        b[2 * d] = map[v[u][d] & 0xFFFFu];
+                        b[2 * d + 1] = map[v[u][d] >> 16];
+                    }
+#pragma unroll
+                    for (int w = 0; w < 8; ++w) hit[u][w] = b[w] != 0;
+                    m[u] = lane_select<1>(hit[u][0]) | lane_select<2>(hit[u][1]) | lane_select<4>(hit[u][2]) |
+                           lane_select<8>(hit[u][3]) | lane_select<16>(hit[u][4]) | lane_select<32>(hit[u][5]) |
+                           lane_select<64>(hit[u][6]) | lane_select<128>(hit[u][7]);
+                }
+                // hit counts per chunk, prefix-summed over the wave two chunks at a time
+                // (16-bit halves: at most 8 x 64 hits per load)
+                uint32_t pre[kU], tot = 0, tot0 = 0;
+                {
+                    const uint32_t ca = static_cast<uint32_t>(__popc(m[0]));
+                    const uint32_t cb = static_cast<uint32_t>(__popc(m[1]));
+                    const uint32_t sc = stream_wave_scan(ca | (cb << 16));
+                    const uint32_t tt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sc), 63));
+                    pre[0] = (sc & 0xFFFFu) - ca;
+                    pre[1] = (tt & 0xFFFFu) + (sc >> 16) - cb;
+                    tot0 = tt & 0xFFFFu;
+                    tot = tot0 + (tt >> 16);
+                }
+                // append the hits of load u; `skip` hits of the batch precede the queue's end
+                auto append = [&](int u, uint32_t skip) {
+                    uint8_t* at = reinterpret_cast<uint8_t*>(q + qn + (pre[u] - skip));   // LDS byte address
+#pragma unroll
+                    for (int w = 0; w < 8; ++w) {
+                        if (hit[u][w]) *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(v[u][w >> 1] >> (16 * (w & 1)));
+                        at += hit[u][w] ? 2 : 0;
+                    }
+                };
+                // trial starts at batch positions [from, to): the hits of the chunk
+                // before the start's position, plus the chunk's queue offset
+                const uint32_t rel = B - c;
+                const uint32_t k = rel >> 3;
+                const int src = static_cast<int>(k & 63u);
+                const uint32_t p0 = static_cast<uint32_t>(__shfl(static_cast<int>((pre[0] << 8) | m[0]), src));
+                const uint32_t p1 = static_cast<uint32_t>(__shfl(static_cast<int>((pre[1] << 8) | m[1]), src));
+                const uint32_t pk = (k >> 6) == 0 ? p0 : p1;
+                const int before = static_cast<int>(pk >> 8) + __popc((pk & 0xFFu) & ((1u << (rel & 7u)) - 1u));
+                auto record = [&](uint32_t from, uint32_t to, int skip) {
+                    if (B >= c && rel >= from && rel < to) qs = qn + before - skip;
+                };
+                if (qn + static_cast<int>(tot) > kQ) drain();
+                if (tot <= static_cast<uint32_t>(kQ)) {
+                    append(0, 0u);
+                    append(1, 0u);
+                    record(0u, kBatch, 0);
+                    qn += static_cast<int>(tot);
+                } else {
+                    // more hits than the queue holds (dense layers): the first load's
+                    // hits, a drain, then the second load's (each fits an empty queue)
+                    const uint32_t t0 = tot0;
+                    append(0, 0u);
+                    record(0u, kBatch / 2, 0);
+                    qn += static_cast<int>(t0);
+                    drain();
+                    append(1, t0);
+                    record(kBatch / 2, kBatch, static_cast<int>(t0));
+                    qn += static_cast<int>(tot - t0);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             };
-            if (qn + static_cast<int>(tot) > kQ) drain();
-            if (tot <= static_cast<uint32_t>(kQ)) {
-                append(0, 0u);
-                append(1, 0u);
-                record(0u, kBatch, 0);
-                qn += static_cast<int>(tot);
-            } else {
-                // more hits than the queue holds (dense layers): the first load's
-                // hits, a drain, then the second load's (each fits an empty queue)
-                const uint32_t t0 = tot0;
-                append(0, 0u);
-                record(0u, kBatch / 2, 0);
-                qn += static_cast<int>(t0);
-                drain();
-                append(1, t0);
-                record(kBatch / 2, kBatch, static_cast<int>(t0));
-                qn += static_cast<int>(tot - t0);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        // Partial sums of the last kHeld groups wait in registers and are stored
-        // together, then waited for at once: a store pending at the next wait
-        // for a batch would make that wait cover every load in flight (stores
-        // and loads share one counter and complete in either order), which at
-        // every group's end would stall the stream
-        auto flush = [&]() {
+            // Partial sums of the last kHeld groups wait in registers and are stored
+            // together, then waited for at once: a store pending at the next wait
+            // for a batch would make that wait cover every load in flight (stores
+            // and loads share one counter and complete in either order), which at
+            // every group's end would stall the stream
+            auto flush = [&]() {
 #pragma unroll
-            for (int k = 0; k < kHeld; ++k) {
-                const int64_t t = (g - k) * G + lane;
-                if (k < n_held && lane < G && t >= a.t_lo && t < a.t_hi) {
-                    out_hi[t - a.t_lo] = held_hi[k];
-                    out_lo[t - a.t_lo] = held_lo[k];
+                for (int k = 0; k < kHeld; ++k) {
+                    const int64_t t = (g - k) * G + lane;
+                    if (k < n_held && lane < G && t >= t_lo && t < t_hi) {
+                        out_hi[t - t_lo] = held_hi[k];
+                        out_lo[t - t_lo] = held_lo[k];
+                    }
                 }
-            }
-            n_held = 0;
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        };
-        // after a batch: advance; at the end of the group drain the queue, hold
-        // the partial sums (the forward) and move to the next group (its first
-        // batch is in flight).  Returns false after the wave's last group.
-        auto step = [&]() -> bool {
-            c += kBatch;
-            if (c < re) return true;
-            drain();
-            if constexpr (!kAdj) {
-                // the group's sums join the held results (newest first)
-#pragma unroll
-                for (int k = kHeld - 1; k > 0; --k) {
-                    held_hi[k] = held_hi[k - 1];
-                    held_lo[k] = held_lo[k - 1];
-                }
-                held_hi[0] = acc_hi + acc_lo;          // renormalised: |lo| <= ulp(hi) / 2
-                held_lo[0] = static_cast<float>(acc_lo - (held_hi[0] - acc_hi));
-                ++n_held;
-                if (n_held == kHeld || g + 1 >= wb) flush();
-                acc_hi = 0.0;
-                acc_lo = 0.0;
-            }
-            qs = kInf;
-            if (g + 1 >= wb) return false;
-            ++g;
-            rs = gs[g];
-            re = gs[g + 1];
-            B = starts(rs, next_ends);
-            if constexpr (kAdj) cls = next_cls;
-            c = rs;
-            return true;
-        };
-
-        // two register buffers in turn, so the next batch's loads stay in
-        // flight while this one is tested
-        u32x4 bufA[kU], bufB[kU];
-        if constexpr (kSplit) {
-            // one unit after the other: trials [tl, th) of a group, from the
-            // 16-byte chunk that holds the first one's first ID
-            for (int64_t u = wa; u < wb; ++u) {
-                g = a.g_lo + u / a.K;
-                const int k = static_cast<int>(u % a.K);
-                tl = G * k / a.K;
-                th = G * (k + 1) / a.K;
-                if (u > wa && k == 0) {
-                    B = starts(gs[g], group_ends(g));
-                    if constexpr (kAdj) cls = group_class(g);
-                }
-                c = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), tl)) & ~7u;
-                re = (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), th)) + 7u) & ~7u;
-                qs = kInf;
-                load_batch(c, re, bufA);
-                while (c < re) {
-                    load_batch(c + kBatch, re, bufB);
-                    process(bufA);
-                    c += kBatch;
-                    if (c >= re) break;
-                    load_batch(c + kBatch, re, bufA);
-                    process(bufB);
-                    c += kBatch;
-                }
+                n_held = 0;
+                __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            };
+            // after a batch: advance; at the end of the group drain the queue, hold
+            // the partial sums (the forward) and move to the next group (its first
+            // batch is in flight).  Returns false after the wave's last group.
+            auto step = [&]() -> bool {
+                c += kBatch;
+                if (c < re) return true;
                 drain();
                 if constexpr (!kAdj) {
-                    const int64_t t = g * G + lane;
-                    if (lane >= tl && lane < th && t >= a.t_lo && t < a.t_hi) {
-                        const double hi = acc_hi + acc_lo;      // renormalised: |lo| <= ulp(hi) / 2
-                        out_hi[t - a.t_lo] = hi;
-                        out_lo[t - a.t_lo] = static_cast<float>(acc_lo - (hi - acc_hi));
+                    // the group's sums join the held results (newest first)
+#pragma unroll
+                    for (int k = kHeld - 1; k > 0; --k) {
+                        held_hi[k] = held_hi[k - 1];
+                        held_lo[k] = held_lo[k - 1];
                     }
+                    held_hi[0] = acc_hi + acc_lo;          // renormalised: |lo| <= ulp(hi) / 2
+                    held_lo[0] = static_cast<float>(acc_lo - (held_hi[0] - acc_hi));
+                    ++n_held;
+                    if (n_held == kHeld || g + 1 >= wb) flush();
                     acc_hi = 0.0;
                     acc_lo = 0.0;
                 }
+                qs = kInf;
+                if (g + 1 >= wb) return false;
+                ++g;
+                rs = gs[g];
+                re = gs[g + 1];
+                B = starts(rs, next_ends);
+                if constexpr (kAdj) cls = next_cls;
+                c = rs;
+                return true;
+            };
+
+            // two register buffers in turn, so the next batch's loads stay in
+            // flight while this one is tested
+            u32x4 bufA[kU], bufB[kU];
+            if constexpr (kSplit) {
+                // one unit after the other: trials [tl, th) of a group, from the
+                // 16-byte chunk that holds the first one's first ID
+                for (int64_t u = wa; u < wb; ++u) {
+                    g = g_lo + u / a.K;
+                    const int k = static_cast<int>(u % a.K);
+                    tl = G * k / a.K;
+                    th = G * (k + 1) / a.K;
+                    if (u > wa && k == 0) {
+                        B = starts(gs[g], group_ends(g));
+                        if constexpr (kAdj) cls = group_class(g);
+                    }
+                    c = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), tl)) & ~7u;
+                    re = (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(B), th)) + 7u) & ~7u;
+                    qs = kInf;
+                    load_batch(c, re, bufA);
+                    while (c < re) {
+                        load_batch(c + kBatch, re, bufB);
+                        process(bufA);
+                        c += kBatch;
+                        if (c >= re) break;
+                        load_batch(c + kBatch, re, bufA);
+                        process(bufB);
+                        c += kBatch;
+                    }
+                    drain();
+                    if constexpr (!kAdj) {
+                        const int64_t t = g * G + lane;
+                        if (lane >= tl && lane < th && t >= t_lo && t < t_hi) {
+                            const double hi = acc_hi + acc_lo;      // renormalised: |lo| <= ulp(hi) / 2
+                            out_hi[t - t_lo] = hi;
+                            out_lo[t - t_lo] = static_cast<float>(acc_lo - (hi - acc_hi));
+                        }
+                        acc_hi = 0.0;
+                        acc_lo = 0.0;
+                    }
+                }
+                continue;
             }
-            continue;
-        }
-        load_batch(c, re, bufA);
-        for (;;) {
-            load_next(bufB);
-            process(bufA);
-            if (!step()) break;
-            load_next(bufA);
-            process(bufB);
-            if (!step()) break;
+            load_batch(c, re, bufA);
+            for (;;) {
+                load_next(bufB);
+                process(bufA);
+                if (!step()) break;
+                load_next(bufA);
+                process(bufB);
+                if (!step()) break;
+            }
         }
     }
     if constexpr (kAdj) {
@@ -1150,26 +1182,29 @@ const float* stream_partials_lo(const StreamLayout& lay, const void* partials, i
 
 namespace {
 
-StreamPassArgs pass_args(const StreamLayout& lay, const LayerArgs& L, void* part_scratch, int n_img_parts) {
+// arguments common to a launch; the fold's outputs of the layers lie at `fold`
+StreamPassArgs pass_args(const StreamLayout& lay, const FoldViews& fold) {
     StreamPassArgs a{};
     a.ids = lay.ids;
     a.part_base = lay.part_base;
     a.gstart = lay.gstart;
     a.gend = lay.gend;
-    a.img = static_cast<const uint8_t*>(part_scratch);
-    a.sb_count = part_superblock_counts(part_scratch, n_img_parts);
-    a.stage = part_stage_values(part_scratch, n_img_parts);
+    a.img = fold.img;
+    a.sb_count = fold.sb_count;
+    a.stage = fold.stage;
+    a.img_stride = fold.img_stride;
+    a.sb_stride = fold.sb_stride;
     a.P = lay.P;
     a.G = lay.G;
     a.NG = lay.NG;
-    a.t_lo = L.trial_begin;
-    a.t_hi = L.trial_begin + L.trial_count;
-    a.g_lo = a.t_lo / lay.G;
-    a.g_hi = (a.t_hi + lay.G - 1) / lay.G;
     a.pad = lay.ids + lay.length;
     a.n_xcd = kXcds;
     return a;
 }
+
+// groups that hold the trials [t_lo, t_hi)
+int64_t first_group(const StreamLayout& lay, int64_t t_lo) { return t_lo / lay.G; }
+int64_t group_end(const StreamLayout& lay, int64_t t_hi) { return (t_hi + lay.G - 1) / lay.G; }
 
 // one 1024-thread workgroup per CU (its LDS holds the part's byte map and
 // values or counters), a multiple of the XCD count
@@ -1210,19 +1245,79 @@ int units_per_group(const StreamLayout& lay, int64_t groups, int64_t waves) {
 // (5e7), so the line lies at 12.
 constexpr double kSpreadHits = 12.0;
 
+// `units` in order, with the partial sums of each after the earlier ones'
 template <bool kAdj>
-void launch_pass(const StreamLayout& lay, StreamPassArgs& a, const StreamAdjArgs& adj, double density, int n_cu,
-                 hipStream_t s) {
+hipError_t launch_pass(const StreamLayout& lay, StreamPassArgs& a, const StreamUnit* units, int n,
+                       const StreamAdjArgs& adj, int n_cu, hipStream_t s) {
+    if (n < 1 || n > kMaxSegs) return hipErrorInvalidValue;
     const uint32_t grid = pass_grid(n_cu);
-    a.K = units_per_group(lay, a.g_hi - a.g_lo, int64_t(grid) * 16);
-    const double hits = density * static_cast<double>(lay.length) / (static_cast<double>(lay.P) * lay.NG * lay.G);
+    SegList segs{};
+    int64_t groups = 0;
+    double hits = 0.0;
+    for (int i = 0; i < n; ++i) {
+        groups += group_end(lay, units[i].t_lo + units[i].count) - first_group(lay, units[i].t_lo);
+        hits = std::max(hits, units[i].density);
+    }
+    hits *= static_cast<double>(lay.length) / (static_cast<double>(lay.P) * lay.NG * lay.G);
+    a.K = units_per_group(lay, groups, int64_t(grid) * 16);
+    a.n_seg = n;
+    int64_t at = 0;
+    for (int i = 0; i < n; ++i) {
+        Seg& g = segs.seg[i];
+        g.t_lo = units[i].t_lo;
+        g.t_hi = units[i].t_lo + units[i].count;
+        g.g_lo = first_group(lay, g.t_lo);
+        g.units = (group_end(lay, g.t_hi) - g.g_lo) * a.K;
+        g.w0 = a.work;
+        g.part_at = at;
+        // a group of a layer with losses for a share d of the events takes about
+        // 1 + 2.2 d times a group without (0.50, 0.60 and 0.85 ms per 1e9 events at
+        // d = 0.01, 0.15 and 0.27)
+        g.weight = static_cast<int32_t>(16.0 * (1.0 + 2.2 * units[i].density) + 0.5);
+        g.layer = units[i].layer;
+        a.work += static_cast<int64_t>(lay.P) * g.units * g.weight;
+        at += static_cast<int64_t>(lay.P) * units[i].count;
+    }
     const dim3 g(grid), t(1024);
     if (a.K > 1)
-        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::split>), g, t, 0, s, a, adj, a.gstart);
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::split>), g, t, 0, s, a, segs, adj, a.gstart);
     else if (hits > kSpreadHits)
-        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::spread>), g, t, 0, s, a, adj, a.gstart);
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::spread>), g, t, 0, s, a, segs, adj, a.gstart);
     else
-        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::plain>), g, t, 0, s, a, adj, a.gstart);
+        hipLaunchKernelGGL((stream_pass_kernel<kAdj, PassMode::plain>), g, t, 0, s, a, segs, adj, a.gstart);
+    return hipGetLastError();
+}
+
+// partial sums of `trials` trials over all units: the high parts, then the low parts
+void place_partials(const StreamLayout& lay, StreamPassArgs& a, void* partials, int64_t trials) {
+    a.part_hi = static_cast<double*>(partials);
+    a.part_lo = reinterpret_cast<float*>(a.part_hi + static_cast<int64_t>(lay.P) * trials);
+}
+
+// the units' partial sums merged, one range of workgroups per unit
+struct CombineUnit {
+    int64_t first_block, count, part_at, out_at;
+    int32_t layer, pad_;
+};
+struct CombineArgs {
+    CombineUnit unit[kMaxSegs];
+    int n;
+};
+__global__ __launch_bounds__(256) void stream_combine_units_kernel(const double* __restrict__ part_hi,
+                                                                   const float* __restrict__ part_lo, int P,
+                                                                   CombineArgs c, const LayerArgs* __restrict__ L_dev,
+                                                                   double* __restrict__ ylt) {
+    int i = 0;
+    while (i + 1 < c.n && static_cast<int64_t>(blockIdx.x) >= c.unit[i + 1].first_block) ++i;
+    const CombineUnit u = c.unit[i];
+    const int64_t k = (static_cast<int64_t>(blockIdx.x) - u.first_block) * blockDim.x + threadIdx.x;
+    if (k >= u.count) return;
+    part_hi += u.part_at;
+    part_lo += u.part_at;
+    double hi = 0.0, lo = 0.0;
+    for (int p = 0; p < P; ++p)
+        dd_merge(hi, lo, part_hi[p * u.count + k], static_cast<double>(part_lo[p * u.count + k]));
+    ylt[u.out_at + k] = apply_terms(hi + lo, L_dev[u.layer].aggR, L_dev[u.layer].aggL);
 }
 
 }  // namespace
@@ -1231,10 +1326,38 @@ hipError_t launch_stream_pass(const StreamLayout& lay, double density, const Lay
                               int n_img_parts, void* partials, int n_cu, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
-    a.part_hi = static_cast<double*>(partials);
-    a.part_lo = reinterpret_cast<float*>(a.part_hi + static_cast<int64_t>(lay.P) * L.trial_count);
-    launch_pass<false>(lay, a, StreamAdjArgs{}, density, n_cu, s);
+    StreamPassArgs a = pass_args(lay, fold_views(part_scratch, n_img_parts));
+    place_partials(lay, a, partials, L.trial_count);
+    const StreamUnit u{0, L.trial_begin, L.trial_count, 0, density};
+    return launch_pass<false>(lay, a, &u, 1, StreamAdjArgs{}, n_cu, s);
+}
+
+int stream_batch_max() { return kMaxSegs; }
+
+hipError_t launch_stream_pass_units(const StreamLayout& lay, const StreamUnit* units, int n, const FoldViews& fold,
+                                    int n_img_parts, void* partials, int n_cu, hipStream_t s) {
+    if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
+    int64_t trials = 0;
+    for (int i = 0; i < n; ++i) trials += units[i].count;
+    StreamPassArgs a = pass_args(lay, fold);
+    place_partials(lay, a, partials, trials);
+    return launch_pass<false>(lay, a, units, n, StreamAdjArgs{}, n_cu, s);
+}
+
+hipError_t launch_stream_combine_units(const StreamLayout& lay, const StreamUnit* units, int n, const LayerArgs* L_dev,
+                                       const void* partials, double* ylt, hipStream_t s) {
+    if (n < 1 || n > kMaxSegs) return hipErrorInvalidValue;
+    CombineArgs c{};
+    c.n = n;
+    int64_t blocks = 0, trials = 0;
+    for (int i = 0; i < n; ++i) {
+        c.unit[i] = CombineUnit{blocks, units[i].count, trials * lay.P, units[i].out_at, units[i].layer, 0};
+        blocks += (units[i].count + 255) / 256;
+        trials += units[i].count;
+    }
+    hipLaunchKernelGGL(stream_combine_units_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s,
+                       static_cast<const double*>(partials), stream_partials_lo(lay, partials, trials), lay.P, c, L_dev,
+                       ylt);
     return hipGetLastError();
 }
 
@@ -1249,8 +1372,9 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const 
                                  hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    StreamPassArgs a = pass_args(lay, L, part_scratch, n_img_parts);
-    const int64_t n_slots = (a.g_hi - a.g_lo) * 64;
+    StreamPassArgs a = pass_args(lay, fold_views(part_scratch, n_img_parts));
+    const int64_t t_lo = L.trial_begin, t_hi = t_lo + L.trial_count, g_lo = first_group(lay, t_lo);
+    const int64_t n_slots = (group_end(lay, t_hi) - g_lo) * 64;
     if (n_slots > scratch_bytes) return hipErrorInvalidValue;
     StreamAdjArgs adj{};
     adj.cls = static_cast<const uint8_t*>(scratch);
@@ -1260,11 +1384,11 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const 
     int64_t cb = (n_slots + 255) / 256;
     if (cb > int64_t(n_cu) * 8) cb = int64_t(n_cu) * 8;
     hipLaunchKernelGGL(stream_class_kernel, dim3(static_cast<uint32_t>(cb)), dim3(256), 0, s, S, ylt, tail, L.aggR,
-                       L.aggL, a.t_lo, a.t_hi, a.G, a.g_lo, n_slots, static_cast<uint8_t*>(scratch));
+                       L.aggL, t_lo, t_hi, a.G, g_lo, n_slots, static_cast<uint8_t*>(scratch));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    launch_pass<true>(lay, a, adj, density, n_cu, s);
-    return hipGetLastError();
+    const StreamUnit u{0, L.trial_begin, L.trial_count, 0, density};
+    return launch_pass<true>(lay, a, &u, 1, adj, n_cu, s);
 }
 
 hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, const LayerArgs* L_dev,
