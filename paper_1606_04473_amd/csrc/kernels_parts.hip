@@ -298,19 +298,20 @@ __global__ __launch_bounds__(256) void part_image_kernel(const double* __restric
 // layer order, the chunk's nonzero entries (distinct events) each add their
 // per-ELT net loss.  An absent loss adds +0.0 (retentions are >= 0), which
 // leaves y unchanged, so y is bit-identical to summing every ELT's dense row in
-// layer order.  The kernel is a chain of memory and LDS latencies, so:
-//  * the entries' net losses are first staged in LDS, four ELTs' loads in
-//    flight per wave (kFoldStage entries a round);
-//  * each wave then sums its own 512 events: their entries are a contiguous
-//    range of each ELT's (found by bisection, one ELT per lane), and a wave's
-//    LDS operations keep their order, so the ELTs need no barrier between them.
-// Then o, the bitmap words, the per-128 ranks and the superblock count are
-// written, and the superblock's nonzero o, packed in event order, go to its
-// 4096-value slot of `stage`.  16 ELTs over 2e6 events: 16.5 us with a barrier
-// per ELT and 256 threads, 13.9 us now.
+// layer order.  The kernel is a chain of memory and LDS latencies: pieces of an
+// ELT's entries, one per thread, are read kFoldAhead ahead, also over the ELTs'
+// ends, and a barrier separates the ELTs.  Then o, the bitmap words, the per-128
+// ranks and the superblock count are written, and the superblock's nonzero o,
+// packed in event order, go to its 4096-value slot of `stage`.  Against staging a
+// round of the ELTs' joined entries in LDS, from which each wave sums its own
+// 512 events: 16 ELTs over 2e6 events, 41 entries per ELT and superblock, 13.9 us
+// both; 12 layers of up to 32 such ELTs 108 -> 71 us; 9 layers of 24 with 82
+// entries 44 -> 29 us; 30 ELTs of 246 entries 23 -> 14.5 us; 27 of 834 79 -> 20 us.
+// 256 threads take 18 and 29 us for the last two, 34 us instead of 36 per batch of
+// the 12 layers.
 constexpr int kFoldThreads = 512;
 constexpr int kFoldWaves = kFoldThreads / 64;
-constexpr int kFoldStage = 4096;
+constexpr int kFoldAhead = 4;                       // pieces of entries in flight
 struct FoldOut {
     double* o;                      // dense o, or null
     uint8_t* img;
@@ -343,8 +344,6 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
     constexpr int kOwn = kSuper / kFoldWaves;       // events a wave sums
     constexpr int kWordsOwn = kOwn / 64;
     __shared__ __attribute__((aligned(16))) double ys[kSuper];
-    __shared__ double sval[kFoldStage];
-    __shared__ uint16_t sev[kFoldStage];
     __shared__ uint64_t wb[64];
     const int64_t sb = blockIdx.x;
     const int64_t e0 = sb * kSuper;
@@ -354,8 +353,7 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
     uint16_t* r16 = reinterpret_cast<uint16_t*>(img + part * kImgBytes + int64_t(kWords) * 8);
     const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    // lane j: ELT j's entries of this chunk in the pool, its terms, and where
-    // its entries start in the chunk's list (J <= kMaxJ <= 64)
+    // lane j: ELT j's entries of this chunk in the pool and its terms (J <= kMaxJ <= 64)
     const int J = sb < sp.n_chunks ? L.J : 0;
     int64_t pool_at = 0;
     int cnt = 0;
@@ -371,96 +369,51 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
         u64x2* own = reinterpret_cast<u64x2*>(ys + w * kOwn);
         for (int i = lane; i < kOwn / 2; i += 64) own[i] = u64x2{0, 0};
     }
-    int pre = cnt;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(pre, off, kWave);
-        if (lane >= off) pre += v;
-    }
-    const int n_list = __builtin_amdgcn_readlane(pre, 63);
-    pre -= cnt;
-    for (int r0 = 0; r0 < n_list; r0 += kFoldStage) {
-        if (r0) __syncthreads();                    // the previous round's entries are used
-        // wave w stages the ELTs w, w + 8, ..., four of them at a time
-        const int lo = r0 > pre ? r0 - pre : 0;     // lane j: entries [lo, hi) of ELT j are in this round
-        int hi = r0 + kFoldStage - pre;
-        hi = hi < cnt ? hi : cnt;
-        for (int j0 = w; j0 < J; j0 += 4 * kFoldWaves) {
-            int f[4], fe[4], to[4];
-            const uint16_t* evs[4];
-            const double* vals[4];
-            double Rj[4], Lj[4];
-            int most = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u * kFoldWaves < J ? j0 + u * kFoldWaves : j0;
-                const int64_t k = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(pool_at), j));
-                const int fl = __builtin_amdgcn_readlane(lo, j);
-                fe[u] = j0 + u * kFoldWaves < J ? __builtin_amdgcn_readlane(hi, j) : fl;
-                f[u] = fl + lane;
-                to[u] = __builtin_amdgcn_readlane(pre, j) - r0;
-                most = fe[u] - fl > most ? fe[u] - fl : most;
-                evs[u] = sp.ev + k;
-                vals[u] = sp.val + k;
-                Rj[u] = readlane_f64(R, j);
-                Lj[u] = readlane_f64(Lim, j);
-            }
-            for (int i = 0; i < most; i += 64) {
-                uint16_t e[4];
-                double v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    e[u] = 0;
-                    v[u] = 0.0;
-                    if (f[u] + i < fe[u]) {
-                        e[u] = evs[u][f[u] + i];
-                        v[u] = vals[u][f[u] + i];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (f[u] + i < fe[u]) {
-                        sev[to[u] + f[u] + i] = e[u];
-                        sval[to[u] + f[u] + i] = apply_terms(v[u], Rj[u], Lj[u]);
-                    }
-            }
+    uint64_t left = __ballot(cnt > 0);              // ELTs with entries that are not begun
+    int pj = -1, pi = 0, pn = 0;                    // the last piece fetched: ELT, first entry, the ELT's entries
+    int64_t pat = 0;
+    int qj[kFoldAhead], qi[kFoldAhead], qn[kFoldAhead];
+    int qe[kFoldAhead];
+    double qv[kFoldAhead];
+    auto fetch = [&](int u) {
+        pi += kFoldThreads;
+        if (pi >= pn) {
+            pi = 0;
+            pj = left ? __builtin_ctzll(left) : -1;
+            pn = left ? __builtin_amdgcn_readlane(cnt, pj & 63) : 0;
+            pat = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(pool_at), pj & 63));
+            left &= left - 1;
         }
-        __syncthreads();
-        // lane j: the wave's entries [a0, a1) of ELT j, by bisection on the event
-        const int from = pre + lo - r0, till = hi > lo ? pre + hi - r0 : from;
-        int a0 = from, b0 = till, a1 = from, b1 = till;
-        while (a0 < b0 || a1 < b1) {
-            const int m0 = (a0 + b0) >> 1, m1 = (a1 + b1) >> 1;
-            const int v0 = a0 < b0 ? sev[m0] : 0, v1 = a1 < b1 ? sev[m1] : 0;
-            if (a0 < b0) {
-                if (v0 < w * kOwn) a0 = m0 + 1; else b0 = m0;
-            }
-            if (a1 < b1) {
-                if (v1 < (w + 1) * kOwn) a1 = m1 + 1; else b1 = m1;
-            }
+        qj[u] = pj;
+        qi[u] = pi;
+        qn[u] = pn;
+        const int i = pi + static_cast<int>(threadIdx.x);
+        qe[u] = 0;
+        qv[u] = 0.0;
+        if (i < pn) {
+            qe[u] = sp.ev[pat + i];
+            qv[u] = sp.val[pat + i];
         }
-        // the ELTs in layer order, the next one's first entries read ahead
-        int f = J > 0 ? __builtin_amdgcn_readlane(a0, 0) + lane : 0;
-        int fe = J > 0 ? __builtin_amdgcn_readlane(a1, 0) : 0;
-        int ev = f < fe ? sev[f] : 0;
-        double x = f < fe ? sval[f] : 0.0;
-        for (int j = 0; j < J; ++j) {
-            const int jn = j + 1 < J ? j + 1 : j;
-            const int fn = __builtin_amdgcn_readlane(a0, jn) + lane;
-            const int fen = __builtin_amdgcn_readlane(a1, jn);
-            const int evn = fn < fen ? sev[fn] : 0;
-            const double xn = fn < fen ? sval[fn] : 0.0;
-            if (f < fe) ys[ev] = ys[ev] + x;
-            for (f += 64; f < fe; f += 64) {
-                const int e2 = sev[f];
-                ys[e2] = ys[e2] + sval[f];
+    };
+#pragma unroll
+    for (int u = 0; u < kFoldAhead; ++u) fetch(u);
+    for (bool more = true; more;) {
+#pragma unroll
+        for (int u = 0; u < kFoldAhead; ++u) {
+            const int j = qj[u], i = qi[u] + static_cast<int>(threadIdx.x), n = qn[u];
+            const int e = qe[u];
+            const double v = qv[u];
+            const bool first = qi[u] == 0;
+            if (j < 0) {
+                more = false;
+                break;
             }
-            __builtin_amdgcn_wave_barrier();
-            f = fn;
-            fe = fen;
-            ev = evn;
-            x = xn;
+            fetch(u);
+            if (first) __syncthreads();             // the ELT before is added (the first: the zeros are set)
+            if (i < n) ys[e] = ys[e] + apply_terms(v, readlane_f64(R, j), readlane_f64(Lim, j));
         }
     }
+    __syncthreads();
     const int64_t eb = e0 + static_cast<int64_t>(w) * kOwn + lane;      // event of word 0 of this wave
     double vk[kWordsOwn];
     uint64_t bk[kWordsOwn];
