@@ -1966,7 +1966,8 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     double* out = dev ? nets : reinterpret_cast<double*>(base + o_bytes + p_bytes + w_bytes);
     HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base + o_bytes, false, probe, s),
             "fold and part images");
-    HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base + o_bytes, P, t->C, probe, L, out, t->n_cu, s),
+    HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base + o_bytes, P, t->C, probe, layer_density(t, L),
+                                   static_cast<double>(n), L, out, t->n_cu, s),
             "net-loss kernel");
     if (!dev) {
         HIP_TRY(hipMemcpyAsync(nets, out, sizeof(double) * n, hipMemcpyDeviceToHost, s), "copy nets");

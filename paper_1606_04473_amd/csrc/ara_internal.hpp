@@ -491,9 +491,11 @@ struct PortfolioSumArgs {
 hipError_t launch_portfolio_sum(const PortfolioSumArgs& a, int n_cu, hipStream_t s);
 // per-event net losses of a layer's trials, in time order, reading o(E)
 // through the probe tables and the superblocks' packed values that
-// launch_fold_parts wrote to `probe` and part_scratch (P = catalogue parts)
+// launch_fold_parts wrote to `probe` and part_scratch (P = catalogue parts);
+// `density` estimates the share of the catalogue with a loss, `events` the layer's events
 hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P, int64_t C,
-                             uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s);
+                             uint64_t* probe, double density, double events, const LayerArgs& L, double* nets,
+                             int n_cu, hipStream_t s);
 // the forward's stride checkpoints in the same time-ordered pass: slot b of
 // `stride` receives the running total S of the trial that owns global event
 // 64b + 63, after that event (slots outside the layer's trials untouched)

@@ -20,6 +20,8 @@
 //    adds the part's partial sum (double-double) into the trial's LDS
 //    accumulator; the trial's owner and the part order are fixed, so the
 //    result does not depend on scheduling.
+#include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstring>
 #include <vector>
@@ -2081,28 +2083,37 @@ __global__ __launch_bounds__(kNetsThreads) void event_nets_kernel(const int64_t*
     }
 }
 
-// The stride checkpoints: the running total S_d of every position d = 64b + 63
-// to slot b.  Steps of 64 kE positions in time order, kE consecutive positions
-// per lane (16-byte loads, the next step's issued before this step's work); a
-// segmented double-double scan over the wave gives each lane's last running
-// total.  Eight events per lane spread the scan over twice the events of four.
-template <int kE>
-__global__ __launch_bounds__(kNetsThreads) void stride_checkpoint_kernel(const int64_t* __restrict__ offsets,
+// Every event scanned: nets where most events are candidates (then queues only
+// add work), and the stride checkpoints.  Steps of 64 kE positions in time order,
+// kE consecutive positions per lane (16-byte loads, the next step's issued
+// before this step's work); a segmented double-double scan over the wave gives
+// each lane's last running total, the lane below's gives the total before its
+// first event, and its own events are added again for their A.  Nets go through
+// a per-wave LDS stage, half a step at a time, and out in stores of 64
+// consecutive values.  With kStride the kernel writes instead the running total
+// S_d of every position d = 64b + 63 to slot b of `nets`.  Eight events per lane
+// spread the scan over twice the events of four.
+template <int kE, bool kStride>
+__global__ __launch_bounds__(kNetsThreads) void event_scan_kernel(const int64_t* __restrict__ offsets,
                                                                   const uint32_t* __restrict__ ids,
                                                                   const uint64_t* __restrict__ probe,
                                                                   const uint32_t* __restrict__ gcoarse, int cshift,
                                                                   int64_t n_cw, const double* __restrict__ losses,
-                                                                  LayerArgs L, double* __restrict__ slots) {
+                                                                  LayerArgs L, double* __restrict__ nets) {
     static_assert(kE == 4 || kE == 8, "four or eight events per lane");
     static_assert(64 % kE == 0, "stride slots are lanes' last events when kE divides 64");
     constexpr int kW = 64 * kE;                                        // positions per step
     static_assert(kW <= kIdPad, "a step may read up to kW - 1 IDs past the table's end");
+    constexpr int kRow = 32 * (kE + 1);        // half a step's nets, one pad slot per lane
+    static_assert(kNetsStageBytes >= (kNetsThreads / 64) * (kRow * 8 + kW / 8), "stage rows fit their LDS share");
+    __shared__ double stage[kNetsThreads / 64][kStride ? 1 : kRow];
     __shared__ uint32_t flag_rows[kNetsThreads / 64][kW / 32];          // bit i: a trial starts at c + i
     extern __shared__ __attribute__((aligned(16))) uint32_t coarse[];  // [n_cw]
     // the coarse map, before any wave can leave (the only workgroup barrier)
     load_coarse(gcoarse, n_cw, coarse);
     __syncthreads();
     const int lane = threadIdx.x & 63;
+    double* st = stage[threadIdx.x >> 6];
     uint32_t* fl = flag_rows[threadIdx.x >> 6];
     const int64_t w = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
     const int64_t n_w = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
@@ -2114,6 +2125,7 @@ __global__ __launch_bounds__(kNetsThreads) void stride_checkpoint_kernel(const i
     if (k0 >= k1) return;
     const int64_t P0 = offsets[k0], P1 = offsets[k1];
     if (P0 >= P1) return;
+    const double A0 = apply_terms(0.0, L.aggR, L.aggL);
     if (lane < kW / 32) fl[lane] = 0;
     int64_t kb = k0;                                                   // trial starts held: kb .. kb + 63
     int64_t bnd = kb + lane < k1 ? offsets[kb + lane] : INT64_MAX;
@@ -2123,6 +2135,7 @@ __global__ __launch_bounds__(kNetsThreads) void stride_checkpoint_kernel(const i
     for (int u = 0; u < kE / 4; ++u)
         nxt[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ids + c0 + lane * kE + 4 * u));
     double ch = 0.0, cl = 0.0;       // running total of the segment open at the step's start
+    double a_prev = A0;              // A of the position before the step
     for (int64_t c = c0; c < P1; c += kW) {
         u32x4 cur[kE / 4];
 #pragma unroll
@@ -2192,10 +2205,56 @@ __global__ __launch_bounds__(kNetsThreads) void stride_checkpoint_kernel(const i
         if (lane == 0 && !sf) dd_merge(h, l, ch, cl);              // the open segment's carry
         double sh = h, sl = l;
         wave_seg_scan_dd(sf, sh, sl);
-        // a lane's first position is a multiple of kE, and kE divides 64, so
-        // each 64b + 63 is some lane's last event, where the running total is
-        // that lane's inclusive scan
-        if (ok[kE - 1] && ((pos + kE - 1) & 63) == 63) slots[(pos + kE - 1) >> 6] = sh + sl;
+        if constexpr (kStride) {
+            // a lane's first position is a multiple of kE, and kE divides 64, so
+            // each 64b + 63 is some lane's last event, where the running total is
+            // that lane's inclusive scan
+            if (ok[kE - 1] && ((pos + kE - 1) & 63) == 63) nets[(pos + kE - 1) >> 6] = sh + sl;
+        } else {
+            // the open segment's total before this lane's first event, then the
+            // running totals again, event by event, and A of each position
+            double rh = __shfl_up(sh, 1, 64), rl = __shfl_up(sl, 1, 64);
+            if (lane == 0) {
+                rh = ch;
+                rl = cl;
+            }
+            double A[kE];
+#pragma unroll
+            for (int q = 0; q < kE; ++q) {
+                if (fq[q]) {
+                    rh = 0.0;
+                    rl = 0.0;
+                }
+                dd_add(rh, rl, oq[q]);
+                A[q] = apply_terms(rh + rl, L.aggR, L.aggL);
+            }
+            // A of the position before each: A_0 before a trial's first event,
+            // the lane below's last A before this lane's first, a_prev before the step's
+            double before = __shfl_up(A[kE - 1], 1, 64);
+            if (lane == 0) before = a_prev;
+            double net[kE];
+#pragma unroll
+            for (int q = 0; q < kE; ++q) net[q] = A[q] - (fq[q] ? A0 : (q == 0 ? before : A[q - 1]));
+            a_prev = readlane_f64(A[kE - 1], 63);
+            // half a step at a time: lanes [32 hf, 32 hf + 32) hold positions
+            // [kW/2 hf, kW/2 (hf + 1)); position i of the half sits at i + i / kE
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                if ((lane >> 5) == hf) {
+#pragma unroll
+                    for (int q = 0; q < kE; ++q) st[(lane & 31) * (kE + 1) + q] = net[q];
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int r = 0; r < kE / 2; ++r) {
+                    const int i = r * 64 + lane;
+                    const int64_t p = c + hf * (kW / 2) + i;
+                    const double v = st[i + i / kE];
+                    if (p >= P0 && p < P1) __builtin_nontemporal_store(v, nets + (p - ev0));
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
         ch = readlane_f64(sh, 63);
         cl = readlane_f64(sl, 63);
         __builtin_amdgcn_wave_barrier();
@@ -2260,13 +2319,30 @@ hipError_t finish_tables(const ProbeTables& t, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_event_nets(const int64_t* offsets, const uint32_t* ids, const void* part_scratch, int P, int64_t C,
-                             uint64_t* probe, const LayerArgs& L, double* nets, int n_cu, hipStream_t s) {
+                             uint64_t* probe, double density, double events, const LayerArgs& L, double* nets, int n_cu,
+                             hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     const PartScratch ps = carve_parts(const_cast<void*>(part_scratch), P);
     const ProbeTables t = probe_tables(probe, C);
     hipError_t e = finish_tables(t, s);
     if (e != hipSuccess) return e;
     const size_t lds = (sizeof(uint32_t) * static_cast<size_t>(t.n_cw) + 15) & ~size_t(15);
+    // Scan every event where most pass the coarse map (a queue of almost all
+    // events only adds work) and the waves have too few steps each to share the
+    // gathers' latency.  Scan against candidates, us per call: 447 trials of 1377
+    // events at 0.3 / 0.6 / 1.0 of the catalogue with a loss 93 / 105 / 124 against
+    // 94 / 111 / 138, 7001 of 137 73 / 80 / 91 against 75 / 83 / 95; with more events
+    // the candidates are as fast or faster at every share: 20000 of 800
+    // 146 / 166 / 196 against 132 / 153 / 187, 60000 of 1000 468 / 665 / 1002 against
+    // 403 / 643 / 1006.
+    const double share =
+        -std::expm1(std::log1p(-std::min(density, 1.0 - 1e-12)) * static_cast<double>(int64_t(1) << t.cshift));
+    if (share > 0.5 && events < 2048.0 * (kNetsThreads / 64) * n_cu) {
+        hipLaunchKernelGGL((event_scan_kernel<8, false>),
+                           dim3(nets_grid(event_scan_kernel<8, false>, lds, L.trial_count, n_cu)), dim3(kNetsThreads),
+                           lds, s, offsets, ids, t.probe, t.coarse, t.cshift, t.n_cw, ps.stage, L, nets);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(event_nets_kernel, dim3(nets_grid(event_nets_kernel, lds, L.trial_count, n_cu)),
                        dim3(kNetsThreads), lds, s, offsets, ids, t.probe, t.coarse, t.cshift, t.n_cw, ps.stage, L, nets);
     return hipGetLastError();
@@ -2281,8 +2357,8 @@ hipError_t launch_stride_checkpoints(const int64_t* offsets, const uint32_t* ids
     hipError_t e = finish_tables(t, s);
     if (e != hipSuccess) return e;
     const size_t lds = (sizeof(uint32_t) * static_cast<size_t>(t.n_cw) + 15) & ~size_t(15);
-    hipLaunchKernelGGL(stride_checkpoint_kernel<8>,
-                       dim3(nets_grid(stride_checkpoint_kernel<8>, lds, L.trial_count, n_cu)), dim3(kNetsThreads), lds,
+    hipLaunchKernelGGL((event_scan_kernel<8, true>),
+                       dim3(nets_grid(event_scan_kernel<8, true>, lds, L.trial_count, n_cu)), dim3(kNetsThreads), lds,
                        s, offsets, ids, t.probe, t.coarse, t.cshift, t.n_cw, ps.stage, L, stride);
     return hipGetLastError();
 }

@@ -29,6 +29,7 @@ def ara():
     (900, 400, 1_200_007, 5, 30_000),       # a coarse bit per two events
     (700, 500, 34_000_000, 1, 30_000),      # a coarse bit per 64 events
     (1, 1_000, 4_096, 2, 1_000),
+    (26_500, 520, 9_001, 3, 8_000),         # nearly every event of 9 million: many steps per wave
 ])
 def test_event_nets_queue_and_coarse_map(ara, n_trials, lam, C, J, nnz):
     yet = make_yet(n_trials, lam, C, seed=3 * n_trials + lam)
