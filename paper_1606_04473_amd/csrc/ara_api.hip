@@ -810,34 +810,75 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     const hipMemcpyKind kind = dev_in ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     if ((e = hipMemcpyAsync(t->offsets, trial_offsets, off_bytes, kind, s)) != hipSuccess)
         return cleanup(hip_fail(e, "copy offsets"));
-    if (n_events && (e = hipMemcpyAsync(t->ids, event_ids, sizeof(uint32_t) * n_events, kind, s)) != hipSuccess)
-        return cleanup(hip_fail(e, "copy event ids"));
-    if ((e = hipMemsetAsync(t->ids + n_events, 0, sizeof(uint32_t) * ara::kIdPad, s)) != hipSuccess)
-        return cleanup(hip_fail(e, "clear id padding"));
     if (elt_bytes && (e = hipMemcpyAsync(t->elts, elt_losses, elt_bytes, kind, s)) != hipSuccess)
         return cleanup(hip_fail(e, "copy ELT pool"));
-    // validation on the device, one flag word read back
-    PoolBuffer flag;
-    if ((e = flag.alloc(sizeof(uint32_t), s)) != hipSuccess) return cleanup(hip_fail(e, "scratch"));
-    if ((e = hipMemsetAsync(flag.p, 0, sizeof(uint32_t), s)) != hipSuccess) return cleanup(hip_fail(e, "memset"));
-    if ((e = ara::launch_validate(t->offsets, n_trials, t->ids, n_events, t->elts,
-                                  base ? 0 : static_cast<int64_t>(n_elts) * catalogue_size, catalogue_size,
-                                  static_cast<uint32_t*>(flag.p), t->n_cu, s)) != hipSuccess)
+    if ((e = hipMemsetAsync(t->ids + n_events, 0, sizeof(uint32_t) * ara::kIdPad, s)) != hipSuccess)
+        return cleanup(hip_fail(e, "clear id padding"));
+    // IDs of the device that lie on 16 bytes are copied by the pass that checks
+    // and counts them
+    const uint32_t* ids_in = t->ids;
+    if (dev_in && reinterpret_cast<uintptr_t>(event_ids) % 16 == 0)
+        ids_in = event_ids;
+    else if (n_events && (e = hipMemcpyAsync(t->ids, event_ids, sizeof(uint32_t) * n_events, kind, s)) != hipSuccess)
+        return cleanup(hip_fail(e, "copy event ids"));
+    // The checks and the sizes of the YET's copies, read back at once: the
+    // offsets first (the counts walk the trials), then one pass over the IDs,
+    // then the copies' starts from the counts.
+    PoolBuffer result, counts;
+    if ((e = result.alloc(sizeof(ara::CreateResult), s)) != hipSuccess) return cleanup(hip_fail(e, "scratch"));
+    ara::CreateResult* d_res = static_cast<ara::CreateResult*>(result.p);
+    if ((e = hipMemsetAsync(d_res, 0, sizeof(ara::CreateResult), s)) != hipSuccess)
+        return cleanup(hip_fail(e, "memset"));
+    if ((e = ara::launch_validate(t->offsets, n_trials, n_events, t->elts,
+                                  base ? 0 : static_cast<int64_t>(n_elts) * catalogue_size, d_res, t->n_cu, s)) !=
+        hipSuccess)
         return cleanup(hip_fail(e, "validate kernel"));
-    uint32_t host_flag = 0;
-    int64_t ends[2] = {0, 0};
-    if ((e = hipMemcpyAsync(&host_flag, flag.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return cleanup(hip_fail(e, "read validation flag"));
-    if ((e = hipMemcpyAsync(&ends[0], t->offsets, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(&ends[1], t->offsets + n_trials, sizeof(int64_t), hipMemcpyDeviceToHost, s)) !=
-            hipSuccess)
-        return cleanup(hip_fail(e, "read offsets"));
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return cleanup(hip_fail(e, "synchronize"));
-    if (host_flag & 1u) return cleanup(fail(ARA_ERR_OUT_OF_RANGE, "an event ID is >= catalogue size %lld",
-                                            (long long)catalogue_size));
-    if ((host_flag & 2u) || ends[0] != 0 || ends[1] != n_events)
+    // counted in the finer parts where the 16-bit copy can be built
+    int shift = ara::kImgShift, bins = 0;
+    if (!(flags & ARA_PLAIN_LAYOUT) && n_trials > 0) {
+        bins = ara::stream_layout_parts(n_trials, catalogue_size);
+        if (bins > 0) shift = ara::kStreamShift;
+        else bins = ara::part_layout_parts(n_trials, catalogue_size);
+    }
+    if (bins > 0) {
+        const size_t cnt_bytes = sizeof(int32_t) * static_cast<size_t>(n_trials) * bins;
+        e = counts.alloc(cnt_bytes, s);
+        if (e == hipSuccess) {
+            if ((e = hipMemsetAsync(counts.p, 0, cnt_bytes, s)) != hipSuccess) return cleanup(hip_fail(e, "memset"));
+        } else if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+            (void)hipGetLastError();
+            bins = 0;                          // not enough memory for the copies: plain layout only
+        } else {
+            return cleanup(hip_fail(e, "scratch"));
+        }
+    }
+    int32_t* cnt = static_cast<int32_t*>(counts.p);
+    if ((e = ara::launch_yet_count(t->offsets, n_trials, ids_in, t->ids, n_events, catalogue_size, shift, bins, cnt,
+                                   d_res, t->n_cu, s)) != hipSuccess)
+        return cleanup(hip_fail(e, "pass over the event ids"));
+    // a copy that does not fit in memory is left out: the passes over the others remain
+    auto left_out = [](hipError_t err) {
+        if (err != hipErrorOutOfMemory && err != hipErrorMemoryAllocation) return false;
+        (void)hipGetLastError();
+        return true;
+    };
+    if (bins > 0) {
+        e = ara::plan_part_layout(cnt, shift, bins, n_trials, catalogue_size, d_res, s, &t->parts);
+        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
+        if (shift == ara::kStreamShift) {
+            e = ara::plan_stream_layout(cnt, n_trials, n_events, catalogue_size, d_res, s, &t->stream);
+            if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));
+        }
+    }
+    ara::CreateResult res;
+    if ((e = hipMemcpyAsync(&res, d_res, sizeof(res), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipStreamSynchronize(s)) != hipSuccess)
+        return cleanup(hip_fail(e, "read checks and sizes"));
+    if (res.flags & ara::kCreateBadId)
+        return cleanup(fail(ARA_ERR_OUT_OF_RANGE, "an event ID is >= catalogue size %lld", (long long)catalogue_size));
+    if (res.flags & ara::kCreateBadOffsets)
         return cleanup(fail(ARA_ERR_INVALID_ARG, "trial offsets must start at 0, not decrease, end at n_events"));
-    if (host_flag & 4u) return cleanup(fail(ARA_ERR_INVALID_ARG, "ELT losses must be finite and >= 0"));
+    if (res.flags & ara::kCreateBadLoss) return cleanup(fail(ARA_ERR_INVALID_ARG, "ELT losses must be finite and >= 0"));
     if (!base) {
         // the pool's nonzero entries, which the per-request fold reads
         if ((e = ara::build_sparse_pool(t->elts, n_elts, catalogue_size, s, &t->sparse)) != hipSuccess ||
@@ -845,24 +886,16 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
             return cleanup(hip_fail(e, "sparse ELT pool"));
         t->bytes += t->sparse.bytes;
     }
-    if (!(flags & ARA_PLAIN_LAYOUT) && n_trials > 0) {
-        e = ara::build_part_layout(t->offsets, t->ids, n_trials, n_events, catalogue_size, t->n_cu, s, &t->parts);
-        if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-            (void)hipGetLastError();
-            t->parts = ara::PartLayout{};      // not enough memory for the copy: plain layout only
-        } else if (e != hipSuccess) {
-            return cleanup(hip_fail(e, "partitioned layout"));
-        }
+    if (bins > 0) {
+        e = ara::fill_part_layout(t->offsets, t->ids, n_trials, res, t->n_cu, s, &t->parts);
+        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
         t->bytes += t->parts.bytes;
-        e = ara::build_stream_layout(t->offsets, t->ids, n_trials, n_events, catalogue_size, t->n_cu, s, &t->stream);
-        if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-            (void)hipGetLastError();
-            t->stream = ara::StreamLayout{};   // not enough memory for the 16-bit copy: 32-bit passes only
-        } else if (e != hipSuccess) {
-            return cleanup(hip_fail(e, "16-bit stream layout"));
-        }
+        e = ara::fill_stream_layout(t->offsets, t->ids, n_trials, res, d_res, t->n_cu, s, &t->stream);
+        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));
         t->bytes += t->stream.bytes;
     }
+    // calls on other streams may follow at once
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return cleanup(hip_fail(e, "synchronize"));
     note_use(t, s);
     *out = t;
     return ARA_OK;
@@ -1030,7 +1063,7 @@ ara_status ara_yet_footprint(int64_t n_trials, int64_t n_events, int64_t catalog
     if (!bytes || n_trials < 0 || n_events < 0 || catalogue_size < 1)
         return fail(ARA_ERR_INVALID_ARG, "NULL output or negative size");
     const int64_t N = n_trials, E = n_events;
-    int64_t b = 8 * (N + 1) + 4 * (E + ara::kIdPad) + 64;          // offsets, IDs, validation flag
+    int64_t b = 8 * (N + 1) + 4 * (E + ara::kIdPad) + 1024;        // offsets, IDs, checks and sizes
     int64_t temp = 0;
     if (!(flags & ARA_PLAIN_LAYOUT) && N > 0) {
         // 32-bit partitioned copy: IDs, segment padding (< 4 per segment,
@@ -1039,7 +1072,7 @@ ara_status ara_yet_footprint(int64_t n_trials, int64_t n_events, int64_t catalog
         if (P <= ara::kMaxParts) {
             const int64_t T = 256, tiles = (N + T - 1) / T;
             b += 4 * (E + 3 * N * P + 32 * tiles + ara::kIdPad) + 4 * tiles * (T * P + 1) + 8 * (tiles + 1);
-            temp = std::max(temp, 4 * N * P + 8 * tiles);
+            temp = 4 * N * P;
         }
         // 16-bit copy: IDs (groups of at least 16 trials padded to 8 IDs per
         // part), trial ends and group starts, part bases; counts while building
@@ -1047,7 +1080,7 @@ ara_status ara_yet_footprint(int64_t n_trials, int64_t n_events, int64_t catalog
         if (Q <= ara::kMaxStreamParts) {
             const int64_t NG = (N + 15) / 16;
             b += 2 * (E + 7 * Q * NG + 512) + 2 * ara::kStreamGroupSlots * Q * NG + 4 * Q * (NG + 1) + 8 * (Q + 1);
-            temp = std::max(temp, 4 * N * Q + 4 * Q * NG + 8 * Q + 4);
+            temp = 4 * N * Q;
         }
     }
     *bytes = b + temp;

@@ -155,6 +155,22 @@ struct CheckpointState {
 // inside a tile part by part, inside a part trial by trial.
 constexpr int kMaxParts = 64;
 
+// What creating tables reads back: findings, and the lengths of the YET's copies
+enum : uint32_t {
+    kCreateBadId = 1u,              // an ID outside the catalogue
+    kCreateBadOffsets = 2u,         // offsets that decrease or don't span the IDs
+    kCreateBadLoss = 4u,
+    kCreateWideTile = 8u,           // a tile, group or part too large for its copy's positions
+    kCreateWideGroup = 16u,
+    kCreateWidePart = 32u,
+};
+struct CreateResult {
+    uint32_t flags;
+    uint32_t pad_;
+    int64_t part_ids;               // IDs of the 32-bit copy, padding included
+    int64_t stream_ids[64];         // IDs of each stream part
+};
+
 // The nonzero entries of the ELT pool, row by row in 4096-event chunks (one
 // superblock of the part images each): entries of chunk c of row r are
 // [chunk_off[r * n_chunks + c], chunk_off[r * n_chunks + c + 1]), in event
@@ -214,8 +230,12 @@ struct StreamLayout {
     uint32_t* gstart = nullptr;     // [P][NG + 1] group starts relative to the part's stream
     uint16_t* gend = nullptr;       // [P][NG][64] end of trial i of the group, relative to the group start
 };
-hipError_t build_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events, int64_t C,
-                               int n_cu, hipStream_t s, StreamLayout* out);
+int stream_layout_parts(int64_t N, int64_t C);      // 0: not used
+// plan: sizes and starts from the trials' counts; fill: the copy, of the lengths read back
+hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, int64_t C, CreateResult* res,
+                              hipStream_t s, StreamLayout* out);
+hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res,
+                              const CreateResult* d_res, int n_cu, hipStream_t s, StreamLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_stream_layout(StreamLayout* L, hipStream_t s);
 // bytes of the per-(part, trial) partial sums of the streaming pass
@@ -470,9 +490,9 @@ struct TrialPassArgs {
     double* stride;       // checkpoints or null
 };
 
-hipError_t launch_validate(const int64_t* offsets, int64_t n_trials, const uint32_t* ids,
-                           int64_t n_events, const double* elts, int64_t n_elt_values,
-                           int64_t C, uint32_t* d_flags, int n_cu, hipStream_t s);
+// the trial offsets and the ELT losses (the IDs are checked as they are counted)
+hipError_t launch_validate(const int64_t* offsets, int64_t n_trials, int64_t n_events, const double* elts,
+                           int64_t n_elt_values, CreateResult* res, int n_cu, hipStream_t s);
 hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t s);
 
 hipError_t launch_fold(const double* elts, int64_t C, const LayerArgs& L, double* o,
@@ -508,8 +528,16 @@ hipError_t launch_debug_lookups(const int64_t* offsets, const uint32_t* ids, con
                                 double* losses_out, hipStream_t s);
 
 // catalogue-partitioned path
-hipError_t build_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events, int64_t C,
-                             int n_cu, hipStream_t s, PartLayout* out);
+// create's pass over the IDs: copied from src (unless src == ids), checked, and
+// each trial's events counted in `bins` parts of 2^shift catalogue events
+// (cnt[trial][bin], zero before); src and ids 16-byte aligned
+hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* src, uint32_t* ids, int64_t n_events,
+                            int64_t C, int shift, int bins, int32_t* cnt, CreateResult* res, int n_cu, hipStream_t s);
+int part_layout_parts(int64_t N, int64_t C);        // 0: not used
+hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
+                            hipStream_t s, PartLayout* out);
+hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res, int n_cu,
+                            hipStream_t s, PartLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_part_layout(PartLayout* L, hipStream_t s);
 int64_t part_scratch_bytes(int64_t C, int P);

@@ -64,55 +64,186 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 // create-time layout
 // ---------------------------------------------------------------------------
 
-// events per (trial, part), one wavefront per trial
-__global__ __launch_bounds__(256) void part_count_kernel(const int64_t* __restrict__ offsets,
-                                                         const uint32_t* __restrict__ ids, int64_t N, int P,
-                                                         int32_t* __restrict__ cnt) {
-    __shared__ int32_t c[4][kMaxParts];
-    const int w = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_waves = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
-    for (int64_t t = uniform_i64((static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6); t < N;
-         t += n_waves) {
-        for (int p = lane; p < P; p += 64) c[w][p] = 0;
-        __builtin_amdgcn_wave_barrier();
-        {
-            // four 64-ID chunks loaded together
-            const int64_t b = offsets[t], e = offsets[t + 1];
-            for (int64_t c0 = b; c0 < e; c0 += 256) {
-                uint32_t idk[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int64_t at = c0 + k * 64 + lane;
-                    idk[k] = at < e ? ids[at] : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (c0 + k * 64 + lane < e) atomicAdd(&c[w][idk[k] >> kPartShift], 1);
-            }
+// smallest t in [lo, hi] with offsets[t] >= target, given offsets[hi] >=
+// target; a 64-way search, all arguments uniform over the wave
+__device__ int64_t first_trial_at(const int64_t* __restrict__ offsets, int64_t lo, int64_t hi, int64_t target,
+                                  int lane) {
+    while (hi - lo >= 64) {
+        const int64_t step = (hi - lo) / 64;
+        const uint64_t m = __ballot(offsets[lo + lane * step] >= target);   // index <= hi - step
+        if (m == 0) {
+            lo = lo + 63 * step + 1;
+        } else {
+            const int f = __builtin_ctzll(m);
+            const int64_t nlo = f > 0 ? lo + (f - 1) * step + 1 : lo;
+            hi = lo + f * step;
+            lo = nlo;
         }
-        __builtin_amdgcn_wave_barrier();
-        for (int p = lane; p < P; p += 64) cnt[t * P + p] = c[w][p];
-        __builtin_amdgcn_wave_barrier();
     }
+    const int64_t idx = lo + lane;
+    const uint64_t m = __ballot(idx <= hi && offsets[idx] >= target);
+    return lo + __builtin_ctzll(m);
 }
 
-// per tile: layout-order exclusive scan of the padded segment sizes
-__global__ __launch_bounds__(256) void tile_scan_kernel(const int32_t* __restrict__ cnt, int64_t N, int P, int T,
-                                                        uint32_t* __restrict__ seg_rel, int64_t* __restrict__ tile_size) {
+// Create's one pass over the IDs, bound by memory: it checks them, counts each trial's events in every part of 2^shift catalogue events (bins parts) and,
+// with kCopy, stores them in the tables (16-byte aligned sources).  Each wave
+// takes an equal run of the IDs in rows of 256, four rows of 16-byte loads in
+// flight while the four before are counted; the counters lie in LDS, repeated for
+// groups of lanes where there are few parts, and go to cnt at each trial's end
+// (added there for the trials that two waves share; cnt is zero before).  One
+// launch instead of a copy, a check and a count for each of the two layouts, 150 M
+// IDs over 31 and 8 parts: 260 + 93 + 187 + 198 us -> 230 us.
+template <bool kCopy>
+__global__ __launch_bounds__(256) void yet_count_kernel(const int64_t* __restrict__ offsets, int64_t N,
+                                                        const uint32_t* __restrict__ src, uint32_t* __restrict__ dst,
+                                                        int64_t n, uint32_t c32, int shift, int bins,
+                                                        int32_t* __restrict__ cnt, uint32_t* __restrict__ flags) {
+    constexpr int kRow = 256, kRows = 4;            // IDs per row, rows in flight
+    __shared__ int32_t counters[4][64];
+    if (*flags & kCreateBadOffsets) bins = 0;       // the trials' ranges can't be trusted
+    int32_t* c = counters[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    const int64_t w = uniform_i64((static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6);
+    const int64_t n_w = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
+    const int64_t rows = (n + kRow - 1) / kRow;
+    const int64_t x0 = rows * w / n_w * kRow;
+    const int64_t x1 = min(rows * (w + 1) / n_w * kRow, n);
+    if (x0 >= x1) return;
+    // counter of a part: [part][copy], the copies for lanes apart (64 in all)
+    const int rep_bits = bins > 0 ? 31 - __builtin_clz(64u / static_cast<uint32_t>(bins)) : 0;
+    const uint32_t rep = static_cast<uint32_t>(lane) & ((1u << rep_bits) - 1u);
+    const uint32_t last_bin = static_cast<uint32_t>(bins > 0 ? bins - 1 : 0);
+    c[lane] = 0;
+    int64_t k = 0, kb = 0, bnd = 0, end = INT64_MAX;
+    bool shared = false;                            // the trial began in an earlier wave's run
+    if (bins > 0) {
+        k = first_trial_at(offsets, 0, N, x0 + 1, lane) - 1;
+        kb = k;
+        bnd = offsets[min(kb + 1 + lane, N)];
+        end = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(bnd), 0));
+        shared = uniform_i64(offsets[k]) < x0;
+    }
+    auto flush = [&](bool add) {
+        __builtin_amdgcn_wave_barrier();
+        if (lane < bins) {
+            int32_t v = 0;
+            for (int r = 0; r < (1 << rep_bits); ++r) {
+                v += c[(lane << rep_bits) + r];
+                c[(lane << rep_bits) + r] = 0;
+            }
+            int32_t* to = cnt + k * bins + lane;
+            if (!add) *to = v;
+            else if (v) atomicAdd(to, v);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    uint32_t bad = 0;
+    u32x4 nxt[kRows];
+    auto load = [&](int64_t x) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int64_t at = x + r * kRow + lane * 4;
+            nxt[r] = u32x4{0, 0, 0, 0};
+            if (at + 4 <= n) {
+                if (x + r * kRow < x1) nxt[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + at));
+            } else {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (at + q < n) nxt[r][q] = src[at + q];
+            }
+        }
+    };
+    load(x0);
+    for (int64_t x = x0; x < x1; x += kRow * kRows) {
+        u32x4 cur[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) cur[r] = nxt[r];
+        if (x + kRow * kRows < x1) load(x + kRow * kRows);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int64_t xr = x + r * kRow;
+            if (xr >= x1) continue;
+            const int64_t xe = min(xr + kRow, x1);
+            const int64_t at = xr + lane * 4;
+            if (kCopy) {
+                if (at + 4 <= n) {
+                    *reinterpret_cast<u32x4*>(dst + at) = cur[r];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        if (at + q < n) dst[at + q] = cur[r][q];
+                }
+            }
+            uint32_t most = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) most = max(most, cur[r][q]);
+            bad |= most >= c32 ? 1u : 0u;
+            if (bins == 0) continue;
+            int32_t* slot[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                slot[q] = c + ((min(cur[r][q] >> shift, last_bin) << rep_bits) | rep);
+            int64_t from = xr;
+            for (;;) {
+                const int64_t to = min(end, xe);
+                if (from == xr && to == xr + kRow) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) atomicAdd(slot[q], 1);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (at + q >= from && at + q < to) atomicAdd(slot[q], 1);
+                }
+                from = to;
+                if (end > xe) break;
+                flush(shared);
+                shared = false;
+                if (++k - kb == 64) {
+                    kb = k;
+                    bnd = offsets[min(kb + 1 + lane, N)];
+                }
+                end = k < N ? static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(bnd), static_cast<int>(k - kb)))
+                            : INT64_MAX;
+                if (from >= xe) break;
+            }
+        }
+    }
+    if (bins > 0 && k < N) flush(true);
+    if (bad) atomicOr(flags, kCreateBadId);
+}
+
+// Per tile: layout-order exclusive scan of the padded segment sizes, from counts
+// in `bins` parts, 2^fine of them to a part here.  The tile's counts, one
+// contiguous piece of cnt, are summed per (part, trial) in LDS (dynamic, [P][Tk])
+// and scanned there.
+__global__ __launch_bounds__(256) void tile_scan_kernel(const int32_t* __restrict__ cnt, int bins, int fine, int64_t N,
+                                                        int P, int T, uint32_t* __restrict__ seg_rel,
+                                                        int64_t* __restrict__ tile_size) {
     __shared__ int64_t part_sum[256];
+    extern __shared__ int32_t sizes[];
     const int64_t tile = blockIdx.x;
     const int64_t t0 = tile * T;
     const int Tk = static_cast<int>(N - t0 < T ? N - t0 : T);
     const int n = P * Tk;
     const int64_t base = tile * (static_cast<int64_t>(T) * P + 1);
+    for (int j = threadIdx.x; j < n; j += 256) sizes[j] = 0;
+    __syncthreads();
+    constexpr int kAhead = 8;                       // counts loaded together
+    for (int j0 = threadIdx.x; j0 < Tk * bins; j0 += 256 * kAhead) {
+        int32_t v[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) v[k] = j0 + k * 256 < Tk * bins ? cnt[t0 * bins + j0 + k * 256] : 0;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int j = j0 + k * 256, i = j / bins;
+            if (j < Tk * bins) atomicAdd(&sizes[((j - i * bins) >> fine) * Tk + i], v[k]);
+        }
+    }
+    __syncthreads();
     const int per = (n + 255) / 256;
     const int j0 = threadIdx.x * per;
     int64_t local = 0;
-    for (int j = j0; j < j0 + per && j < n; ++j) {
-        const int p = j / Tk, i = j % Tk;
-        local += (cnt[(t0 + i) * P + p] + 3) & ~3;
-    }
+    for (int j = j0; j < j0 + per && j < n; ++j) local += (static_cast<int64_t>(sizes[j]) + 3) & ~int64_t(3);
     part_sum[threadIdx.x] = local;
     __syncthreads();
     for (int off = 1; off < 256; off <<= 1) {
@@ -123,13 +254,48 @@ __global__ __launch_bounds__(256) void tile_scan_kernel(const int32_t* __restric
     }
     int64_t run = part_sum[threadIdx.x] - local;
     for (int j = j0; j < j0 + per && j < n; ++j) {
-        const int p = j / Tk, i = j % Tk;
-        seg_rel[base + j] = static_cast<uint32_t>(run);
-        run += (cnt[(t0 + i) * P + p] + 3) & ~3;
+        const int64_t size = (static_cast<int64_t>(sizes[j]) + 3) & ~int64_t(3);
+        sizes[j] = static_cast<int32_t>(static_cast<uint32_t>(run));
+        run += size;
     }
+    __syncthreads();
+    for (int j = threadIdx.x; j < n; j += 256) seg_rel[base + j] = static_cast<uint32_t>(sizes[j]);
     if (threadIdx.x == 255) {
         seg_rel[base + n] = static_cast<uint32_t>(part_sum[255]);
         tile_size[tile] = part_sum[255];
+    }
+}
+
+// tile sizes -> tile starts in place (each padded to kTileAlign IDs), one workgroup
+__global__ __launch_bounds__(1024) void tile_starts_kernel(int64_t* __restrict__ v, int64_t n_tiles,
+                                                           CreateResult* __restrict__ res) {
+    __shared__ int64_t tsum[1024];
+    const int64_t per = (n_tiles + 1023) / 1024;
+    const int64_t j0 = static_cast<int64_t>(threadIdx.x) * per;
+    int64_t local = 0;
+    bool wide = false;
+    for (int64_t j = j0; j < j0 + per && j < n_tiles; ++j) {
+        wide |= v[j] >= (int64_t(1) << 31);
+        local += (v[j] + kTileAlign - 1) & ~int64_t(kTileAlign - 1);
+    }
+    if (wide) atomicOr(&res->flags, kCreateWideTile);
+    tsum[threadIdx.x] = local;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int64_t add = static_cast<int>(threadIdx.x) >= off ? tsum[threadIdx.x - off] : 0;
+        __syncthreads();
+        tsum[threadIdx.x] += add;
+        __syncthreads();
+    }
+    int64_t run = tsum[threadIdx.x] - local;
+    for (int64_t j = j0; j < j0 + per && j < n_tiles; ++j) {
+        const int64_t size = (v[j] + kTileAlign - 1) & ~int64_t(kTileAlign - 1);
+        v[j] = run;
+        run += size;
+    }
+    if (threadIdx.x == 1023) {
+        v[n_tiles] = tsum[1023];
+        res->part_ids = tsum[1023];
     }
 }
 
@@ -150,7 +316,8 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 // bit's ballot or its complement; a lane's rank among the earlier ones places
 // it, all 64 write in one store, and the last lane of each part moves its
 // cursor on.  A run whose IDs exceed the stage is scattered straight to the
-// copy.
+// copy, after its ranges are filled with the sentinel.  The run that ends a tile
+// fills the tile's padding, the last one the readable IDs after the copy.
 constexpr int kChunkTrials = 32;
 constexpr int kPartStageIds = 36 * 1024;        // 144 KB of LDS
 __global__ __launch_bounds__(1024) void part_scatter_kernel(const int64_t* __restrict__ offsets,
@@ -191,6 +358,18 @@ __global__ __launch_bounds__(1024) void part_scatter_kernel(const int64_t* __res
         const bool staged = sseg[P] <= static_cast<uint32_t>(kPartStageIds);
         if (staged) {                                  // segments end in sentinel padding, as in the copy
             for (uint32_t u = threadIdx.x; u < sseg[P]; u += blockDim.x) stage[u] = kSentinel;
+        } else {
+            for (int p = w; p < P; p += 16) {
+                uint32_t* dst = pids + tile_start[tile] + seg_rel[base + static_cast<int64_t>(p) * Tk + i0];
+                for (uint32_t u = lane; u < sseg[p + 1] - sseg[p]; u += 64) dst[u] = kSentinel;
+            }
+            __threadfence();
+        }
+        if (i1 == Tk) {
+            const int64_t tile_end = tile_start[tile + 1] + (tile + 1 == n_tiles ? kIdPad : 0);
+            for (int64_t u = tile_start[tile] + seg_rel[base + static_cast<int64_t>(P) * Tk] + threadIdx.x; u < tile_end;
+                 u += blockDim.x)
+                pids[u] = kSentinel;
         }
         __syncthreads();
         for (int i = i0 + w; i < i1; i += 16) {
@@ -1523,89 +1702,88 @@ void free_sparse_pool(SparsePool* sp) {
 int64_t part_size() { return kPartSize; }
 int part_tile_trials() { return kTileMax; }
 
-hipError_t build_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events, int64_t C,
-                             int n_cu, hipStream_t s, PartLayout* out) {
+hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* src, uint32_t* ids, int64_t n_events,
+                            int64_t C, int shift, int bins, int32_t* cnt, CreateResult* res, int n_cu, hipStream_t s) {
+    if (n_events <= 0) return hipSuccess;
+    if (bins < 0 || bins > 64) return hipErrorInvalidValue;
+    const bool copy = src != ids;
+    if (reinterpret_cast<uintptr_t>(src) % 16 || reinterpret_cast<uintptr_t>(ids) % 16) return hipErrorInvalidValue;
+    // 32 waves per CU, at least four loads of 1024 IDs each
+    int64_t waves = (n_events + 4095) / 4096;
+    waves = std::min(waves, int64_t(n_cu) * 32);
+    const dim3 g(static_cast<uint32_t>((waves + 3) / 4)), b(256);
+    const uint32_t c32 = static_cast<uint32_t>(std::min<int64_t>(C, 0xFFFFFFFFll));
+    if (copy)
+        hipLaunchKernelGGL(yet_count_kernel<true>, g, b, 0, s, offsets, N, src, ids, n_events, c32, shift, bins, cnt,
+                           &res->flags);
+    else
+        hipLaunchKernelGGL(yet_count_kernel<false>, g, b, 0, s, offsets, N, src, ids, n_events, c32, shift, bins, cnt,
+                           &res->flags);
+    return hipGetLastError();
+}
+
+int part_layout_parts(int64_t N, int64_t C) {
+    const int64_t P = (C + kPartSize - 1) / kPartSize;
+    return N < 1 || P < 1 || P > kMaxParts ? 0 : static_cast<int>(P);
+}
+
+hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
+                            hipStream_t s, PartLayout* out) {
     *out = PartLayout{};
-    const int P = static_cast<int>((C + kPartSize - 1) / kPartSize);
-    if (P < 1 || P > kMaxParts || N < 1) return hipSuccess;            // layout not used
+    const int P = part_layout_parts(N, C);
+    if (P == 0) return hipSuccess;                                     // layout not used
     const int T = kTileMax;
     const int64_t n_tiles = (N + T - 1) / T;
-    hipError_t e;
-    int32_t* cnt = nullptr;
-    int64_t* tsize = nullptr;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&cnt), sizeof(int32_t) * N * P, s)) != hipSuccess) return e;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->seg_rel),
-                            sizeof(uint32_t) * (n_tiles * (static_cast<int64_t>(T) * P + 1)), s)) != hipSuccess)
-        goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&tsize), sizeof(int64_t) * n_tiles, s)) != hipSuccess) goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->tile_start), sizeof(int64_t) * (n_tiles + 1), s)) !=
-        hipSuccess)
-        goto fail;
-    {
-        int64_t blocks = (N + 3) / 4;
-        if (blocks > int64_t(n_cu) * 16) blocks = int64_t(n_cu) * 16;
-        hipLaunchKernelGGL(part_count_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, offsets, ids, N,
-                           P, cnt);
-        if ((e = hipGetLastError()) != hipSuccess) goto fail;
-        hipLaunchKernelGGL(tile_scan_kernel, dim3(static_cast<uint32_t>(n_tiles)), dim3(256), 0, s, cnt, N, P, T,
-                           out->seg_rel, tsize);
-        if ((e = hipGetLastError()) != hipSuccess) goto fail;
-        std::vector<int64_t> h(n_tiles), st(n_tiles + 1);
-        if ((e = hipMemcpyAsync(h.data(), tsize, sizeof(int64_t) * n_tiles, hipMemcpyDeviceToHost, s)) != hipSuccess)
-            goto fail;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) goto fail;
-        st[0] = 0;
-        for (int64_t k = 0; k < n_tiles; ++k) {
-            if (h[k] >= (int64_t(1) << 31)) {   // too large for 32-bit positions: keep the plain layout
-                dev_free(cnt, s);
-                dev_free(tsize, s);
-                dev_free(out->seg_rel, s);
-                dev_free(out->tile_start, s);
-                (void)hipStreamSynchronize(s);
-                *out = PartLayout{};
-                return hipSuccess;
-            }
-            st[k + 1] = st[k] + ((h[k] + kTileAlign - 1) & ~int64_t(kTileAlign - 1));   // padded with sentinels
-        }
-        const int64_t total = st[n_tiles];
-        if ((e = hipMemcpyAsync(out->tile_start, st.data(), sizeof(int64_t) * (n_tiles + 1), hipMemcpyHostToDevice,
-                                s)) != hipSuccess)
-            goto fail;
-        if ((e = dev_alloc(reinterpret_cast<void**>(&out->pids), sizeof(uint32_t) * (total + kIdPad), s)) !=
-            hipSuccess)
-            goto fail;
-        int64_t fb = (total + kIdPad + 255) / 256;
-        if (fb > 8192) fb = 8192;
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(static_cast<uint32_t>(fb)), dim3(256), 0, s, out->pids, total + kIdPad,
-                           kSentinel);
-        if ((e = hipGetLastError()) != hipSuccess) goto fail;
-        {
-            // one 16-wave workgroup per CU (the stage fills LDS), over runs of kChunkTrials trials
-            int64_t sb = n_tiles * ((T + kChunkTrials - 1) / kChunkTrials);
-            if (sb > int64_t(n_cu)) sb = n_cu;
-            hipLaunchKernelGGL(part_scatter_kernel, dim3(static_cast<uint32_t>(sb)), dim3(1024), 0, s, offsets, ids, N,
-                               P, T, out->seg_rel, out->tile_start, out->pids);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) goto fail;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) goto fail;
-        (void)n_events;
-        out->P = P;
-        out->T = T;
-        out->n_tiles = n_tiles;
-        out->length = total;
-        out->bytes = sizeof(uint32_t) * (total + kIdPad) + sizeof(uint32_t) * (n_tiles * (int64_t(T) * P + 1)) +
-                     sizeof(int64_t) * (n_tiles + 1);
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->seg_rel),
+                             sizeof(uint32_t) * (n_tiles * (static_cast<int64_t>(T) * P + 1)), s);
+    if (e == hipSuccess)
+        e = dev_alloc(reinterpret_cast<void**>(&out->tile_start), sizeof(int64_t) * (n_tiles + 1), s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(tile_scan_kernel, dim3(static_cast<uint32_t>(n_tiles)), dim3(256),
+                           sizeof(int32_t) * static_cast<size_t>(T) * P, s, cnt, bins,
+                           kPartShift - shift, N, P, T, out->seg_rel, out->tile_start);
+        e = hipGetLastError();
     }
-    // temporaries go back to the library's device memory cache: no free waits for the device
-    dev_free(cnt, s);
-    dev_free(tsize, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(tile_starts_kernel, dim3(1), dim3(1024), 0, s, out->tile_start, n_tiles, res);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+        free_part_layout(out, s);
+        return e;
+    }
+    out->P = P;
+    out->T = T;
+    out->n_tiles = n_tiles;
     return hipSuccess;
-fail:
-    if (cnt) dev_free(cnt, s);
-    if (tsize) dev_free(tsize, s);
-    free_part_layout(out, s);
-    (void)hipStreamSynchronize(s);
-    return e;
+}
+
+hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res, int n_cu,
+                            hipStream_t s, PartLayout* out) {
+    if (out->P == 0) return hipSuccess;
+    if (res.flags & kCreateWideTile) {      // too large for 32-bit positions: keep the plain layout
+        free_part_layout(out, s);
+        return hipSuccess;
+    }
+    const int64_t total = res.part_ids;
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->pids), sizeof(uint32_t) * (total + kIdPad), s);
+    if (e == hipSuccess) {
+        // one 16-wave workgroup per CU (the stage fills LDS), over runs of kChunkTrials trials
+        int64_t sb = out->n_tiles * ((out->T + kChunkTrials - 1) / kChunkTrials);
+        if (sb > int64_t(n_cu)) sb = n_cu;
+        hipLaunchKernelGGL(part_scatter_kernel, dim3(static_cast<uint32_t>(sb)), dim3(1024), 0, s, offsets, ids, N,
+                           out->P, out->T, out->seg_rel, out->tile_start, out->pids);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+        free_part_layout(out, s);
+        return e;
+    }
+    out->length = total;
+    out->bytes = static_cast<int64_t>(sizeof(uint32_t)) * (total + kIdPad) +
+                 static_cast<int64_t>(sizeof(uint32_t)) * (out->n_tiles * (int64_t(out->T) * out->P + 1)) +
+                 static_cast<int64_t>(sizeof(int64_t)) * (out->n_tiles + 1);
+    return hipSuccess;
 }
 
 void free_part_layout(PartLayout* L, hipStream_t s) {
@@ -1704,27 +1882,6 @@ __device__ __forceinline__ void wave_seg_scan_dd(uint32_t& f, double& h, double&
     seg_stage<0x118, 0xF>(f, h, l);
     seg_stage<0x142, 0xA>(f, h, l);
     seg_stage<0x143, 0xC>(f, h, l);
-}
-
-// smallest t in [lo, hi] with offsets[t] >= target, given offsets[hi] >=
-// target; a 64-way search, all arguments uniform over the wave
-__device__ int64_t first_trial_at(const int64_t* __restrict__ offsets, int64_t lo, int64_t hi, int64_t target,
-                                  int lane) {
-    while (hi - lo >= 64) {
-        const int64_t step = (hi - lo) / 64;
-        const uint64_t m = __ballot(offsets[lo + lane * step] >= target);   // index <= hi - step
-        if (m == 0) {
-            lo = lo + 63 * step + 1;
-        } else {
-            const int f = __builtin_ctzll(m);
-            const int64_t nlo = f > 0 ? lo + (f - 1) * step + 1 : lo;
-            hi = lo + f * step;
-            lo = nlo;
-        }
-    }
-    const int64_t idx = lo + lane;
-    const uint64_t m = __ballot(idx <= hi && offsets[idx] >= target);
-    return lo + __builtin_ctzll(m);
 }
 
 // coarse map: bit i is set when any of events [i << cshift, (i + 1) << cshift)

@@ -60,74 +60,50 @@ __device__ __forceinline__ uint64_t stream_lanemask_lt() {
 // create-time layout
 // ---------------------------------------------------------------------------
 
-// cnt[t * P + q] = events of trial t in stream part q; one wave per trial
-__global__ __launch_bounds__(256) void stream_count_kernel(const int64_t* __restrict__ offsets,
-                                                           const uint32_t* __restrict__ ids, int64_t N, int P,
-                                                           int32_t* __restrict__ cnt) {
-    __shared__ int32_t c[4][kMaxStreamParts];
-    const int w = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_waves = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
-    for (int64_t t = uniform_i64((static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6); t < N;
-         t += n_waves) {
-        for (int p = lane; p < P; p += 64) c[w][p] = 0;
-        __builtin_amdgcn_wave_barrier();
-        {
-            // four 64-ID chunks loaded together
-            const int64_t b = offsets[t], e = offsets[t + 1];
-            for (int64_t c0 = b; c0 < e; c0 += 256) {
-                uint32_t idk[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int64_t at = c0 + k * 64 + lane;
-                    idk[k] = at < e ? ids[at] : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (c0 + k * 64 + lane < e) atomicAdd(&c[w][idk[k] >> kStreamShift], 1);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        for (int p = lane; p < P; p += 64) cnt[t * P + p] = c[w][p];
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// per (part, group) k = q * NG + g: the end of each of the group's trials
+// Per (part, group) k = q * NG + g: the end of each of the group's trials
 // relative to the group start (slots past the group's trials repeat the
-// group's end), and the group's size padded to whole 16-byte chunks.  Flags
-// bit 0 when a group holds more than 65535 IDs of one part.
+// group's end), and the group's size padded to whole 16-byte chunks (to its
+// place in gstart, scanned there next).  Flags a group with more than 65535 IDs
+// of one part.  A workgroup per group: its trials' counts, one contiguous piece
+// of cnt, go through LDS; a wave then scans a part over its lanes, one trial
+// each, and stores the 64 ends at once (a thread per group and part, walking the
+// trials, took 72 us for 150000 trials over 31 parts).
 __global__ __launch_bounds__(256) void stream_group_kernel(const int32_t* __restrict__ cnt, int64_t N, int P, int G,
                                                            int64_t NG, uint16_t* __restrict__ gend,
-                                                           uint32_t* __restrict__ gsize, uint32_t* __restrict__ flag) {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k >= static_cast<int64_t>(P) * NG) return;
-    const int q = static_cast<int>(k / NG);
-    const int64_t g = k - static_cast<int64_t>(q) * NG;
-    uint32_t run = 0;
-    for (int i = 0; i < kStreamGroupSlots; ++i) {
-        const int64_t t = g * G + i;
-        if (i < G && t < N) run += static_cast<uint32_t>(cnt[t * P + q]);
-        gend[k * kStreamGroupSlots + i] = static_cast<uint16_t>(run < 65535u ? run : 65535u);
+                                                           uint32_t* __restrict__ gstart, CreateResult* __restrict__ res) {
+    __shared__ int32_t c[kStreamGroupMax * (kMaxStreamParts + 1)];
+    const int lane = threadIdx.x & 63;
+    const int64_t g = blockIdx.x;
+    const int n = static_cast<int>(min(static_cast<int64_t>(G), N - g * G));
+    const int row = P | 1;                          // odd: a part's counts lie in different banks
+    for (int i = threadIdx.x; i < n * P; i += blockDim.x) c[i / P * row + i % P] = cnt[g * G * P + i];
+    __syncthreads();
+    for (int q = threadIdx.x >> 6; q < P; q += 4) {
+        uint32_t run = lane < n ? static_cast<uint32_t>(c[lane * row + q]) : 0u;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(run, off, 64);
+            if (lane >= off) run = run + v < run ? 0xFFFFFF00u : run + v;      // sums past 32 bits stay above 65535
+        }
+        const int64_t k = static_cast<int64_t>(q) * NG + g;
+        gend[k * kStreamGroupSlots + lane] = static_cast<uint16_t>(run < 65535u ? run : 65535u);
+        if (lane == 63) {
+            if (run > 65535u) atomicOr(&res->flags, kCreateWideGroup);
+            gstart[k + q] = (run + kChunkIds - 1) & ~static_cast<uint32_t>(kChunkIds - 1);
+        }
     }
-    if (run > 65535u) atomicOr(flag, 1u);
-    gsize[k] = (run + kChunkIds - 1) & ~static_cast<uint32_t>(kChunkIds - 1);
 }
 
-// per part (one workgroup each): exclusive scan of the padded group sizes;
-// flags bit 1 when a part's stream reaches 2^32 IDs
-__global__ __launch_bounds__(1024) void stream_scan_kernel(const uint32_t* __restrict__ gsize, int64_t NG,
-                                                           uint32_t* __restrict__ gstart,
-                                                           uint64_t* __restrict__ part_len,
-                                                           uint32_t* __restrict__ flag) {
+// per part (one workgroup each): exclusive scan of the padded group sizes, in
+// place; flags a part whose stream reaches 2^32 IDs
+__global__ __launch_bounds__(1024) void stream_scan_kernel(int64_t NG, uint32_t* __restrict__ gstart,
+                                                           CreateResult* __restrict__ res) {
     __shared__ uint64_t tsum[1024];
     const int q = blockIdx.x;
-    const uint32_t* src = gsize + static_cast<int64_t>(q) * NG;
     uint32_t* dst = gstart + static_cast<int64_t>(q) * (NG + 1);
     const int64_t per = (NG + 1023) / 1024;
     const int64_t j0 = static_cast<int64_t>(threadIdx.x) * per;
     uint64_t local = 0;
-    for (int64_t j = j0; j < j0 + per && j < NG; ++j) local += src[j];
+    for (int64_t j = j0; j < j0 + per && j < NG; ++j) local += dst[j];
     tsum[threadIdx.x] = local;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
@@ -138,20 +114,16 @@ __global__ __launch_bounds__(1024) void stream_scan_kernel(const uint32_t* __res
     }
     uint64_t run = tsum[threadIdx.x] - local;
     for (int64_t j = j0; j < j0 + per && j < NG; ++j) {
+        const uint32_t size = dst[j];
         dst[j] = static_cast<uint32_t>(run);
-        run += src[j];
+        run += size;
     }
     if (threadIdx.x == 1023) {
         const uint64_t total = tsum[1023];
         dst[NG] = static_cast<uint32_t>(total);
-        part_len[q] = total;
-        if (total >= (uint64_t(1) << 32) - 4096) atomicOr(flag, 2u);
+        res->stream_ids[q] = static_cast<int64_t>(total);
+        if (total >= (uint64_t(1) << 32) - 4096) atomicOr(&res->flags, kCreateWidePart);
     }
-}
-
-__global__ void stream_fill_kernel(uint32_t* p, int64_t n, uint32_t v) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
 // Stable scatter of each trial's events into its segments of the part
@@ -165,17 +137,35 @@ __global__ void stream_fill_kernel(uint32_t* p, int64_t n, uint32_t v) {
 // part's segment then leaves in 16-byte stores to its place in the stream:
 // whole lines instead of 2-byte writes spread over up to P lines per 64
 // events.  A group whose padded segments exceed the stage is scattered
-// straight to the stream.
+// straight to the stream, after its segments are filled with 0xFFFF.  The parts'
+// streams follow each other: every workgroup sums their lengths, the first one
+// stores the bases and the readable 0xFFFF after the last part.
 constexpr int kGroupStageIds = 72 * 1024;     // 144 KB of LDS
 __global__ __launch_bounds__(1024) void stream_group_scatter_kernel(
     const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int G, int64_t NG,
-    const int64_t* __restrict__ part_base, const uint32_t* __restrict__ gstart, const uint16_t* __restrict__ gend,
-    uint16_t* __restrict__ out) {
+    const CreateResult* __restrict__ res, int64_t* __restrict__ bases, const uint32_t* __restrict__ gstart,
+    const uint16_t* __restrict__ gend, uint16_t* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) uint16_t stage[kGroupStageIds];
     __shared__ uint32_t seg[kMaxStreamParts + 1];     // staged start of each part's segment
     __shared__ int64_t cur[16][kMaxStreamParts];       // per wave: where each part's next event goes
+    __shared__ int64_t part_base[kMaxStreamParts + 1];
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
+    if (w == 0) {
+        const int64_t len = lane < P ? res->stream_ids[lane] : 0;
+        int64_t inc = len;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        part_base[lane + 1] = inc;
+        if (lane == 0) part_base[0] = 0;
+        if (blockIdx.x == 0 && lane < P) bases[lane + 1] = inc;
+        if (blockIdx.x == 0 && lane == 0) bases[0] = 0;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0)
+        for (int64_t u = threadIdx.x; u < kStreamPad; u += blockDim.x) out[part_base[P] + u] = 0xFFFFu;
     const int n_bits = P > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(P - 1)) : 0;
     const uint64_t below = stream_lanemask_lt();
     const uint64_t above = lane == 63 ? 0ull : (~0ull << (lane + 1));
@@ -200,6 +190,14 @@ __global__ __launch_bounds__(1024) void stream_group_scatter_kernel(
         if (staged) {
             for (uint32_t u = threadIdx.x; u < total / 8; u += blockDim.x)
                 reinterpret_cast<u32x4*>(stage)[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+        } else {
+            for (int q = w; q < P; q += 16) {
+                u32x4* dst = reinterpret_cast<u32x4*>(out + part_base[q] +
+                                                      gstart[static_cast<int64_t>(q) * (NG + 1) + g]);
+                for (uint32_t u = lane; u < (seg[q + 1] - seg[q]) / 8; u += 64)
+                    dst[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+            }
+            __threadfence();
         }
         __syncthreads();
         const int64_t t0 = g * G;
@@ -1066,101 +1064,67 @@ int choose_group_trials(double lam) {
 
 }  // namespace
 
-hipError_t build_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events, int64_t C,
-                               int n_cu, hipStream_t s, StreamLayout* out) {
+int stream_layout_parts(int64_t N, int64_t C) {
+    const int64_t P = (C + kQSize - 1) / kQSize;
+    return N < 1 || P < 1 || P > kMaxStreamParts ? 0 : static_cast<int>(P);
+}
+
+hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, int64_t C, CreateResult* res,
+                              hipStream_t s, StreamLayout* out) {
     *out = StreamLayout{};
-    const int P = static_cast<int>((C + kQSize - 1) / kQSize);
-    if (N < 1 || P < 1 || P > kMaxStreamParts) return hipSuccess;      // layout not used
+    const int P = stream_layout_parts(N, C);
+    if (P == 0) return hipSuccess;                                     // layout not used
     const int G = choose_group_trials(static_cast<double>(n_events) / (static_cast<double>(N) * P));
     const int64_t NG = (N + G - 1) / G;
     const int64_t n_grp = static_cast<int64_t>(P) * NG;
-    hipError_t e;
-    int32_t* cnt = nullptr;
-    uint32_t* gsize = nullptr;
-    uint64_t* plen = nullptr;
-    uint32_t* flag = nullptr;
-    std::vector<uint64_t> h_len(P);
-    std::vector<int64_t> h_base(P + 1);
-    uint32_t h_flag = 0;
-    int64_t blocks = (N + 3) / 4;
-    if (blocks > int64_t(n_cu) * 16) blocks = int64_t(n_cu) * 16;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&cnt), sizeof(int32_t) * N * P, s)) != hipSuccess) goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&gsize), sizeof(uint32_t) * n_grp, s)) != hipSuccess) goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&plen), sizeof(uint64_t) * P, s)) != hipSuccess) goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&flag), sizeof(uint32_t), s)) != hipSuccess) goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->gend), sizeof(uint16_t) * n_grp * kStreamGroupSlots, s)) !=
-        hipSuccess)
-        goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * P * (NG + 1), s)) != hipSuccess)
-        goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (P + 1), s)) != hipSuccess)
-        goto fail;
-    if ((e = hipMemsetAsync(flag, 0, sizeof(uint32_t), s)) != hipSuccess) goto fail;
-    hipLaunchKernelGGL(stream_count_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, offsets, ids, N, P,
-                       cnt);
-    if ((e = hipGetLastError()) != hipSuccess) goto fail;
-    hipLaunchKernelGGL(stream_group_kernel, dim3(static_cast<uint32_t>((n_grp + 255) / 256)), dim3(256), 0, s, cnt, N,
-                       P, G, NG, out->gend, gsize, flag);
-    if ((e = hipGetLastError()) != hipSuccess) goto fail;
-    hipLaunchKernelGGL(stream_scan_kernel, dim3(static_cast<uint32_t>(P)), dim3(1024), 0, s, gsize, NG, out->gstart,
-                       plen, flag);
-    if ((e = hipGetLastError()) != hipSuccess) goto fail;
-    if ((e = hipMemcpyAsync(h_len.data(), plen, sizeof(uint64_t) * P, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(&h_flag, flag, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-        goto fail;
-    if (h_flag) {                       // a group or a part too large for 16/32-bit offsets: not used
-        e = hipSuccess;
-        goto fail;
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->gend), sizeof(uint16_t) * n_grp * kStreamGroupSlots, s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * P * (NG + 1), s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (P + 1), s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(stream_group_kernel, dim3(static_cast<uint32_t>(NG)), dim3(256), 0, s, cnt, N, P, G, NG,
+                           out->gend, out->gstart, res);
+        e = hipGetLastError();
     }
-    h_base[0] = 0;
-    for (int q = 0; q < P; ++q) h_base[q + 1] = h_base[q] + static_cast<int64_t>(h_len[q]);
-    out->length = h_base[P];
-    if ((e = hipMemcpyAsync(out->part_base, h_base.data(), sizeof(int64_t) * (P + 1), hipMemcpyHostToDevice, s)) !=
-        hipSuccess)
-        goto fail;
-    if ((e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (out->length + kStreamPad), s)) !=
-        hipSuccess)
-        goto fail;
-    {
-        const int64_t n32 = (out->length + kStreamPad) / 2;
-        int64_t fb = (n32 + 255) / 256;
-        if (fb > 8192) fb = 8192;
-        hipLaunchKernelGGL(stream_fill_kernel, dim3(static_cast<uint32_t>(fb)), dim3(256), 0, s,
-                           reinterpret_cast<uint32_t*>(out->ids), n32, 0xFFFFFFFFu);
-        if ((e = hipGetLastError()) != hipSuccess) goto fail;
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(stream_scan_kernel, dim3(static_cast<uint32_t>(P)), dim3(1024), 0, s, NG, out->gstart, res);
+        e = hipGetLastError();
     }
-    {
-        int64_t gb = NG;
-        if (gb > int64_t(n_cu)) gb = n_cu;                 // one 16-wave workgroup per CU (the stage fills LDS)
-        hipLaunchKernelGGL(stream_group_scatter_kernel, dim3(static_cast<uint32_t>(gb)), dim3(1024), 0, s, offsets,
-                           ids, N, P, G, NG, out->part_base, out->gstart, out->gend, out->ids);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) goto fail;
-    // temporaries go back to the library's device memory cache: no free waits for the device
-    dev_free(cnt, s);
-    dev_free(gsize, s);
-    dev_free(plen, s);
-    dev_free(flag, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) {
+    if (e != hipSuccess) {
         free_stream_layout(out, s);
         return e;
     }
     out->P = P;
     out->G = G;
     out->NG = NG;
-    out->bytes = static_cast<int64_t>(sizeof(uint16_t)) * (out->length + kStreamPad) +
-                 static_cast<int64_t>(sizeof(uint16_t)) * n_grp * kStreamGroupSlots +
-                 static_cast<int64_t>(sizeof(uint32_t)) * P * (NG + 1) + static_cast<int64_t>(sizeof(int64_t)) * (P + 1);
     return hipSuccess;
-fail:
-    if (cnt) dev_free(cnt, s);
-    if (gsize) dev_free(gsize, s);
-    if (plen) dev_free(plen, s);
-    if (flag) dev_free(flag, s);
-    free_stream_layout(out, s);
-    (void)hipStreamSynchronize(s);
-    return e;
+}
+
+hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res,
+                              const CreateResult* d_res, int n_cu, hipStream_t s, StreamLayout* out) {
+    if (out->P == 0) return hipSuccess;
+    if (res.flags & (kCreateWideGroup | kCreateWidePart)) {     // too large for 16/32-bit offsets: not used
+        free_stream_layout(out, s);
+        return hipSuccess;
+    }
+    int64_t length = 0;
+    for (int q = 0; q < out->P; ++q) length += res.stream_ids[q];
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (length + kStreamPad), s);
+    if (e == hipSuccess) {
+        const int64_t gb = std::min(out->NG, int64_t(n_cu));   // one 16-wave workgroup per CU (the stage fills LDS)
+        hipLaunchKernelGGL(stream_group_scatter_kernel, dim3(static_cast<uint32_t>(gb)), dim3(1024), 0, s, offsets,
+                           ids, N, out->P, out->G, out->NG, d_res, out->part_base, out->gstart, out->gend, out->ids);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+        free_stream_layout(out, s);
+        return e;
+    }
+    out->length = length;
+    out->bytes = static_cast<int64_t>(sizeof(uint16_t)) * (length + kStreamPad) +
+                 static_cast<int64_t>(sizeof(uint16_t)) * out->P * out->NG * kStreamGroupSlots +
+                 static_cast<int64_t>(sizeof(uint32_t)) * out->P * (out->NG + 1) +
+                 static_cast<int64_t>(sizeof(int64_t)) * (out->P + 1);
+    return hipSuccess;
 }
 
 void free_stream_layout(StreamLayout* L, hipStream_t s) {

@@ -16,6 +16,8 @@
 // double-double so the rounded S is the correctly rounded sum of the
 // occurrence losses (up to ties within ~K u^2 S).  A group of LPT lanes owns
 // one trial; LPT = 64 is a whole wavefront.
+#include <algorithm>
+
 #include "ara_internal.hpp"
 
 namespace ara {
@@ -174,29 +176,17 @@ __global__ void debug_lookups_kernel(const int64_t* offsets, const uint32_t* ids
     }
 }
 
-// flags: bit 0 = ID out of range, bit 1 = offsets decrease, bit 2 = bad loss
-__global__ void validate_kernel(const int64_t* offsets, int64_t n_trials, const uint32_t* ids,
-                                int64_t n_events, const double* elts, int64_t n_vals, int64_t C,
-                                uint32_t* flags) {
+__global__ void validate_kernel(const int64_t* offsets, int64_t n_trials, int64_t n_events, const double* elts,
+                                int64_t n_vals, uint32_t* flags) {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     uint32_t f = 0;
-    // the IDs 16 bytes at a time (the allocation is 256-byte aligned), then the tail
-    const int64_t n4 = n_events / 4;
-    const u32x4* ids4 = reinterpret_cast<const u32x4*>(ids);
-    const uint32_t c32 = C > 0xFFFFFFFFll ? 0xFFFFFFFFu : static_cast<uint32_t>(C);
-    const bool wide = C > 0xFFFFFFFFll;              // every 32-bit ID is below C
-    for (int64_t i = tid; i < n4; i += stride) {
-        const u32x4 v = __builtin_nontemporal_load(ids4 + i);
-        if (!wide && (v.x >= c32 || v.y >= c32 || v.z >= c32 || v.w >= c32)) f |= 1u;
-    }
-    for (int64_t i = 4 * n4 + tid; i < n_events; i += stride)
-        if (static_cast<int64_t>(ids[i]) >= C) f |= 1u;
+    if (tid == 0 && (offsets[0] != 0 || offsets[n_trials] != n_events)) f |= kCreateBadOffsets;
     for (int64_t i = tid; i < n_trials; i += stride)
-        if (offsets[i + 1] < offsets[i]) f |= 2u;
+        if (offsets[i + 1] < offsets[i]) f |= kCreateBadOffsets;
     for (int64_t i = tid; i < n_vals; i += stride) {
         const double v = elts[i];
-        if (!(v >= 0.0) || __builtin_isinf(v)) f |= 4u;
+        if (!(v >= 0.0) || __builtin_isinf(v)) f |= kCreateBadLoss;
     }
     if (f) atomicOr(flags, f);
 }
@@ -260,12 +250,13 @@ hipError_t launch_debug_lookups(const int64_t* offsets, const uint32_t* ids, con
     return hipGetLastError();
 }
 
-hipError_t launch_validate(const int64_t* offsets, int64_t n_trials, const uint32_t* ids,
-                           int64_t n_events, const double* elts, int64_t n_elt_values, int64_t C,
-                           uint32_t* d_flags, int n_cu, hipStream_t s) {
-    const int blocks = n_cu * 8;                 // 32 waves per CU
-    hipLaunchKernelGGL(validate_kernel, dim3(blocks), dim3(256), 0, s, offsets, n_trials, ids, n_events,
-                       elts, n_elt_values, C, d_flags);
+hipError_t launch_validate(const int64_t* offsets, int64_t n_trials, int64_t n_events, const double* elts,
+                           int64_t n_elt_values, CreateResult* res, int n_cu, hipStream_t s) {
+    // at most 32 waves per CU
+    const int64_t work = (std::max(n_trials, n_elt_values) + 255) / 256;
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(work, int64_t(n_cu) * 8));
+    hipLaunchKernelGGL(validate_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, offsets, n_trials,
+                       n_events, elts, n_elt_values, &res->flags);
     return hipGetLastError();
 }
 
