@@ -887,10 +887,10 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         t->bytes += t->sparse.bytes;
     }
     if (bins > 0) {
-        e = ara::fill_part_layout(t->offsets, t->ids, n_trials, res, t->n_cu, s, &t->parts);
+        e = ara::fill_part_layout(t->offsets, t->ids, n_trials, n_events, res, s, &t->parts);
         if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
         t->bytes += t->parts.bytes;
-        e = ara::fill_stream_layout(t->offsets, t->ids, n_trials, res, d_res, t->n_cu, s, &t->stream);
+        e = ara::fill_stream_layout(t->offsets, t->ids, n_trials, n_events, res, d_res, s, &t->stream);
         if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));
         t->bytes += t->stream.bytes;
     }

@@ -234,8 +234,8 @@ int stream_layout_parts(int64_t N, int64_t C);      // 0: not used
 // plan: sizes and starts from the trials' counts; fill: the copy, of the lengths read back
 hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, int64_t C, CreateResult* res,
                               hipStream_t s, StreamLayout* out);
-hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res,
-                              const CreateResult* d_res, int n_cu, hipStream_t s, StreamLayout* out);
+hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                              const CreateResult& res, const CreateResult* d_res, hipStream_t s, StreamLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_stream_layout(StreamLayout* L, hipStream_t s);
 // bytes of the per-(part, trial) partial sums of the streaming pass
@@ -536,8 +536,8 @@ hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* s
 int part_layout_parts(int64_t N, int64_t C);        // 0: not used
 hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
                             hipStream_t s, PartLayout* out);
-hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res, int n_cu,
-                            hipStream_t s, PartLayout* out);
+hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                            const CreateResult& res, hipStream_t s, PartLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_part_layout(PartLayout* L, hipStream_t s);
 int64_t part_scratch_bytes(int64_t C, int P);

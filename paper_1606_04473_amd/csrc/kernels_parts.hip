@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "ara_internal.hpp"
+#include "scatter.hpp"
 
 namespace ara {
 
@@ -304,128 +305,93 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// Scatter of each trial's IDs into its per-part segments of the tiled copy,
-// one workgroup per run of kChunkTrials trials of a tile.  Inside a tile each
-// part's segments of consecutive trials are consecutive, so the run's
-// segments of every part form one contiguous range per part: they are staged
-// in LDS (part after part, the padding that ends each trial's segment filled
-// with the sentinel), the trials scattered there one wave per trial,
-// and each part's range then leaves in coalesced 4-byte stores instead of
-// writes spread over up to P lines per 64 IDs.  Per 64 IDs the lanes holding
-// an ID of this lane's part are the AND, over the part number's bits, of that
-// bit's ballot or its complement; a lane's rank among the earlier ones places
-// it, all 64 write in one store, and the last lane of each part moves its
-// cursor on.  A run whose IDs exceed the stage is scattered straight to the
-// copy, after its ranges are filled with the sentinel.  The run that ends a tile
-// fills the tile's padding, the last one the readable IDs after the copy.
-constexpr int kChunkTrials = 32;
-constexpr int kPartStageIds = 36 * 1024;        // 144 KB of LDS
-__global__ __launch_bounds__(1024) void part_scatter_kernel(const int64_t* __restrict__ offsets,
-                                                            const uint32_t* __restrict__ ids, int64_t N, int P, int T,
-                                                            const uint32_t* __restrict__ seg_rel,
-                                                            const int64_t* __restrict__ tile_start,
-                                                            uint32_t* __restrict__ pids) {
-    __shared__ uint32_t stage[kPartStageIds];
-    __shared__ uint32_t sseg[kMaxParts + 1];          // staged start of each part's range
-    __shared__ int64_t cur[16][kMaxParts];
+// Scatter of each trial's IDs into its per-part segments of the tiled copy, one
+// workgroup per `per` consecutive trials of a tile.  Inside a tile each part's
+// segments of consecutive trials are consecutive, so the unit's segments of every
+// part form one run per part, whole 16-byte chunks: the runs are staged in LDS and
+// leave in 16-byte stores.  A trial's segment ends in sentinels up to four IDs.
+// The unit that ends a tile fills the tile's padding, the last one the readable
+// IDs after the copy.  A unit past the stage is scattered straight to the copy.
+constexpr int kScatterStage32 = 9 * 1024;           // IDs: 36 KB
+template <int kBits>
+__global__ __launch_bounds__(kScatterThreads) void part_scatter_kernel(
+    const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int T, int per,
+    const uint32_t* __restrict__ seg_rel, const int64_t* __restrict__ tile_start, uint32_t* __restrict__ pids) {
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kScatterStage32];
+    __shared__ uint32_t cursors[kScatterWaves][kMaxParts];
+    __shared__ uint32_t seg[kMaxParts + 1];         // staged start of each part's run
+    extern __shared__ uint32_t starts[];            // [P][per + 1] segment starts in the tile
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
-    const int n_bits = P > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(P - 1)) : 0;
-    const uint64_t above = lane == 63 ? 0ull : (~0ull << (lane + 1));
     const int64_t n_tiles = (N + T - 1) / T;
-    const int64_t per_tile = (T + kChunkTrials - 1) / kChunkTrials;
-    for (int64_t r = blockIdx.x; r < n_tiles * per_tile; r += gridDim.x) {
-        const int64_t tile = r / per_tile;
-        const int64_t t0 = tile * T;
-        const int Tk = static_cast<int>(N - t0 < T ? N - t0 : T);
-        const int i0 = static_cast<int>(r - tile * per_tile) * kChunkTrials;
-        if (i0 >= Tk) continue;                                   // uniform over the workgroup
-        const int i1 = i0 + kChunkTrials < Tk ? i0 + kChunkTrials : Tk;
-        const int64_t base = tile * (static_cast<int64_t>(T) * P + 1);
-        if (w == 0) {                                  // each part's range size, scanned over the wave
-            uint32_t n = 0;
+    const int units = (T + per - 1) / per;
+    const int64_t unit = scatter_unit_index(n_tiles * units);
+    if (unit >= n_tiles * units) return;
+    const int64_t tile = unit / units;
+    const int64_t t0 = tile * T;
+    const int Tk = static_cast<int>(N - t0 < T ? N - t0 : T);
+    const int i0 = static_cast<int>(unit - tile * units) * per;
+    const int n = min(per, Tk - i0);
+    if (n <= 0) return;
+    const int row = per + 1;
+    const uint32_t* rel = seg_rel + tile * (static_cast<int64_t>(T) * P + 1);
+    uint32_t* copy = pids + tile_start[tile];
+    for (int j = threadIdx.x; j < P * row; j += kScatterThreads) {
+        const int p = j / row, i = i0 + min(j - p * row, n);
+        starts[j] = rel[static_cast<int64_t>(p) * Tk + i];          // i = Tk: the next part's first
+    }
+    if (i0 + n == Tk) {
+        const int64_t tile_end = tile_start[tile + 1] + (tile + 1 == n_tiles ? kIdPad : 0);
+        for (int64_t u = tile_start[tile] + rel[static_cast<int64_t>(P) * Tk] + threadIdx.x; u < tile_end;
+             u += blockDim.x)
+            pids[u] = kSentinel;
+    }
+    __syncthreads();
+    if (w == 0) {
+        const uint32_t size = lane < P ? starts[lane * row + n] - starts[lane * row] : 0u;
+        uint64_t inc = size;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        const uint32_t at = static_cast<uint32_t>(min<uint64_t>(inc, kSentinel));
+        if (lane < P) seg[lane] = at - size;
+        if (lane == P - 1) seg[P] = at;
+    }
+    __syncthreads();
+    if (seg[P] > static_cast<uint32_t>(kScatterStage32)) {
+        int64_t* big = reinterpret_cast<int64_t*>(stage) + w * kMaxParts;      // the stage holds the cursors
+        const int n_bits = P > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(P - 1)) : 0;
+        for (int i = w; i < n; i += kScatterWaves) {
+            if (lane < P) big[lane] = starts[lane * row + i];
+            __builtin_amdgcn_wave_barrier();
+            scatter_trial_direct(ids, offsets[t0 + i0 + i], offsets[t0 + i0 + i + 1], kPartShift, n_bits, big, copy);
+            __builtin_amdgcn_wave_barrier();
             if (lane < P)
-                n = seg_rel[base + static_cast<int64_t>(lane) * Tk + i1] - seg_rel[base + static_cast<int64_t>(lane) * Tk + i0];
-            uint32_t inc = n;
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t v = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += v;
-            }
-            if (lane < P) sseg[lane] = inc - n;
-            if (lane == P - 1) sseg[P] = inc;
-        }
-        __syncthreads();
-        const bool staged = sseg[P] <= static_cast<uint32_t>(kPartStageIds);
-        if (staged) {                                  // segments end in sentinel padding, as in the copy
-            for (uint32_t u = threadIdx.x; u < sseg[P]; u += blockDim.x) stage[u] = kSentinel;
-        } else {
-            for (int p = w; p < P; p += 16) {
-                uint32_t* dst = pids + tile_start[tile] + seg_rel[base + static_cast<int64_t>(p) * Tk + i0];
-                for (uint32_t u = lane; u < sseg[p + 1] - sseg[p]; u += 64) dst[u] = kSentinel;
-            }
-            __threadfence();
-        }
-        if (i1 == Tk) {
-            const int64_t tile_end = tile_start[tile + 1] + (tile + 1 == n_tiles ? kIdPad : 0);
-            for (int64_t u = tile_start[tile] + seg_rel[base + static_cast<int64_t>(P) * Tk] + threadIdx.x; u < tile_end;
-                 u += blockDim.x)
-                pids[u] = kSentinel;
-        }
-        __syncthreads();
-        for (int i = i0 + w; i < i1; i += 16) {
-            const int64_t t = t0 + i;
-            for (int p = lane; p < P; p += 64) {
-                const int64_t k = base + static_cast<int64_t>(p) * Tk;
-                cur[w][p] = staged ? sseg[p] + (seg_rel[k + i] - seg_rel[k + i0]) : tile_start[tile] + seg_rel[k + i];
-            }
-            __builtin_amdgcn_wave_barrier();
-            const int64_t b = offsets[t], e = offsets[t + 1];
-            constexpr int kAhead = 8;                   // chunks of 64 IDs loaded together
-            for (int64_t c0 = b; c0 < e; c0 += 64 * kAhead) {
-                uint32_t idk[kAhead];
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int64_t at = c0 + k * 64 + lane;
-                    idk[k] = at < e ? ids[at] : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int64_t c = c0 + k * 64;
-                    if (c >= e) break;
-                    const bool valid = c + lane < e;
-                    const uint32_t id = idk[k];
-                    const int pid = static_cast<int>(id >> kPartShift);
-                    uint64_t same = __ballot(valid);
-                    for (int bit = 0; bit < n_bits; ++bit) {
-                        const bool set = ((pid >> bit) & 1) != 0;
-                        const uint64_t lanes = __ballot(set);
-                        same &= set ? lanes : ~lanes;
-                    }
-                    const int64_t at = cur[w][pid];
-                    if (valid) {
-                        const int64_t to = at + __popcll(same & lanemask_lt());
-                        if (staged)
-                            stage[to] = id;
-                        else
-                            pids[to] = id;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    if (valid && (same & above) == 0) cur[w][pid] = at + __popcll(same);
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
+                for (int64_t u = big[lane]; u < starts[lane * row + i + 1]; ++u) copy[u] = kSentinel;
             __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
-        if (staged) {
-            for (int p = w; p < P; p += 16) {
-                const int64_t k = base + static_cast<int64_t>(p) * Tk;
-                uint32_t* dst = pids + tile_start[tile] + seg_rel[k + i0];
-                const uint32_t s0 = sseg[p], n = sseg[p + 1] - s0;
-                for (uint32_t u = lane; u < n; u += 64) dst[u] = stage[s0 + u];
-            }
-        }
-        __syncthreads();
+        return;
+    }
+    uint32_t* cur = cursors[w];
+    scatter_unit<kBits>(
+        offsets, ids, t0 + i0, n, kPartShift, cur, stage,
+        [&](int i) {
+            if (lane < P) cur[lane] = seg[lane] + (starts[lane * row + i] - starts[lane * row]);
+        },
+        [&](int i) {
+            if (lane < P)
+                for (uint32_t u = cur[lane]; u < seg[lane] + (starts[lane * row + i + 1] - starts[lane * row]); ++u)
+                    stage[u] = kSentinel;
+        });
+    __syncthreads();
+    // a run per group of 16, 32 or 64 lanes
+    const int lanes = P > 16 ? 16 : (P > 8 ? 32 : 64);
+    for (int p = threadIdx.x / lanes; p < P; p += kScatterThreads / lanes) {
+        uint32_t* dst = copy + starts[p * row];
+        const uint32_t s0 = seg[p], n_ids = seg[p + 1] - s0;
+        for (uint32_t u = (threadIdx.x % lanes) * 4; u < n_ids; u += lanes * 4)
+            *reinterpret_cast<u32x4*>(dst + u) = *reinterpret_cast<const u32x4*>(stage + s0 + u);
     }
 }
 
@@ -1758,8 +1724,8 @@ hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, 
     return hipSuccess;
 }
 
-hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res, int n_cu,
-                            hipStream_t s, PartLayout* out) {
+hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                            const CreateResult& res, hipStream_t s, PartLayout* out) {
     if (out->P == 0) return hipSuccess;
     if (res.flags & kCreateWideTile) {      // too large for 32-bit positions: keep the plain layout
         free_part_layout(out, s);
@@ -1768,11 +1734,18 @@ hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t
     const int64_t total = res.part_ids;
     hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->pids), sizeof(uint32_t) * (total + kIdPad), s);
     if (e == hipSuccess) {
-        // one 16-wave workgroup per CU (the stage fills LDS), over runs of kChunkTrials trials
-        int64_t sb = out->n_tiles * ((out->T + kChunkTrials - 1) / kChunkTrials);
-        if (sb > int64_t(n_cu)) sb = n_cu;
-        hipLaunchKernelGGL(part_scatter_kernel, dim3(static_cast<uint32_t>(sb)), dim3(1024), 0, s, offsets, ids, N,
-                           out->P, out->T, out->seg_rel, out->tile_start, out->pids);
+        const double lam = static_cast<double>(n_events) / static_cast<double>(N);
+        const int fit = scatter_trials(lam + 1.5 * out->P, 0.0, kScatterStage32, 64);
+        const int units = (out->T + fit - 1) / fit, per = (out->T + units - 1) / units;
+        const int64_t n_units = out->n_tiles * ((out->T + per - 1) / per);
+        const dim3 grid(static_cast<uint32_t>((n_units + kXcds - 1) / kXcds * kXcds)), b(kScatterThreads);
+        const size_t lds = sizeof(uint32_t) * static_cast<size_t>(out->P) * (per + 1);
+        if (out->P <= 8)
+            hipLaunchKernelGGL(part_scatter_kernel<3>, grid, b, lds, s, offsets, ids, N, out->P, out->T, per,
+                               out->seg_rel, out->tile_start, out->pids);
+        else
+            hipLaunchKernelGGL(part_scatter_kernel<6>, grid, b, lds, s, offsets, ids, N, out->P, out->T, per,
+                               out->seg_rel, out->tile_start, out->pids);
         e = hipGetLastError();
     }
     if (e != hipSuccess) {

@@ -40,6 +40,7 @@
 #include <vector>
 
 #include "ara_internal.hpp"
+#include "scatter.hpp"
 
 namespace ara {
 
@@ -126,139 +127,128 @@ __global__ __launch_bounds__(1024) void stream_scan_kernel(int64_t NG, uint32_t*
     }
 }
 
-// Stable scatter of each trial's events into its segments of the part
-// streams, one workgroup per group of G trials.  The group's segments of
-// every part are staged in LDS (each padded with 0xFFFF as in the stream) and
-// its trials are scattered there, one wave per trial, sixteen at a time: for
-// each 64 events every lane finds the lanes holding an event of its own part
-// -- the AND over the part number's bits of that bit's ballot or its
-// complement -- takes its rank among the earlier ones, and all 64 write in
-// one store; the last lane of each part moves that part's cursor on.  Each
-// part's segment then leaves in 16-byte stores to its place in the stream:
-// whole lines instead of 2-byte writes spread over up to P lines per 64
-// events.  A group whose padded segments exceed the stage is scattered
-// straight to the stream, after its segments are filled with 0xFFFF.  The parts'
-// streams follow each other: every workgroup sums their lengths, the first one
-// stores the bases and the readable 0xFFFF after the last part.
-constexpr int kGroupStageIds = 72 * 1024;     // 144 KB of LDS
-__global__ __launch_bounds__(1024) void stream_group_scatter_kernel(
-    const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int G, int64_t NG,
+// Stable scatter of each trial's events into its segments of the part streams, one
+// workgroup per `per` consecutive trials of a group.  Their run of every part is
+// staged in LDS with the run's place in a 16-byte chunk kept, so the run leaves
+// in 16-byte stores but for its first and last chunk, which other units may share
+// and which go ID by ID.  A group's last unit ends its segments with 0xFFFF.
+// Several workgroups per CU overlap one's loads with another's stores.  A unit past
+// the stage is scattered straight to the stream.  The parts' streams follow each
+// other: every workgroup sums their lengths, the first one stores the bases and
+// the readable 0xFFFF after the last part.
+constexpr int kScatterStage16 = 16 * 1024;          // IDs: 32 KB
+struct ScatterEnds16 {                              // dynamic LDS: [P][per + 1] IDs of the group's earlier trials
+    uint32_t base[kMaxStreamParts];                 // stage index of the group's first ID of a part (mod 2^32)
+    uint32_t seg[kMaxStreamParts + 1];              // staged start of each part's run (whole chunks)
+    int64_t out[kMaxStreamParts];                   // where a group's part begins in the stream
+    int64_t part_base[kMaxStreamParts + 1];
+};
+template <int kBits>
+__global__ __launch_bounds__(kScatterThreads) void stream_scatter_kernel(
+    const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int G, int64_t NG, int per,
     const CreateResult* __restrict__ res, int64_t* __restrict__ bases, const uint32_t* __restrict__ gstart,
     const uint16_t* __restrict__ gend, uint16_t* __restrict__ out) {
-    __shared__ __attribute__((aligned(16))) uint16_t stage[kGroupStageIds];
-    __shared__ uint32_t seg[kMaxStreamParts + 1];     // staged start of each part's segment
-    __shared__ int64_t cur[16][kMaxStreamParts];       // per wave: where each part's next event goes
-    __shared__ int64_t part_base[kMaxStreamParts + 1];
+    __shared__ __attribute__((aligned(16))) uint16_t stage[kScatterStage16];
+    __shared__ __attribute__((aligned(16))) int64_t cursors[kScatterWaves][kMaxStreamParts / 2];
+    __shared__ ScatterEnds16 sh;
+    extern __shared__ uint32_t ends[];
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
-    if (w == 0) {
-        const int64_t len = lane < P ? res->stream_ids[lane] : 0;
-        int64_t inc = len;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t v = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += v;
+    const int units = (G + per - 1) / per;
+    const int64_t unit = scatter_unit_index(NG * units);
+    if (unit >= NG * units) return;
+    const int64_t g = unit / units;
+    const int i0 = static_cast<int>(unit - g * units) * per;
+    const int n_group = static_cast<int>(min(static_cast<int64_t>(G), N - g * G));
+    const int n = min(per, n_group - i0);
+    const int row = per + 1;
+    if (unit == 0 || n > 0) {
+        for (int j = threadIdx.x; n > 0 && j < P * row; j += kScatterThreads) {
+            const int q = j / row, i = i0 + min(j - q * row, n);
+            ends[j] = i ? gend[(static_cast<int64_t>(q) * NG + g) * kStreamGroupSlots + i - 1] : 0u;
         }
-        part_base[lane + 1] = inc;
-        if (lane == 0) part_base[0] = 0;
-        if (blockIdx.x == 0 && lane < P) bases[lane + 1] = inc;
-        if (blockIdx.x == 0 && lane == 0) bases[0] = 0;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0)
-        for (int64_t u = threadIdx.x; u < kStreamPad; u += blockDim.x) out[part_base[P] + u] = 0xFFFFu;
-    const int n_bits = P > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(P - 1)) : 0;
-    const uint64_t below = stream_lanemask_lt();
-    const uint64_t above = lane == 63 ? 0ull : (~0ull << (lane + 1));
-    for (int64_t g = blockIdx.x; g < NG; g += gridDim.x) {
-        if (w == 0) {                                  // each part's padded segment, scanned over the wave
-            uint32_t n = 0;
-            if (lane < P) {
-                const int64_t k = static_cast<int64_t>(lane) * (NG + 1) + g;
-                n = gstart[k + 1] - gstart[k];
-            }
-            uint32_t inc = n;
+        if (w == 0) {
+            int64_t inc = lane < P ? res->stream_ids[lane] : 0;
             for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t v = __shfl_up(inc, off, 64);
+                const int64_t v = __shfl_up(inc, off, 64);
                 if (lane >= off) inc += v;
             }
-            if (lane < P) seg[lane] = inc - n;
-            if (lane == P - 1) seg[P] = inc;
+            sh.part_base[lane + 1] = inc;
+            if (lane == 0) sh.part_base[0] = 0;
+            if (unit == 0 && lane < P) bases[lane + 1] = inc;
+            if (unit == 0 && lane == 0) bases[0] = 0;
         }
-        __syncthreads();
-        const uint32_t total = seg[P];
-        const bool staged = total <= static_cast<uint32_t>(kGroupStageIds);
-        if (staged) {
-            for (uint32_t u = threadIdx.x; u < total / 8; u += blockDim.x)
-                reinterpret_cast<u32x4*>(stage)[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-        } else {
-            for (int q = w; q < P; q += 16) {
-                u32x4* dst = reinterpret_cast<u32x4*>(out + part_base[q] +
-                                                      gstart[static_cast<int64_t>(q) * (NG + 1) + g]);
-                for (uint32_t u = lane; u < (seg[q + 1] - seg[q]) / 8; u += 64)
-                    dst[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-            }
-            __threadfence();
+    }
+    __syncthreads();
+    if (unit == 0)
+        for (int64_t u = threadIdx.x; u < kStreamPad; u += blockDim.x) out[sh.part_base[P] + u] = 0xFFFFu;
+    if (n <= 0) return;
+    const bool last = i0 + n == n_group;
+    if (w == 0) {
+        uint32_t len = 0, phase = 0, rel = 0;
+        if (lane < P) {
+            const int64_t k = static_cast<int64_t>(lane) * (NG + 1) + g;
+            const uint32_t start = gstart[k];
+            rel = ends[lane * row];
+            phase = rel % kChunkIds;
+            len = (last ? gstart[k + 1] - start : ends[lane * row + n]) - rel;
+            sh.out[lane] = sh.part_base[lane] + start;
         }
-        __syncthreads();
-        const int64_t t0 = g * G;
-        const int64_t t1 = t0 + G < N ? t0 + G : N;
-        for (int64_t t = t0 + w; t < t1; t += 16) {
-            const int i = static_cast<int>(t - t0);
-            for (int q = lane; q < P; q += 64) {
-                const int64_t k = static_cast<int64_t>(q) * NG + g;
-                const int64_t rel = i ? gend[k * kStreamGroupSlots + i - 1] : 0;
-                cur[w][q] = staged ? seg[q] + rel
-                                   : part_base[q] + gstart[static_cast<int64_t>(q) * (NG + 1) + g] + rel;
-            }
+        uint32_t inc = len ? (phase + len + kChunkIds - 1) / kChunkIds * kChunkIds : 0u;
+        const uint32_t size = inc;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        if (lane < P) {
+            sh.seg[lane] = inc - size;
+            sh.base[lane] = inc - size + phase - rel;
+        }
+        if (lane == P - 1) sh.seg[P] = inc;
+    }
+    __syncthreads();
+    const int64_t t0 = g * G + i0;
+    if (sh.seg[P] > static_cast<uint32_t>(kScatterStage16)) {
+        int64_t* big = reinterpret_cast<int64_t*>(stage) + w * kMaxStreamParts;    // the stage holds the cursors
+        const int n_bits = P > 1 ? 32 - __builtin_clz(static_cast<uint32_t>(P - 1)) : 0;
+        for (int i = w; i < n; i += kScatterWaves) {
+            if (lane < P) big[lane] = sh.out[lane] + ends[lane * row + i];
             __builtin_amdgcn_wave_barrier();
-            const int64_t b = offsets[t], e = offsets[t + 1];
-            constexpr int kAhead = 8;                   // chunks of 64 IDs loaded together
-            for (int64_t c0 = b; c0 < e; c0 += 64 * kAhead) {
-                uint32_t idk[kAhead];
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int64_t at = c0 + k * 64 + lane;
-                    idk[k] = at < e ? ids[at] : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) {
-                    const int64_t c = c0 + k * 64;
-                    if (c >= e) break;
-                    const bool valid = c + lane < e;
-                    const uint32_t id = idk[k];
-                    const int pid = static_cast<int>(id >> kStreamShift);
-                    uint64_t same = __ballot(valid);
-                    for (int bit = 0; bit < n_bits; ++bit) {
-                        const bool set = ((pid >> bit) & 1) != 0;
-                        const uint64_t lanes = __ballot(set);
-                        same &= set ? lanes : ~lanes;
-                    }
-                    const int64_t at = cur[w][pid];
-                    if (valid) {
-                        const int64_t to = at + __popcll(same & below);
-                        if (staged)
-                            stage[to] = static_cast<uint16_t>(id);
-                        else
-                            out[to] = static_cast<uint16_t>(id);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    if (valid && (same & above) == 0) cur[w][pid] = at + __popcll(same);
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
+            scatter_trial_direct(ids, offsets[t0 + i], offsets[t0 + i + 1], kStreamShift, n_bits, big, out);
             __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
-        if (staged) {
-            // segments are whole 8-ID chunks, here and in the stream
-            for (int q = w; q < P; q += 16) {
-                const uint32_t s0 = seg[q] / 8, s1 = seg[q + 1] / 8;
-                u32x4* dst = reinterpret_cast<u32x4*>(out + part_base[q] +
-                                                      gstart[static_cast<int64_t>(q) * (NG + 1) + g]);
-                for (uint32_t u = s0 + lane; u < s1; u += 64) dst[u - s0] = reinterpret_cast<const u32x4*>(stage)[u];
+        if (last && w == 0 && lane < P) {
+            const int64_t k = static_cast<int64_t>(lane) * (NG + 1) + g;
+            for (uint32_t u = ends[lane * row + n]; u < gstart[k + 1] - gstart[k]; ++u) out[sh.out[lane] + u] = 0xFFFFu;
+        }
+        return;
+    }
+    if (last && w == kScatterWaves - 1 && lane < P) {
+        const uint32_t to = sh.base[lane] + ends[lane * row + n];
+        for (uint32_t u = to; u % kChunkIds; ++u) stage[u] = 0xFFFFu;
+    }
+    uint32_t* cur = reinterpret_cast<uint32_t*>(cursors[w]);
+    scatter_unit<kBits>(
+        offsets, ids, t0, n, kStreamShift, cur, stage,
+        [&](int i) {
+            if (lane < P) cur[lane] = sh.base[lane] + ends[lane * row + i];
+        },
+        [](int) {});
+    __syncthreads();
+    // a run per group of 16, 32 or 64 lanes
+    const int lanes = P > 16 ? 16 : (P > 8 ? 32 : 64);
+    for (int q = threadIdx.x / lanes; q < P; q += kScatterThreads / lanes) {
+        const uint32_t s0 = sh.seg[q], s1 = sh.seg[q + 1];
+        const uint32_t from = sh.base[q] + ends[q * row];
+        const uint32_t to = last ? s1 : sh.base[q] + ends[q * row + n];
+        uint16_t* dst = out + sh.out[q] - static_cast<int32_t>(sh.base[q]);     // of stage index 0
+        for (uint32_t u = s0 + (threadIdx.x % lanes) * kChunkIds; u < s1; u += lanes * kChunkIds) {
+            if (u >= from && u + kChunkIds <= to) {
+                *reinterpret_cast<u32x4*>(dst + u) = *reinterpret_cast<const u32x4*>(stage + u);
+            } else {
+                for (uint32_t v = max(u, from); v < min(u + kChunkIds, to); ++v) dst[v] = stage[v];
             }
         }
-        __syncthreads();
     }
 }
 
@@ -1099,8 +1089,8 @@ hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, i
     return hipSuccess;
 }
 
-hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, const CreateResult& res,
-                              const CreateResult* d_res, int n_cu, hipStream_t s, StreamLayout* out) {
+hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                              const CreateResult& res, const CreateResult* d_res, hipStream_t s, StreamLayout* out) {
     if (out->P == 0) return hipSuccess;
     if (res.flags & (kCreateWideGroup | kCreateWidePart)) {     // too large for 16/32-bit offsets: not used
         free_stream_layout(out, s);
@@ -1110,9 +1100,22 @@ hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64
     for (int q = 0; q < out->P; ++q) length += res.stream_ids[q];
     hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (length + kStreamPad), s);
     if (e == hipSuccess) {
-        const int64_t gb = std::min(out->NG, int64_t(n_cu));   // one 16-wave workgroup per CU (the stage fills LDS)
-        hipLaunchKernelGGL(stream_group_scatter_kernel, dim3(static_cast<uint32_t>(gb)), dim3(1024), 0, s, offsets,
-                           ids, N, out->P, out->G, out->NG, d_res, out->part_base, out->gstart, out->gend, out->ids);
+        // units of even size within a group, each part's run up to 14 IDs from whole chunks
+        const double lam = static_cast<double>(n_events) / static_cast<double>(N);
+        const int fit = scatter_trials(lam, 14.0 * out->P, kScatterStage16, out->G);
+        const int units = (out->G + fit - 1) / fit, per = (out->G + units - 1) / units;
+        const int64_t n_units = out->NG * ((out->G + per - 1) / per);
+        const dim3 grid(static_cast<uint32_t>((n_units + kXcds - 1) / kXcds * kXcds)), b(kScatterThreads);
+        const size_t lds = sizeof(uint32_t) * static_cast<size_t>(out->P) * (per + 1);
+        if (out->P <= 8)
+            hipLaunchKernelGGL(stream_scatter_kernel<3>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
+                               d_res, out->part_base, out->gstart, out->gend, out->ids);
+        else if (out->P <= 32)
+            hipLaunchKernelGGL(stream_scatter_kernel<5>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
+                               d_res, out->part_base, out->gstart, out->gend, out->ids);
+        else
+            hipLaunchKernelGGL(stream_scatter_kernel<6>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
+                               d_res, out->part_base, out->gstart, out->gend, out->ids);
         e = hipGetLastError();
     }
     if (e != hipSuccess) {
