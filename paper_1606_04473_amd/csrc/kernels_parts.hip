@@ -126,13 +126,11 @@ __global__ __launch_bounds__(256) void yet_count_kernel(const int64_t* __restric
     }
     auto flush = [&](bool add) {
         __builtin_amdgcn_wave_barrier();
-        if (lane < bins) {
-            int32_t v = 0;
-            for (int r = 0; r < (1 << rep_bits); ++r) {
-                v += c[(lane << rep_bits) + r];
-                c[(lane << rep_bits) + r] = 0;
-            }
-            int32_t* to = cnt + k * bins + lane;
+        int32_t v = c[lane];
+        c[lane] = 0;
+        for (int off = 1; off < (1 << rep_bits); off <<= 1) v += __shfl_xor(v, off, 64);
+        if (rep == 0 && (lane >> rep_bits) < bins) {
+            int32_t* to = cnt + k * bins + (lane >> rep_bits);
             if (!add) *to = v;
             else if (v) atomicAdd(to, v);
         }

@@ -369,14 +369,15 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
     // then the forward's copy of the part's nonzero o(E), followed by one 0.0
     // that the drain's idle slots read, or the backward's counters.  A part
     // with more nonzero events than LDS holds keeps those of each superblock's
-    // first ones (kSbCap, kSbCnt); its ranks are positions in the superblocks'
-    // 4096-value slots of the stage, so the others are read there directly
+    // first ones (kSbCap); its ranks are positions in the superblocks' 4096-value
+    // slots of the stage, so the others are read there directly.  The backward
+    // counts such a part in 16-bit halves, the ranks past those in memory
     constexpr uint32_t kMapOff = (kQSize / 128) * 4;
     constexpr uint32_t kQueueOff = kMapOff + kQSize;
     constexpr uint32_t kValOff = kQueueOff + 16 * kQ * 2;
     constexpr int kCap = static_cast<int>((160 * 1024 - kValOff) / 8) - 1;
     constexpr int kCnt = static_cast<int>((160 * 1024 - kValOff) / 4);
-    constexpr uint32_t kSbCap = kCap / kPartSuper, kSbCnt = kCnt / kPartSuper;
+    constexpr uint32_t kSbCap = kCap / kPartSuper, kCnt16 = 2 * kCnt;
     static_assert(kValOff % 16 == 0 && kCap > 0 && kMapOff < 65536, "LDS layout");
     constexpr uint32_t kLdsBytes = kAdj ? kValOff + kCnt * 4 : kValOff + (kCap + 1) * 8;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
@@ -409,12 +410,9 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
         for (int e = threadIdx.x; e < kQSize; e += blockDim.x) {
             const uint32_t b = map[e];
             if (!b) continue;
-            uint32_t r = bases[e >> 7] + b;
-            if (!prev_fits) {
-                if ((r & (kSuperEvents - 1)) >= kSbCnt) continue;
-                r = (r / kSuperEvents) * kSbCnt + (r & (kSuperEvents - 1));
-            }
-            const uint32_t cv = cnt[r];
+            const uint32_t r = bases[e >> 7] + b;
+            if (!prev_fits && r >= kCnt16) continue;
+            const uint32_t cv = prev_fits ? cnt[r] : (cnt[r >> 1] >> (16 * (r & 1u))) & 0xFFFFu;
             if (cv) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e]),
                               static_cast<unsigned long long>(cv));
         }
@@ -496,7 +494,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
             if (threadIdx.x < kQSize / 128) {           // two superblocks of 32 blocks per wave
                 const int sb = 2 * wv + (lane >> 5);
                 const uint32_t s0 = static_cast<uint32_t>(__shfl(static_cast<int>(sb_start), sb));
-                bases[threadIdx.x] = (fits ? s0 : static_cast<uint32_t>(sb) * kSuperEvents) + r16 - 1u;
+                bases[threadIdx.x] = (kAdj || fits ? s0 : static_cast<uint32_t>(sb) * kSuperEvents) + r16 - 1u;
             }
             if constexpr (kAdj) {
                 for (int k = threadIdx.x; k < kCnt; k += blockDim.x) cnt[k] = 0u;
@@ -594,9 +592,42 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
                 // plus the byte, which is 1 + the rank inside the block
                 return bases[e >> 7] + map[e];
             };
-            // !fits: an entry's index inside its superblock, and the LDS slot of index i < per
+            // !fits: an entry's index inside its superblock, and the LDS slot of index i < kSbCap
             auto sb_index = [&](uint32_t rk) -> uint32_t { return rk & (kSuperEvents - 1); };
-            auto sb_slot = [&](uint32_t rk, uint32_t i, uint32_t per) -> uint32_t { return rk / kSuperEvents * per + i; };
+            auto sb_slot = [&](uint32_t rk, uint32_t i) -> uint32_t { return rk / kSuperEvents * kSbCap + i; };
+            // The backward with !fits: one occurrence of each event e with `on`, in
+            // the 16-bit counter of its rank, past those in memory.  The lane that
+            // brings a counter to 2^15 moves that many to memory; a lane that finds
+            // it there or above takes its own back and adds it in memory, so a
+            // counter never holds more than 2^15 and one for each of the four
+            // entries of 1024 lanes.  The pass with losses for 0.97, 0.85 and
+            // 0.6 of the events, against 32-bit counters of half as many events and
+            // memory for the others: 650 -> 158 us (5.5e7 events, one part), 545 ->
+            // 200 us (5e7, eight parts), 270 -> 183 us (4e7, two parts).
+            auto count16 = [&](const uint32_t* e, const uint32_t* rk, const bool* on) {
+                constexpr int kN = 4;
+                uint32_t old[kN];
+                bool rare = false;
+#pragma unroll
+                for (int r2 = 0; r2 < kN; ++r2) {
+                    old[r2] = 0;
+                    const uint32_t sh = 16 * (rk[r2] & 1u);
+                    if (on[r2] && rk[r2] < kCnt16)
+                        old[r2] = (atomicAdd(&cnt[rk[r2] >> 1], 1u << sh) >> sh) & 0xFFFFu;
+                    else if (on[r2])
+                        atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
+                    rare |= old[r2] >= 0x7FFFu;
+                }
+                if (!__ballot(rare)) return;
+#pragma unroll
+                for (int r2 = 0; r2 < kN; ++r2) {
+                    if (old[r2] < 0x7FFFu) continue;
+                    const uint32_t moved = old[r2] == 0x7FFFu ? 0x8000u : 1u;
+                    atomicSub(&cnt[rk[r2] >> 1], moved << (16 * (rk[r2] & 1u)));
+                    atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]),
+                              static_cast<unsigned long long>(moved));
+                }
+            };
             // With many hits of few trials in the queue (long trials over few
             // parts, dense layers) one lane per trial leaves most lanes idle: then
             // 2^s lanes take a trial's entries in turn and their sums are merged,
@@ -634,15 +665,21 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
                             for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2 * per];
 #pragma unroll
                             for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                            bool on[kR];
 #pragma unroll
-                            for (int r2 = 0; r2 < kR; ++r2) {
-                                if (j + r2 * per >= jend) continue;
-                                const uint32_t i = sb_index(rk[r2]);
-                                if (fits || i < kSbCnt)
-                                    atomicAdd(&cnt[fits ? rk[r2] : sb_slot(rk[r2], i, kSbCnt)], 1u);
-                                else
-                                    atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
-                                if (wt) atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + e[r2]]), wt);
+                            for (int r2 = 0; r2 < kR; ++r2) on[r2] = j + r2 * per < jend;
+                            if (fits) {
+#pragma unroll
+                                for (int r2 = 0; r2 < kR; ++r2)
+                                    if (on[r2]) atomicAdd(&cnt[rk[r2]], 1u);
+                            } else {
+                                count16(e, rk, on);
+                            }
+                            if (wt) {
+#pragma unroll
+                                for (int r2 = 0; r2 < kR; ++r2)
+                                    if (on[r2])
+                                        atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_tvar[ebase + e[r2]]), wt);
                             }
                         }
                     } else {
@@ -668,7 +705,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
 #pragma unroll
                                 for (int r2 = 0; r2 < kR; ++r2) {
                                     const uint32_t i = sb_index(rk[r2]);
-                                    v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                                    v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1)) : kCap];
                                     spill |= valid[r2] && i >= kSbCap;
                                 }
                                 if (__ballot(spill)) {
@@ -722,15 +759,10 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
                             for (int r2 = 0; r2 < kR; ++r2) e[r2] = q[j + r2];
 #pragma unroll
                             for (int r2 = 0; r2 < kR; ++r2) rk[r2] = rank(e[r2]);
+                            bool on[kR];
 #pragma unroll
-                            for (int r2 = 0; r2 < kR; ++r2) {
-                                if (j + r2 >= hi) continue;
-                                const uint32_t i = sb_index(rk[r2]);
-                                if (i < kSbCnt)
-                                    atomicAdd(&cnt[sb_slot(rk[r2], i, kSbCnt)], 1u);
-                                else
-                                    atomicAdd(reinterpret_cast<unsigned long long*>(&adj.w_mean[ebase + e[r2]]), 1ull);
-                            }
+                            for (int r2 = 0; r2 < kR; ++r2) on[r2] = j + r2 < hi;
+                            count16(e, rk, on);
                         }
                     }
                     if (cls & 6u) {
@@ -785,7 +817,7 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
 #pragma unroll
                         for (int r2 = 0; r2 < kR; ++r2) {
                             const uint32_t i = sb_index(rk[r2]);
-                            v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1), kSbCap) : kCap];
+                            v[r2] = vals[valid[r2] ? sb_slot(rk[r2], min(i, kSbCap - 1)) : kCap];
                             spill |= valid[r2] && i >= kSbCap;
                         }
                         if (__ballot(spill)) {

@@ -58,3 +58,27 @@ def test_long_dense_trials(ara, n_trials, lam, C, J, nnz):
                          spec.agg_retention, spec.agg_limit, lo, n)
     assert np.array_equal(ara.run_layers(tables, [part]), ylt[lo:lo + n])
     tables.close()
+
+
+# dense parts (past the backward's 32-bit counters) where one event makes up four
+# fifths of the table: a workgroup's 16-bit counter of it passes 2^15; long
+# trials (lanes share a trial) and short ones
+@pytest.mark.parametrize("n_trials,lam", [(12_000, 2_000), (800_000, 28)])
+def test_one_event_past_a_counter(ara, n_trials, lam):
+    C = 60_000
+    yet = make_yet(n_trials, lam, C, seed=lam)
+    rng = np.random.default_rng(lam)
+    yet.ids[rng.random(yet.ids.size) < 0.8] = 77
+    pool = make_elt_pool(3, C, 25_000, seed=5)
+    pool.losses[0, 77] = 12_345.0
+    idx = np.arange(3, dtype=np.int32)
+    layer = Layer(idx, 0.0, 4.0e6, 1.0, np.inf, 0, n_trials)
+    spec = ara.LayerSpec.from_layer(layer, pool, n_trials)
+    tables = ara.create_tables(yet.offsets, yet.ids, pool.losses)
+    assert tables.layout()["stream_parts"] == 1
+    ref, S = oracle.run_layer(yet, pool, layer)
+    ara.run_layers(tables, [spec], flags=ara.ARA_CHECKPOINT_S)
+    gm, gt = ara.backward(tables, spec, 0.9)
+    g = oracle.gradients(yet, pool, layer, 0.9, ylt=ref, S=S)
+    assert np.array_equal(gm, g["grad_mean"]) and np.array_equal(gt, g["grad_tvar"])
+    tables.close()
