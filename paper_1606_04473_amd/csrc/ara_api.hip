@@ -93,6 +93,11 @@ void cache_stats(int device, int64_t* held, int64_t* idle) {
 
 int64_t cache_release(int device) { return release_idle(device_cache(device)); }
 
+// Events that order work on one device only: nothing on the host reads what came
+// before them, so they carry no system-scope fence (a record costs the stream
+// 3.4 us instead of 4.5).
+constexpr unsigned kOrderEvent = hipEventDisableTiming | hipEventDisableSystemFence;
+
 hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s) {
     *p = nullptr;
     int device = 0;
@@ -139,7 +144,7 @@ void dev_free(void* p, hipStream_t s) {
     auto it = c.blocks.find(p);
     if (it == c.blocks.end()) return;
     CacheBlock& b = it->second;
-    if (!b.ready && hipEventCreateWithFlags(&b.ready, hipEventDisableTiming) != hipSuccess) b.ready = nullptr;
+    if (!b.ready && hipEventCreateWithFlags(&b.ready, kOrderEvent) != hipSuccess) b.ready = nullptr;
     if (b.ready && hipEventRecord(b.ready, s) != hipSuccess) {
         // without an event the block can only go back to work on s
         (void)hipEventDestroy(b.ready);
@@ -226,7 +231,7 @@ hipError_t scratch_acquire(std::mutex& mu, std::vector<ara::ScratchBuffer*>& set
         pick->busy = true;
     }
     hipError_t e = hipSuccess;
-    if (!pick->done) e = hipEventCreateWithFlags(&pick->done, hipEventDisableTiming);
+    if (!pick->done) e = hipEventCreateWithFlags(&pick->done, ara::kOrderEvent);
     if (e == hipSuccess && pick->cap < bytes) {
         // growing: the old memory may still be read by work on its last
         // stream, so it goes back to the cache in that stream's order; the new
@@ -290,7 +295,7 @@ void note_use(ara_tables* t, hipStream_t s) {
             return;
         }
     hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
+    if (hipEventCreateWithFlags(&ev, ara::kOrderEvent) != hipSuccess) return;
     if (hipEventRecord(ev, s) != hipSuccess) {
         (void)hipEventDestroy(ev);
         return;
@@ -298,10 +303,13 @@ void note_use(ara_tables* t, hipStream_t s) {
     t->fences.emplace_back(s, ev);
 }
 
-// note_use on scope exit, so a call's error returns are covered too
+// note_use on scope exit, so a call's error returns are covered too; a call that
+// holds scratch of the tables hands over to the event its release records anyway
+// (destroying the tables waits for those first)
 struct UseFence {
     ara_tables* t;
     hipStream_t s;
+    void hand_over() { t = nullptr; }
     UseFence(ara_tables* tt, hipStream_t ss) : t(tt), s(ss) {}
     ~UseFence() {
         if (t) note_use(t, s);
@@ -918,6 +926,8 @@ void ara_destroy_tables(ara_tables* t) {
         }
         t->fences.clear();
     }
+    for (auto* b : t->scratch)
+        if (b->done) (void)hipStreamWaitEvent(fs, b->done, 0);
     if (t->offsets) ara::dev_free(t->offsets, fs);
     if (t->ids) ara::dev_free(t->ids, fs);
     scratch_free_all(t->scratch, fs);
@@ -1179,6 +1189,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             e = scratch_acquire(t->scratch_mu, t->scratch, o_bytes + p_bytes + x_bytes + 256, s, &lease.b);
         }
         HIP_TRY(e, "scratch for occurrence losses, part images and partial sums");
+        use_fence.hand_over();
         base = static_cast<char*>(lease.b->p);
     }
     struct {
@@ -1502,6 +1513,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
         me = scratch_acquire(t->scratch_mu, t->scratch, w_bytes + l_bytes + g_bytes + f_bytes + 256, s, &lease.b);
     }
     HIP_TRY(me, "portfolio scratch");
+    use_fence.hand_over();
     char* base = static_cast<char*>(lease.b->p);
     double* o_buf = reinterpret_cast<double*>(base);
     void* p_buf = base + o_bytes;
@@ -1969,12 +1981,15 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     if (!ds.ok) return fail(ARA_ERR_DEVICE, "cannot select the tables' device");
     hipStream_t s = static_cast<hipStream_t>(stream);
     UseFence use_fence(t, s);           // the tables' memory outlives this call's work
-    int64_t be[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(&be[0], t->offsets + L.trial_begin, sizeof(int64_t), hipMemcpyDeviceToHost, s), "offsets");
-    HIP_TRY(hipMemcpyAsync(&be[1], t->offsets + L.trial_begin + L.trial_count, sizeof(int64_t), hipMemcpyDeviceToHost,
-                           s),
-            "offsets");
-    HIP_TRY(hipStreamSynchronize(s), "synchronize");
+    // the events of the range; those of the whole table are known
+    int64_t be[2] = {0, t->n_events};
+    const int64_t t_end = L.trial_begin + L.trial_count;
+    if (L.trial_begin > 0)
+        HIP_TRY(hipMemcpyAsync(&be[0], t->offsets + L.trial_begin, sizeof(int64_t), hipMemcpyDeviceToHost, s),
+                "offsets");
+    if (t_end < t->n_trials)
+        HIP_TRY(hipMemcpyAsync(&be[1], t->offsets + t_end, sizeof(int64_t), hipMemcpyDeviceToHost, s), "offsets");
+    if (L.trial_begin > 0 || t_end < t->n_trials) HIP_TRY(hipStreamSynchronize(s), "synchronize");
     const int64_t n = be[1] - be[0];
     *n_out = n;
     if (n > capacity) return fail(ARA_ERR_BUFFER_TOO_SMALL, "the layer's trials hold %lld events, capacity %lld",
@@ -1994,6 +2009,7 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     lease.s = s;
     HIP_TRY(scratch_acquire(t->scratch_mu, t->scratch, o_bytes + p_bytes + w_bytes + n_bytes + 256, s, &lease.b),
             "scratch for occurrence losses, part images, probe words and net losses");
+    use_fence.hand_over();
     char* base = static_cast<char*>(lease.b->p);
     uint64_t* probe = reinterpret_cast<uint64_t*>(base + o_bytes + p_bytes);
     double* out = dev ? nets : reinterpret_cast<double*>(base + o_bytes + p_bytes + w_bytes);
