@@ -606,10 +606,14 @@ struct SplitPass {
         return ara::launch_xcd_pass(t->parts, t->n_trials, t->C, L, part_scratch, static_cast<double*>(partials),
                                     t->n_cu, s);
     }
+    // with S the checkpoint of the year losses is written too
     hipError_t combine(const ara::LayerArgs& L, const ara::LayerArgs* L_dev, const void* partials, double* ylt,
-                       double* S, hipStream_t s) const {
-        if (stream) return ara::launch_stream_combine(t->stream, L, L_dev, partials, ylt, S, s);
-        return ara::launch_xcd_combine(t->parts, L, L_dev, static_cast<const double*>(partials), ylt, S, s);
+                       double* ylt_too, double* S, hipStream_t s) const {
+        if (stream) return ara::launch_stream_combine(t->stream, L, L_dev, partials, ylt, ylt_too, S, s);
+        const hipError_t e =
+            ara::launch_xcd_combine(t->parts, L, L_dev, static_cast<const double*>(partials), ylt, S, s);
+        if (e != hipSuccess || !ylt_too || L.trial_count <= 0) return e;
+        return hipMemcpyAsync(ylt_too, ylt, sizeof(double) * L.trial_count, hipMemcpyDeviceToDevice, s);
     }
 };
 
@@ -1274,7 +1278,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             for (int i = 0; i < n_layers && le == hipSuccess && !joined; ++i) {
                 le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
                 if (le == hipSuccess) le = split.pass(L[i], gp, gx, s);
-                if (le == hipSuccess) le = split.combine(L[i], dL + i, gx, out + L[i].out_offset, nullptr, s);
+                if (le == hipSuccess) le = split.combine(L[i], dL + i, gx, out + L[i].out_offset, nullptr, nullptr, s);
             }
             e = hipStreamEndCapture(s, &ge->graph);
             if (js != ARA_OK) {
@@ -1393,7 +1397,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             HIP_TRY(split.pass(L[i], pbuf.p, xbuf.p, s), "trial pass");
             kp.done();
             KernelTimer kc(t, s, prof, ARA_KERNEL_COMBINE);
-            HIP_TRY(split.combine(L[i], nullptr, xbuf.p, a.ylt, a.S, s), "partial sums merge");
+            HIP_TRY(split.combine(L[i], nullptr, xbuf.p, a.ylt, ckpt ? t->ck.ylt : nullptr, a.S, s), "partial sums merge");
             kc.done();
             if (stride_buf) {
                 HIP_TRY(ara::launch_stride_checkpoints(t->offsets, t->ids, pbuf.p, t->parts.P, t->C,
@@ -1412,8 +1416,9 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
         kt.done();
     }
     if (ckpt) {
-        HIP_TRY(hipMemcpyAsync(t->ck.ylt, out, sizeof(double) * L[0].trial_count, hipMemcpyDeviceToDevice, s),
-                "keep YLT");
+        if (!use_xcd)
+            HIP_TRY(hipMemcpyAsync(t->ck.ylt, out, sizeof(double) * L[0].trial_count, hipMemcpyDeviceToDevice, s),
+                    "keep YLT");
         t->ck.key = L[0];
         t->ck.valid = true;
     }
@@ -1555,7 +1560,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
                 HIP_TRY(split.pass(Li, p_buf, x_buf, s), "trial pass");
                 kp.done();
                 KernelTimer kc(t, s, prof, ARA_KERNEL_COMBINE);
-                HIP_TRY(split.combine(Li, nullptr, x_buf, ylt_i, nullptr, s), "partial sums merge");
+                HIP_TRY(split.combine(Li, nullptr, x_buf, ylt_i, nullptr, nullptr, s), "partial sums merge");
                 kc.done();
             } else if (use_parts) {
                 KernelTimer kp(t, s, prof, ARA_KERNEL_TRIAL_PASS);
@@ -1751,7 +1756,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
                                              L.trial_count, dL, ylt, m.data(), n_probs, gm, mo, s);
         } else {
             bool primed = true;
-            if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, s);
+            if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, nullptr, s);
             if (le == hipSuccess) le = ara::launch_metrics(ylt, L.trial_count, m.data(), n_probs, gm, &primed, mo, s);
         }
         e = hipStreamEndCapture(s, &ge->graph);
@@ -1840,18 +1845,18 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
     const bool use_stream = use_parts && t->tuning.pass_variant == 0 && t->stream.P > 0;
     if (use_parts) {
         const ara_tuning tu = t->tuning;   // t->mu is held
-        HIP_TRY(obuf.alloc(sizeof(double) * t->C, s), "scratch for occurrence losses");
         HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
-        if (t->sparse.chunk_off) {
-            // the forward's fold from the sparse pool (o, images and superblock counts)
-            HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, t->parts.P, pbuf.p, false, nullptr, s),
-                    "fold");
-        } else {
+        if (!t->sparse.chunk_off) {
+            HIP_TRY(obuf.alloc(sizeof(double) * t->C, s), "scratch for occurrence losses");
             HIP_TRY(ara::launch_fold(t->elts, t->C, L, static_cast<double*>(obuf.p), tu, s), "fold");
             HIP_TRY(ara::launch_part_fold(static_cast<const double*>(obuf.p), t->C, t->parts.P, pbuf.p, s, false),
                     "images");
         }
     }
+    if (t->sparse.chunk_off)
+        HIP_TRY(ara::launch_adjoint_fold(t->sparse, t->C, L, use_parts ? t->parts.P : ara::part_count(t->C), pbuf.p,
+                                         scratch.p, s),
+                "fold");
     HIP_TRY(ara::launch_adjoint(t->offsets, t->ids, t->elts, t->C, L, t->ck.S, t->ck.ylt, m, scratch.p, gm, gt,
                                 t->n_cu, s, use_parts ? &t->parts : nullptr, pbuf.p, t->n_trials,
                                 t->sparse.chunk_off ? &t->sparse : nullptr, use_stream ? &t->stream : nullptr,

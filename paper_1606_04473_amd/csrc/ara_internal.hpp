@@ -266,7 +266,7 @@ hipError_t launch_store_terms(const LayerArgs* L, int n, LayerArgs* dst, hipStre
 hipError_t launch_stream_pass(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                               int n_img_parts, void* partials, int n_cu, hipStream_t s);
 hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, const LayerArgs* L_dev,
-                                 const void* partials, double* ylt, double* S, hipStream_t s);
+                                 const void* partials, double* ylt, double* ylt_too, double* S, hipStream_t s);
 // the same for several layers or trial ranges in one launch each (at most
 // stream_batch_max() units): `layer` indexes the fold's views and L_dev, the
 // unit's year losses go to ylt + out_at.  Partials of stream_partials_bytes(all
@@ -285,14 +285,16 @@ hipError_t launch_stream_combine_units(const StreamLayout& lay, const StreamUnit
 struct TailStats;
 // the backward histogram over the same stream: for the trials inside the
 // aggregate band, occurrences of each nonzero-o(E) event added to w_mean and
-// TVaR weights to w_tvar (both [C], zeroed by the caller); S and ylt are the
+// TVaR weights to w_tvar (both [C], zeroed by the caller), and the partials of
+// the two aggregate terms to agg_mean[0..1] and agg_tvar[0..1], of one of `copies`
+// copies `stride` apart (summed by the caller); S and ylt are the
 // checkpointed forward's, tail its order statistics on the device.  scratch
 // holds stream_adjoint_scratch_bytes(L.trial_count) bytes.
 int64_t stream_adjoint_scratch_bytes(int64_t trials);
 hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                                  int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
-                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
-                                 hipStream_t s);
+                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar,
+                                 long long* agg_mean, long long* agg_tvar, int copies, int stride, int n_cu, hipStream_t s);
 
 constexpr int kXcds = 8;           // gfx950 (MI355X): 8 XCDs, workgroups dispatched round-robin
 
@@ -551,6 +553,18 @@ hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hi
 // (probe_table_bytes(C))
 hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L, const LayerArgs* L_dev, double* o,
                              int P, void* scratch, bool compact, uint64_t* probe, hipStream_t s);
+// the fold at the start of a backward: part images and packed values (with a
+// scratch for them), where each event's loss lies against the occurrence terms,
+// and the histogram cleared
+struct FoldBack {
+    uint8_t* band;                  // [C]: 1 inside the occurrence band, 2 above it, else 0
+    uint64_t* w_mean;               // [C], cleared
+    uint64_t* w_tvar;
+    long long* acc;                 // [n_acc], cleared
+    int n_acc;
+};
+hipError_t launch_fold_back(const SparsePool& sp, int64_t C, const LayerArgs& L, int P, void* scratch,
+                            const FoldBack& back, hipStream_t s);
 // the XCD-affine pass writes per-part partial sums; the combine merges them
 hipError_t launch_xcd_pass(const PartLayout& lay, int64_t N, int64_t C, const LayerArgs& L, void* part_scratch,
                            double* partials, int n_cu, hipStream_t s);
@@ -610,6 +624,11 @@ hipError_t launch_part_adjoint(const PartLayout& lay, int64_t N, const LayerArgs
 // the histogram pass runs over the partitioned layout, or over the 16-bit
 // stream when `stream` is given and holds one
 int64_t adjoint_scratch_bytes(int64_t C, int J, int64_t n);
+// with a sparse pool `sp` launch_adjoint_fold goes first: it clears the sums, finds
+// each event's place against the occurrence terms, and with `part_scratch` writes
+// the part images and packed values there
+hipError_t launch_adjoint_fold(const SparsePool& sp, int64_t C, const LayerArgs& L, int P, void* part_scratch,
+                               void* scratch, hipStream_t s);
 hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const double* elts,
                           int64_t C, const LayerArgs& L, const double* S, const double* ylt,
                           int64_t m, void* scratch, double* d_grad_mean, double* d_grad_tvar,

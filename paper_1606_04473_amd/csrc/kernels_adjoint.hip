@@ -21,6 +21,8 @@ namespace ara {
 namespace {
 
 constexpr int kMaxP = 2 * kMaxJ + 4;
+// copies of the numerators, one per XCD for the workgroups that finish at once
+constexpr int kAccCopies = 8;
 
 // signed 64-bit add through the unsigned atomic (two's complement wraps)
 __device__ __forceinline__ void add_i64(long long* p, long long v) {
@@ -31,28 +33,26 @@ struct AdjScratch {
     uint8_t* mark;         // [C]
     uint64_t* w_mean;      // [C]
     uint64_t* w_tvar;      // [C]
-    long long* acc;        // [2][kMaxP] integer numerators
+    long long* acc;        // [kAccCopies][2][kMaxP] integer numerators, summed at the end
     TailStats* tail;
     void* cls;             // trial classes of the stream histogram
     int64_t cls_bytes;
     void* tail_scratch;
 };
 
-// The same numerators from the sparse ELT pool: one workgroup per chunk of
-// kSparseChunk events.  y(E) is rebuilt in LDS as the forward fold does it
-// (each ELT's entries added in layer order; an absent loss would add +0.0),
-// so it is bit-identical to the dense sum.  Each event with a weight then adds
-// its occurrence-term slopes, and each nonzero loss (E, l) of ELT j its
-// per-ELT slopes; an absent loss has l - R_j <= 0 and no slope, so the sparse
-// entries give the dense kernel's integer sums.
-//
-// The chunk's entries of the layer's ELTs (in layer order) are first copied to
-// LDS, kStage at a time, with all their loads in flight together; the fold
-// and the per-ELT slopes then read LDS only, so the ordered fold costs one
-// barrier per ELT and no memory latency.  The weights of the chunk's events
-// are kept in LDS for the slopes.
+// The same numerators from the sparse ELT pool, after a fold that left each
+// event's place against the occurrence terms: one workgroup per chunk of
+// kSparseChunk events.  Each event with a weight adds its occurrence-term slopes;
+// the weights of those inside the band go to LDS, where each nonzero loss (E, l)
+// of ELT j finds them for its per-ELT slopes (an absent loss has l - R_j <= 0 and
+// no slope, so the sparse entries give the dense kernel's integer sums).  A wave
+// takes whole ELTs, so it sums in registers; its first entries load before the
+// weights are in place.  Refolding the chunk's losses here, with their entries
+// staged in LDS, one workgroup per CU, took 38 us where this takes 16 (16 ELTs over
+// 2e6 events); it takes 90 with the device atomics ELT by ELT and 22 with one copy
+// of the sums for all workgroups.
 constexpr int kSparseChunk = 4096;                  // events per chunk of the sparse pool
-constexpr int kStage = 4096;                        // pool entries staged in LDS at a time
+constexpr int kSparseThreads = 512;
 
 // sum over the wave's lanes
 __device__ __forceinline__ long long wave_sum_i64(long long v) {
@@ -61,147 +61,110 @@ __device__ __forceinline__ long long wave_sum_i64(long long v) {
     return v;
 }
 
-__global__ __launch_bounds__(1024) void catalogue_sparse_kernel(SparsePool sp, int64_t C, LayerArgs L,
-                                                                const uint64_t* __restrict__ w_mean,
-                                                                const uint64_t* __restrict__ w_tvar,
-                                                                long long* __restrict__ acc) {
-    __shared__ double ys[kSparseChunk];
+__global__ __launch_bounds__(kSparseThreads) void catalogue_sparse_kernel(SparsePool sp, int64_t C, LayerArgs L,
+                                                                          const uint8_t* __restrict__ band,
+                                                                          const uint64_t* __restrict__ w_mean,
+                                                                          const uint64_t* __restrict__ w_tvar,
+                                                                          long long* __restrict__ acc) {
+    constexpr int kPer = kSparseChunk / kSparseThreads, kWaves = kSparseThreads / 64;
     __shared__ long long wms[kSparseChunk], wvs[kSparseChunk];
-    __shared__ uint8_t act[kSparseChunk];           // inside the occurrence band, with a weight
-    __shared__ double s_val[kStage];
-    __shared__ uint16_t s_ev[kStage];
-    __shared__ uint8_t s_j[kStage];
-    __shared__ long long lacc[2 * kMaxP];
-    __shared__ int64_t rb[kMaxJ], pre[kMaxJ + 1];
-    __shared__ double sR[kMaxJ], sLim[kMaxJ];
+    __shared__ long long red[kWaves][4];
+    __shared__ long long lacc[2 * kMaxP];           // the workgroup's sums: one pass of device atomics at the end
     const int t = threadIdx.x;
-    const int nt = blockDim.x;
+    const int lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t chunk = blockIdx.x;
     const int64_t e0 = chunk * kSparseChunk;
     const int J = L.J;
-    const int P = 2 * J + 4;
-    for (int i = t; i < kSparseChunk; i += nt) ys[i] = 0.0;
-    for (int i = t; i < 2 * kMaxP; i += nt) lacc[i] = 0;
-    if (t < J) {
-        sR[t] = L.R[t];
-        sLim[t] = L.Lim[t];
+    for (int i = t; i < 2 * kMaxP; i += kSparseThreads) lacc[i] = 0;
+    // lane j: ELT j's entries of the chunk
+    int64_t at = 0;
+    int cnt = 0;
+    if (lane < J) {
+        const int64_t key = static_cast<int64_t>(L.idx[lane]) * sp.n_chunks + chunk;
+        at = sp.chunk_off[key];
+        cnt = static_cast<int>(sp.chunk_off[key + 1] - at);
     }
-    if (t == 0) {
-        int64_t run = 0;
-        for (int j = 0; j < J; ++j) {
-            const int64_t key = static_cast<int64_t>(L.idx[j]) * sp.n_chunks + chunk;
-            const int64_t b = sp.chunk_off[key];
-            rb[j] = b;
-            pre[j] = run;
-            run += sp.chunk_off[key + 1] - b;
-        }
-        pre[J] = run;
+    uint8_t b[kPer];
+    long long wm[kPer], wv[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t e = e0 + k * kSparseThreads + t;
+        b[k] = e < C ? band[e] : 0;
+        wm[k] = e < C ? static_cast<long long>(w_mean[e]) : 0;
+        wv[k] = e < C ? static_cast<long long>(w_tvar[e]) : 0;
     }
-    __syncthreads();
-    const int64_t n_ent = pre[J];
-    // entries [r0, r0 + nr) of the chunk's list (ELT by ELT) to LDS
-    auto stage = [&](int64_t r0, int nr) {
-        for (int i = t; i < nr; i += nt) {
-            const int64_t f = r0 + i;
-            int lo = 0, hi = J;                     // the ELT whose range holds f: pre[lo] <= f < pre[lo + 1]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (pre[mid] <= f) lo = mid; else hi = mid;
-            }
-            const int64_t k = rb[lo] + (f - pre[lo]);
-            s_ev[i] = sp.ev[k];
-            s_val[i] = sp.val[k];
-            s_j[i] = static_cast<uint8_t>(lo);
+    // the next 64 entries of ELT j from f on
+    int ev = 0;
+    double v = 0.0;
+    auto fetch = [&](int j, int f) {
+        const int64_t from = __shfl(at, j, 64);
+        const int n = __builtin_amdgcn_readlane(cnt, j);
+        ev = -1;
+        if (f + lane < n) {
+            ev = sp.ev[from + f + lane];
+            v = sp.val[from + f + lane];
         }
     };
-    // the fold, ELT by ELT in layer order
-    for (int64_t r0 = 0; r0 < n_ent; r0 += kStage) {
-        const int nr = static_cast<int>(n_ent - r0 < kStage ? n_ent - r0 : kStage);
-        __syncthreads();                            // the previous round's entries are used
-        stage(r0, nr);
-        __syncthreads();
-        for (int j = 0; j < J; ++j) {
-            const int64_t a = pre[j] > r0 ? pre[j] : r0;
-            const int64_t b = pre[j + 1] < r0 + nr ? pre[j + 1] : r0 + nr;
-            if (a >= b) continue;                   // uniform: no ELT j entries in this round
-            const double R = L.R[j], Lim = L.Lim[j];
-            for (int64_t f = a + t; f < b; f += nt) {
-                const int i = static_cast<int>(f - r0);
-                const int ev = s_ev[i];
-                ys[ev] = ys[ev] + apply_terms(s_val[i], R, Lim);
-            }
-            __syncthreads();
+    if (w < J) fetch(w, 0);
+    long long sums[4] = {0, 0, 0, 0};               // above, inside; each of the mean and of the TVaR
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        if (b[k] == 2) {
+            sums[0] += wm[k];
+            sums[1] += wv[k];
+        } else if (b[k] == 1) {
+            sums[2] += wm[k];
+            sums[3] += wv[k];
         }
+        wms[k * kSparseThreads + t] = b[k] == 1 ? wm[k] : 0;
+        wvs[k * kSparseThreads + t] = b[k] == 1 ? wv[k] : 0;
     }
-    // occurrence-term slopes; the events' weights and band flags to LDS
-    {
-        long long over_m = 0, over_v = 0, in_m = 0, in_v = 0;
-        for (int i = t; i < kSparseChunk; i += nt) {
-            const int64_t e = e0 + i;
-            long long wm = 0, wv = 0;
-            uint8_t a = 0;
-            if (e < C) {
-                wm = static_cast<long long>(w_mean[e]);
-                wv = static_cast<long long>(w_tvar[e]);
-                if (wm != 0 || wv != 0) {
-                    const double to = ys[i] - L.occR;
-                    if (to > L.occL) {
-                        over_m += wm;
-                        over_v += wv;
-                    }
-                    if ((to > 0.0) && (to < L.occL)) {
-                        in_m += wm;
-                        in_v += wv;
-                        a = 1;
-                    }
-                }
-            }
-            wms[i] = wm;
-            wvs[i] = wv;
-            act[i] = a;
-        }
-        over_m = wave_sum_i64(over_m);
-        over_v = wave_sum_i64(over_v);
-        in_m = wave_sum_i64(in_m);
-        in_v = wave_sum_i64(in_v);
-        if ((t & 63) == 0) {
-            if (over_m) add_i64(&lacc[2 * J + 1], over_m);
-            if (over_v) add_i64(&lacc[kMaxP + 2 * J + 1], over_v);
-            if (in_m) add_i64(&lacc[2 * J], -in_m);
-            if (in_v) add_i64(&lacc[kMaxP + 2 * J], -in_v);
-        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        sums[q] = wave_sum_i64(sums[q]);
+        if (lane == 0) red[w][q] = sums[q];
     }
-    // per-ELT slopes of the events inside the occurrence band (the staged
-    // entries are still in LDS when the list fit in one round)
-    for (int64_t r0 = 0; r0 < n_ent; r0 += kStage) {
-        const int nr = static_cast<int>(n_ent - r0 < kStage ? n_ent - r0 : kStage);
-        __syncthreads();
-        if (n_ent > kStage) {
-            stage(r0, nr);
-            __syncthreads();
-        }
-        for (int i = t; i < nr; i += nt) {
-            const int ev = s_ev[i];
-            if (!act[ev]) continue;
-            const int j = s_j[i];
-            const long long wm = wms[ev], wv = wvs[ev];
-            const double tj = s_val[i] - sR[j];
-            const double Lim = sLim[j];
+    __syncthreads();
+    if (t < 4) {
+        long long s = 0;
+        for (int k = 0; k < kWaves; ++k) s += red[k][t];
+        lacc[(t & 1) * kMaxP + 2 * J + (t < 2 ? 1 : 0)] = t < 2 ? s : -s;
+    }
+    for (int j = w; j < J; j += kWaves) {
+        const double R = L.R[j], Lim = L.Lim[j];
+        const int n = __builtin_amdgcn_readlane(cnt, j);
+        long long in_m = 0, in_v = 0, over_m = 0, over_v = 0;
+        for (int f = 0; f < n; f += 64) {
+            const int e = ev;
+            const double tj = v - R;
+            if (f + 64 < n) fetch(j, f + 64);
+            else if (j + kWaves < J) fetch(j + kWaves, 0);
+            if (e < 0) continue;
             if (tj > 0.0 && tj < Lim) {
-                add_i64(&lacc[j], -wm);
-                if (wv) add_i64(&lacc[kMaxP + j], -wv);
+                in_m += wms[e];
+                in_v += wvs[e];
             }
             if (tj > Lim) {
-                add_i64(&lacc[J + j], wm);
-                if (wv) add_i64(&lacc[kMaxP + J + j], wv);
+                over_m += wms[e];
+                over_v += wvs[e];
             }
+        }
+        if (n == 0 && j + kWaves < J) fetch(j + kWaves, 0);
+        in_m = wave_sum_i64(in_m);
+        over_m = wave_sum_i64(over_m);
+        in_v = wave_sum_i64(in_v);
+        over_v = wave_sum_i64(over_v);
+        if (lane == 0) {
+            lacc[j] = -in_m;
+            lacc[kMaxP + j] = -in_v;
+            lacc[J + j] = over_m;
+            lacc[kMaxP + J + j] = over_v;
         }
     }
     __syncthreads();
-    for (int i = t; i < 2 * kMaxP; i += nt) {
-        const int q = i % kMaxP;
-        if (q < P - 2 && lacc[i] != 0) add_i64(&acc[i], lacc[i]);
-    }
+    for (int i = t; i < 2 * kMaxP; i += kSparseThreads)
+        if (lacc[i] != 0) add_i64(&acc[blockIdx.x % kAccCopies * (2 * kMaxP) + i], lacc[i]);
 }
 
 __global__ __launch_bounds__(256) void mark_kernel(const double* __restrict__ elts, int64_t C, LayerArgs L,
@@ -219,7 +182,7 @@ __global__ __launch_bounds__(256) void mark_kernel(const double* __restrict__ el
 }
 
 __global__ void clear_acc_kernel(long long* acc) {
-    for (int i = threadIdx.x; i < 2 * kMaxP; i += blockDim.x) acc[i] = 0;
+    for (int i = threadIdx.x; i < kAccCopies * 2 * kMaxP; i += blockDim.x) acc[i] = 0;
 }
 
 // one wavefront per trial; only trials inside the aggregate band read events
@@ -387,8 +350,14 @@ __global__ void finalize_kernel(const long long* acc, const TailStats* tail, int
     const int i = threadIdx.x;
     if (i >= P) return;
     const TailStats ts = *tail;
-    if (grad_mean) grad_mean[i] = static_cast<double>(acc[i]) / static_cast<double>(n);
-    if (grad_tvar) grad_tvar[i] = static_cast<double>(acc[kMaxP + i]) / static_cast<double>(ts.m * ts.c_eq);
+    long long mean = 0, tvar = 0;
+#pragma unroll
+    for (int c = 0; c < kAccCopies; ++c) {
+        mean += acc[c * 2 * kMaxP + i];
+        tvar += acc[c * 2 * kMaxP + kMaxP + i];
+    }
+    if (grad_mean) grad_mean[i] = static_cast<double>(mean) / static_cast<double>(n);
+    if (grad_tvar) grad_tvar[i] = static_cast<double>(tvar) / static_cast<double>(ts.m * ts.c_eq);
 }
 
 AdjScratch carve(void* base, int64_t C, int64_t n) {
@@ -400,7 +369,7 @@ AdjScratch carve(void* base, int64_t C, int64_t n) {
     s.w_tvar = reinterpret_cast<uint64_t*>(p);
     p += Ca * sizeof(uint64_t);
     s.acc = reinterpret_cast<long long*>(p);
-    p += 2 * kMaxP * sizeof(long long);
+    p += kAccCopies * 2 * kMaxP * sizeof(long long);
     s.tail = reinterpret_cast<TailStats*>(p);
     p += 256;
     s.mark = reinterpret_cast<uint8_t*>(p);
@@ -417,8 +386,14 @@ AdjScratch carve(void* base, int64_t C, int64_t n) {
 int64_t adjoint_scratch_bytes(int64_t C, int J, int64_t n) {
     (void)J;
     const int64_t Ca = (C + 255) & ~int64_t(255);
-    return Ca * (2 * sizeof(uint64_t) + 1) + 2 * kMaxP * sizeof(long long) + 256 +
+    return Ca * (2 * sizeof(uint64_t) + 1) + kAccCopies * 2 * kMaxP * sizeof(long long) + 256 +
            ((stream_adjoint_scratch_bytes(n) + 255) & ~int64_t(255)) + tail_stats_scratch_bytes(n);
+}
+
+hipError_t launch_adjoint_fold(const SparsePool& sp, int64_t C, const LayerArgs& L, int P, void* part_scratch,
+                               void* scratch, hipStream_t s) {
+    const AdjScratch a = carve(scratch, C, L.trial_count);
+    return launch_fold_back(sp, C, L, P, part_scratch, FoldBack{a.mark, a.w_mean, a.w_tvar, a.acc, kAccCopies * 2 * kMaxP}, s);
 }
 
 hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const double* elts, int64_t C,
@@ -429,29 +404,32 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
     AdjScratch a = carve(scratch, C, L.trial_count);
     hipError_t err;
     const int64_t n = L.trial_count;
+    const int P = 2 * L.J + 4;
+    const bool use_parts = parts && parts->P > 0 && part_scratch;
     if ((err = launch_tail_stats(ylt, n, m, a.tail_scratch, a.tail, s)) != hipSuccess) return err;
-    hipLaunchKernelGGL(clear_acc_kernel, dim3(1), dim3(256), 0, s, a.acc);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    const uint32_t cblocks = static_cast<uint32_t>((C + 255) / 256);
-    const int with_mark = (parts && parts->P > 0 && part_scratch) ? 0 : 1;
-    hipLaunchKernelGGL(mark_kernel, dim3(cblocks), dim3(256), 0, s, elts, C, L, a.mark, a.w_mean, a.w_tvar,
-                       with_mark);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (parts && parts->P > 0 && part_scratch) {
+    if (!sp) {                                      // else launch_adjoint_fold cleared the sums
+        hipLaunchKernelGGL(clear_acc_kernel, dim3(1), dim3(256), 0, s, a.acc);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        const uint32_t cblocks = static_cast<uint32_t>((C + 255) / 256);
+        hipLaunchKernelGGL(mark_kernel, dim3(cblocks), dim3(256), 0, s, elts, C, L, a.mark, a.w_mean, a.w_tvar,
+                           use_parts ? 0 : 1);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
+    if (use_parts && stream && stream->P > 0 && (stream->P - 1) / 4 < parts->P) {
+        if ((err = launch_stream_adjoint(*stream, density, L, part_scratch, parts->P, S, ylt, a.tail, a.cls,
+                                         a.cls_bytes, a.w_mean, a.w_tvar, a.acc + P - 2, a.acc + kMaxP + P - 2,
+                                         kAccCopies, 2 * kMaxP, n_cu, s)) != hipSuccess)
+            return err;
+    } else if (use_parts) {
         int64_t ab = (n + 255) / 256;
         if (ab > int64_t(n_cu)) ab = int64_t(n_cu);
         if (ab < 1) ab = 1;
         hipLaunchKernelGGL(agg_counts_kernel, dim3(static_cast<uint32_t>(ab)), dim3(256), 0, s, L, S, ylt, a.tail,
                            a.acc);
         if ((err = hipGetLastError()) != hipSuccess) return err;
-        if (stream && stream->P > 0 && (stream->P - 1) / 4 < parts->P) {
-            if ((err = launch_stream_adjoint(*stream, density, L, part_scratch, parts->P, S, ylt, a.tail, a.cls,
-                                             a.cls_bytes, a.w_mean, a.w_tvar, n_cu, s)) != hipSuccess)
-                return err;
-        } else if ((err = launch_part_adjoint(*parts, n_trials_total, L, part_scratch, S, ylt, a.tail, a.w_mean,
-                                              a.w_tvar, n_cu, s)) != hipSuccess) {
+        if ((err = launch_part_adjoint(*parts, n_trials_total, L, part_scratch, S, ylt, a.tail, a.w_mean, a.w_tvar,
+                                       n_cu, s)) != hipSuccess)
             return err;
-        }
     } else {
         int64_t tblocks = (n + 3) / 4;
         if (tblocks > int64_t(n_cu) * 8) tblocks = int64_t(n_cu) * 8;
@@ -460,9 +438,9 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                            ids, L, S, ylt, a.tail, a.mark, a.w_mean, a.w_tvar, a.acc);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    if (sp && sp->chunk_off && sp->n_chunks == (C + kSparseChunk - 1) / kSparseChunk) {
-        hipLaunchKernelGGL(catalogue_sparse_kernel, dim3(static_cast<uint32_t>(sp->n_chunks)), dim3(1024), 0, s, *sp,
-                           C, L, a.w_mean, a.w_tvar, a.acc);
+    if (sp) {
+        hipLaunchKernelGGL(catalogue_sparse_kernel, dim3(static_cast<uint32_t>(sp->n_chunks)), dim3(kSparseThreads), 0,
+                           s, *sp, C, L, a.mark, a.w_mean, a.w_tvar, a.acc);
     } else {
         int64_t gblocks = (C + 255) / 256;
         if (gblocks > int64_t(n_cu) * 4) gblocks = int64_t(n_cu) * 4;
@@ -470,8 +448,7 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                            a.w_mean, a.w_tvar, a.acc);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(256), 0, s, a.acc, a.tail, 2 * L.J + 4, n, d_grad_mean,
-                       d_grad_tvar);
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(256), 0, s, a.acc, a.tail, P, n, d_grad_mean, d_grad_tvar);
     return hipGetLastError();
 }
 

@@ -469,6 +469,7 @@ struct FoldOut {
     uint64_t* probe;
     uint32_t* coarse;
     int cshift;
+    FoldBack back;                  // kBack
 };
 
 // OR of each pair of adjacent bits, packed into the low half
@@ -480,6 +481,7 @@ __device__ __forceinline__ uint32_t or_pairs(uint32_t x) {
     return (x | (x >> 8)) & 0x0000FFFFu;
 }
 
+template <bool kBack>
 __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C, const LayerArgs& L,
                                                 const FoldOut& out) {
     double* __restrict__ o = out.o;
@@ -565,8 +567,15 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
 #pragma unroll
     for (int k = 0; k < kWordsOwn; ++k) {
         const int64_t E = eb + k * 64;
-        const double v = apply_terms(ys[w * kOwn + k * 64 + lane], L.occR, L.occL);
+        const double y = ys[w * kOwn + k * 64 + lane];
+        const double v = apply_terms(y, L.occR, L.occL);
         if (o && E < C) o[E] = v;
+        if (kBack && E < C) {
+            const double to = y - L.occR;
+            out.back.band[E] = to > L.occL ? 2 : (to > 0.0 && to < L.occL ? 1 : 0);
+            out.back.w_mean[E] = 0;
+            out.back.w_tvar[E] = 0;
+        }
         vk[k] = v;
         bk[k] = __ballot(E < C && v != 0.0);
         if (lane == 0) wb[w * kWordsOwn + k] = bk[k];
@@ -581,6 +590,7 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
     }
     const int total = __builtin_amdgcn_readlane(before, 63);
     before -= __popcll(word);
+    if (kBack && !img) return;                      // no passes over the images
     if (w == 0) {
         bm[ls * 64 + lane] = word;
         if ((lane & 1) == 0) r16[ls * 32 + (lane >> 1)] = static_cast<uint16_t>(before);
@@ -624,7 +634,12 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
 // terms as kernel arguments (eager runs) or read from device memory (graph
 // replays, whose terms may change between replays)
 __global__ __launch_bounds__(kFoldThreads) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
-    fold_image_body(sp, C, L, out);
+    fold_image_body<false>(sp, C, L, out);
+}
+__global__ __launch_bounds__(kFoldThreads) void fold_back_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < out.back.n_acc; i += blockDim.x) out.back.acc[i] = 0;
+    fold_image_body<true>(sp, C, L, out);
 }
 // layer blockIdx.y of several
 __global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool sp, int64_t C,
@@ -633,7 +648,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool
     out.img += blockIdx.y * img_stride;
     out.sb_count += blockIdx.y * sb_stride;
     out.stage += blockIdx.y * sb_stride * kSuper;
-    fold_image_body(sp, C, L[blockIdx.y], out);
+    fold_image_body<false>(sp, C, L[blockIdx.y], out);
 }
 
 // Layer arguments packed into kernel arguments (which take 4 KB): per layer the
@@ -2510,7 +2525,7 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
                              int P, void* scratch, bool compact, uint64_t* probe, hipStream_t s) {
     PartScratch ps = carve_parts(scratch, P);
     const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
-    FoldOut out{o, ps.img, ps.sb_count, ps.stage, nullptr, nullptr, 0};
+    FoldOut out{o, ps.img, ps.sb_count, ps.stage, nullptr, nullptr, 0, {}};
     if (probe) {
         const ProbeTables t = probe_tables(probe, C);
         out.probe = t.probe;
@@ -2529,10 +2544,24 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
     return hipGetLastError();
 }
 
+hipError_t launch_fold_back(const SparsePool& sp, int64_t C, const LayerArgs& L, int P, void* scratch,
+                            const FoldBack& back, hipStream_t s) {
+    FoldOut out{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, back};
+    if (scratch) {
+        const PartScratch ps = carve_parts(scratch, P);
+        out.img = ps.img;
+        out.sb_count = ps.sb_count;
+        out.stage = ps.stage;
+    }
+    hipLaunchKernelGGL(fold_back_kernel, dim3(static_cast<uint32_t>(P) * kBase32), dim3(kFoldThreads), 0, s, sp, C, L,
+                       out);
+    return hipGetLastError();
+}
+
 hipError_t launch_fold_batch(const SparsePool& sp, int64_t C, const LayerArgs* L_dev, int n_layers, int P, void* scratch,
                              hipStream_t s) {
     const FoldViews v = fold_batch_views(scratch, n_layers, P);
-    const FoldOut out{nullptr, v.img, v.sb_count, v.stage, nullptr, nullptr, 0};
+    const FoldOut out{nullptr, v.img, v.sb_count, v.stage, nullptr, nullptr, 0, {}};
     hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(v.sb_stride), static_cast<uint32_t>(n_layers)),
                        dim3(kFoldThreads), 0, s, sp, C, L_dev, out, v.img_stride, v.sb_stride);
     return hipGetLastError();

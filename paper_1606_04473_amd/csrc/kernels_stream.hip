@@ -1018,27 +1018,65 @@ __global__ __launch_bounds__(1024) void stream_pass_kernel(StreamPassArgs a, Seg
     }
 }
 
-// the trial classes of StreamAdjArgs, one byte per (group, lane) slot
+// The trial classes of StreamAdjArgs, one byte per (group, lane) slot, and the
+// partials of the aggregate terms: the trials inside the aggregate band (-1 each
+// for the retention) and above it (+1 for the limit), counted for the mean and
+// with their TVaR weights.  Four slots per thread in flight; one set of device
+// atomics per workgroup.
 __global__ __launch_bounds__(256) void stream_class_kernel(const double* __restrict__ S, const double* __restrict__ ylt,
                                                            const TailStats* __restrict__ tail, double aggR, double aggL,
                                                            int64_t t_lo, int64_t t_hi, int G, int64_t g_lo,
-                                                           int64_t n_slots, uint8_t* __restrict__ cls) {
+                                                           int64_t n_slots, uint8_t* __restrict__ cls,
+                                                           long long* __restrict__ agg_mean,
+                                                           long long* __restrict__ agg_tvar, int copies, int stride_of) {
+    constexpr int kU = 4;
     const TailStats ts = *tail;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n_slots; i += stride) {
-        const int lane = static_cast<int>(i & 63);
-        const int64_t t = (g_lo + (i >> 6)) * G + lane;
-        uint32_t c = 0;
-        if (lane < G && t >= t_lo && t < t_hi) {
-            const int64_t k = t - t_lo;
-            const double ta = S[k] - aggR;
-            if ((ta > 0.0) && (ta < aggL)) {
-                // year losses are >= 0, so their bit patterns order like their values
-                const uint64_t key = __double_as_longlong(ylt[k] + 0.0);
-                c = 1u | (key > ts.v_bits ? 2u : (key == ts.v_bits ? 4u : 0u));
-            }
+    long long sums[4] = {0, 0, 0, 0};               // mean: retention, limit; TVaR: the same
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i0 < n_slots; i0 += kU * stride) {
+        double sv[kU], yv[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + u * stride;
+            const int lane = static_cast<int>(i & 63);
+            const int64_t t = (g_lo + (i >> 6)) * G + lane;
+            const bool in = i < n_slots && lane < G && t >= t_lo && t < t_hi;
+            sv[u] = in ? S[t - t_lo] : aggR;        // no trial: neither inside nor above
+            yv[u] = in ? ylt[t - t_lo] : 0.0;
         }
-        cls[i] = static_cast<uint8_t>(c);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + u * stride;
+            const double ta = sv[u] - aggR;
+            // year losses are >= 0, so their bit patterns order like their values
+            const uint64_t key = __double_as_longlong(yv[u] + 0.0);
+            const uint32_t tail_bits = key > ts.v_bits ? 2u : (key == ts.v_bits ? 4u : 0u);
+            const long long wt = (tail_bits & 2u) ? ts.c_eq : ((tail_bits & 4u) ? ts.m - ts.c_gt : 0);
+            const bool in_band = (ta > 0.0) && (ta < aggL);
+            if (in_band) {
+                sums[0] -= 1;
+                sums[2] -= wt;
+            }
+            if (ta > aggL) {
+                sums[1] += 1;
+                sums[3] += wt;
+            }
+            if (i < n_slots) cls[i] = static_cast<uint8_t>(in_band ? 1u | tail_bits : 0u);
+        }
+    }
+    __shared__ long long red[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        for (int off = 32; off >= 1; off >>= 1) sums[q] += __shfl_xor(sums[q], off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = sums[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        long long v = 0;
+        for (int w = 0; w < 4; ++w) v += red[w][threadIdx.x];
+        long long* to = (threadIdx.x < 2 ? agg_mean : agg_tvar) + (threadIdx.x & 1) +
+                        static_cast<int64_t>(blockIdx.x % copies) * stride_of;
+        if (v) atomicAdd(reinterpret_cast<unsigned long long*>(to), static_cast<unsigned long long>(v));
     }
 }
 
@@ -1046,7 +1084,8 @@ __global__ __launch_bounds__(256) void stream_combine_kernel(const double* __res
                                                              const float* __restrict__ part_lo, int P, int64_t count,
                                                              double aggR, double aggL,
                                                              const LayerArgs* __restrict__ L_dev,
-                                                             double* __restrict__ ylt, double* __restrict__ S_out) {
+                                                             double* __restrict__ ylt, double* __restrict__ ylt_too,
+                                                             double* __restrict__ S_out) {
     const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (k >= count) return;
     if (L_dev) {                                    // terms from device memory (graph replays)
@@ -1057,7 +1096,9 @@ __global__ __launch_bounds__(256) void stream_combine_kernel(const double* __res
     for (int p = 0; p < P; ++p)
         dd_merge(hi, lo, part_hi[p * count + k], static_cast<double>(part_lo[p * count + k]));
     const double S = hi + lo;
-    ylt[k] = apply_terms(S, aggR, aggL);
+    const double y = apply_terms(S, aggR, aggL);
+    ylt[k] = y;
+    if (ylt_too) ylt_too[k] = y;
     if (S_out) S_out[k] = S;
 }
 
@@ -1367,7 +1408,8 @@ int64_t stream_adjoint_scratch_bytes(int64_t trials) {
 
 hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
                                  int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
-                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
+                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar,
+                                 long long* agg_mean, long long* agg_tvar, int copies, int stride, int n_cu,
                                  hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
@@ -1380,10 +1422,11 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const 
     adj.w_mean = w_mean;
     adj.w_tvar = w_tvar;
     adj.tail = tail;
-    int64_t cb = (n_slots + 255) / 256;
-    if (cb > int64_t(n_cu) * 8) cb = int64_t(n_cu) * 8;
+    // the workgroups of a copy add to the same four sums
+    const int64_t cb = std::min((n_slots + 255) / 256, int64_t(n_cu));
     hipLaunchKernelGGL(stream_class_kernel, dim3(static_cast<uint32_t>(cb)), dim3(256), 0, s, S, ylt, tail, L.aggR,
-                       L.aggL, t_lo, t_hi, a.G, g_lo, n_slots, static_cast<uint8_t*>(scratch));
+                       L.aggL, t_lo, t_hi, a.G, g_lo, n_slots, static_cast<uint8_t*>(scratch), agg_mean, agg_tvar,
+                       copies, stride);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const StreamUnit u{0, L.trial_begin, L.trial_count, 0, density};
@@ -1391,13 +1434,13 @@ hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const 
 }
 
 hipError_t launch_stream_combine(const StreamLayout& lay, const LayerArgs& L, const LayerArgs* L_dev,
-                                 const void* partials, double* ylt, double* S, hipStream_t s) {
+                                 const void* partials, double* ylt, double* ylt_too, double* S, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     const double* hi = static_cast<const double*>(partials);
     const float* lo = stream_partials_lo(lay, partials, L.trial_count);
     const int64_t blocks = (L.trial_count + 255) / 256;
     hipLaunchKernelGGL(stream_combine_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, hi, lo, lay.P,
-                       L.trial_count, L.aggR, L.aggL, L_dev, ylt, S);
+                       L.trial_count, L.aggR, L.aggL, L_dev, ylt, ylt_too, S);
     return hipGetLastError();
 }
 
