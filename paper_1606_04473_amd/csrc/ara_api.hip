@@ -239,7 +239,6 @@ hipError_t scratch_acquire(std::mutex& mu, std::vector<ara::ScratchBuffer*>& set
         if (pick->p) ara::dev_free(pick->p, pick->stream);
         pick->p = nullptr;
         pick->cap = 0;
-        pick->primed = false;
         if (e == hipSuccess) e = ara::dev_alloc(&pick->p, bytes, s);
         if (e == hipSuccess) pick->cap = bytes;
     }
@@ -1653,7 +1652,7 @@ ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* p
     // through the results buffer [mean, PML_0, TVaR_0, PML_1, ...]
     const ara::MetricsOut out = dev ? ara::MetricsOut{mean_out, pml_out, tvar_out, 1}
                                     : ara::MetricsOut{r, r + 1, r + 2, 2};
-    HIP_TRY(ara::launch_metrics(x, n_trials, m.data(), n_probs, scratch.b->p, &scratch.b->primed, out, s),
+    HIP_TRY(ara::launch_metrics(x, n_trials, m.data(), n_probs, scratch.b->p, out, s),
             "metrics kernels");
     if (dev) return ARA_OK;
     std::vector<double> h(1 + 2 * n_probs);
@@ -1704,9 +1703,8 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
                                 flags & ARA_DEVICE_PTR, stream);
     }
     // one graph: fold, pass, combine and the metrics kernels, on scratch the
-    // graph owns (the metrics part primed once; each replay leaves it ready
-    // for the next).  Terms and ELT choices are read from device memory, so
-    // new terms reuse the graph.
+    // graph owns.  Terms and ELT choices are read from device memory, so new
+    // terms reuse the graph.
     DeviceScope ds(t->device);
     if (!ds.ok) return fail(ARA_ERR_DEVICE, "cannot select the tables' device");
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1742,7 +1740,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
         void* gp = gb + la_bytes + o_bytes;
         void* gx = gb + la_bytes + o_bytes + p_bytes;
         void* gm = gb + la_bytes + o_bytes + p_bytes + xg_bytes;
-        if ((e = upload(ge)) != hipSuccess || (e = ara::launch_metrics_prime(gm, s)) != hipSuccess ||
+        if ((e = upload(ge)) != hipSuccess ||
             (e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
             free_graph(ge);
             return hip_fail(e, "graph capture");
@@ -1755,9 +1753,8 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
                                              ara::stream_partials_lo(t->stream, gx, L.trial_count), t->stream.P,
                                              L.trial_count, dL, ylt, m.data(), n_probs, gm, mo, s);
         } else {
-            bool primed = true;
             if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, nullptr, s);
-            if (le == hipSuccess) le = ara::launch_metrics(ylt, L.trial_count, m.data(), n_probs, gm, &primed, mo, s);
+            if (le == hipSuccess) le = ara::launch_metrics(ylt, L.trial_count, m.data(), n_probs, gm, mo, s);
         }
         e = hipStreamEndCapture(s, &ge->graph);
         if (le != hipSuccess || e != hipSuccess ||
@@ -1800,10 +1797,7 @@ ara_status ara_risk_metrics_noalloc(const double* ylt, int64_t n_trials, const d
                     "(n_probs * n_trials <= %lld); use ara_risk_metrics",
                     (long long)n_trials, n_probs, (long long)need, (long long)capacity,
                     (long long)ARA_METRICS_NOALLOC_KEYS);
-    // not primed: the counters that earlier calls on this device left in the
-    // shared array are cleared first
-    bool primed = false;
-    HIP_TRY(ara::launch_metrics(ylt, n_trials, m, n_probs, scratch, &primed,
+    HIP_TRY(ara::launch_metrics(ylt, n_trials, m, n_probs, scratch,
                                 ara::MetricsOut{mean_out, pml_out, tvar_out, 1}, static_cast<hipStream_t>(stream)),
             "metrics kernels");
     return ARA_OK;

@@ -426,7 +426,6 @@ struct ScratchBuffer {
     hipEvent_t done = nullptr;      // recorded on `stream` after the last use
     hipStream_t stream = nullptr;
     bool busy = false;
-    bool primed = false;            // metrics: left ready by a whole launch sequence (cleared on growth)
 };
 
 // A captured batched run: persistent scratch, a graph, and the shape it was
@@ -588,13 +587,10 @@ struct MetricsOut {
 };
 // scratch of launch_metrics for n_probs probabilities over n year losses
 int64_t metrics_scratch_bytes(int n_probs, int64_t n);
-// `primed`: the scratch is ready, by launch_metrics_prime or because the last
-// sequence that used it was enqueued whole; kept up to date by the call
-hipError_t launch_metrics_prime(void* scratch, hipStream_t s);
 hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs,
-                          void* scratch, bool* primed, MetricsOut out, hipStream_t s);
+                          void* scratch, MetricsOut out, hipStream_t s);
 
-// the same on a primed scratch, with the merge of the streaming pass's partial
+// the same with the merge of the streaming pass's partial
 // sums into `ylt` as its first launch (terms from L_dev); for YLTs of more values
 // than one workgroup takes (combine_metrics_apply)
 hipError_t launch_combine_metrics(const double* part_hi, const float* part_lo, int P, int64_t n, const LayerArgs* L_dev,

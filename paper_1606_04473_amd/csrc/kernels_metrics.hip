@@ -421,13 +421,9 @@ __device__ __forceinline__ void write_bad(int n_probs, const MetricsOut& out, Ta
     }
 }
 
-// a new scratch: nothing collected
-__global__ void select_init_kernel(Scratch s) {
-    if (threadIdx.x < kMaxProbs) s.ccount[threadIdx.x] = 0;
-}
-
 // A workgroup's part of the first launch: its sum and largest key, and its share
-// of the histogram cleared for the second.
+// of the histogram and the counts cleared for the next ones, so the scratch may
+// hold anything before a call (a launch of its own for the counts took 4.5 us).
 __device__ __forceinline__ void store_partials(ReduceLds& sh, const Scratch& s, double hi, double lo, uint64_t mx) {
     double h[1] = {hi}, l[1] = {lo};
     block_sums(sh, h, l, 1);
@@ -438,6 +434,7 @@ __device__ __forceinline__ void store_partials(ReduceLds& sh, const Scratch& s, 
         s.part_max[blockIdx.x] = mx;
     }
     for (int i = blockIdx.x * kThreads + threadIdx.x; i < kBins; i += gridDim.x * kThreads) s.hist[i] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kMaxProbs) s.ccount[threadIdx.x] = 0;
 }
 
 // launch 1 where the year losses are formed: the merge of the streaming pass's
@@ -618,7 +615,6 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(int64_t n, Scratch s, 
     double l[1] = {in ? s.part_lo[row * kSumBlocks + threadIdx.x] : 0.0};
     const Pick p = mean ? Pick{0, 0, 1, 0} : s.pick[q];
     const bool bad = top_key(sh.red, s, n_part) == kBadKey;
-    if (!mean && threadIdx.x == 0) s.ccount[q] = 0;        // ready for the next call
     if (bad) {
         if (q == 0) write_bad(n_probs, out, tail, ma);
         return;
@@ -726,8 +722,8 @@ hipError_t launch_selection(const double* ylt, int64_t n, const MArgs& ma, int n
     return hipGetLastError();
 }
 
-hipError_t launch_all(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch, bool* primed,
-                      MetricsOut out, TailStats* tail, hipStream_t st) {
+hipError_t launch_all(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch, MetricsOut out,
+                      TailStats* tail, hipStream_t st) {
     if (n_probs > kMaxProbs || n < 1) return hipErrorInvalidValue;
     const Scratch s = carve(scratch);
     MArgs ma{};
@@ -743,16 +739,10 @@ hipError_t launch_all(const double* ylt, int64_t n, const int64_t* m_host, int n
         return hipGetLastError();
     }
     hipError_t err;
-    if (!*primed) {
-        if ((err = launch_metrics_prime(scratch, st)) != hipSuccess) return err;
-    }
-    *primed = false;
     const int b = sum_blocks(n);
     hipLaunchKernelGGL(sum_max_kernel, dim3(b), dim3(kThreads), 0, st, ylt, n, s);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    if ((err = launch_selection(ylt, n, ma, n_probs, s, b, out, tail, st)) != hipSuccess) return err;
-    *primed = true;
-    return hipSuccess;
+    return launch_selection(ylt, n, ma, n_probs, s, b, out, tail, st);
 }
 
 }  // namespace
@@ -762,14 +752,9 @@ int64_t metrics_scratch_bytes(int n_probs, int64_t n) {
     return base + static_cast<int64_t>(n_probs) * n * static_cast<int64_t>(sizeof(uint64_t));
 }
 
-hipError_t launch_metrics_prime(void* scratch, hipStream_t st) {
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(64), 0, st, carve(scratch));
-    return hipGetLastError();
-}
-
-hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch, bool* primed,
+hipError_t launch_metrics(const double* ylt, int64_t n, const int64_t* m_host, int n_probs, void* scratch,
                           MetricsOut out, hipStream_t st) {
-    return launch_all(ylt, n, m_host, n_probs, scratch, primed, out, nullptr, st);
+    return launch_all(ylt, n, m_host, n_probs, scratch, out, nullptr, st);
 }
 
 hipError_t launch_combine_metrics(const double* part_hi, const float* part_lo, int P, int64_t n, const LayerArgs* L_dev,
@@ -795,8 +780,7 @@ int64_t tail_stats_scratch_bytes(int64_t n) { return metrics_scratch_bytes(1, n)
 // the m-th largest year loss with the counts above and at it: the metrics'
 // launches, whose last workgroup writes the statistics instead
 hipError_t launch_tail_stats(const double* ylt, int64_t n, int64_t m, void* scratch, TailStats* out, hipStream_t st) {
-    bool primed = false;
-    return launch_all(ylt, n, &m, 1, scratch, &primed, MetricsOut{}, out, st);
+    return launch_all(ylt, n, &m, 1, scratch, MetricsOut{}, out, st);
 }
 
 // The device address of `scratch` on the current device, looked up once per
