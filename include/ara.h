@@ -166,8 +166,10 @@ typedef struct ara_tuning {
     int32_t fold_events_per_thread; /* reserved (0) */
     int32_t schedule;               /* batched pass work order: 0 = decreasing cost, 1 = layer-major */
     int32_t pass_variant;           /* pass over the YET: 0 = the 16-bit part-major copy streamed
-                                       against per-part LDS byte maps and loss copies (falls back
-                                       to 2 when the tables hold no such copy), 1 = the 32-bit
+                                       against per-part LDS byte maps and loss copies, or the copy
+                                       of the pool's events against per-part loss tables,
+                                       whichever is estimated faster (falls back
+                                       to 2 when the tables hold no 16-bit copy), 1 = the 32-bit
                                        partitioned copy with LDS ranks + compact values, one
                                        persistent launch for several layers, 2 = the 32-bit
                                        partitioned copy, each XCD serving its own catalogue parts.
@@ -200,7 +202,14 @@ typedef struct ara_tuning {
  * part one stream of part-relative IDs holding, group of consecutive trials
  * after group, each trial's events of that part in time order (about 2 bytes
  * per event).  Both depend on the YET alone, so every layer run on the
- * tables uses them (ara_layout_info_get reports their sizes).
+ * tables uses them (ara_layout_info_get reports their sizes).  A third,
+ * again 16-bit, holds only the events with a loss in some table of the pool,
+ * by their number among those: layers need no others, so the default pass
+ * reads it where that is faster.  It is left out, as in tables that share
+ * another's pool (ara_create_yet), where there are no such events or more
+ * than its 64 parts hold (20479 each), where trials are so short that it
+ * would be padding, or where building it would take over a quarter of the
+ * device's free memory.
  *   out            receives the handle; freed by ara_destroy_tables.
  *
  * The arrays are caller-owned and only read during the call: the library
@@ -335,7 +344,7 @@ ara_status ara_risk_metrics_noalloc(const double* ylt, int64_t n_trials, const d
  * are host memory (2J + 4 doubles each), or device memory with
  * ARA_DEVICE_PTR.  Either may be NULL to skip it.  The per-event occurrence
  * counts come from one pass over the YET: with pass_variant 0 (the default)
- * over the 16-bit part-major copy, else over the 32-bit partitioned copy
+ * over a 16-bit part-major copy, else over the 32-bit partitioned copy
  * (the plain layout's own pass without either); all give the same integers.
  */
 ara_status ara_backward(ara_tables* tables, const ara_layer* layer, double tvar_p,
@@ -378,7 +387,9 @@ ara_status ara_footprint(const ara_tables* tables, const ara_layer* layers, int3
 /*
  * Device bytes, for admission control (upper bounds, computed on the host):
  * ara_yet_footprint     -- the peak that ara_create_tables (without its ELT
- *                          pool) or ara_create_yet holds for a YET of these
+ *                          pool, and the copy of that pool's events, which
+ *                          only takes memory that is free) or
+ *                          ara_create_yet holds for a YET of these
  *                          sizes with `flags` (ARA_PLAIN_LAYOUT: no
  *                          partitioned copies), its build temporaries included;
  * ara_metrics_footprint -- the scratch of one ara_risk_metrics call over

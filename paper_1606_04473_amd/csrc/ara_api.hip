@@ -154,6 +154,25 @@ void dev_free(void* p, hipStream_t s) {
     b.in_use = false;
 }
 
+void dev_drop(void* p, hipStream_t s) {
+    constexpr size_t kKept = size_t(1) << 30;
+    int device = 0;
+    if (!p || hipGetDevice(&device) != hipSuccess) return;
+    DeviceCache& c = device_cache(device);
+    {
+        std::lock_guard<std::mutex> g(c.mu);
+        auto it = c.blocks.find(p);
+        if (it == c.blocks.end()) return;
+        if (it->second.size > kKept) {
+            if (it->second.ready) (void)hipEventDestroy(it->second.ready);
+            c.blocks.erase(it);
+            (void)hipFree(p);
+            return;
+        }
+    }
+    dev_free(p, s);
+}
+
 }  // namespace ara
 
 namespace {
@@ -585,20 +604,70 @@ double layer_density(const ara_tables* t, const ara::LayerArgs& L) {
     return cells > 0.0 ? -std::expm1(-L.J * static_cast<double>(t->sparse.nnz) / cells) : 0.0;
 }
 
+// Whether the copy of the pool's events alone is the faster one to stream, for layers
+// over `trials` trials in all whose densities add up to `dense` (each times its
+// trials).  An estimate of both passes and merges in us, fitted to measured ones.
+// That copy costs by its rows (64 trials' slots, padded to the longest) and groups,
+// whatever the layer, and by the tables a workgroup takes from part to part; the full
+// one by its events, its (part, trial) pairs and its hits, and a start-up that its
+// waves share.  Passes, that copy against the full one: 200000 trials of 1000 events
+// over 64 tables, a layer of 1: 103 / 115 us where 47 % of the events are in the pool
+// (47 parts / 31), 124 / 107 where 73 % are (36 / 16); 16 tables of 16, 15 % of the
+// events, 10^6 trials: 155 / 590; whole calls: 554 trials of 38 events 44 / 52 us,
+// 20000 of 300 over a pool of 92 %, with the backward: 119 / 104.
+bool losses_faster(const ara_tables* t, double trials, double dense) {
+    if (t->losses.P <= 0 || trials <= 0.0) return t->losses.P > 0;
+    const double per_trial = static_cast<double>(t->n_events) / static_cast<double>(t->n_trials);
+    const double rows = static_cast<double>(t->losses.length) / 256.0 * (trials / static_cast<double>(t->n_trials));
+    const double groups = t->losses.P * std::ceil(trials / 64.0);
+    auto merge = [&](int parts) { return std::max(1.75e-6 * parts * trials, 0.31 * parts); };
+    const double here = (t->loss_index.P > 1 && groups > t->n_cu ? 4.0 : 0.0) + 0.104e-3 * rows + 0.078e-3 * groups +
+                        merge(t->losses.P);
+    const double full = 5.0 + 19.0 * std::min(1.0, trials / 2e5) + 0.3e-6 * per_trial * trials +
+                        2.7e-6 * t->stream.P * trials + 1.6e-6 * per_trial * dense + merge(t->stream.P);
+    return here <= full;
+}
+bool losses_faster(const ara_tables* t, const ara::LayerArgs* L, int64_t n) {
+    double trials = 0.0, dense = 0.0;
+    for (int64_t i = 0; i < n; ++i) {
+        const double k = static_cast<double>(std::max<int64_t>(L[i].trial_count, 0));
+        trials += k;
+        dense += k * layer_density(t, L[i]);
+    }
+    return losses_faster(t, trials, dense);
+}
+
 // The passes that write per-(part, trial) partial sums for a merge: the
-// streaming pass over the 16-bit part-major copy (default), or the XCD-affine
-// pass over the 32-bit partitioned copy (pass_variant 2, or tables without
-// the 16-bit copy).
+// streaming pass over a 16-bit part-major copy (default; the whole one, or the
+// pool's events alone), or the XCD-affine pass over the 32-bit partitioned copy
+// (pass_variant 2, or tables without the 16-bit copy).
 struct SplitPass {
     const ara_tables* t;
     bool stream;
-    SplitPass(const ara_tables* tt, const ara_tuning& tu) : t(tt), stream(tu.pass_variant == 0 && tt->stream.P > 0) {}
+    bool losses;                    // over the copy of the pool's events alone
+    SplitPass(const ara_tables* tt, const ara_tuning& tu, bool by_losses)
+        : t(tt), stream(tu.pass_variant == 0 && tt->stream.P > 0), losses(stream && tt->losses.P > 0 && by_losses) {}
+    const ara::StreamLayout& lay() const { return losses ? t->losses : t->stream; }
+    // the fold, its outputs in part_scratch (terms from L_dev where given)
+    hipError_t fold(const ara::LayerArgs& L, const ara::LayerArgs* L_dev, void* part_scratch, uint64_t* probe,
+                    hipStream_t s) const {
+        if (losses)
+            return ara::launch_fold_losses(t->sparse, t->loss_index, t->C, &L, L_dev, 1,
+                                           static_cast<double*>(part_scratch), s);
+        return ara::launch_fold_parts(t->sparse, t->C, L, L_dev, nullptr, t->parts.P, part_scratch, !stream, probe, s);
+    }
     size_t partial_bytes(int64_t trials) const {
         const int64_t n = trials > 0 ? trials : 1;
-        return stream ? static_cast<size_t>(ara::stream_partials_bytes(t->stream, n))
+        return stream ? static_cast<size_t>(ara::stream_partials_bytes(lay(), n))
                       : sizeof(double) * 2 * static_cast<size_t>(t->parts.P) * n;
     }
     hipError_t pass(const ara::LayerArgs& L, void* part_scratch, void* partials, hipStream_t s) const {
+        if (losses) {
+            if (L.trial_count <= 0) return hipSuccess;
+            const ara::StreamUnit u{0, L.trial_begin, L.trial_count, 0, 0.0};
+            return ara::launch_loss_pass_units(t->losses, t->loss_index, &u, 1, static_cast<double*>(part_scratch),
+                                               partials, t->n_cu, s);
+        }
         if (stream)
             return ara::launch_stream_pass(t->stream, layer_density(t, L), L, part_scratch, t->parts.P, partials,
                                            t->n_cu, s);
@@ -608,7 +677,7 @@ struct SplitPass {
     // with S the checkpoint of the year losses is written too
     hipError_t combine(const ara::LayerArgs& L, const ara::LayerArgs* L_dev, const void* partials, double* ylt,
                        double* ylt_too, double* S, hipStream_t s) const {
-        if (stream) return ara::launch_stream_combine(t->stream, L, L_dev, partials, ylt, ylt_too, S, s);
+        if (stream) return ara::launch_stream_combine(lay(), L, L_dev, partials, ylt, ylt_too, S, s);
         const hipError_t e =
             ara::launch_xcd_combine(t->parts, L, L_dev, static_cast<const double*>(partials), ylt, S, s);
         if (e != hipSuccess || !ylt_too || L.trial_count <= 0) return e;
@@ -631,6 +700,7 @@ struct StreamBatches {
         int first_unit, n_units;
         int first_layer, n_layers;
     };
+    SplitPass split;
     std::vector<ara::StreamUnit> units;     // `layer` relative to its batch's first
     std::vector<Batch> batches;
     int64_t scratch_bytes = 0;              // fold outputs and partial sums of the largest batch
@@ -638,9 +708,13 @@ struct StreamBatches {
     static int64_t up(int64_t n) { return (n + 255) & ~int64_t(255); }
     // units in order of their layers; those of no trials are dropped, and
     // neighbours that continue one layer's range and output are joined
-    StreamBatches(const ara_tables* t, const std::vector<ara::StreamUnit>& in) {
+    int64_t fold_bytes(int n_layers) const {
+        return up(split.losses ? n_layers * ara::loss_table_bytes(split.t->loss_index)
+                               : ara::fold_batch_bytes(n_layers, split.t->parts.P));
+    }
+    StreamBatches(const SplitPass& sp, const std::vector<ara::StreamUnit>& in) : split(sp) {
         auto bytes_of = [&](int n_layers, int64_t trials) {
-            return up(ara::fold_batch_bytes(n_layers, t->parts.P)) + up(ara::stream_partials_bytes(t->stream, trials));
+            return fold_bytes(n_layers) + up(ara::stream_partials_bytes(split.lay(), trials));
         };
         int64_t most = kBatchBytes;
         for (const auto& u : in) most = std::max(most, bytes_of(1, u.count));
@@ -682,19 +756,25 @@ struct StreamBatches {
     ara_status run(ara_tables* t, const ara::LayerArgs* dL, void* scratch, double* ylt, bool prof, hipStream_t s) const {
         for (const Batch& b : batches) {
             const ara::StreamUnit* u = units.data() + b.first_unit;
-            void* partials = static_cast<char*>(scratch) + up(ara::fold_batch_bytes(b.n_layers, t->parts.P));
+            void* partials = static_cast<char*>(scratch) + fold_bytes(b.n_layers);
             KernelTimer kf(t, s, prof, ARA_KERNEL_FOLD);
-            HIP_TRY(ara::launch_fold_batch(t->sparse, t->C, dL + b.first_layer, b.n_layers, t->parts.P, scratch, s),
+            HIP_TRY(split.losses
+                        ? ara::launch_fold_losses(t->sparse, t->loss_index, t->C, nullptr, dL + b.first_layer,
+                                                  b.n_layers, static_cast<double*>(scratch), s)
+                        : ara::launch_fold_batch(t->sparse, t->C, dL + b.first_layer, b.n_layers, t->parts.P, scratch, s),
                     "folds and part images");
             kf.done();
             KernelTimer kp(t, s, prof, ARA_KERNEL_TRIAL_PASS);
-            HIP_TRY(ara::launch_stream_pass_units(t->stream, u, b.n_units,
-                                                  ara::fold_batch_views(scratch, b.n_layers, t->parts.P), t->parts.P,
-                                                  partials, t->n_cu, s),
+            HIP_TRY(split.losses
+                        ? ara::launch_loss_pass_units(t->losses, t->loss_index, u, b.n_units,
+                                                      static_cast<double*>(scratch), partials, t->n_cu, s)
+                        : ara::launch_stream_pass_units(t->stream, u, b.n_units,
+                                                        ara::fold_batch_views(scratch, b.n_layers, t->parts.P),
+                                                        t->parts.P, partials, t->n_cu, s),
                     "trial pass");
             kp.done();
             KernelTimer kc(t, s, prof, ARA_KERNEL_COMBINE);
-            HIP_TRY(ara::launch_stream_combine_units(t->stream, u, b.n_units, dL + b.first_layer, partials, ylt, s),
+            HIP_TRY(ara::launch_stream_combine_units(split.lay(), u, b.n_units, dL + b.first_layer, partials, ylt, s),
                     "partial sums merge");
             kc.done();
         }
@@ -905,6 +985,14 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));
         t->bytes += t->stream.bytes;
     }
+    // Also the copy of the pool's events alone, for tables that hold both, where the
+    // memory is there: the passes then read that where it is faster.
+    if (!base && t->stream.P > 0) {
+        e = ara::build_losses(t->sparse, n_elts, catalogue_size, t->offsets, t->ids, n_trials, n_events, t->n_cu, s,
+                              &t->loss_index, &t->losses);
+        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit copy of the events with a loss"));
+        t->bytes += t->losses.bytes + t->loss_index.bytes;
+    }
     // calls on other streams may follow at once
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return cleanup(hip_fail(e, "synchronize"));
     note_use(t, s);
@@ -936,6 +1024,8 @@ void ara_destroy_tables(ara_tables* t) {
     scratch_free_all(t->scratch, fs);
     ara::free_part_layout(&t->parts, fs);
     ara::free_stream_layout(&t->stream, fs);
+    ara::free_stream_layout(&t->losses, fs);
+    ara::free_loss_index(&t->loss_index, fs);
     if (t->elts && t->owns_elts) (void)hipFree(t->elts);
     if (t->owns_elts) ara::free_sparse_pool(&t->sparse);
     free_checkpoints(t->ck);
@@ -1054,13 +1144,17 @@ ara_status ara_footprint(const ara_tables* t, const ara_layer* layers, int32_t n
             std::lock_guard<std::mutex> g(const_cast<ara_tables*>(t)->mu);
             tu = t->tuning;
         }
-        const SplitPass split(t, tu);
-        int64_t need = ara::part_scratch_bytes(t->C, t->parts.P) + static_cast<int64_t>(split.partial_bytes(most));
-        if (split.stream && n_layers > 1 && !(flags & (ARA_CHECKPOINT_S | ARA_CHECKPOINT_STRIDE))) {
-            std::vector<ara::StreamUnit> units;
-            for (int i = 0; i < n_layers; ++i) units.push_back({i, 0, layers[i].trial_count, total, 0.0});
-            need = std::max(need, StreamBatches(t, units).scratch_bytes +
-                                      static_cast<int64_t>(sizeof(ara::LayerArgs)) * n_layers + 512);
+        int64_t need = 0;
+        for (const bool by_losses : {false, true}) {                   // whichever copy the call streams
+            const SplitPass split(t, tu, by_losses);
+            need = std::max(need, ara::part_scratch_bytes(t->C, t->parts.P) +
+                                      static_cast<int64_t>(split.partial_bytes(most)));
+            if (split.stream && n_layers > 1 && !(flags & (ARA_CHECKPOINT_S | ARA_CHECKPOINT_STRIDE))) {
+                std::vector<ara::StreamUnit> units;
+                for (int i = 0; i < n_layers; ++i) units.push_back({i, 0, layers[i].trial_count, total, 0.0});
+                need = std::max(need, StreamBatches(split, units).scratch_bytes +
+                                          static_cast<int64_t>(sizeof(ara::LayerArgs)) * n_layers + 512);
+            }
         }
         b += need;
     }
@@ -1153,7 +1247,8 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     // write per-part partial sums; pass_variant 1 selects the rank-based pass
     // with the compact value array
     const bool use_xcd = use_parts && tu.pass_variant != 1;
-    const SplitPass split(t, tu);
+    // (the stride checkpoints read the part images of the whole copy's fold)
+    const SplitPass split(t, tu, !(flags & ARA_CHECKPOINT_STRIDE) && losses_faster(t, L.data(), n_layers));
     const bool use_stream = use_xcd && split.stream;
     // several layers run as one persistent rank-based launch with pass_variant
     // 1; with the streaming (default) or XCD-affine pass they run one launch
@@ -1167,7 +1262,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     if (joined)
         for (int i = 0; i < n_layers; ++i)
             units.push_back({i, L[i].trial_begin, L[i].trial_count, L[i].out_offset, layer_density(t, L[i])});
-    const StreamBatches joint(t, units);
+    const StreamBatches joint(split, units);
     // one kept scratch buffer for the per-layer path: occurrence losses, part
     // images, partial sums (the batched path and graphs keep their own)
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
@@ -1275,7 +1370,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
             hipError_t le = hipSuccess;
             ara_status js = joined ? joint.run(t, dL, gb + la_bytes, out, false, s) : ARA_OK;
             for (int i = 0; i < n_layers && le == hipSuccess && !joined; ++i) {
-                le = ara::launch_fold_parts(t->sparse, t->C, L[i], dL + i, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
+                le = split.fold(L[i], dL + i, gp, nullptr, s);
                 if (le == hipSuccess) le = split.pass(L[i], gp, gx, s);
                 if (le == hipSuccess) le = split.combine(L[i], dL + i, gx, out + L[i].out_offset, nullptr, nullptr, s);
             }
@@ -1384,8 +1479,9 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
         if (!literal) {
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
-                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, nullptr, t->parts.P, pbuf.p, !use_stream,
-                                               static_cast<uint64_t*>(probe.p), s),
+                HIP_TRY(use_xcd ? split.fold(L[i], nullptr, pbuf.p, static_cast<uint64_t*>(probe.p), s)
+                                : ara::launch_fold_parts(t->sparse, t->C, L[i], nullptr, nullptr, t->parts.P, pbuf.p,
+                                                         true, static_cast<uint64_t*>(probe.p), s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[i], static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1481,7 +1577,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
     }
     const bool use_parts = !literal && t->parts.P > 0;
     const bool use_xcd = use_parts && tu.pass_variant != 1;
-    const SplitPass split(t, tu);
+    const SplitPass split(t, tu, losses_faster(t, L.data(), n_layers));
     // split i covers [b(i), b(i + 1)): Algorithm 1's YET_i
     auto split_at = [&](int64_t i) { return begin + (n * i) / n_splits; };
     int64_t most = 0;
@@ -1499,7 +1595,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
             for (int64_t i = 0; i < n_splits; ++i)
                 units.push_back({static_cast<int32_t>(l), split_at(i), split_at(i + 1) - split_at(i),
                                  l * n + (split_at(i) - begin), layer_density(t, L[l])});
-    const StreamBatches joint(t, units);
+    const StreamBatches joint(split, units);
     const size_t la_bytes = up(sizeof(ara::LayerArgs) * n_layers);
     const size_t x_bytes = use_xcd ? up(split.partial_bytes(most)) : 0;
     size_t w_bytes = joined ? la_bytes + up(joint.scratch_bytes) : o_bytes + p_bytes + x_bytes;
@@ -1541,8 +1637,9 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
         if (!literal) {
             KernelTimer kt(t, s, prof, ARA_KERNEL_FOLD);
             if (use_parts)
-                HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L[l], nullptr, nullptr, t->parts.P, p_buf,
-                                               !(use_xcd && split.stream), nullptr, s),
+                HIP_TRY(use_xcd ? split.fold(L[l], nullptr, p_buf, nullptr, s)
+                                : ara::launch_fold_parts(t->sparse, t->C, L[l], nullptr, nullptr, t->parts.P, p_buf,
+                                                         true, nullptr, s),
                         "fold and part images");
             else
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[l], o_buf, tu, s), "fold");
@@ -1709,7 +1806,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
     if (!ds.ok) return fail(ARA_ERR_DEVICE, "cannot select the tables' device");
     hipStream_t s = static_cast<hipStream_t>(stream);
     UseFence use_fence(t, s);           // the tables' memory outlives this call's work
-    const SplitPass split(t, tu);
+    const SplitPass split(t, tu, losses_faster(t, &L, 1));
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     const size_t la_bytes = up(sizeof(ara::LayerArgs));
     const size_t o_bytes = up(sizeof(double) * t->C);
@@ -1745,12 +1842,12 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
             free_graph(ge);
             return hip_fail(e, "graph capture");
         }
-        hipError_t le = ara::launch_fold_parts(t->sparse, t->C, L, dL, nullptr, t->parts.P, gp, !split.stream, nullptr, s);
+        hipError_t le = split.fold(L, dL, gp, nullptr, s);
         if (le == hipSuccess) le = split.pass(L, gp, gx, s);
         const ara::MetricsOut mo{metrics, metrics + 1, metrics + 1 + n_probs, 1};
         if (le == hipSuccess && split.stream && ara::combine_metrics_apply(L.trial_count)) {
             le = ara::launch_combine_metrics(static_cast<const double*>(gx),
-                                             ara::stream_partials_lo(t->stream, gx, L.trial_count), t->stream.P,
+                                             ara::stream_partials_lo(split.lay(), gx, L.trial_count), split.lay().P,
                                              L.trial_count, dL, ylt, m.data(), n_probs, gm, mo, s);
         } else {
             if (le == hipSuccess) le = split.combine(L, dL, gx, ylt, nullptr, nullptr, s);
@@ -1837,9 +1934,13 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
     // pass_variant 0: the histogram streams the 16-bit copy when the tables
     // hold one; else the XCD-affine pass over the 32-bit partitioned copy
     const bool use_stream = use_parts && t->tuning.pass_variant == 0 && t->stream.P > 0;
+    const bool use_losses = use_stream && t->sparse.chunk_off && losses_faster(t, &L, 1);
     if (use_parts) {
         const ara_tuning tu = t->tuning;   // t->mu is held
-        HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
+        if (use_losses)                 // that copy's histogram needs no images
+            HIP_TRY(pbuf.alloc(ara::loss_adjoint_bytes(t->loss_index, t->n_cu), s), "scratch for counts");
+        else
+            HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
         if (!t->sparse.chunk_off) {
             HIP_TRY(obuf.alloc(sizeof(double) * t->C, s), "scratch for occurrence losses");
             HIP_TRY(ara::launch_fold(t->elts, t->C, L, static_cast<double*>(obuf.p), tu, s), "fold");
@@ -1848,13 +1949,14 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
         }
     }
     if (t->sparse.chunk_off)
-        HIP_TRY(ara::launch_adjoint_fold(t->sparse, t->C, L, use_parts ? t->parts.P : ara::part_count(t->C), pbuf.p,
-                                         scratch.p, s),
+        HIP_TRY(ara::launch_adjoint_fold(t->sparse, t->C, L, use_parts ? t->parts.P : ara::part_count(t->C),
+                                         use_losses ? nullptr : pbuf.p, scratch.p, s),
                 "fold");
     HIP_TRY(ara::launch_adjoint(t->offsets, t->ids, t->elts, t->C, L, t->ck.S, t->ck.ylt, m, scratch.p, gm, gt,
-                                t->n_cu, s, use_parts ? &t->parts : nullptr, pbuf.p, t->n_trials,
-                                t->sparse.chunk_off ? &t->sparse : nullptr, use_stream ? &t->stream : nullptr,
-                                layer_density(t, L)),
+                                t->n_cu, s, use_parts ? &t->parts : nullptr, use_losses ? nullptr : pbuf.p, t->n_trials,
+                                t->sparse.chunk_off ? &t->sparse : nullptr,
+                                use_losses ? &t->losses : (use_stream ? &t->stream : nullptr), layer_density(t, L),
+                                use_losses ? &t->loss_index : nullptr, pbuf.p),
             "adjoint kernels");
     if (!dev) {
         std::vector<double> h(2 * P);

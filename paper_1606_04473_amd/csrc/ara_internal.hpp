@@ -22,6 +22,9 @@ constexpr int kWave = 64;
 // once s has reached the free.  Blocks are kept, not returned to the runtime.
 hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s);
 void dev_free(void* p, hipStream_t s);
+// dev_free for a temporary whose work has completed: a large one goes back to the
+// runtime (hipFree), so that it does not stay with the process
+void dev_drop(void* p, hipStream_t s);
 // bytes the cache of `device` holds, and of those not in use
 void cache_stats(int device, int64_t* held, int64_t* idle);
 // hipFree of the idle blocks of `device` whose last use has completed
@@ -283,18 +286,57 @@ hipError_t launch_stream_pass_units(const StreamLayout& lay, const StreamUnit* u
 hipError_t launch_stream_combine_units(const StreamLayout& lay, const StreamUnit* units, int n, const LayerArgs* L_dev,
                                        const void* partials, double* ylt, hipStream_t s);
 struct TailStats;
+// The events with a loss in some table of the pool, numbered in catalogue order
+// and cut into parts of whole superblocks (kernels_losses.hpp); event E with its
+// bit set in probe[E >> 5] has the slot (high half) + (set bits below it), as
+// part << 16 | slot.  The second 16-bit copy of the YET holds those slots.
+constexpr int kLossSlots = 20480;   // of a part (160 KB of LDS); the last one is never an event's
+struct LossIndex {
+    int P = 0;                      // parts; 0 = not used
+    int64_t n_events = 0;
+    int64_t bytes = 0;
+    uint64_t* probe = nullptr;      // [(C + 31) / 32]
+    uint32_t* events = nullptr;     // [P][kLossSlots] the slots' events
+    uint32_t* part_n = nullptr;     // [P] slots in use
+};
+struct SparsePool;
+void free_loss_index(LossIndex* ix, hipStream_t s);
+// the index and the copy, or neither where it is not used; their memory from dev_alloc
+hipError_t build_losses(const SparsePool& sp, int n_rows, int64_t C, const int64_t* offsets, const uint32_t* ids,
+                        int64_t N, int64_t n_events, int n_cu, hipStream_t s, LossIndex* ix, StreamLayout* out);
+// a layer's o(E) by slot: [P][kLossSlots]; n_layers of them from launch_fold_losses
+// (terms from L_dev, or of one layer from L)
+int64_t loss_table_bytes(const LossIndex& ix);
+hipError_t launch_fold_losses(const SparsePool& sp, const LossIndex& ix, int64_t C, const LayerArgs* L,
+                              const LayerArgs* L_dev, int n_layers, double* tab, hipStream_t s);
+// the streaming pass and the backward's histogram over that copy (units as in
+// launch_stream_pass_units, the classes' masks as launch_stream_classes leaves them)
+hipError_t launch_loss_pass_units(const StreamLayout& lay, const LossIndex& ix, const StreamUnit* units, int n,
+                                  const double* tab, void* partials, int n_cu, hipStream_t s);
+// (scratch: loss_adjoint_bytes(ix, n_cu), its first loss_tvar_words zeroed; w_mean and
+// w_tvar of the slots' events stored, not added)
+int64_t loss_tvar_words(const LossIndex& ix);
+int64_t loss_adjoint_bytes(const LossIndex& ix, int n_cu);
+hipError_t launch_loss_adjoint(const StreamLayout& lay, const LossIndex& ix, const LayerArgs& L, const uint64_t* masks,
+                               const TailStats* tail, void* scratch, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
+                               hipStream_t s);
+// the trial classes of a backward over a copy's groups, and the partials of the
+// two aggregate terms to agg_mean[0..1] and agg_tvar[0..1], of one of `copies`
+// copies `stride` apart (summed by the caller).  to_clear: words zeroed on the way;
+// with it (groups of 64 only) the classes are masks, four words a group: the trials
+// inside the band, and of those the ones in the tail above and at its threshold
+hipError_t launch_stream_classes(const StreamLayout& lay, const LayerArgs& L, const double* S, const double* ylt,
+                                 const TailStats* tail, void* scratch, int64_t scratch_bytes, long long* agg_mean,
+                                 long long* agg_tvar, int copies, int stride, uint64_t* to_clear, int64_t n_clear,
+                                 int n_cu, hipStream_t s);
 // the backward histogram over the same stream: for the trials inside the
 // aggregate band, occurrences of each nonzero-o(E) event added to w_mean and
-// TVaR weights to w_tvar (both [C], zeroed by the caller), and the partials of
-// the two aggregate terms to agg_mean[0..1] and agg_tvar[0..1], of one of `copies`
-// copies `stride` apart (summed by the caller); S and ylt are the
-// checkpointed forward's, tail its order statistics on the device.  scratch
-// holds stream_adjoint_scratch_bytes(L.trial_count) bytes.
+// TVaR weights to w_tvar (both [C], zeroed by the caller), from the trials'
+// classes; tail: the forward's order statistics on the device
 int64_t stream_adjoint_scratch_bytes(int64_t trials);
 hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
-                                 int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
-                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar,
-                                 long long* agg_mean, long long* agg_tvar, int copies, int stride, int n_cu, hipStream_t s);
+                                 int n_img_parts, const uint8_t* cls, const TailStats* tail, uint64_t* w_mean,
+                                 uint64_t* w_tvar, int n_cu, hipStream_t s);
 
 constexpr int kXcds = 8;           // gfx950 (MI355X): 8 XCDs, workgroups dispatched round-robin
 
@@ -460,6 +502,8 @@ struct ara_tables {
     ara::CheckpointState ck;
     ara::PartLayout parts;
     ara::StreamLayout stream;     // 16-bit part-major copy for the streaming pass
+    ara::LossIndex loss_index;    // the pool's events and the 16-bit copy of theirs alone,
+    ara::StreamLayout losses;     // both or neither
     std::mutex stage_mu;          // guards stage and graphs
     ara::HostStage stage;
     std::vector<ara::GraphEntry*> graphs;
@@ -535,6 +579,8 @@ hipError_t launch_debug_lookups(const int64_t* offsets, const uint32_t* ids, con
 hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* src, uint32_t* ids, int64_t n_events,
                             int64_t C, int shift, int bins, int32_t* cnt, CreateResult* res, int n_cu, hipStream_t s);
 int part_layout_parts(int64_t N, int64_t C);        // 0: not used
+// exclusive prefix sums of v[0..n) in place, the total to v[n]
+hipError_t launch_scan_i64(int64_t* v, int64_t n, hipStream_t s);
 hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
                             hipStream_t s, PartLayout* out);
 hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
@@ -618,7 +664,8 @@ hipError_t launch_part_adjoint(const PartLayout& lay, int64_t N, const LayerArgs
 
 // adjoint; with `parts` (and `part_scratch` holding the forward's part images)
 // the histogram pass runs over the partitioned layout, or over the 16-bit
-// stream when `stream` is given and holds one
+// stream when `stream` is given and holds one (with `losses` that of the events
+// with a loss)
 int64_t adjoint_scratch_bytes(int64_t C, int J, int64_t n);
 // with a sparse pool `sp` launch_adjoint_fold goes first: it clears the sums, finds
 // each event's place against the occurrence terms, and with `part_scratch` writes
@@ -629,6 +676,7 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                           int64_t C, const LayerArgs& L, const double* S, const double* ylt,
                           int64_t m, void* scratch, double* d_grad_mean, double* d_grad_tvar,
                           int n_cu, hipStream_t s, const PartLayout* parts, void* part_scratch,
-                          int64_t n_trials_total, const SparsePool* sp, const StreamLayout* stream, double density);
+                          int64_t n_trials_total, const SparsePool* sp, const StreamLayout* stream, double density,
+                          const LossIndex* losses, void* counts);
 
 }  // namespace ara

@@ -400,7 +400,8 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                           const LayerArgs& L, const double* S, const double* ylt, int64_t m, void* scratch,
                           double* d_grad_mean, double* d_grad_tvar, int n_cu, hipStream_t s,
                           const PartLayout* parts, void* part_scratch, int64_t n_trials_total,
-                          const SparsePool* sp, const StreamLayout* stream, double density) {
+                          const SparsePool* sp, const StreamLayout* stream, double density, const LossIndex* losses,
+                          void* counts) {
     AdjScratch a = carve(scratch, C, L.trial_count);
     hipError_t err;
     const int64_t n = L.trial_count;
@@ -415,11 +416,17 @@ hipError_t launch_adjoint(const int64_t* offsets, const uint32_t* ids, const dou
                            use_parts ? 0 : 1);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    if (use_parts && stream && stream->P > 0 && (stream->P - 1) / 4 < parts->P) {
-        if ((err = launch_stream_adjoint(*stream, density, L, part_scratch, parts->P, S, ylt, a.tail, a.cls,
-                                         a.cls_bytes, a.w_mean, a.w_tvar, a.acc + P - 2, a.acc + kMaxP + P - 2,
-                                         kAccCopies, 2 * kMaxP, n_cu, s)) != hipSuccess)
+    if (stream && stream->P > 0 && (losses || (use_parts && (stream->P - 1) / 4 < parts->P))) {
+        if ((err = launch_stream_classes(*stream, L, S, ylt, a.tail, a.cls, a.cls_bytes, a.acc + P - 2,
+                                         a.acc + kMaxP + P - 2, kAccCopies, 2 * kMaxP,
+                                         losses ? static_cast<uint64_t*>(counts) : nullptr,
+                                         losses ? loss_tvar_words(*losses) : 0, n_cu, s)) != hipSuccess)
             return err;
+        err = losses ? launch_loss_adjoint(*stream, *losses, L, static_cast<const uint64_t*>(a.cls), a.tail, counts,
+                                           a.w_mean, a.w_tvar, n_cu, s)
+                     : launch_stream_adjoint(*stream, density, L, part_scratch, parts->P,
+                                             static_cast<const uint8_t*>(a.cls), a.tail, a.w_mean, a.w_tvar, n_cu, s);
+        if (err != hipSuccess) return err;
     } else if (use_parts) {
         int64_t ab = (n + 255) / 256;
         if (ab > int64_t(n_cu)) ab = int64_t(n_cu);

@@ -1,0 +1,799 @@
+// Streaming pass over the events that can lose: a second 16-bit copy of the YET
+// that holds only the events with a loss in some table of the ELT pool.
+//
+// An event without a loss in any table of the pool adds zero to every layer, so
+// the passes over layers need not read it.  At table creation the pool's events
+// are numbered in catalogue order and cut into parts of at most kSlots - 1, whole
+// superblocks of 4096 catalogue events each; per request the fold writes o(E) to
+// the event's slot of a table per part, zero where the layer has no loss, and a
+// workgroup copies its part's table to LDS: an event costs one LDS read and a
+// double-double addition, no test, queue or rank.  Zeros leave a double-double sum
+// unchanged, so the sums are those of the full copy.
+//
+// A lane sums one trial: the copy holds the slots of 64 consecutive trials row by
+// row, four slots of each lane's trial, short trials padded with the slot that is
+// always zero.  A row is one 8-byte load per lane at consecutive addresses, nothing
+// goes through LDS, no lane asks where its trial ends, and the sums leave in
+// consecutive stores.  (Sorting windows of 1024 trials by their counts saves four
+// rows in ten, but then each lane's sum goes to a line of its own: 290 us where this
+// order took 190.)  Parts whose trials are long and few are cut into columns (splits
+// of each trial's events) to fill the chip.  Partial sums per (column, trial) merge as
+// those of the full copy do.
+//
+// Bound: the rows' bytes and, next to it, 28 fp64 additions and four LDS reads a row.
+// 10^6 trials of 1000 events, 16 tables of 20000 events in 2 * 10^6 (15 % of the
+// events, 1.17 * 10^6 rows, 600 MB): 155 us, 3.9 TB/s; the full copy's pass 590 us.
+// Compiled as a part of kernels_portfolio.hip.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+#include "ara_internal.hpp"
+
+namespace ara {
+
+namespace {
+
+constexpr int kSlots = kLossSlots;
+constexpr int kSuperEvents = 4096;
+constexpr uint32_t kPadSlot = kSlots - 1;       // always zero, never an event's
+constexpr int kRowIds = 4;                      // slots per lane and row
+constexpr int kTrials = 64;                     // trials of a group, one per lane
+
+// ---------------------------------------------------------------------------
+// the pool's events
+// ---------------------------------------------------------------------------
+
+// per superblock: the bits of its events with a loss in some table (low halves of
+// the probe words) and their number
+__global__ __launch_bounds__(256) void loss_bits_kernel(SparsePool sp, int n_rows, int64_t C,
+                                                        uint64_t* __restrict__ probe, uint32_t* __restrict__ count) {
+    __shared__ uint32_t bits[kSuperEvents / 32];
+    __shared__ uint32_t total;
+    const int64_t sb = blockIdx.x;
+    for (int i = threadIdx.x; i < kSuperEvents / 32; i += blockDim.x) bits[i] = 0;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    for (int r = threadIdx.x >> 6; r < n_rows; r += static_cast<int>(blockDim.x >> 6)) {
+        const int64_t key = static_cast<int64_t>(r) * sp.n_chunks + sb;
+        for (int64_t k = sp.chunk_off[key] + (threadIdx.x & 63); k < sp.chunk_off[key + 1]; k += 64)
+            atomicOr(&bits[sp.ev[k] >> 5], 1u << (sp.ev[k] & 31u));
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSuperEvents / 32; i += blockDim.x) {
+        const int64_t w = sb * (kSuperEvents / 32) + i;
+        if (w < (C + 31) / 32) probe[w] = bits[i];
+        if (bits[i]) atomicAdd(&total, static_cast<uint32_t>(__popc(bits[i])));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) count[sb] = total;
+}
+
+// what the host asks of the plan
+struct LossPlan {
+    int64_t events;                 // with a loss in some table
+    int64_t kept;                   // their occurrences in the YET
+    int32_t parts;                  // past `most_parts`: more than there may be
+    int32_t pad_;
+};
+
+// the superblocks' counts in place[] to the places of their first events, part << 16 |
+// slot: whole superblocks to a part, its last slot kept free (one wave)
+__global__ __launch_bounds__(64) void loss_plan_kernel(int64_t n_sb, int most_parts, uint32_t* __restrict__ place,
+                                                       uint32_t* __restrict__ part_n, LossPlan* __restrict__ plan) {
+    const int lane = threadIdx.x;
+    int part = 0;
+    uint32_t at = 0;
+    int64_t events = 0;
+    for (int64_t k0 = 0; k0 < n_sb; k0 += 64) {
+        const uint32_t own = k0 + lane < n_sb ? place[k0 + lane] : 0u;
+        uint32_t mine = 0;
+        for (int i = 0; i < 64; ++i) {
+            const uint32_t n = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(own), i));
+            if (at + n > kPadSlot) {
+                if (part < most_parts && lane == 0) part_n[part] = at;
+                if (part < most_parts) ++part;
+                at = 0;
+            }
+            if (i == lane) mine = static_cast<uint32_t>(part) << 16 | at;
+            at += n;
+            events += n;
+        }
+        if (k0 + lane < n_sb) place[k0 + lane] = mine;
+    }
+    if (lane == 0) {
+        if (part < most_parts) part_n[part] = at;
+        plan->events = events;
+        plan->parts = part + 1;
+    }
+}
+
+// per superblock (one wave): the slots of its events, the first one's at place[sb],
+// to the high halves of the probe words, and the events of the slots
+__global__ __launch_bounds__(64) void loss_place_kernel(int64_t C, int most_parts, const uint32_t* __restrict__ place,
+                                                        uint64_t* __restrict__ probe, uint32_t* __restrict__ events) {
+    const int64_t sb = blockIdx.x;
+    const int lane = threadIdx.x;
+    uint32_t at = place[sb];
+    if (static_cast<int>(at >> 16) >= most_parts) return;              // not used
+    for (int h = 0; h < kSuperEvents / 32 / 64; ++h) {
+        const int64_t w = sb * (kSuperEvents / 32) + h * 64 + lane;
+        const uint32_t bits = w < (C + 31) / 32 ? static_cast<uint32_t>(probe[w]) : 0u;
+        uint32_t inc = static_cast<uint32_t>(__popc(bits));
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        uint32_t first = at + inc - static_cast<uint32_t>(__popc(bits));
+        if (w < (C + 31) / 32) probe[w] = (static_cast<uint64_t>(first) << 32) | bits;
+        for (uint32_t b = bits; b; b &= b - 1, ++first)
+            events[static_cast<int64_t>(first >> 16) * kSlots + (first & 0xFFFFu)] =
+                static_cast<uint32_t>(w * 32 + __builtin_ctz(b));
+        at += static_cast<uint32_t>(__shfl(static_cast<int>(inc), 63, 64));
+    }
+}
+
+// Per trial (one wave): its events with a loss, counted (kFill false) or their
+// part << 16 | slot stored in order from start[t] on and counted per part
+// (cnt[t][part]).  A probe word is a gather from
+// L2, 64 lines an instruction: 5.2 ms per 1e9 events with a gather each.  So a
+// workgroup holds a map with a bit per 2^shift events in LDS and gathers the words of
+// the events whose bit is set (the other lanes share the first word's line): 1.5 ms
+// at 15 % of the events.  shift < 0: no map (a catalogue past kMapShift bits).
+constexpr int kMapWords = 39936;                // 156 KB
+constexpr int kMapShift = 2;
+template <bool kFill, int kAhead>
+__global__ __launch_bounds__(1024) void loss_filter_kernel(const int64_t* __restrict__ offsets,
+                                                           const uint32_t* __restrict__ ids, int64_t N,
+                                                           const uint64_t* __restrict__ probe, int64_t n_words,
+                                                           int shift, int64_t* __restrict__ start,
+                                                           uint32_t* __restrict__ out, int P,
+                                                           int32_t* __restrict__ cnt) {
+    __shared__ uint32_t map[kMapWords];
+    __shared__ uint32_t counts[16][kMaxStreamParts];
+    if (shift >= 0) {
+        for (int i = threadIdx.x; i < kMapWords; i += blockDim.x) map[i] = 0;
+        __syncthreads();
+        for (int64_t w = threadIdx.x; w < n_words; w += blockDim.x) {
+            uint32_t b = static_cast<uint32_t>(probe[w]);
+            if (shift >= 1) {                       // pairs, then fours, to the low bits
+                b = (b | b >> 1) & 0x55555555u;
+                b = (b | b >> 1) & 0x33333333u;
+                b = (b | b >> 2) & 0x0F0F0F0Fu;
+                b = (b | b >> 4) & 0x00FF00FFu;
+                b = (b | b >> 8) & 0x0000FFFFu;
+            }
+            if (shift >= 2) {
+                b = (b | b >> 1) & 0x55555555u;
+                b = (b | b >> 1) & 0x33333333u;
+                b = (b | b >> 2) & 0x0F0F0F0Fu;
+                b = (b | b >> 4) & 0x00FF00FFu;
+            }
+            const int per = 32 >> shift;            // bits of the map a word gives
+            if (b) atomicOr(&map[w * per >> 5], b << (static_cast<int>(w * per) & 31));
+        }
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63;
+    uint32_t* count = counts[threadIdx.x >> 6];     // this wave's
+    if (kFill && lane < P) count[lane] = 0;
+    const int64_t n_waves = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 6;
+    for (int64_t t = uniform_i64((static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6); t < N;
+         t += n_waves) {
+        const int64_t b = uniform_i64(offsets[t]), e = uniform_i64(offsets[t + 1]);
+        int64_t to = kFill ? uniform_i64(start[t]) : 0;
+        for (int64_t c = b; c < e; c += 64 * kAhead) {
+            uint32_t id[kAhead];
+            uint64_t w[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) id[k] = ids[min(c + k * 64 + lane, e - 1)];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                uint32_t at = id[k] >> 5;
+                if (shift >= 0) {
+                    const uint32_t m = id[k] >> shift;
+                    at = map[m >> 5] >> (m & 31u) & 1u ? at : 0u;
+                }
+                w[k] = probe[at];
+                if (at != id[k] >> 5) w[k] = 0;
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const uint32_t bits = static_cast<uint32_t>(w[k]);
+                const bool keep = c + k * 64 + lane < e && (bits >> (id[k] & 31u) & 1u);
+                const uint64_t kept = __ballot(keep);
+                if (kFill && keep) {
+                    const uint32_t slot =
+                        static_cast<uint32_t>(w[k] >> 32) + __popc(bits & ((1u << (id[k] & 31u)) - 1u));
+                    out[to + __popcll(kept & ((1ull << lane) - 1))] = slot;
+                    if (P > 1) atomicAdd(&count[slot >> 16], 1u);
+                }
+                to += __popcll(kept);
+            }
+        }
+        if (!kFill && lane == 0) start[t] = to;
+        if (kFill && P == 1 && lane == 0) cnt[t] = static_cast<int32_t>(to - start[t]);
+        if (kFill && P > 1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < P) {
+                cnt[t * P + lane] = static_cast<int32_t>(count[lane]);
+                count[lane] = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the copy, from the kept events part by part (a StreamLayout of their slots)
+// ---------------------------------------------------------------------------
+
+// IDs of trial t in part p of the intermediate copy: [from, to) in the part's stream
+__device__ __forceinline__ void stream_segment(const StreamLayout& in, int p, int64_t t, uint32_t& from, uint32_t& to) {
+    const int64_t g = t / in.G;
+    const int i = static_cast<int>(t - g * in.G);
+    const uint32_t start = in.gstart[static_cast<int64_t>(p) * (in.NG + 1) + g];
+    const uint16_t* ends = in.gend + (static_cast<int64_t>(p) * in.NG + g) * kStreamGroupSlots;
+    from = start + (i ? ends[i - 1] : 0u);
+    to = start + ends[i];
+}
+
+// one wave per (part, group): the rows of its splits to their places in gstart
+__global__ __launch_bounds__(256) void loss_group_kernel(StreamLayout in, int64_t N, int S, int64_t NG,
+                                                         uint32_t* __restrict__ gstart) {
+    const int lane = threadIdx.x & 63;
+    const int64_t g = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (g >= NG) return;
+    const int p = static_cast<int>(blockIdx.y);
+    uint32_t from = 0, to = 0;
+    if (g * kTrials + lane < N) stream_segment(in, p, g * kTrials + lane, from, to);
+    const uint64_t n = to - from;
+    for (int s = 0; s < S; ++s) {
+        uint32_t rows = static_cast<uint32_t>(n * (s + 1) / S - n * s / S + kRowIds - 1) / kRowIds;
+        for (int off = 32; off >= 1; off >>= 1)
+            rows = max(rows, static_cast<uint32_t>(__shfl_xor(static_cast<int>(rows), off, 64)));
+        // at least one, so that every group ends with a row
+        if (lane == 0) gstart[(static_cast<int64_t>(p) * S + s) * (NG + 1) + g] = max(rows, 1u);
+    }
+}
+
+// per column: exclusive sums of its groups' rows in place, the total to rows[q]
+__global__ __launch_bounds__(1024) void loss_scan_kernel(int64_t NG, uint32_t* __restrict__ gstart,
+                                                         int64_t* __restrict__ rows) {
+    __shared__ int64_t tsum[1024];
+    uint32_t* v = gstart + static_cast<int64_t>(blockIdx.x) * (NG + 1);
+    const int64_t per = (NG + 1023) / 1024, j0 = static_cast<int64_t>(threadIdx.x) * per;
+    int64_t local = 0;
+    for (int64_t j = j0; j < j0 + per && j < NG; ++j) local += v[j];
+    tsum[threadIdx.x] = local;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int64_t add = static_cast<int>(threadIdx.x) >= off ? tsum[threadIdx.x - off] : 0;
+        __syncthreads();
+        tsum[threadIdx.x] += add;
+        __syncthreads();
+    }
+    int64_t run = tsum[threadIdx.x] - local;
+    for (int64_t j = j0; j < j0 + per && j < NG; ++j) {
+        const uint32_t size = v[j];
+        v[j] = static_cast<uint32_t>(run);
+        run += size;
+    }
+    if (threadIdx.x == 1023) {
+        v[NG] = static_cast<uint32_t>(tsum[1023]);
+        rows[blockIdx.x] = tsum[1023];
+    }
+}
+
+// one wave per (column, group): the rows
+__global__ __launch_bounds__(256) void loss_rows_kernel(StreamLayout in, int64_t N, int S, int64_t NG,
+                                                        const uint32_t* __restrict__ gstart,
+                                                        const int64_t* __restrict__ base, uint64_t* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int64_t g = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (g >= NG) return;
+    const int q = static_cast<int>(blockIdx.y), p = q / S, s = q - p * S;
+    const int64_t t = g * kTrials + lane;
+    uint32_t from = 0, to = 0;
+    if (t < N) stream_segment(in, p, t, from, to);
+    const uint64_t n = to - from;
+    to = from + static_cast<uint32_t>(n * (s + 1) / S);
+    from += static_cast<uint32_t>(n * s / S);
+    const uint16_t* ids = in.ids + in.part_base[p];
+    const uint32_t r0 = gstart[static_cast<int64_t>(q) * (NG + 1) + g], r1 = gstart[static_cast<int64_t>(q) * (NG + 1) + g + 1];
+    uint64_t* dst = out + (base[q] / (64 * kRowIds) + r0) * 64 + lane;
+    // Four rows at a time, each lane's 16 slots in two 16-byte loads at the ID's own
+    // alignment; what they read past the lane's last slot (inside the copy's padding)
+    // is masked.  One load per slot asked the L2 for a line each, as 32 waves' lines
+    // do not stay in the first-level cache: 2500 us for 288M slots, this 480.
+    struct __attribute__((packed, aligned(2))) Slots {
+        uint64_t row[4];
+    };
+    constexpr uint64_t kPadRow = kPadSlot * 0x0001000100010001ull;
+    for (uint32_t r = r0; r < r1; r += 4, from += 4 * kRowIds, dst += 4 * 64) {
+        Slots v;
+        __builtin_memcpy(&v, ids + min(from, to), sizeof(v));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t at = from + k * kRowIds, n = at < to ? to - at : 0u;
+            const uint64_t valid = n >= kRowIds ? ~0ull : (1ull << (16 * n)) - 1;
+            if (r + k < r1) dst[64 * k] = (v.row[k] & valid) | (kPadRow & ~valid);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the pass
+// ---------------------------------------------------------------------------
+
+// one layer over one range of trials: its (column, group) items follow the
+// earlier segments' in the work list
+struct LossSeg {
+    int64_t t_lo, t_hi;
+    int64_t g_lo;                   // first group that holds its trials
+    int64_t groups;                 // groups per column
+    int64_t w0;                     // items before it
+    int64_t part_at;                // its partial sums' place
+    int64_t layer;
+};
+constexpr int kMaxSegs = 32;
+struct LossSegs {
+    LossSeg seg[kMaxSegs];
+};
+struct LossPassArgs {
+    const uint64_t* rows;           // [row][64]: four slots of each lane's trial
+    const int64_t* col_base;        // a column's first slot in the copy (64 x 4 to a row)
+    const double* tab;              // [layer][part][kSlots]
+    const uint32_t* part_n;         // slots in use of each part
+    int Q, S, P, n_seg;             // columns, columns per part, parts
+    int64_t NG;
+    int64_t work;
+    double* part_hi;
+    float* part_lo;
+};
+struct LossAdjArgs {
+    uint32_t* counts;               // [workgroup + part][kSlots]: what a workgroup counted in a part
+    uint64_t* w_tvar;               // [part][kSlots], zeroed by the caller
+    const TailStats* tail;
+};
+
+// The forward (kAdj false) sums; the backward counts the occurrences of each slot
+// in the trials inside the aggregate band in LDS.  A wave takes consecutive groups
+// of a column, whose rows lie one after the other: eight rows are always in flight,
+// whatever group they belong to, as nothing but their loads and the groups' stores
+// uses the vector memory counter (group ends and class masks are scalar loads) and
+// the loop leaves in whole rounds only.  With a group's first rows read ahead and
+// its others on their own, the forward above took 260 us and its backward at half
+// the trials 160, now 155 and 75.
+template <bool kAdj>
+__global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSegs segs, LossAdjArgs adj,
+                                                         const uint32_t* __restrict__ gstart,
+                                                         const uint64_t* __restrict__ cls_masks) {
+    constexpr int kAhead = 8;                       // rows read ahead
+    __shared__ __attribute__((aligned(16))) uint8_t lds[(kAdj ? 4 : 8) * kSlots];
+    double* vals = reinterpret_cast<double*>(lds);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    TailStats ts{};
+    if constexpr (kAdj) ts = *adj.tail;
+    // each XCD takes a contiguous share of the items
+    const int64_t n_wg = gridDim.x;
+    const int64_t l = n_wg % kXcds ? static_cast<int64_t>(blockIdx.x)
+                                   : static_cast<int64_t>(blockIdx.x % kXcds) * (n_wg / kXcds) + blockIdx.x / kXcds;
+    const int64_t w_begin = l * a.work / n_wg, w_end = (l + 1) * a.work / n_wg;
+    int held = -1;                                  // the part whose table (counters) LDS holds
+    int64_t held_layer = -1;
+    auto flush_counts = [&] {
+        __syncthreads();
+        u32x4* to = reinterpret_cast<u32x4*>(adj.counts + (l + held) * kSlots);
+        for (int i = threadIdx.x; i < kSlots / 4; i += blockDim.x) to[i] = reinterpret_cast<const u32x4*>(cnt)[i];
+    };
+    for (int sg = 0; sg < (kAdj ? 1 : a.n_seg); ++sg) {
+        const LossSeg sgm = segs.seg[sg];
+        const int64_t n_items = static_cast<int64_t>(a.Q) * sgm.groups;
+        int64_t it = w_begin - sgm.w0 < 0 ? 0 : (w_begin - sgm.w0 < n_items ? w_begin - sgm.w0 : n_items);
+        const int64_t it_end = w_end - sgm.w0 < 0 ? 0 : (w_end - sgm.w0 < n_items ? w_end - sgm.w0 : n_items);
+        const int64_t t_lo = sgm.t_lo, t_hi = sgm.t_hi, count = t_hi - t_lo;
+        while (it < it_end) {
+            const int col = static_cast<int>(it / sgm.groups);
+            const int part = col / a.S;
+            const int64_t seg_end = min(it_end, static_cast<int64_t>(col + 1) * sgm.groups);
+            const int64_t ga = sgm.g_lo + it - static_cast<int64_t>(col) * sgm.groups;
+            const int64_t gb = sgm.g_lo + seg_end - static_cast<int64_t>(col) * sgm.groups;
+            it = seg_end;
+            if (part != held || sgm.layer != held_layer) {
+                if constexpr (kAdj) {
+                    if (held >= 0) flush_counts();
+                }
+                __syncthreads();                    // the part before is done
+                held = part;
+                held_layer = sgm.layer;
+                if constexpr (kAdj) {
+                    for (int i = threadIdx.x; i < kSlots / 4; i += blockDim.x)
+                        reinterpret_cast<u32x4*>(cnt)[i] = u32x4{0, 0, 0, 0};
+                } else {
+                    const int n2 = static_cast<int>((a.part_n[part] + 1) / 2);
+                    const u64x2* src = reinterpret_cast<const u64x2*>(a.tab + (sgm.layer * a.P + part) * kSlots);
+                    u64x2 v[kSlots / 2048];
+#pragma unroll
+                    for (int k = 0; k < kSlots / 2048; ++k)
+                        if (k * 1024 + static_cast<int>(threadIdx.x) < n2) v[k] = src[k * 1024 + threadIdx.x];
+#pragma unroll
+                    for (int k = 0; k < kSlots / 2048; ++k)
+                        if (k * 1024 + static_cast<int>(threadIdx.x) < n2)
+                            reinterpret_cast<u64x2*>(vals)[k * 1024 + threadIdx.x] = v[k];
+                    __syncthreads();
+                    if (threadIdx.x == 0) vals[kPadSlot] = 0.0;
+                }
+                __syncthreads();
+            }
+            // this wave's groups [g, g_end) of the column, rows [r, r_end)
+            const int64_t n = gb - ga;
+            int64_t g = ga + wv * n / 16;
+            const int64_t g_end = ga + (wv + 1) * n / 16;
+            if (g >= g_end) continue;
+            const uint32_t* gs = gstart + static_cast<int64_t>(col) * (a.NG + 1);
+            const uint64_t* rows = a.rows + a.col_base[col] / kRowIds + lane;
+            double* out_hi = a.part_hi + sgm.part_at + static_cast<int64_t>(col) * count;
+            float* out_lo = a.part_lo + sgm.part_at + static_cast<int64_t>(col) * count;
+            unsigned long long* tvar = reinterpret_cast<unsigned long long*>(adj.w_tvar) + static_cast<int64_t>(part) * kSlots;
+            const uint32_t r_last = max(gs[g_end], 1u) - 1u;
+            auto row = [&](uint32_t at) -> uint64_t {
+                return __builtin_nontemporal_load(rows + static_cast<int64_t>(at < r_last ? at : r_last) * 64);
+            };
+            double acc_hi = 0.0, acc_lo = 0.0;
+            auto add_row = [&](uint64_t x, uint32_t cls) {
+                uint32_t e[kRowIds];
+#pragma unroll
+                for (int i = 0; i < kRowIds; ++i) e[i] = static_cast<uint32_t>(x >> (16 * i)) & 0xFFFFu;
+                if constexpr (kAdj) {
+                    if (!(cls & 1u)) return;        // outside the aggregate band: no weight
+#pragma unroll
+                    for (int i = 0; i < kRowIds; ++i)
+                        if (e[i] != kPadSlot) atomicAdd(&cnt[e[i]], 1u);
+                    if (cls & 6u) {                 // a tail trial: its TVaR weight on each of its events
+                        const unsigned long long wt =
+                            static_cast<unsigned long long>((cls & 2u) ? ts.c_eq : ts.m - ts.c_gt);
+#pragma unroll
+                        for (int i = 0; i < kRowIds; ++i)
+                            if (e[i] != kPadSlot)
+                                atomicAdd(tvar + e[i], wt);
+                    }
+                } else {
+                    double v[kRowIds];
+#pragma unroll
+                    for (int i = 0; i < kRowIds; ++i) v[i] = vals[e[i]];
+#pragma unroll
+                    for (int i = 0; i < kRowIds; ++i) dd_add(acc_hi, acc_lo, v[i]);
+                }
+            };
+            // the backward's trial classes, a mask per class and group: scalar loads too, so
+            // that no load but the rows' is waited for
+            struct Masks {
+                uint64_t band, above, at;
+            } masks{}, masks_next{};
+            auto masks_of = [&](int64_t grp) {
+                const uint64_t* m = cls_masks + (min(grp, g_end - 1) - sgm.g_lo) * 4;
+                return Masks{m[0], m[1], m[2]};
+            };
+            auto class_of = [&](const Masks& m) -> uint32_t {
+                return static_cast<uint32_t>(m.band >> lane & 1u) | static_cast<uint32_t>(m.above >> lane & 1u) << 1 |
+                       static_cast<uint32_t>(m.at >> lane & 1u) << 2;
+            };
+            uint32_t cls = 0;
+            if constexpr (kAdj) {
+                cls = class_of(masks_of(g));
+                masks_next = masks_of(g + 1);
+            }
+            // where the group ends and the next one does (scalar loads, one group ahead)
+            uint32_t r = gs[g], end = gs[g + 1], next = gs[min(g + 2, g_end)];
+            uint64_t x[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) x[k] = row(r + k);
+            // whole rounds of kAhead rows; those past the last group add to no group
+            for (uint32_t left = gs[g_end] - r + kAhead - 1; left >= kAhead; left -= kAhead) {
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const uint64_t y = x[k];
+                    x[k] = row(r + kAhead);
+                    add_row(y, cls);
+                    if (++r != end) continue;
+                    if constexpr (!kAdj) {
+                        const double hi = acc_hi + acc_lo;              // renormalised: |lo| <= ulp(hi) / 2
+                        const int64_t t = g * kTrials + lane;
+                        if (t >= t_lo && t < t_hi) {
+                            out_hi[t - t_lo] = hi;
+                            out_lo[t - t_lo] = static_cast<float>(acc_lo - (hi - acc_hi));
+                        }
+                        acc_hi = 0.0;
+                        acc_lo = 0.0;
+                    }
+                    ++g;
+                    end = g < g_end ? next : ~0u;
+                    next = gs[min(g + 2, g_end)];
+                    if constexpr (kAdj) {
+                        masks = masks_next;
+                        masks_next = masks_of(g + 1);
+                        cls = g < g_end ? class_of(masks) : 0u;
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (kAdj) {
+        if (held >= 0) flush_counts();
+    }
+}
+
+// The workgroups' counts of a part summed to its events.  A workgroup's share of the
+// items is contiguous, so it holds few parts, and (workgroup + part) tells all of
+// them apart; 256 workgroups' counts added by device atomics took about 100 us for
+// 300000 events, stored and summed here 12.
+__global__ __launch_bounds__(256) void loss_counts_kernel(LossPassArgs a, int64_t groups, int64_t n_wg,
+                                                          const uint32_t* __restrict__ events,
+                                                          const uint32_t* __restrict__ counts,
+                                                          const uint64_t* __restrict__ tvar,
+                                                          uint64_t* __restrict__ w_mean,
+                                                          uint64_t* __restrict__ w_tvar) {
+    const int part = static_cast<int>(blockIdx.y);
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.part_n[part]) return;
+    // workgroup l's items are [l work / n_wg, (l + 1) work / n_wg), not empty
+    const int64_t first = static_cast<int64_t>(part) * a.S * groups, last = first + static_cast<int64_t>(a.S) * groups - 1;
+    const int64_t l0 = ((first + 1) * n_wg - 1) / a.work, l1 = ((last + 1) * n_wg - 1) / a.work;
+    uint64_t sum = 0;
+    const uint32_t* c = counts + (l0 + part) * kSlots + i;
+#pragma unroll 8
+    for (int k = 0; k <= static_cast<int>(l1 - l0); ++k) sum += c[static_cast<int64_t>(k) * kSlots];
+    const uint32_t E = events[static_cast<int64_t>(part) * kSlots + i];
+    w_mean[E] = sum;
+    w_tvar[E] = tvar[static_cast<int64_t>(part) * kSlots + i];
+}
+
+int64_t first_group(int64_t t_lo) { return t_lo / kTrials; }
+int64_t group_end(int64_t t_hi) { return (t_hi + kTrials - 1) / kTrials; }
+
+// one 1024-thread workgroup per CU (its LDS holds the part's table or counters)
+int64_t pass_grid(int n_cu) {
+    const int64_t grid = int64_t(n_cu) - n_cu % kXcds;
+    return grid < kXcds ? kXcds : grid;
+}
+
+template <bool kAdj>
+hipError_t launch_pass(const StreamLayout& lay, const LossIndex& ix, const StreamUnit* units, int n, const double* tab,
+                       void* partials, const LossAdjArgs& adj, const uint64_t* masks, uint64_t* w_mean,
+                       uint64_t* w_tvar, int n_cu, hipStream_t s) {
+    if (n < 1 || n > kMaxSegs || lay.P <= 0 || ix.P <= 0 || lay.P % ix.P) return hipErrorInvalidValue;
+    LossPassArgs a{};
+    a.rows = reinterpret_cast<const uint64_t*>(lay.ids);
+    a.col_base = lay.part_base;
+    a.tab = tab;
+    a.part_n = ix.part_n;
+    a.Q = lay.P;
+    a.P = ix.P;
+    a.S = lay.P / ix.P;
+    a.NG = lay.NG;
+    a.n_seg = n;
+    int64_t trials = 0;
+    for (int i = 0; i < n; ++i) trials += units[i].count;
+    a.part_hi = static_cast<double*>(partials);
+    a.part_lo = reinterpret_cast<float*>(a.part_hi + static_cast<int64_t>(lay.P) * trials);
+    LossSegs segs{};
+    int64_t at = 0;
+    for (int i = 0; i < n; ++i) {
+        LossSeg& g = segs.seg[i];
+        g.t_lo = units[i].t_lo;
+        g.t_hi = units[i].t_lo + units[i].count;
+        g.g_lo = first_group(g.t_lo);
+        g.groups = group_end(g.t_hi) - g.g_lo;
+        g.w0 = a.work;
+        g.part_at = at;
+        g.layer = units[i].layer;
+        a.work += static_cast<int64_t>(lay.P) * g.groups;
+        at += static_cast<int64_t>(lay.P) * units[i].count;
+    }
+    int64_t grid = pass_grid(n_cu);
+    if (kAdj) {                                     // a group per wave: fewer counters to store and sum
+        grid = std::min(grid, std::max<int64_t>(a.work / 16, 1));
+        if (grid > kXcds) grid -= grid % kXcds;
+    }
+    hipLaunchKernelGGL(loss_pass_kernel<kAdj>, dim3(static_cast<uint32_t>(grid)), dim3(1024), 0, s, a, segs, adj,
+                       lay.gstart, masks);
+    hipError_t e = hipGetLastError();
+    if (!kAdj || e != hipSuccess) return e;
+    hipLaunchKernelGGL(loss_counts_kernel, dim3(kSlots / 256, static_cast<uint32_t>(a.P)), dim3(256), 0, s, a,
+                       segs.seg[0].groups, grid, ix.events, adj.counts, adj.w_tvar, w_mean, w_tvar);
+    return hipGetLastError();
+}
+
+// columns per part: enough that the whole table's groups fill the waves four
+// times, unless that leaves a trial fewer than 32 events, or costs more in the merge
+// (0.25 us a column) than the shorter columns save (about 0.1 us a row of a group)
+int splits_of(int P, int64_t N, int64_t kept, int n_cu) {
+    const double lam = static_cast<double>(kept) / (static_cast<double>(N) * P);
+    const double items = static_cast<double>(P) * ((N + 63) / 64);
+    const double want = std::min({std::ceil(lam / 32.0), std::ceil(64.0 * n_cu / items), std::sqrt(0.1 * lam / P)});
+    return static_cast<int>(std::max(1.0, std::min(want, 64.0)));
+}
+
+// the copy from the intermediate one, unless it takes more than `most` bytes
+hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t most, int n_cu, hipStream_t s,
+                      StreamLayout* out) {
+    const int S = splits_of(in.P, N, kept, n_cu), Q = in.P * S;
+    const int64_t NG = (N + kTrials - 1) / kTrials;
+    std::vector<int64_t> base(Q + 1);
+    int64_t* rows = nullptr;
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * Q * (NG + 1), s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (Q + 1), s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&rows), sizeof(int64_t) * Q, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(loss_group_kernel, dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(in.P)),
+                           dim3(256), 0, s, in, N, S, NG, out->gstart);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(loss_scan_kernel, dim3(static_cast<uint32_t>(Q)), dim3(1024), 0, s, NG, out->gstart, rows);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(base.data() + 1, rows, sizeof(int64_t) * Q, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (rows) dev_free(rows, s);
+    if (e != hipSuccess) return e;
+    base[0] = 0;
+    for (int q = 0; q < Q; ++q) {
+        if (base[q + 1] >= (int64_t(1) << 32) - 4096) return hipErrorOutOfMemory;      // past 32-bit rows
+        base[q + 1] = base[q] + base[q + 1] * 64 * kRowIds;
+    }
+    if (static_cast<int64_t>(sizeof(uint16_t)) * base[Q] > most) {        // not used
+        free_stream_layout(out, s);
+        return hipSuccess;
+    }
+    out->length = base[Q];
+    e = hipMemcpyAsync(out->part_base, base.data(), sizeof(int64_t) * (Q + 1), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (out->length + 64 * kRowIds), s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(loss_rows_kernel, dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(Q)),
+                           dim3(256), 0, s, in, N, S, NG, out->gstart, out->part_base,
+                           reinterpret_cast<uint64_t*>(out->ids));
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    out->P = Q;
+    out->G = kTrials;
+    out->NG = NG;
+    out->bytes = static_cast<int64_t>(sizeof(uint16_t)) * (out->length + 64 * kRowIds) +
+                 static_cast<int64_t>(sizeof(uint32_t)) * Q * (NG + 1) + static_cast<int64_t>(sizeof(int64_t)) * (Q + 1);
+    return hipSuccess;
+}
+
+}  // namespace
+
+int64_t loss_table_bytes(const LossIndex& ix) { return static_cast<int64_t>(sizeof(double)) * kSlots * ix.P; }
+
+hipError_t launch_loss_pass_units(const StreamLayout& lay, const LossIndex& ix, const StreamUnit* units, int n,
+                                  const double* tab, void* partials, int n_cu, hipStream_t s) {
+    return launch_pass<false>(lay, ix, units, n, tab, partials, LossAdjArgs{}, nullptr, nullptr, nullptr, n_cu, s);
+}
+
+int64_t loss_tvar_words(const LossIndex& ix) { return static_cast<int64_t>(kSlots) * ix.P; }
+
+int64_t loss_adjoint_bytes(const LossIndex& ix, int n_cu) {
+    return loss_tvar_words(ix) * static_cast<int64_t>(sizeof(uint64_t)) +
+           static_cast<int64_t>(sizeof(uint32_t)) * kSlots * (pass_grid(n_cu) + ix.P);
+}
+
+hipError_t launch_loss_adjoint(const StreamLayout& lay, const LossIndex& ix, const LayerArgs& L, const uint64_t* masks,
+                               const TailStats* tail, void* scratch, uint64_t* w_mean, uint64_t* w_tvar, int n_cu,
+                               hipStream_t s) {
+    if (L.trial_count <= 0) return hipSuccess;
+    uint64_t* tvar = static_cast<uint64_t*>(scratch);
+    const LossAdjArgs adj{reinterpret_cast<uint32_t*>(tvar + loss_tvar_words(ix)), tvar, tail};
+    const StreamUnit u{0, L.trial_begin, L.trial_count, 0, 0.0};
+    return launch_pass<true>(lay, ix, &u, 1, nullptr, nullptr, adj, masks, w_mean, w_tvar, n_cu, s);
+}
+
+void free_loss_index(LossIndex* ix, hipStream_t s) {
+    if (ix->probe) dev_free(ix->probe, s);
+    if (ix->events) dev_free(ix->events, s);
+    if (ix->part_n) dev_free(ix->part_n, s);
+    *ix = LossIndex{};
+}
+
+hipError_t build_losses(const SparsePool& sp, int n_rows, int64_t C, const int64_t* offsets, const uint32_t* ids,
+                        int64_t N, int64_t n_events, int n_cu, hipStream_t s, LossIndex* ix, StreamLayout* out) {
+    *ix = LossIndex{};
+    *out = StreamLayout{};
+    if (n_rows < 1 || sp.n_chunks < 1 || N < 1) return hipSuccess;
+    const int64_t n_sb = sp.n_chunks, n_words = (C + 31) / 32;
+    // two neighbouring parts hold more than kSlots - 1 events
+    const int most_parts = static_cast<int>(std::min<int64_t>(kMaxStreamParts, 2 * (C / (kSlots - 1)) + 1));
+    uint32_t* place = nullptr;
+    int64_t* start = nullptr;
+    uint32_t* kept_ids = nullptr;
+    int32_t* cnt = nullptr;
+    CreateResult* d_res = nullptr;
+    CreateResult res{};
+    StreamLayout by_part{};
+    LossPlan plan{};
+    int shift = 0;
+    while (shift <= kMapShift && C > (int64_t(kMapWords) * 32 << shift)) ++shift;
+    if (shift > kMapShift) shift = -1;
+    const dim3 g(static_cast<uint32_t>(std::min((N + 15) / 16, int64_t(n_cu)))), b(1024);
+    const bool long_trials = n_events / N > 256;
+
+    // the events' slots, and how many events the trials keep
+    LossPlan* d_plan = nullptr;
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&ix->probe), sizeof(uint64_t) * n_words, s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&ix->events), sizeof(uint32_t) * kSlots * most_parts, s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&ix->part_n), sizeof(uint32_t) * kMaxStreamParts, s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&place), sizeof(uint32_t) * n_sb, s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&start), sizeof(int64_t) * (N + 1), s);
+    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&d_plan), sizeof(LossPlan), s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(loss_bits_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, n_rows, C,
+                           ix->probe, place);
+        hipLaunchKernelGGL(loss_plan_kernel, dim3(1), dim3(64), 0, s, n_sb, most_parts, place, ix->part_n, d_plan);
+        hipLaunchKernelGGL(loss_place_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(64), 0, s, C, most_parts, place,
+                           ix->probe, ix->events);
+        hipLaunchKernelGGL((long_trials ? loss_filter_kernel<false, 16> : loss_filter_kernel<false, 4>), g, b, 0, s,
+                           offsets, ids, N, ix->probe, n_words, shift, start, kept_ids, 0, cnt);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = launch_scan_i64(start, N, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&d_plan->kept, start + N, sizeof(int64_t), hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&plan, d_plan, sizeof(plan), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+
+    // Not used without a kept event, past the parts a copy can have, where trials are so
+    // short that most of the copy would be padding (a row takes 8 bytes of each trial),
+    // or where the copy and its temporaries take more than a quarter of the free memory.
+    const int P = plan.parts;
+    const int64_t kept = plan.kept, most = 4 * n_events + (int64_t(128) << 20);
+    size_t mem_free = 0, mem_all = 0;
+    if (e == hipSuccess && kept > 0 && P <= most_parts && 16 * N * P <= most &&
+        hipMemGetInfo(&mem_free, &mem_all) == hipSuccess &&
+        12 * kept + 16 * N * P + most <= static_cast<int64_t>(mem_free / 4)) {
+        e = dev_alloc(reinterpret_cast<void**>(&kept_ids), sizeof(uint32_t) * (kept + kIdPad), s);
+        if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&cnt), sizeof(int32_t) * N * P, s);
+        if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&d_res), sizeof(CreateResult), s);
+        if (e == hipSuccess) e = hipMemsetAsync(d_res, 0, sizeof(CreateResult), s);
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL((long_trials ? loss_filter_kernel<true, 16> : loss_filter_kernel<true, 4>), g, b, 0, s,
+                               offsets, ids, N, ix->probe, n_words, shift, start, kept_ids, P, cnt);
+            e = hipGetLastError();
+        }
+        // a part's slots as 2^16 catalogue events
+        if (e == hipSuccess)
+            e = plan_stream_layout(cnt, N, kept, static_cast<int64_t>(P) << kStreamShift, d_res, s, &by_part);
+        if (e == hipSuccess) e = hipMemcpyAsync(&res, d_res, sizeof(res), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = fill_stream_layout(start, kept_ids, N, kept, res, d_res, s, &by_part);
+        if (e == hipSuccess && by_part.P > 0) e = build_rows(by_part, N, kept, most, n_cu, s, out);
+        (void)hipStreamSynchronize(s);
+    }
+    dev_drop(by_part.ids, s);
+    by_part.ids = nullptr;
+    free_stream_layout(&by_part, s);
+    dev_drop(kept_ids, s);
+    for (void* p : {static_cast<void*>(place), static_cast<void*>(start), static_cast<void*>(cnt),
+                    static_cast<void*>(d_res), static_cast<void*>(d_plan)})
+        if (p) dev_free(p, s);
+    ix->P = P;
+    ix->n_events = plan.events;
+    ix->bytes = static_cast<int64_t>(sizeof(uint64_t)) * n_words +
+                static_cast<int64_t>(sizeof(uint32_t)) * (static_cast<int64_t>(kSlots) * most_parts + kMaxStreamParts);
+    if (e != hipSuccess || out->P == 0) {
+        free_stream_layout(out, s);
+        free_loss_index(ix, s);
+    }
+    return e;
+}
+
+}  // namespace ara

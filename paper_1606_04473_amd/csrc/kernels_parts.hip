@@ -469,7 +469,9 @@ struct FoldOut {
     uint64_t* probe;
     uint32_t* coarse;
     int cshift;
-    FoldBack back;                  // kBack
+    FoldBack back;                  // back
+    const uint64_t* slots;          // losses: the pool's events (LossIndex::probe) and the table by slot
+    double* tab;
 };
 
 // OR of each pair of adjacent bits, packed into the low half
@@ -481,9 +483,11 @@ __device__ __forceinline__ uint32_t or_pairs(uint32_t x) {
     return (x | (x >> 8)) & 0x0000FFFFu;
 }
 
-template <bool kBack>
+enum class FoldKind { images, back, losses };
+template <FoldKind kKind>
 __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C, const LayerArgs& L,
                                                 const FoldOut& out) {
+    constexpr bool kBack = kKind == FoldKind::back, kLosses = kKind == FoldKind::losses;
     double* __restrict__ o = out.o;
     uint8_t* __restrict__ img = out.img;
     uint32_t* __restrict__ sb_count = out.sb_count;
@@ -515,6 +519,11 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
     {
         u64x2* own = reinterpret_cast<u64x2*>(ys + w * kOwn);
         for (int i = lane; i < kOwn / 2; i += 64) own[i] = u64x2{0, 0};
+    }
+    uint64_t slots = 0;                             // lane i < 16: the wave's i-th 32 events
+    if constexpr (kLosses) {
+        const int64_t i = (e0 >> 5) + w * (kOwn / 32) + lane;
+        if (lane < kOwn / 32 && i < (C + 31) / 32) slots = out.slots[i];
     }
     uint64_t left = __ballot(cnt > 0);              // ELTs with entries that are not begun
     int pj = -1, pi = 0, pn = 0;                    // the last piece fetched: ELT, first entry, the ELT's entries
@@ -576,10 +585,21 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
             out.back.w_mean[E] = 0;
             out.back.w_tvar[E] = 0;
         }
+        if constexpr (kLosses) {
+            // an event's slot in its part's table, also where the layer has no loss
+            const uint64_t a = readlane_u64(slots, 2 * k), b = readlane_u64(slots, 2 * k + 1);
+            const uint64_t bits = (b << 32) | (a & 0xFFFFFFFFull);
+            const uint32_t first = static_cast<uint32_t>(a >> 32);
+            if ((bits >> lane) & 1ull)
+                out.tab[static_cast<int64_t>(first >> 16) * kLossSlots + (first & 0xFFFFu) +
+                        __popcll(bits & lanemask_lt())] = v;
+            continue;
+        }
         vk[k] = v;
         bk[k] = __ballot(E < C && v != 0.0);
         if (lane == 0) wb[w * kWordsOwn + k] = bk[k];
     }
+    if constexpr (kLosses) return;
     __syncthreads();
     // lane i: bitmap word i and the nonzero events before it, in every wave
     const uint64_t word = wb[lane];
@@ -634,12 +654,12 @@ __device__ __forceinline__ void fold_image_body(const SparsePool& sp, int64_t C,
 // terms as kernel arguments (eager runs) or read from device memory (graph
 // replays, whose terms may change between replays)
 __global__ __launch_bounds__(kFoldThreads) void fold_image_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
-    fold_image_body<false>(sp, C, L, out);
+    fold_image_body<FoldKind::images>(sp, C, L, out);
 }
 __global__ __launch_bounds__(kFoldThreads) void fold_back_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < out.back.n_acc; i += blockDim.x) out.back.acc[i] = 0;
-    fold_image_body<true>(sp, C, L, out);
+    fold_image_body<FoldKind::back>(sp, C, L, out);
 }
 // layer blockIdx.y of several
 __global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool sp, int64_t C,
@@ -648,7 +668,17 @@ __global__ __launch_bounds__(kFoldThreads) void fold_image_dev_kernel(SparsePool
     out.img += blockIdx.y * img_stride;
     out.sb_count += blockIdx.y * sb_stride;
     out.stage += blockIdx.y * sb_stride * kSuper;
-    fold_image_body<false>(sp, C, L[blockIdx.y], out);
+    fold_image_body<FoldKind::images>(sp, C, L[blockIdx.y], out);
+}
+// the tables by slot of one layer, or of layer blockIdx.y
+__global__ __launch_bounds__(kFoldThreads) void fold_losses_kernel(SparsePool sp, int64_t C, LayerArgs L, FoldOut out) {
+    fold_image_body<FoldKind::losses>(sp, C, L, out);
+}
+__global__ __launch_bounds__(kFoldThreads) void fold_losses_dev_kernel(SparsePool sp, int64_t C,
+                                                                       const LayerArgs* __restrict__ L, FoldOut out,
+                                                                       int64_t tab_stride) {
+    out.tab += blockIdx.y * tab_stride;
+    fold_image_body<FoldKind::losses>(sp, C, L[blockIdx.y], out);
 }
 
 // Layer arguments packed into kernel arguments (which take 4 KB): per layer the
@@ -725,27 +755,63 @@ __global__ __launch_bounds__(256) void sparse_count_kernel(const double* __restr
     if (threadIdx.x == 0) counts[row * n_chunks + chunk] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-// exclusive scan of n counts in place (one workgroup), with the total at [n]
-__global__ __launch_bounds__(1024) void sparse_scan_kernel(int64_t* __restrict__ v, int64_t n) {
-    __shared__ int64_t sh[1024];
-    int64_t carry = 0;
-    for (int64_t c0 = 0; c0 < n; c0 += 1024) {
-        const int64_t i = c0 + threadIdx.x;
-        const int64_t x = i < n ? v[i] : 0;
-        sh[threadIdx.x] = x;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const int64_t add = threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += add;
-            __syncthreads();
-        }
-        if (i < n) v[i] = carry + sh[threadIdx.x] - x;
-        const int64_t total = sh[1023];
-        __syncthreads();
-        carry += total;
+constexpr int kScanChunk = 16384;
+
+// the sums of chunks of kScanChunk entries
+__global__ __launch_bounds__(1024) void chunk_sum_kernel(const int64_t* __restrict__ v, int64_t n,
+                                                         int64_t* __restrict__ sums) {
+    __shared__ int64_t wsum[16];
+    const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kScanChunk;
+    int64_t own = 0;
+    for (int k = threadIdx.x; k < kScanChunk; k += 1024)
+        if (c0 + k < n) own += v[c0 + k];
+    for (int off = 32; off >= 1; off >>= 1) own += __shfl_xor(own, off, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = own;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t total = 0;
+        for (int w = 0; w < 16; ++w) total += wsum[w];
+        sums[blockIdx.x] = total;
     }
-    if (threadIdx.x == 0) v[n] = carry;
+}
+
+// exclusive scan of n counts in place, the total at [n]: each workgroup takes `per`
+// entries in rounds, from[blockIdx.x] before them (0 where `from` is null)
+__global__ __launch_bounds__(1024) void sparse_scan_kernel(int64_t* __restrict__ v, int64_t n,
+                                                           const int64_t* __restrict__ from, int64_t per) {
+    constexpr int kPer = kScanChunk / 1024;         // entries of a thread and round
+    __shared__ int64_t wsum[16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int64_t carry = from ? from[blockIdx.x] : 0;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * per, last = min(n, first + per);
+    for (int64_t c0 = first; c0 < last; c0 += kScanChunk) {
+        const int64_t i0 = c0 + static_cast<int64_t>(threadIdx.x) * kPer;
+        int64_t x[kPer], own = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            x[k] = i0 + k < n ? v[i0 + k] : 0;
+            own += x[k];
+        }
+        int64_t inc = own;                          // inclusive over the wave
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t add = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += add;
+        }
+        if (lane == 63) wsum[wv] = inc;
+        __syncthreads();
+        int64_t at = carry + inc - own;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wv) at += wsum[w];
+            carry += wsum[w];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (i0 + k < n) v[i0 + k] = at;
+            at += x[k];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && last == n) v[n] = carry;
 }
 
 // each chunk's nonzero entries, in event order, at its offset; grid (n_chunks, n_rows)
@@ -1656,8 +1722,7 @@ hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipS
     const dim3 grid(static_cast<uint32_t>(n_chunks), static_cast<uint32_t>(n_rows));
     hipLaunchKernelGGL(sparse_count_kernel, grid, dim3(256), 0, s, elts, C, n_chunks, out->chunk_off);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(sparse_scan_kernel, dim3(1), dim3(1024), 0, s, out->chunk_off, n);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_scan_i64(out->chunk_off, n, s)) != hipSuccess) return e;
     int64_t nnz = 0;
     if ((e = hipMemcpyAsync(&nnz, out->chunk_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
@@ -2525,7 +2590,7 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
                              int P, void* scratch, bool compact, uint64_t* probe, hipStream_t s) {
     PartScratch ps = carve_parts(scratch, P);
     const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
-    FoldOut out{o, ps.img, ps.sb_count, ps.stage, nullptr, nullptr, 0, {}};
+    FoldOut out{o, ps.img, ps.sb_count, ps.stage, nullptr, nullptr, 0, {}, nullptr, nullptr};
     if (probe) {
         const ProbeTables t = probe_tables(probe, C);
         out.probe = t.probe;
@@ -2546,7 +2611,7 @@ hipError_t launch_fold_parts(const SparsePool& sp, int64_t C, const LayerArgs& L
 
 hipError_t launch_fold_back(const SparsePool& sp, int64_t C, const LayerArgs& L, int P, void* scratch,
                             const FoldBack& back, hipStream_t s) {
-    FoldOut out{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, back};
+    FoldOut out{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, back, nullptr, nullptr};
     if (scratch) {
         const PartScratch ps = carve_parts(scratch, P);
         out.img = ps.img;
@@ -2558,10 +2623,44 @@ hipError_t launch_fold_back(const SparsePool& sp, int64_t C, const LayerArgs& L,
     return hipGetLastError();
 }
 
+hipError_t launch_fold_losses(const SparsePool& sp, const LossIndex& ix, int64_t C, const LayerArgs* L,
+                              const LayerArgs* L_dev, int n_layers, double* tab, hipStream_t s) {
+    if (n_layers < 1 || (!L_dev && n_layers != 1)) return hipErrorInvalidValue;
+    const FoldOut out{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, {}, ix.probe, tab};
+    const dim3 g(static_cast<uint32_t>(sp.n_chunks), static_cast<uint32_t>(n_layers)), b(kFoldThreads);
+    if (L_dev)
+        hipLaunchKernelGGL(fold_losses_dev_kernel, g, b, 0, s, sp, C, L_dev, out,
+                           static_cast<int64_t>(ix.P) * kLossSlots);
+    else
+        hipLaunchKernelGGL(fold_losses_kernel, g, b, 0, s, sp, C, *L, out);
+    return hipGetLastError();
+}
+
+// One workgroup takes a round of kScanChunk entries at a time, 18 us each: past one
+// round the chunks are summed side by side, their sums scanned, the chunks scanned
+// (1e6 entries: 1100 us in rounds).
+hipError_t launch_scan_i64(int64_t* v, int64_t n, hipStream_t s) {
+    const int64_t chunks = (n + kScanChunk - 1) / kScanChunk;
+    if (chunks <= 1) {
+        hipLaunchKernelGGL(sparse_scan_kernel, dim3(1), dim3(1024), 0, s, v, n, nullptr, n);
+        return hipGetLastError();
+    }
+    int64_t* sums = nullptr;
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&sums), sizeof(int64_t) * (chunks + 1), s);
+    if (e != hipSuccess) return e;
+    const dim3 grid(static_cast<uint32_t>(chunks));
+    hipLaunchKernelGGL(chunk_sum_kernel, grid, dim3(1024), 0, s, v, n, sums);
+    hipLaunchKernelGGL(sparse_scan_kernel, dim3(1), dim3(1024), 0, s, sums, chunks, nullptr, chunks);
+    hipLaunchKernelGGL(sparse_scan_kernel, grid, dim3(1024), 0, s, v, n, sums, int64_t(kScanChunk));
+    e = hipGetLastError();
+    dev_free(sums, s);
+    return e;
+}
+
 hipError_t launch_fold_batch(const SparsePool& sp, int64_t C, const LayerArgs* L_dev, int n_layers, int P, void* scratch,
                              hipStream_t s) {
     const FoldViews v = fold_batch_views(scratch, n_layers, P);
-    const FoldOut out{nullptr, v.img, v.sb_count, v.stage, nullptr, nullptr, 0, {}};
+    const FoldOut out{nullptr, v.img, v.sb_count, v.stage, nullptr, nullptr, 0, {}, nullptr, nullptr};
     hipLaunchKernelGGL(fold_image_dev_kernel, dim3(static_cast<uint32_t>(v.sb_stride), static_cast<uint32_t>(n_layers)),
                        dim3(kFoldThreads), 0, s, sp, C, L_dev, out, v.img_stride, v.sb_stride);
     return hipGetLastError();

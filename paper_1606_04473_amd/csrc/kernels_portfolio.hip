@@ -8,6 +8,7 @@
 // and the pass moves (n_layers + n_programs + 1) x 8 bytes per trial, bound
 // by HBM bandwidth.  Sums are double-double in layer order, rounded once.
 #include "ara_internal.hpp"
+#include "kernels_losses.hpp"
 
 namespace ara {
 

@@ -1028,10 +1028,12 @@ __global__ __launch_bounds__(256) void stream_class_kernel(const double* __restr
                                                            int64_t t_lo, int64_t t_hi, int G, int64_t g_lo,
                                                            int64_t n_slots, uint8_t* __restrict__ cls,
                                                            long long* __restrict__ agg_mean,
-                                                           long long* __restrict__ agg_tvar, int copies, int stride_of) {
+                                                           long long* __restrict__ agg_tvar, int copies, int stride_of,
+                                                           uint64_t* __restrict__ to_clear, int64_t n_clear) {
     constexpr int kU = 4;
     const TailStats ts = *tail;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n_clear; i += stride) to_clear[i] = 0;
     long long sums[4] = {0, 0, 0, 0};               // mean: retention, limit; TVaR: the same
     for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i0 < n_slots; i0 += kU * stride) {
         double sv[kU], yv[kU];
@@ -1047,6 +1049,7 @@ __global__ __launch_bounds__(256) void stream_class_kernel(const double* __restr
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int64_t i = i0 + u * stride;
+            const int lane = static_cast<int>(i & 63);
             const double ta = sv[u] - aggR;
             // year losses are >= 0, so their bit patterns order like their values
             const uint64_t key = __double_as_longlong(yv[u] + 0.0);
@@ -1061,7 +1064,14 @@ __global__ __launch_bounds__(256) void stream_class_kernel(const double* __restr
                 sums[1] += 1;
                 sums[3] += wt;
             }
-            if (i < n_slots) cls[i] = static_cast<uint8_t>(in_band ? 1u | tail_bits : 0u);
+            if (to_clear) {                         // a wave holds a group's 64 trials
+                const uint64_t band = __ballot(in_band), above = __ballot(in_band && (tail_bits & 2u)),
+                               at = __ballot(in_band && (tail_bits & 4u));
+                if (lane < 3 && i < n_slots)
+                    reinterpret_cast<uint64_t*>(cls)[(i >> 6) * 4 + lane] = lane == 0 ? band : (lane == 1 ? above : at);
+            } else if (i < n_slots) {
+                cls[i] = static_cast<uint8_t>(in_band ? 1u | tail_bits : 0u);
+            }
         }
     }
     __shared__ long long red[4][4];
@@ -1406,29 +1416,30 @@ int64_t stream_adjoint_scratch_bytes(int64_t trials) {
     return 4 * (trials > 0 ? trials : 0) + 256;
 }
 
-hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
-                                 int n_img_parts, const double* S, const double* ylt, const TailStats* tail,
-                                 void* scratch, int64_t scratch_bytes, uint64_t* w_mean, uint64_t* w_tvar,
-                                 long long* agg_mean, long long* agg_tvar, int copies, int stride, int n_cu,
-                                 hipStream_t s) {
+hipError_t launch_stream_classes(const StreamLayout& lay, const LayerArgs& L, const double* S, const double* ylt,
+                                 const TailStats* tail, void* scratch, int64_t scratch_bytes, long long* agg_mean,
+                                 long long* agg_tvar, int copies, int stride, uint64_t* to_clear, int64_t n_clear,
+                                 int n_cu, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
-    if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
-    StreamPassArgs a = pass_args(lay, fold_views(part_scratch, n_img_parts));
+    if (to_clear && lay.G != 64) return hipErrorInvalidValue;
     const int64_t t_lo = L.trial_begin, t_hi = t_lo + L.trial_count, g_lo = first_group(lay, t_lo);
     const int64_t n_slots = (group_end(lay, t_hi) - g_lo) * 64;
     if (n_slots > scratch_bytes) return hipErrorInvalidValue;
-    StreamAdjArgs adj{};
-    adj.cls = static_cast<const uint8_t*>(scratch);
-    adj.w_mean = w_mean;
-    adj.w_tvar = w_tvar;
-    adj.tail = tail;
     // the workgroups of a copy add to the same four sums
     const int64_t cb = std::min((n_slots + 255) / 256, int64_t(n_cu));
     hipLaunchKernelGGL(stream_class_kernel, dim3(static_cast<uint32_t>(cb)), dim3(256), 0, s, S, ylt, tail, L.aggR,
-                       L.aggL, t_lo, t_hi, a.G, g_lo, n_slots, static_cast<uint8_t*>(scratch), agg_mean, agg_tvar,
-                       copies, stride);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+                       L.aggL, t_lo, t_hi, lay.G, g_lo, n_slots, static_cast<uint8_t*>(scratch), agg_mean, agg_tvar,
+                       copies, stride, to_clear, n_clear);
+    return hipGetLastError();
+}
+
+hipError_t launch_stream_adjoint(const StreamLayout& lay, double density, const LayerArgs& L, void* part_scratch,
+                                 int n_img_parts, const uint8_t* cls, const TailStats* tail, uint64_t* w_mean,
+                                 uint64_t* w_tvar, int n_cu, hipStream_t s) {
+    if (L.trial_count <= 0) return hipSuccess;
+    if (lay.P <= 0 || (lay.P - 1) / 4 >= n_img_parts) return hipErrorInvalidValue;
+    StreamPassArgs a = pass_args(lay, fold_views(part_scratch, n_img_parts));
+    const StreamAdjArgs adj{cls, w_mean, w_tvar, tail};
     const StreamUnit u{0, L.trial_begin, L.trial_count, 0, density};
     return launch_pass<true>(lay, a, &u, 1, adj, n_cu, s);
 }

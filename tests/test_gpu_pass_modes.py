@@ -65,6 +65,7 @@ def test_long_dense_trials(ara, n_trials, lam, C, J, nnz):
 # trials (lanes share a trial) and short ones
 @pytest.mark.parametrize("n_trials,lam", [(12_000, 2_000), (800_000, 28)])
 def test_one_event_past_a_counter(ara, n_trials, lam):
+    import torch
     C = 60_000
     yet = make_yet(n_trials, lam, C, seed=lam)
     rng = np.random.default_rng(lam)
@@ -74,11 +75,14 @@ def test_one_event_past_a_counter(ara, n_trials, lam):
     idx = np.arange(3, dtype=np.int32)
     layer = Layer(idx, 0.0, 4.0e6, 1.0, np.inf, 0, n_trials)
     spec = ara.LayerSpec.from_layer(layer, pool, n_trials)
-    tables = ara.create_tables(yet.offsets, yet.ids, pool.losses)
-    assert tables.layout()["stream_parts"] == 1
+    both = ara.create_tables(yet.offsets, yet.ids, pool.losses)
+    # tables without the copy of the events with a loss
+    whole = ara.create_yet(both, torch.from_numpy(yet.offsets).cuda(), torch.from_numpy(yet.ids.view(np.int32)).cuda())
     ref, S = oracle.run_layer(yet, pool, layer)
-    ara.run_layers(tables, [spec], flags=ara.ARA_CHECKPOINT_S)
-    gm, gt = ara.backward(tables, spec, 0.9)
     g = oracle.gradients(yet, pool, layer, 0.9, ylt=ref, S=S)
-    assert np.array_equal(gm, g["grad_mean"]) and np.array_equal(gt, g["grad_tvar"])
-    tables.close()
+    for tables in (whole, both):
+        assert tables.layout()["stream_parts"] == 1
+        ara.run_layers(tables, [spec], flags=ara.ARA_CHECKPOINT_S)
+        gm, gt = ara.backward(tables, spec, 0.9)
+        assert np.array_equal(gm, g["grad_mean"]) and np.array_equal(gt, g["grad_tvar"])
+        tables.close()
