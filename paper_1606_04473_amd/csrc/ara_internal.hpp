@@ -323,7 +323,7 @@ hipError_t launch_loss_adjoint(const StreamLayout& lay, const LossIndex& ix, con
 // the trial classes of a backward over a copy's groups, and the partials of the
 // two aggregate terms to agg_mean[0..1] and agg_tvar[0..1], of one of `copies`
 // copies `stride` apart (summed by the caller).  to_clear: words zeroed on the way;
-// with it (groups of 64 only) the classes are masks, four words a group: the trials
+// with it the classes are masks, four words per 64 trials: the trials
 // inside the band, and of those the ones in the tail above and at its threshold
 hipError_t launch_stream_classes(const StreamLayout& lay, const LayerArgs& L, const double* S, const double* ylt,
                                  const TailStats* tail, void* scratch, int64_t scratch_bytes, long long* agg_mean,

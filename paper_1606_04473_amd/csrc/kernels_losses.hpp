@@ -16,13 +16,18 @@
 // goes through LDS, no lane asks where its trial ends, and the sums leave in
 // consecutive stores.  (Sorting windows of 1024 trials by their counts saves four
 // rows in ten, but then each lane's sum goes to a line of its own: 290 us where this
-// order took 190.)  Parts whose trials are long and few are cut into columns (splits
-// of each trial's events) to fill the chip.  Partial sums per (column, trial) merge as
-// those of the full copy do.
+// order took 190.)  In larger copies a lane holds two trials, one of each half of a
+// group of 128, the shorter ones with the longer ones: a third less padding, and the
+// sums still leave in the group's own lines.  Bit 15 of a row's first slot ends the
+// lane's first trial, those of the others give the trials' places in the group, three
+// bits a row.  Parts whose trials are long and few are cut into columns (splits of each
+// trial's events) to fill the chip.  Partial sums per (column, trial) merge as those of
+// the full copy do.
 //
 // Bound: the rows' bytes and, next to it, 28 fp64 additions and four LDS reads a row.
 // 10^6 trials of 1000 events, 16 tables of 20000 events in 2 * 10^6 (15 % of the
-// events, 1.17 * 10^6 rows, 600 MB): 155 us, 3.9 TB/s; the full copy's pass 590 us.
+// events): 155 us with a trial per lane (600 MB of rows), 128 with two (400 MB); the
+// full copy's pass 590 us.
 // Compiled as a part of kernels_portfolio.hip.
 #pragma once
 
@@ -40,7 +45,8 @@ constexpr int kSlots = kLossSlots;
 constexpr int kSuperEvents = 4096;
 constexpr uint32_t kPadSlot = kSlots - 1;       // always zero, never an event's
 constexpr int kRowIds = 4;                      // slots per lane and row
-constexpr int kTrials = 64;                     // trials of a group, one per lane
+constexpr int kSlotBits = 0x7FFF;               // of a slot's 16 bits; the last is free for marks
+constexpr int kMetaRows = 4;                    // least rows of a group whose lanes hold two trials
 
 // ---------------------------------------------------------------------------
 // the pool's events
@@ -240,7 +246,51 @@ __device__ __forceinline__ void stream_segment(const StreamLayout& in, int p, in
     to = start + ends[i];
 }
 
+// A lane of a paired group holds one trial of its first 64 and one of its last 64, the
+// i-th shortest of the ones with the i-th longest of the others, so that the lanes'
+// rows differ little.  Both trials' slots, and where they are in the group:
+struct Pair {
+    uint32_t from_a, to_a, from_b, to_b;
+    int rows_a, rows_b;                         // the first trial has a row even when empty
+    int pos_a, pos_b;
+};
+__device__ __forceinline__ int rank_of(int v, int lane) {
+    int rank = 0;
+    for (int i = 0; i < 64; ++i) {
+        const int o = __builtin_amdgcn_readlane(v, i);
+        rank += (o < v || (o == v && i < lane)) ? 1 : 0;
+    }
+    return rank;
+}
+__device__ __forceinline__ Pair pair_of(const StreamLayout& in, int p, int64_t t0, int64_t N, int s, int S, int lane) {
+    uint32_t from[2] = {0, 0}, to[2] = {0, 0};
+    int rows[2], rank[2];
+    for (int h = 0; h < 2; ++h) {
+        const int64_t t = t0 + h * 64 + lane;
+        if (t < N) stream_segment(in, p, t, from[h], to[h]);
+        const uint64_t n = to[h] - from[h];
+        to[h] = from[h] + static_cast<uint32_t>(n * (s + 1) / S);
+        from[h] += static_cast<uint32_t>(n * s / S);
+        rows[h] = static_cast<int>(to[h] - from[h] + kRowIds - 1) / kRowIds;
+        if (h == 0 && rows[h] == 0) rows[h] = 1;
+        rank[h] = rank_of(rows[h], lane);
+    }
+    rank[1] = 63 - rank[1];
+    Pair q;
+    auto push = [](int to_lane, int v) { return __builtin_amdgcn_ds_permute(to_lane * 4, v); };
+    q.from_a = static_cast<uint32_t>(push(rank[0], static_cast<int>(from[0])));
+    q.to_a = static_cast<uint32_t>(push(rank[0], static_cast<int>(to[0])));
+    q.rows_a = push(rank[0], rows[0]);
+    q.pos_a = push(rank[0], lane);
+    q.from_b = static_cast<uint32_t>(push(rank[1], static_cast<int>(from[1])));
+    q.to_b = static_cast<uint32_t>(push(rank[1], static_cast<int>(to[1])));
+    q.rows_b = push(rank[1], rows[1]);
+    q.pos_b = push(rank[1], lane);
+    return q;
+}
+
 // one wave per (part, group): the rows of its splits to their places in gstart
+template <bool kPair>
 __global__ __launch_bounds__(256) void loss_group_kernel(StreamLayout in, int64_t N, int S, int64_t NG,
                                                          uint32_t* __restrict__ gstart) {
     const int lane = threadIdx.x & 63;
@@ -248,14 +298,19 @@ __global__ __launch_bounds__(256) void loss_group_kernel(StreamLayout in, int64_
     if (g >= NG) return;
     const int p = static_cast<int>(blockIdx.y);
     uint32_t from = 0, to = 0;
-    if (g * kTrials + lane < N) stream_segment(in, p, g * kTrials + lane, from, to);
+    if (!kPair && g * 64 + lane < N) stream_segment(in, p, g * 64 + lane, from, to);
     const uint64_t n = to - from;
     for (int s = 0; s < S; ++s) {
         uint32_t rows = static_cast<uint32_t>(n * (s + 1) / S - n * s / S + kRowIds - 1) / kRowIds;
+        if constexpr (kPair) {
+            const Pair q = pair_of(in, p, g * 128, N, s, S, lane);
+            rows = static_cast<uint32_t>(q.rows_a + q.rows_b);
+        }
         for (int off = 32; off >= 1; off >>= 1)
             rows = max(rows, static_cast<uint32_t>(__shfl_xor(static_cast<int>(rows), off, 64)));
         // at least one, so that every group ends with a row
-        if (lane == 0) gstart[(static_cast<int64_t>(p) * S + s) * (NG + 1) + g] = max(rows, 1u);
+        if (lane == 0)
+            gstart[(static_cast<int64_t>(p) * S + s) * (NG + 1) + g] = max(rows, static_cast<uint32_t>(kPair ? kMetaRows : 1));
     }
 }
 
@@ -287,7 +342,21 @@ __global__ __launch_bounds__(1024) void loss_scan_kernel(int64_t NG, uint32_t* _
     }
 }
 
-// one wave per (column, group): the rows
+// One wave per (column, group): the rows.  A lane's 16 slots of four rows are two
+// 16-byte loads at the slot's own alignment; what they read past the lane's last slot
+// (inside the copy's padding) is masked.  One load per slot asked the L2 for a line
+// each, as 32 waves' lines do not stay in the first-level cache: 2500 us for 288M
+// slots, this 480.
+struct __attribute__((packed, aligned(2))) FourRows {
+    uint64_t row[4];
+};
+__device__ __forceinline__ uint64_t padded(uint64_t row, uint32_t at, uint32_t to) {
+    constexpr uint64_t kPadRow = kPadSlot * 0x0001000100010001ull;
+    const uint32_t n = at < to ? to - at : 0u;
+    const uint64_t valid = n >= kRowIds ? ~0ull : (1ull << (16 * n)) - 1;
+    return (row & valid) | (kPadRow & ~valid);
+}
+template <bool kPair>
 __global__ __launch_bounds__(256) void loss_rows_kernel(StreamLayout in, int64_t N, int S, int64_t NG,
                                                         const uint32_t* __restrict__ gstart,
                                                         const int64_t* __restrict__ base, uint64_t* __restrict__ out) {
@@ -295,32 +364,49 @@ __global__ __launch_bounds__(256) void loss_rows_kernel(StreamLayout in, int64_t
     const int64_t g = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (g >= NG) return;
     const int q = static_cast<int>(blockIdx.y), p = q / S, s = q - p * S;
-    const int64_t t = g * kTrials + lane;
+    const uint16_t* ids = in.ids + in.part_base[p];
+    const uint32_t r0 = gstart[static_cast<int64_t>(q) * (NG + 1) + g], r1 = gstart[static_cast<int64_t>(q) * (NG + 1) + g + 1];
+    uint64_t* dst = out + (base[q] / (64 * kRowIds) + r0) * 64 + lane;
+    FourRows v;
+    if constexpr (kPair) {
+        const Pair c = pair_of(in, p, g * 128, N, s, S, lane);
+        const int meta = c.pos_a | c.pos_b << 6;
+        // each lane copies its two trials by itself: the second starts where the first ends
+        const int rows = static_cast<int>(r1 - r0);
+        auto put = [&](int r, uint64_t row) {
+            if (r == c.rows_a - 1) row |= 0x8000ull;            // the first trial's last row
+            if (r < kMetaRows) {                                // the trials' places, three bits a row
+                const uint64_t m = static_cast<uint64_t>(meta >> (3 * r) & 7);
+                row |= (m & 1) << 31 | (m & 2) << 46 | (m & 4) << 61;
+            }
+            if (r < rows) dst[static_cast<int64_t>(r) * 64] = row;
+        };
+        for (int r = 0; r < c.rows_a; r += 4) {
+            const uint32_t at = c.from_a + static_cast<uint32_t>(r) * kRowIds;
+            __builtin_memcpy(&v, ids + min(at, c.to_a), sizeof(v));
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (r + k < c.rows_a) put(r + k, padded(v.row[k], at + k * kRowIds, c.to_a));
+        }
+        for (int r = 0; r < rows - c.rows_a; r += 4) {
+            const uint32_t at = c.from_b + static_cast<uint32_t>(r) * kRowIds;
+            __builtin_memcpy(&v, ids + min(at, c.to_b), sizeof(v));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put(c.rows_a + r + k, padded(v.row[k], at + k * kRowIds, c.to_b));
+        }
+        return;
+    }
+    const int64_t t = g * 64 + lane;
     uint32_t from = 0, to = 0;
     if (t < N) stream_segment(in, p, t, from, to);
     const uint64_t n = to - from;
     to = from + static_cast<uint32_t>(n * (s + 1) / S);
     from += static_cast<uint32_t>(n * s / S);
-    const uint16_t* ids = in.ids + in.part_base[p];
-    const uint32_t r0 = gstart[static_cast<int64_t>(q) * (NG + 1) + g], r1 = gstart[static_cast<int64_t>(q) * (NG + 1) + g + 1];
-    uint64_t* dst = out + (base[q] / (64 * kRowIds) + r0) * 64 + lane;
-    // Four rows at a time, each lane's 16 slots in two 16-byte loads at the ID's own
-    // alignment; what they read past the lane's last slot (inside the copy's padding)
-    // is masked.  One load per slot asked the L2 for a line each, as 32 waves' lines
-    // do not stay in the first-level cache: 2500 us for 288M slots, this 480.
-    struct __attribute__((packed, aligned(2))) Slots {
-        uint64_t row[4];
-    };
-    constexpr uint64_t kPadRow = kPadSlot * 0x0001000100010001ull;
     for (uint32_t r = r0; r < r1; r += 4, from += 4 * kRowIds, dst += 4 * 64) {
-        Slots v;
         __builtin_memcpy(&v, ids + min(from, to), sizeof(v));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t at = from + k * kRowIds, n = at < to ? to - at : 0u;
-            const uint64_t valid = n >= kRowIds ? ~0ull : (1ull << (16 * n)) - 1;
-            if (r + k < r1) dst[64 * k] = (v.row[k] & valid) | (kPadRow & ~valid);
-        }
+        for (int k = 0; k < 4; ++k)
+            if (r + k < r1) dst[64 * k] = padded(v.row[k], from + k * kRowIds, to);
     }
 }
 
@@ -343,7 +429,7 @@ struct LossSegs {
     LossSeg seg[kMaxSegs];
 };
 struct LossPassArgs {
-    const uint64_t* rows;           // [row][64]: four slots of each lane's trial
+    const uint64_t* rows;           // [row][64]: four slots of each lane's trial (or trials)
     const int64_t* col_base;        // a column's first slot in the copy (64 x 4 to a row)
     const double* tab;              // [layer][part][kSlots]
     const uint32_t* part_n;         // slots in use of each part
@@ -356,22 +442,25 @@ struct LossPassArgs {
 struct LossAdjArgs {
     uint32_t* counts;               // [workgroup + part][kSlots]: what a workgroup counted in a part
     uint64_t* w_tvar;               // [part][kSlots], zeroed by the caller
+    int64_t masks_lo, masks_n;      // the 64-trial groups that have class masks
     const TailStats* tail;
 };
 
 // The forward (kAdj false) sums; the backward counts the occurrences of each slot
 // in the trials inside the aggregate band in LDS.  A wave takes consecutive groups
-// of a column, whose rows lie one after the other: eight rows are always in flight,
+// of a column, whose rows lie one after the other: eight rows are in flight (twelve in
+// paired groups, which read the places from a group's first four when it starts),
 // whatever group they belong to, as nothing but their loads and the groups' stores
 // uses the vector memory counter (group ends and class masks are scalar loads) and
 // the loop leaves in whole rounds only.  With a group's first rows read ahead and
 // its others on their own, the forward above took 260 us and its backward at half
-// the trials 160, now 155 and 75.
-template <bool kAdj>
+// the trials 160, with the ring of rows 155 and 75, in paired groups 128 and 66.
+template <bool kAdj, bool kPair>
 __global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSegs segs, LossAdjArgs adj,
                                                          const uint32_t* __restrict__ gstart,
                                                          const uint64_t* __restrict__ cls_masks) {
-    constexpr int kAhead = 8;                       // rows read ahead
+    constexpr int kAhead = kPair ? 12 : 8;          // rows read ahead
+    constexpr int kTrials = kPair ? 128 : 64;       // of a group
     __shared__ __attribute__((aligned(16))) uint8_t lds[(kAdj ? 4 : 8) * kSlots];
     double* vals = reinterpret_cast<double*>(lds);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);
@@ -448,7 +537,7 @@ __global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSeg
             auto add_row = [&](uint64_t x, uint32_t cls) {
                 uint32_t e[kRowIds];
 #pragma unroll
-                for (int i = 0; i < kRowIds; ++i) e[i] = static_cast<uint32_t>(x >> (16 * i)) & 0xFFFFu;
+                for (int i = 0; i < kRowIds; ++i) e[i] = static_cast<uint32_t>(x >> (16 * i)) & (kPair ? kSlotBits : 0xFFFF);
                 if constexpr (kAdj) {
                     if (!(cls & 1u)) return;        // outside the aggregate band: no weight
 #pragma unroll
@@ -470,43 +559,84 @@ __global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSeg
                     for (int i = 0; i < kRowIds; ++i) dd_add(acc_hi, acc_lo, v[i]);
                 }
             };
-            // the backward's trial classes, a mask per class and group: scalar loads too, so
-            // that no load but the rows' is waited for
+            // the backward's trial classes, a mask per class and 64 trials: scalar loads too,
+            // so that no load but the rows' is waited for
             struct Masks {
                 uint64_t band, above, at;
-            } masks{}, masks_next{};
-            auto masks_of = [&](int64_t grp) {
-                const uint64_t* m = cls_masks + (min(grp, g_end - 1) - sgm.g_lo) * 4;
-                return Masks{m[0], m[1], m[2]};
+            } masks[2]{}, masks_next[2]{};
+            auto masks_of = [&](int64_t grp, Masks(&to)[2]) {
+                for (int h = 0; h < (kPair ? 2 : 1); ++h) {
+                    const int64_t k = grp * (kTrials / 64) + h - adj.masks_lo;
+                    const bool in = k >= 0 && k < adj.masks_n;
+                    const uint64_t* m = cls_masks + (in ? k : 0) * 4;
+                    to[h] = Masks{in ? m[0] : 0, in ? m[1] : 0, in ? m[2] : 0};
+                }
             };
-            auto class_of = [&](const Masks& m) -> uint32_t {
-                return static_cast<uint32_t>(m.band >> lane & 1u) | static_cast<uint32_t>(m.above >> lane & 1u) << 1 |
-                       static_cast<uint32_t>(m.at >> lane & 1u) << 2;
+            auto class_of = [&](const Masks& m, int pos) -> uint32_t {
+                return static_cast<uint32_t>(m.band >> pos & 1u) | static_cast<uint32_t>(m.above >> pos & 1u) << 1 |
+                       static_cast<uint32_t>(m.at >> pos & 1u) << 2;
             };
-            uint32_t cls = 0;
             if constexpr (kAdj) {
-                cls = class_of(masks_of(g));
-                masks_next = masks_of(g + 1);
+                masks_of(g, masks);
+                masks_of(g + 1, masks_next);
             }
+            // where a lane's trials are in the group, and their classes
+            int pos_a = lane, pos_b = 0;
+            uint32_t cls = 0, cls_b = 0;
+            auto start_group = [&](uint64_t y0, uint64_t y1, uint64_t y2, uint64_t y3) {
+                if constexpr (kPair) {
+                    auto m = [](uint64_t y) {
+                        return static_cast<int>((y >> 31 & 1) | (y >> 46 & 2) | (y >> 61 & 4));
+                    };
+                    pos_a = m(y0) | m(y1) << 3;
+                    pos_b = m(y2) | m(y3) << 3;
+                }
+                if constexpr (kAdj) {
+                    cls = class_of(masks[0], pos_a);
+                    if constexpr (kPair) cls_b = class_of(masks[1], pos_b);
+                }
+            };
             // where the group ends and the next one does (scalar loads, one group ahead)
             uint32_t r = gs[g], end = gs[g + 1], next = gs[min(g + 2, g_end)];
             uint64_t x[kAhead];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) x[k] = row(r + k);
-            // whole rounds of kAhead rows; those past the last group add to no group
+            start_group(x[0], x[1], x[2], x[3]);
+            double first_hi = 0.0, first_lo = 0.0;  // a pair's first trial
+            auto store = [&](int64_t t, double sum_hi, double sum_lo) {
+                const double hi = sum_hi + sum_lo;                      // renormalised: |lo| <= ulp(hi) / 2
+                if (t >= t_lo && t < t_hi) {
+                    out_hi[t - t_lo] = hi;
+                    out_lo[t - t_lo] = static_cast<float>(sum_lo - (hi - sum_hi));
+                }
+            };
+            // whole rounds of kAhead rows, the last one's past the last group left out
             for (uint32_t left = gs[g_end] - r + kAhead - 1; left >= kAhead; left -= kAhead) {
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) {
                     const uint64_t y = x[k];
                     x[k] = row(r + kAhead);
+                    if (r > r_last) continue;           // past the wave's groups
                     add_row(y, cls);
-                    if (++r != end) continue;
+                    if constexpr (kPair) {
+                        const bool ends = y & 0x8000u;                  // the lane's first trial
+                        if constexpr (kAdj) {
+                            cls = ends ? cls_b : cls;
+                        } else {
+                            first_hi = ends ? acc_hi : first_hi;
+                            first_lo = ends ? acc_lo : first_lo;
+                            acc_hi = ends ? 0.0 : acc_hi;
+                            acc_lo = ends ? 0.0 : acc_lo;
+                        }
+                    }
+                    ++r;
+                    if (r != end) continue;
                     if constexpr (!kAdj) {
-                        const double hi = acc_hi + acc_lo;              // renormalised: |lo| <= ulp(hi) / 2
-                        const int64_t t = g * kTrials + lane;
-                        if (t >= t_lo && t < t_hi) {
-                            out_hi[t - t_lo] = hi;
-                            out_lo[t - t_lo] = static_cast<float>(acc_lo - (hi - acc_hi));
+                        if constexpr (kPair) {
+                            store(g * kTrials + pos_a, first_hi, first_lo);
+                            store(g * kTrials + 64 + pos_b, acc_hi, acc_lo);
+                        } else {
+                            store(g * kTrials + lane, acc_hi, acc_lo);
                         }
                         acc_hi = 0.0;
                         acc_lo = 0.0;
@@ -515,10 +645,10 @@ __global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSeg
                     end = g < g_end ? next : ~0u;
                     next = gs[min(g + 2, g_end)];
                     if constexpr (kAdj) {
-                        masks = masks_next;
-                        masks_next = masks_of(g + 1);
-                        cls = g < g_end ? class_of(masks) : 0u;
+                        for (int h = 0; h < 2; ++h) masks[h] = g < g_end ? masks_next[h] : Masks{0, 0, 0};
+                        masks_of(g + 1, masks_next);
                     }
+                    start_group(x[(k + 1) % kAhead], x[(k + 2) % kAhead], x[(k + 3) % kAhead], x[(k + 4) % kAhead]);
                 }
             }
         }
@@ -553,9 +683,6 @@ __global__ __launch_bounds__(256) void loss_counts_kernel(LossPassArgs a, int64_
     w_tvar[E] = tvar[static_cast<int64_t>(part) * kSlots + i];
 }
 
-int64_t first_group(int64_t t_lo) { return t_lo / kTrials; }
-int64_t group_end(int64_t t_hi) { return (t_hi + kTrials - 1) / kTrials; }
-
 // one 1024-thread workgroup per CU (its LDS holds the part's table or counters)
 int64_t pass_grid(int n_cu) {
     const int64_t grid = int64_t(n_cu) - n_cu % kXcds;
@@ -566,7 +693,8 @@ template <bool kAdj>
 hipError_t launch_pass(const StreamLayout& lay, const LossIndex& ix, const StreamUnit* units, int n, const double* tab,
                        void* partials, const LossAdjArgs& adj, const uint64_t* masks, uint64_t* w_mean,
                        uint64_t* w_tvar, int n_cu, hipStream_t s) {
-    if (n < 1 || n > kMaxSegs || lay.P <= 0 || ix.P <= 0 || lay.P % ix.P) return hipErrorInvalidValue;
+    if (n < 1 || n > kMaxSegs || lay.P <= 0 || ix.P <= 0 || lay.P % ix.P || (lay.G != 64 && lay.G != 128))
+        return hipErrorInvalidValue;
     LossPassArgs a{};
     a.rows = reinterpret_cast<const uint64_t*>(lay.ids);
     a.col_base = lay.part_base;
@@ -587,8 +715,8 @@ hipError_t launch_pass(const StreamLayout& lay, const LossIndex& ix, const Strea
         LossSeg& g = segs.seg[i];
         g.t_lo = units[i].t_lo;
         g.t_hi = units[i].t_lo + units[i].count;
-        g.g_lo = first_group(g.t_lo);
-        g.groups = group_end(g.t_hi) - g.g_lo;
+        g.g_lo = g.t_lo / lay.G;
+        g.groups = (g.t_hi + lay.G - 1) / lay.G - g.g_lo;
         g.w0 = a.work;
         g.part_at = at;
         g.layer = units[i].layer;
@@ -600,8 +728,8 @@ hipError_t launch_pass(const StreamLayout& lay, const LossIndex& ix, const Strea
         grid = std::min(grid, std::max<int64_t>(a.work / 16, 1));
         if (grid > kXcds) grid -= grid % kXcds;
     }
-    hipLaunchKernelGGL(loss_pass_kernel<kAdj>, dim3(static_cast<uint32_t>(grid)), dim3(1024), 0, s, a, segs, adj,
-                       lay.gstart, masks);
+    hipLaunchKernelGGL((lay.G == 128 ? loss_pass_kernel<kAdj, true> : loss_pass_kernel<kAdj, false>),
+                       dim3(static_cast<uint32_t>(grid)), dim3(1024), 0, s, a, segs, adj, lay.gstart, masks);
     hipError_t e = hipGetLastError();
     if (!kAdj || e != hipSuccess) return e;
     hipLaunchKernelGGL(loss_counts_kernel, dim3(kSlots / 256, static_cast<uint32_t>(a.P)), dim3(256), 0, s, a,
@@ -619,18 +747,28 @@ int splits_of(int P, int64_t N, int64_t kept, int n_cu) {
     return static_cast<int>(std::max(1.0, std::min(want, 64.0)));
 }
 
+// Two trials per lane (calls in us, one and two): from 3 slots per trial and column on,
+// below which a group's least rows are longer than it, while padding is much of a row
+// (up to 64 slots), and where the copy has two groups of 128 for each of the chip's
+// waves: 10^6 trials 249 / 215, 12 layers of a library 1030 / 872, 16 layers over 16778
+// trials 160 / 183 (a wave's last group is a larger part of its share).
+constexpr double kPairLeast = 3.0, kPairMost = 64.0;
+
 // the copy from the intermediate one, unless it takes more than `most` bytes
 hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t most, int n_cu, hipStream_t s,
                       StreamLayout* out) {
     const int S = splits_of(in.P, N, kept, n_cu), Q = in.P * S;
-    const int64_t NG = (N + kTrials - 1) / kTrials;
+    const double lam = static_cast<double>(kept) / (static_cast<double>(N) * Q);
+    const bool pair = lam >= kPairLeast && lam <= kPairMost && Q * (N / 128) >= 32 * int64_t(n_cu);
+    const int G = pair ? 128 : 64;
+    const int64_t NG = (N + G - 1) / G;
     std::vector<int64_t> base(Q + 1);
     int64_t* rows = nullptr;
     hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * Q * (NG + 1), s);
     if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (Q + 1), s);
     if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&rows), sizeof(int64_t) * Q, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(loss_group_kernel, dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(in.P)),
+        hipLaunchKernelGGL((pair ? loss_group_kernel<true> : loss_group_kernel<false>), dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(in.P)),
                            dim3(256), 0, s, in, N, S, NG, out->gstart);
         e = hipGetLastError();
     }
@@ -657,7 +795,7 @@ hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t m
     if (e == hipSuccess)
         e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (out->length + 64 * kRowIds), s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(loss_rows_kernel, dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(Q)),
+        hipLaunchKernelGGL((pair ? loss_rows_kernel<true> : loss_rows_kernel<false>), dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(Q)),
                            dim3(256), 0, s, in, N, S, NG, out->gstart, out->part_base,
                            reinterpret_cast<uint64_t*>(out->ids));
         e = hipGetLastError();
@@ -665,7 +803,7 @@ hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t m
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     out->P = Q;
-    out->G = kTrials;
+    out->G = G;
     out->NG = NG;
     out->bytes = static_cast<int64_t>(sizeof(uint16_t)) * (out->length + 64 * kRowIds) +
                  static_cast<int64_t>(sizeof(uint32_t)) * Q * (NG + 1) + static_cast<int64_t>(sizeof(int64_t)) * (Q + 1);
@@ -693,7 +831,8 @@ hipError_t launch_loss_adjoint(const StreamLayout& lay, const LossIndex& ix, con
                                hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
     uint64_t* tvar = static_cast<uint64_t*>(scratch);
-    const LossAdjArgs adj{reinterpret_cast<uint32_t*>(tvar + loss_tvar_words(ix)), tvar, tail};
+    const int64_t m_lo = L.trial_begin / 64, m_hi = (L.trial_begin + L.trial_count + 63) / 64;
+    const LossAdjArgs adj{reinterpret_cast<uint32_t*>(tvar + loss_tvar_words(ix)), tvar, m_lo, m_hi - m_lo, tail};
     const StreamUnit u{0, L.trial_begin, L.trial_count, 0, 0.0};
     return launch_pass<true>(lay, ix, &u, 1, nullptr, nullptr, adj, masks, w_mean, w_tvar, n_cu, s);
 }

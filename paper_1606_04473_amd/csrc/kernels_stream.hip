@@ -1421,14 +1421,15 @@ hipError_t launch_stream_classes(const StreamLayout& lay, const LayerArgs& L, co
                                  long long* agg_tvar, int copies, int stride, uint64_t* to_clear, int64_t n_clear,
                                  int n_cu, hipStream_t s) {
     if (L.trial_count <= 0) return hipSuccess;
-    if (to_clear && lay.G != 64) return hipErrorInvalidValue;
-    const int64_t t_lo = L.trial_begin, t_hi = t_lo + L.trial_count, g_lo = first_group(lay, t_lo);
-    const int64_t n_slots = (group_end(lay, t_hi) - g_lo) * 64;
+    // (the masks are of 64 trials, whatever the copy's groups)
+    const int G = to_clear ? 64 : lay.G;
+    const int64_t t_lo = L.trial_begin, t_hi = t_lo + L.trial_count, g_lo = t_lo / G;
+    const int64_t n_slots = ((t_hi + G - 1) / G - g_lo) * 64;
     if (n_slots > scratch_bytes) return hipErrorInvalidValue;
     // the workgroups of a copy add to the same four sums
     const int64_t cb = std::min((n_slots + 255) / 256, int64_t(n_cu));
     hipLaunchKernelGGL(stream_class_kernel, dim3(static_cast<uint32_t>(cb)), dim3(256), 0, s, S, ylt, tail, L.aggR,
-                       L.aggL, t_lo, t_hi, lay.G, g_lo, n_slots, static_cast<uint8_t*>(scratch), agg_mean, agg_tvar,
+                       L.aggL, t_lo, t_hi, G, g_lo, n_slots, static_cast<uint8_t*>(scratch), agg_mean, agg_tvar,
                        copies, stride, to_clear, n_clear);
     return hipGetLastError();
 }

@@ -1,7 +1,7 @@
 """The copy of the events with a loss in some table: its parts' boundary (20479
-events), its groups of 64 trials, trials split into columns, unions of one event
-and of none, each way of finding an event's slot at creation, empty trials.  Year
-losses and gradients equal the oracle's and those of tables without that copy
+events), its groups of 64 trials and of 128 in pairs, trials split into columns,
+unions of one event and of none, each way of finding an event's slot at creation,
+empty trials.  Year losses and gradients equal the oracle's and those of tables without that copy
 (losses are whole numbers, so every order of a sum gives the same)."""
 
 import numpy as np
@@ -30,6 +30,10 @@ pytestmark = pytest.mark.gpu
     (400, 3_000, 1_300_000, [50]),                          # a bit per two events
     (400, 3_000, 3_000_000, [25]),                          # per four
     (200, 4_000, 5_200_000, [13]),                          # no map
+    (1_048_576, 4, 9_000, [4096]),                          # pairs: whole groups, short
+    (1_048_703, 8, 9_000, [3000, 0]),                       # a group of 127
+    (300_001, 30, 90_000, [4096]),                          # several parts, a group of 97
+    (1_100_001, 5, 9_000, [3500, 1]),                       # a group of 97, empty trials
 ])
 def test_against_the_whole_copy(n_trials, lam, C, union):
     import torch
