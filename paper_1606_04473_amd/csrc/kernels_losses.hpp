@@ -434,6 +434,7 @@ struct LossPassArgs {
     const double* tab;              // [layer][part][kSlots]
     const uint32_t* part_n;         // slots in use of each part
     int Q, S, P, n_seg;             // columns, columns per part, parts
+    int whole;                      // a workgroup's share lies in one part (whole_share)
     int64_t NG;
     int64_t work;
     double* part_hi;
@@ -445,6 +446,18 @@ struct LossAdjArgs {
     int64_t masks_lo, masks_n;      // the 64-trial groups that have class masks
     const TailStats* tail;
 };
+
+// Workgroups [p n_wg / P, (p + 1) n_wg / P) share part p's items evenly: each loads (or
+// clears and stores) one table, and its waves' shares are not cut at a part's end.
+// Passes in us, cut where the part ends and whole: 100003 trials of 500 events in 21
+// parts 45.3 / 39.1, 10^6 in 15 parts 129.7 / 124.5, 500000 71.8 / 67.8, their backward
+// 62.8 / 59.7; with a group or two per wave the divisions cost more (7.9 / 8.9).
+__device__ __host__ __forceinline__ int64_t first_wg(int64_t p, int64_t n_wg, int P) { return (p * n_wg + P - 1) / P; }
+__device__ __forceinline__ void whole_share(int64_t l, int64_t n_wg, int P, int64_t items, int64_t& begin, int64_t& end) {
+    const int64_t p = l * P / n_wg, f = first_wg(p, n_wg, P), c = first_wg(p + 1, n_wg, P) - f;
+    begin = p * items + (l - f) * items / c;
+    end = p * items + (l - f + 1) * items / c;
+}
 
 // The forward (kAdj false) sums; the backward counts the occurrences of each slot
 // in the trials inside the aggregate band in LDS.  A wave takes consecutive groups
@@ -472,7 +485,8 @@ __global__ __launch_bounds__(1024) void loss_pass_kernel(LossPassArgs a, LossSeg
     const int64_t n_wg = gridDim.x;
     const int64_t l = n_wg % kXcds ? static_cast<int64_t>(blockIdx.x)
                                    : static_cast<int64_t>(blockIdx.x % kXcds) * (n_wg / kXcds) + blockIdx.x / kXcds;
-    const int64_t w_begin = l * a.work / n_wg, w_end = (l + 1) * a.work / n_wg;
+    int64_t w_begin = l * a.work / n_wg, w_end = (l + 1) * a.work / n_wg;
+    if (a.whole) whole_share(l, n_wg, a.P, a.work / a.P, w_begin, w_end);
     int held = -1;                                  // the part whose table (counters) LDS holds
     int64_t held_layer = -1;
     auto flush_counts = [&] {
@@ -673,7 +687,8 @@ __global__ __launch_bounds__(256) void loss_counts_kernel(LossPassArgs a, int64_
     if (i >= a.part_n[part]) return;
     // workgroup l's items are [l work / n_wg, (l + 1) work / n_wg), not empty
     const int64_t first = static_cast<int64_t>(part) * a.S * groups, last = first + static_cast<int64_t>(a.S) * groups - 1;
-    const int64_t l0 = ((first + 1) * n_wg - 1) / a.work, l1 = ((last + 1) * n_wg - 1) / a.work;
+    const int64_t l0 = a.whole ? first_wg(part, n_wg, a.P) : ((first + 1) * n_wg - 1) / a.work;
+    const int64_t l1 = a.whole ? first_wg(part + 1, n_wg, a.P) - 1 : ((last + 1) * n_wg - 1) / a.work;
     uint64_t sum = 0;
     const uint32_t* c = counts + (l0 + part) * kSlots + i;
 #pragma unroll 8
@@ -728,6 +743,9 @@ hipError_t launch_pass(const StreamLayout& lay, const LossIndex& ix, const Strea
         grid = std::min(grid, std::max<int64_t>(a.work / 16, 1));
         if (grid > kXcds) grid -= grid % kXcds;
     }
+    // where there are three groups per wave and the shares stay within 6 % of even
+    const int64_t each = grid / a.P;
+    a.whole = n == 1 && a.P > 1 && a.work >= 48 * grid && grid <= 1.06 * static_cast<double>(each * a.P);
     hipLaunchKernelGGL((lay.G == 128 ? loss_pass_kernel<kAdj, true> : loss_pass_kernel<kAdj, false>),
                        dim3(static_cast<uint32_t>(grid)), dim3(1024), 0, s, a, segs, adj, lay.gstart, masks);
     hipError_t e = hipGetLastError();
