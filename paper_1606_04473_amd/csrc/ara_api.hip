@@ -637,6 +637,16 @@ bool losses_faster(const ara_tables* t, const ara::LayerArgs* L, int64_t n) {
     return losses_faster(t, trials, dense);
 }
 
+// A call that finds no memory for its scratch over that copy, which may have more parts,
+// runs over the whole one: f(whether that copy may be used).
+template <class F>
+ara_status on_either_copy(const ara_tables* t, F f) {
+    const ara_status st = f(true);
+    if (st != ARA_ERR_NO_MEMORY || !t || t->losses.P == 0) return st;
+    (void)hipGetLastError();
+    return f(false);
+}
+
 // The passes that write per-(part, trial) partial sums for a merge: the
 // streaming pass over a 16-bit part-major copy (default; the whole one, or the
 // pool's events alone), or the XCD-affine pass over the 32-bit partitioned copy
@@ -1202,8 +1212,8 @@ ara_status ara_metrics_footprint(int64_t n_trials, int32_t n_probs, uint32_t fla
     return ARA_OK;
 }
 
-ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_layers, double* ylt,
-                          int64_t ylt_capacity, uint32_t flags, void* stream) {
+static ara_status run_layers(ara_tables* t, const ara_layer* layers, int32_t n_layers, double* ylt,
+                             int64_t ylt_capacity, uint32_t flags, void* stream, bool by_losses) {
     if (!t || !layers || n_layers < 1) return fail(ARA_ERR_INVALID_ARG, "NULL argument or no layer");
     if (flags & ARA_CHECKPOINT_STRIDE) flags |= ARA_CHECKPOINT_S;
     const bool ckpt = (flags & ARA_CHECKPOINT_S) != 0;
@@ -1248,7 +1258,7 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     // with the compact value array
     const bool use_xcd = use_parts && tu.pass_variant != 1;
     // (the stride checkpoints read the part images of the whole copy's fold)
-    const SplitPass split(t, tu, !(flags & ARA_CHECKPOINT_STRIDE) && losses_faster(t, L.data(), n_layers));
+    const SplitPass split(t, tu, by_losses && !(flags & ARA_CHECKPOINT_STRIDE) && losses_faster(t, L.data(), n_layers));
     const bool use_stream = use_xcd && split.stream;
     // several layers run as one persistent rank-based launch with pass_variant
     // 1; with the streaming (default) or XCD-affine pass they run one launch
@@ -1524,8 +1534,15 @@ ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_laye
     return ARA_OK;
 }
 
-ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t n_programs, int32_t n_splits,
-                             const ara_portfolio_out* out, uint32_t flags, void* stream) {
+ara_status ara_run_layers(ara_tables* t, const ara_layer* layers, int32_t n_layers, double* ylt,
+                          int64_t ylt_capacity, uint32_t flags, void* stream) {
+    return on_either_copy(t, [&](bool by_losses) {
+        return run_layers(t, layers, n_layers, ylt, ylt_capacity, flags, stream, by_losses);
+    });
+}
+
+static ara_status run_portfolio(ara_tables* t, const ara_program* programs, int32_t n_programs, int32_t n_splits,
+                                const ara_portfolio_out* out, uint32_t flags, void* stream, bool by_losses) {
     if (!t || !programs || !out) return fail(ARA_ERR_INVALID_ARG, "NULL argument");
     if (n_programs < 1) return fail(ARA_ERR_INVALID_ARG, "a portfolio needs at least one program");
     if (n_programs > ARA_MAX_PROGRAMS)
@@ -1577,7 +1594,7 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
     }
     const bool use_parts = !literal && t->parts.P > 0;
     const bool use_xcd = use_parts && tu.pass_variant != 1;
-    const SplitPass split(t, tu, losses_faster(t, L.data(), n_layers));
+    const SplitPass split(t, tu, by_losses && losses_faster(t, L.data(), n_layers));
     // split i covers [b(i), b(i + 1)): Algorithm 1's YET_i
     auto split_at = [&](int64_t i) { return begin + (n * i) / n_splits; };
     int64_t most = 0;
@@ -1703,6 +1720,13 @@ ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t
     return ARA_OK;
 }
 
+ara_status ara_run_portfolio(ara_tables* t, const ara_program* programs, int32_t n_programs, int32_t n_splits,
+                             const ara_portfolio_out* out, uint32_t flags, void* stream) {
+    return on_either_copy(t, [&](bool by_losses) {
+        return run_portfolio(t, programs, n_programs, n_splits, out, flags, stream, by_losses);
+    });
+}
+
 ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* probs, int32_t n_probs,
                             double* mean_out, double* pml_out, double* tvar_out, uint32_t flags, void* stream) {
     if (!ylt || !mean_out || n_probs < 0 || (n_probs > 0 && (!probs || !pml_out || !tvar_out)))
@@ -1764,8 +1788,8 @@ ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* p
     return ARA_OK;
 }
 
-ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* probs, int32_t n_probs, double* ylt,
-                       int64_t ylt_capacity, double* metrics, uint32_t flags, void* stream) {
+static ara_status analyze(ara_tables* t, const ara_layer* layer, const double* probs, int32_t n_probs, double* ylt,
+                          int64_t ylt_capacity, double* metrics, uint32_t flags, void* stream, bool by_losses) {
     if (!t || !layer || !ylt || !metrics || n_probs < 0 || (n_probs > 0 && !probs))
         return fail(ARA_ERR_INVALID_ARG, "NULL argument");
     if (n_probs > 4) return fail(ARA_ERR_UNSUPPORTED, "at most 4 probabilities per call");
@@ -1806,7 +1830,7 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
     if (!ds.ok) return fail(ARA_ERR_DEVICE, "cannot select the tables' device");
     hipStream_t s = static_cast<hipStream_t>(stream);
     UseFence use_fence(t, s);           // the tables' memory outlives this call's work
-    const SplitPass split(t, tu, losses_faster(t, &L, 1));
+    const SplitPass split(t, tu, by_losses && losses_faster(t, &L, 1));
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     const size_t la_bytes = up(sizeof(ara::LayerArgs));
     const size_t o_bytes = up(sizeof(double) * t->C);
@@ -1873,6 +1897,13 @@ ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* prob
     return ARA_OK;
 }
 
+ara_status ara_analyze(ara_tables* t, const ara_layer* layer, const double* probs, int32_t n_probs, double* ylt,
+                       int64_t ylt_capacity, double* metrics, uint32_t flags, void* stream) {
+    return on_either_copy(t, [&](bool by_losses) {
+        return analyze(t, layer, probs, n_probs, ylt, ylt_capacity, metrics, flags, stream, by_losses);
+    });
+}
+
 ara_status ara_risk_metrics_noalloc(const double* ylt, int64_t n_trials, const double* probs, int32_t n_probs,
                                     double* mean_out, double* pml_out, double* tvar_out, void* stream) {
     if (!ylt || !mean_out || n_probs < 0 || (n_probs > 0 && (!probs || !pml_out || !tvar_out)))
@@ -1900,8 +1931,8 @@ ara_status ara_risk_metrics_noalloc(const double* ylt, int64_t n_trials, const d
     return ARA_OK;
 }
 
-ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, double* grad_mean,
-                        double* grad_tvar, uint32_t flags, void* stream) {
+static ara_status backward(ara_tables* t, const ara_layer* layer, double tvar_p, double* grad_mean,
+                           double* grad_tvar, uint32_t flags, void* stream, bool by_losses) {
     if (!t || !layer) return fail(ARA_ERR_INVALID_ARG, "NULL argument");
     if (!(tvar_p > 0.0 && tvar_p < 1.0)) return fail(ARA_ERR_INVALID_ARG, "tvar_p must lie in (0, 1)");
     ara::LayerArgs L;
@@ -1934,7 +1965,7 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
     // pass_variant 0: the histogram streams the 16-bit copy when the tables
     // hold one; else the XCD-affine pass over the 32-bit partitioned copy
     const bool use_stream = use_parts && t->tuning.pass_variant == 0 && t->stream.P > 0;
-    const bool use_losses = use_stream && t->sparse.chunk_off && losses_faster(t, &L, 1);
+    const bool use_losses = by_losses && use_stream && t->sparse.chunk_off && losses_faster(t, &L, 1);
     if (use_parts) {
         const ara_tuning tu = t->tuning;   // t->mu is held
         if (use_losses)                 // that copy's histogram needs no images
@@ -1966,6 +1997,13 @@ ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, do
         if (grad_tvar) std::memcpy(grad_tvar, h.data() + P, sizeof(double) * P);
     }
     return ARA_OK;
+}
+
+ara_status ara_backward(ara_tables* t, const ara_layer* layer, double tvar_p, double* grad_mean,
+                        double* grad_tvar, uint32_t flags, void* stream) {
+    return on_either_copy(t, [&](bool by_losses) {
+        return backward(t, layer, tvar_p, grad_mean, grad_tvar, flags, stream, by_losses);
+    });
 }
 
 ara_status ara_debug_lookups(ara_tables* t, const ara_layer* layer, int64_t trial, uint32_t* ids_out,
