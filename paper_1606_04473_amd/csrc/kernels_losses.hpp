@@ -146,7 +146,7 @@ __global__ __launch_bounds__(64) void loss_place_kernel(int64_t C, int most_part
 // (cnt[t][part]).  A probe word is a gather from
 // L2, 64 lines an instruction: 5.2 ms per 1e9 events with a gather each.  So a
 // workgroup holds a map with a bit per 2^shift events in LDS and gathers the words of
-// the events whose bit is set (the other lanes share the first word's line): 1.5 ms
+// the events whose bit is set (the other lanes share the first word's line): 2.1 ms
 // at 15 % of the events.  shift < 0: no map (a catalogue past kMapShift bits).
 constexpr int kMapWords = 39936;                // 156 KB
 constexpr int kMapShift = 2;
