@@ -614,14 +614,16 @@ double layer_density(const ara_tables* t, const ara::LayerArgs& L) {
 // over 64 tables, a layer of 1: 103 / 115 us where 47 % of the events are in the pool
 // (47 parts / 31), 124 / 107 where 73 % are (36 / 16); 16 tables of 16, 15 % of the
 // events, 10^6 trials: 155 / 590; whole calls: 554 trials of 38 events 44 / 52 us,
-// 20000 of 300 over a pool of 92 %, with the backward: 119 / 104.
+// 20000 of 300 over a pool of 92 %, with the backward: 119 / 104, the 73 % above, with
+// two trials per lane: 167 / 159.
 bool losses_faster(const ara_tables* t, double trials, double dense) {
     if (t->losses.P <= 0 || trials <= 0.0) return t->losses.P > 0;
     const double per_trial = static_cast<double>(t->n_events) / static_cast<double>(t->n_trials);
     const double rows = static_cast<double>(t->losses.length) / 256.0 * (trials / static_cast<double>(t->n_trials));
     const double groups = t->losses.P * std::ceil(trials / 64.0);
+    const double row = t->losses.G == 128 ? 0.127e-3 : 0.104e-3;        // two trials per lane: fewer rows
     auto merge = [&](int parts) { return std::max(1.75e-6 * parts * trials, 0.31 * parts); };
-    const double here = (t->loss_index.P > 1 && groups > t->n_cu ? 4.0 : 0.0) + 0.104e-3 * rows + 0.078e-3 * groups +
+    const double here = (t->loss_index.P > 1 && groups > t->n_cu ? 4.0 : 0.0) + row * rows + 0.078e-3 * groups +
                         merge(t->losses.P);
     const double full = 5.0 + 19.0 * std::min(1.0, trials / 2e5) + 0.3e-6 * per_trial * trials +
                         2.7e-6 * t->stream.P * trials + 1.6e-6 * per_trial * dense + merge(t->stream.P);
