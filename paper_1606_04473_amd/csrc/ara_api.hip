@@ -724,10 +724,23 @@ struct StreamBatches {
         return up(split.losses ? n_layers * ara::loss_table_bytes(split.t->loss_index)
                                : ara::fold_batch_bytes(n_layers, split.t->parts.P));
     }
+    int64_t bytes_of(int n_layers, int64_t trials) const {
+        return fold_bytes(n_layers) + up(ara::stream_partials_bytes(split.lay(), trials));
+    }
+    // How many splits of at most `trials` trials a unit may cover without taking more
+    // scratch than a batch: a caller's splits are joined so before they are listed, as a
+    // call may name more of them than there is host memory for
+    static int64_t splits_per_unit(const SplitPass& sp, int64_t trials, int64_t splits) {
+        const StreamBatches b(sp, {});
+        int64_t lo = 1, hi = splits;
+        while (lo < hi) {
+            const int64_t mid = hi - (hi - lo) / 2;
+            if (b.bytes_of(1, mid * trials) <= kBatchBytes) lo = mid;
+            else hi = mid - 1;
+        }
+        return lo;
+    }
     StreamBatches(const SplitPass& sp, const std::vector<ara::StreamUnit>& in) : split(sp) {
-        auto bytes_of = [&](int n_layers, int64_t trials) {
-            return fold_bytes(n_layers) + up(ara::stream_partials_bytes(split.lay(), trials));
-        };
         int64_t most = kBatchBytes;
         for (const auto& u : in) most = std::max(most, bytes_of(1, u.count));
         int64_t trials = 0;
@@ -1597,10 +1610,12 @@ static ara_status run_portfolio(ara_tables* t, const ara_program* programs, int3
     const bool use_parts = !literal && t->parts.P > 0;
     const bool use_xcd = use_parts && tu.pass_variant != 1;
     const SplitPass split(t, tu, by_losses && losses_faster(t, L.data(), n_layers));
-    // split i covers [b(i), b(i + 1)): Algorithm 1's YET_i
-    auto split_at = [&](int64_t i) { return begin + (n * i) / n_splits; };
+    // split i covers [b(i), b(i + 1)): Algorithm 1's YET_i.  More splits than trials are
+    // one of each trial and empty ones.
+    const int64_t splits = std::min<int64_t>(n_splits, n);
+    auto split_at = [&](int64_t i) { return begin + (n * i) / splits; };
     int64_t most = 0;
-    for (int64_t i = 0; i < n_splits; ++i) most = std::max(most, split_at(i + 1) - split_at(i));
+    for (int64_t i = 0; i < splits; ++i) most = std::max(most, split_at(i + 1) - split_at(i));
     // one kept scratch buffer: occurrence losses, part images, partial sums of
     // the largest split, and whatever output the caller keeps on the host
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
@@ -1609,11 +1624,13 @@ static ara_status run_portfolio(ara_tables* t, const ara_program* programs, int3
     // over the streaming pass the layers and splits share launches
     bool joined = use_xcd && split.stream;
     std::vector<ara::StreamUnit> units;
-    if (joined)
+    if (joined) {
+        const int64_t per = StreamBatches::splits_per_unit(split, most, splits);
         for (int64_t l = 0; l < n_layers; ++l)
-            for (int64_t i = 0; i < n_splits; ++i)
-                units.push_back({static_cast<int32_t>(l), split_at(i), split_at(i + 1) - split_at(i),
+            for (int64_t i = 0; i < splits; i += per)
+                units.push_back({static_cast<int32_t>(l), split_at(i), split_at(std::min(i + per, splits)) - split_at(i),
                                  l * n + (split_at(i) - begin), layer_density(t, L[l])});
+    }
     const StreamBatches joint(split, units);
     const size_t la_bytes = up(sizeof(ara::LayerArgs) * n_layers);
     const size_t x_bytes = use_xcd ? up(split.partial_bytes(most)) : 0;
@@ -1664,11 +1681,10 @@ static ara_status run_portfolio(ara_tables* t, const ara_program* programs, int3
                 HIP_TRY(ara::launch_fold(t->elts, t->C, L[l], o_buf, tu, s), "fold");
             kt.done();
         }
-        for (int64_t i = 0; i < n_splits; ++i) {
+        for (int64_t i = 0; i < splits; ++i) {
             ara::LayerArgs Li = L[l];
             Li.trial_begin = split_at(i);
             Li.trial_count = split_at(i + 1) - Li.trial_begin;
-            if (Li.trial_count == 0) continue;
             double* ylt_i = layer_rows + l * n + (Li.trial_begin - begin);
             if (use_xcd) {
                 KernelTimer kp(t, s, prof, ARA_KERNEL_TRIAL_PASS);
