@@ -343,6 +343,15 @@ struct ScratchLease {
     ~ScratchLease() { scratch_release(mu, b, s); }
 };
 
+// memory that kernels on `device` read as their own: another device's needs peer
+// access, which only the runtime's copies do without
+bool memory_of_device(const void* p, int device) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeDevice && a.device == device;
+    (void)hipGetLastError();
+    return false;
+}
+
 bool bad_term(double v) { return std::isnan(v) || v < 0.0; }
 
 ara_status build_layer_args(const ara_tables* t, const ara_layer& in, ara::LayerArgs& L) {
@@ -930,10 +939,10 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         return cleanup(hip_fail(e, "copy ELT pool"));
     if ((e = hipMemsetAsync(t->ids + n_events, 0, sizeof(uint32_t) * ara::kIdPad, s)) != hipSuccess)
         return cleanup(hip_fail(e, "clear id padding"));
-    // IDs of the device that lie on 16 bytes are copied by the pass that checks
-    // and counts them
+    // IDs in this device's memory that lie on 16 bytes are copied by the pass that
+    // checks and counts them
     const uint32_t* ids_in = t->ids;
-    if (dev_in && reinterpret_cast<uintptr_t>(event_ids) % 16 == 0)
+    if (dev_in && reinterpret_cast<uintptr_t>(event_ids) % 16 == 0 && memory_of_device(event_ids, device))
         ids_in = event_ids;
     else if (n_events && (e = hipMemcpyAsync(t->ids, event_ids, sizeof(uint32_t) * n_events, kind, s)) != hipSuccess)
         return cleanup(hip_fail(e, "copy event ids"));
