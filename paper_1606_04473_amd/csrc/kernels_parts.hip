@@ -314,7 +314,8 @@ constexpr int kScatterStage32 = 9 * 1024;           // IDs: 36 KB
 template <int kBits>
 __global__ __launch_bounds__(kScatterThreads) void part_scatter_kernel(
     const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int T, int per,
-    const uint32_t* __restrict__ seg_rel, const int64_t* __restrict__ tile_start, uint32_t* __restrict__ pids) {
+    int64_t first_unit, int64_t n_units, const uint32_t* __restrict__ seg_rel, const int64_t* __restrict__ tile_start,
+    uint32_t* __restrict__ pids) {
     __shared__ __attribute__((aligned(16))) uint32_t stage[kScatterStage32];
     __shared__ uint32_t cursors[kScatterWaves][kMaxParts];
     __shared__ uint32_t seg[kMaxParts + 1];         // staged start of each part's run
@@ -323,8 +324,9 @@ __global__ __launch_bounds__(kScatterThreads) void part_scatter_kernel(
     const int lane = threadIdx.x & 63;
     const int64_t n_tiles = (N + T - 1) / T;
     const int units = (T + per - 1) / per;
-    const int64_t unit = scatter_unit_index(n_tiles * units);
-    if (unit >= n_tiles * units) return;
+    const int64_t of_launch = scatter_unit_index(n_units);
+    if (of_launch >= n_units) return;
+    const int64_t unit = first_unit + of_launch;
     const int64_t tile = unit / units;
     const int64_t t0 = tile * T;
     const int Tk = static_cast<int>(N - t0 < T ? N - t0 : T);
@@ -1816,15 +1818,13 @@ hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t
         const int fit = scatter_trials(lam + 1.5 * out->P, 0.0, kScatterStage32, 64);
         const int units = (out->T + fit - 1) / fit, per = (out->T + units - 1) / units;
         const int64_t n_units = out->n_tiles * ((out->T + per - 1) / per);
-        const dim3 grid(static_cast<uint32_t>((n_units + kXcds - 1) / kXcds * kXcds)), b(kScatterThreads);
         const size_t lds = sizeof(uint32_t) * static_cast<size_t>(out->P) * (per + 1);
-        if (out->P <= 8)
-            hipLaunchKernelGGL(part_scatter_kernel<3>, grid, b, lds, s, offsets, ids, N, out->P, out->T, per,
+        const auto kernel = out->P <= 8 ? part_scatter_kernel<3> : part_scatter_kernel<6>;
+        e = in_launches(n_units, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>((n + kXcds - 1) / kXcds * kXcds)),
+                               dim3(kScatterThreads), lds, s, offsets, ids, N, out->P, out->T, per, first, n,
                                out->seg_rel, out->tile_start, out->pids);
-        else
-            hipLaunchKernelGGL(part_scatter_kernel<6>, grid, b, lds, s, offsets, ids, N, out->P, out->T, per,
-                               out->seg_rel, out->tile_start, out->pids);
-        e = hipGetLastError();
+        });
     }
     if (e != hipSuccess) {
         free_part_layout(out, s);

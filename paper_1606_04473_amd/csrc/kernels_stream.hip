@@ -70,11 +70,11 @@ __device__ __forceinline__ uint64_t stream_lanemask_lt() {
 // each, and stores the 64 ends at once (a thread per group and part, walking the
 // trials, took 72 us for 150000 trials over 31 parts).
 __global__ __launch_bounds__(256) void stream_group_kernel(const int32_t* __restrict__ cnt, int64_t N, int P, int G,
-                                                           int64_t NG, uint16_t* __restrict__ gend,
+                                                           int64_t NG, int64_t first, uint16_t* __restrict__ gend,
                                                            uint32_t* __restrict__ gstart, CreateResult* __restrict__ res) {
     __shared__ int32_t c[kStreamGroupMax * (kMaxStreamParts + 1)];
     const int lane = threadIdx.x & 63;
-    const int64_t g = blockIdx.x;
+    const int64_t g = first + blockIdx.x;
     const int n = static_cast<int>(min(static_cast<int64_t>(G), N - g * G));
     const int row = P | 1;                          // odd: a part's counts lie in different banks
     for (int i = threadIdx.x; i < n * P; i += blockDim.x) c[i / P * row + i % P] = cnt[g * G * P + i];
@@ -146,8 +146,8 @@ struct ScatterEnds16 {                              // dynamic LDS: [P][per + 1]
 template <int kBits>
 __global__ __launch_bounds__(kScatterThreads) void stream_scatter_kernel(
     const int64_t* __restrict__ offsets, const uint32_t* __restrict__ ids, int64_t N, int P, int G, int64_t NG, int per,
-    const CreateResult* __restrict__ res, int64_t* __restrict__ bases, const uint32_t* __restrict__ gstart,
-    const uint16_t* __restrict__ gend, uint16_t* __restrict__ out) {
+    int64_t first_unit, int64_t n_units, const CreateResult* __restrict__ res, int64_t* __restrict__ bases,
+    const uint32_t* __restrict__ gstart, const uint16_t* __restrict__ gend, uint16_t* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) uint16_t stage[kScatterStage16];
     __shared__ __attribute__((aligned(16))) int64_t cursors[kScatterWaves][kMaxStreamParts / 2];
     __shared__ ScatterEnds16 sh;
@@ -155,8 +155,9 @@ __global__ __launch_bounds__(kScatterThreads) void stream_scatter_kernel(
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int units = (G + per - 1) / per;
-    const int64_t unit = scatter_unit_index(NG * units);
-    if (unit >= NG * units) return;
+    const int64_t of_launch = scatter_unit_index(n_units);
+    if (of_launch >= n_units) return;
+    const int64_t unit = first_unit + of_launch;
     const int64_t g = unit / units;
     const int i0 = static_cast<int>(unit - g * units) * per;
     const int n_group = static_cast<int>(min(static_cast<int64_t>(G), N - g * G));
@@ -1154,9 +1155,10 @@ hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, i
     if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * P * (NG + 1), s);
     if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (P + 1), s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(stream_group_kernel, dim3(static_cast<uint32_t>(NG)), dim3(256), 0, s, cnt, N, P, G, NG,
-                           out->gend, out->gstart, res);
-        e = hipGetLastError();
+        e = in_launches(NG, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL(stream_group_kernel, dim3(static_cast<uint32_t>(n)), dim3(256), 0, s, cnt, N, P, G, NG,
+                               first, out->gend, out->gstart, res);
+        });
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(stream_scan_kernel, dim3(static_cast<uint32_t>(P)), dim3(1024), 0, s, NG, out->gstart, res);
@@ -1188,18 +1190,14 @@ hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64
         const int fit = scatter_trials(lam, 14.0 * out->P, kScatterStage16, out->G);
         const int units = (out->G + fit - 1) / fit, per = (out->G + units - 1) / units;
         const int64_t n_units = out->NG * ((out->G + per - 1) / per);
-        const dim3 grid(static_cast<uint32_t>((n_units + kXcds - 1) / kXcds * kXcds)), b(kScatterThreads);
         const size_t lds = sizeof(uint32_t) * static_cast<size_t>(out->P) * (per + 1);
-        if (out->P <= 8)
-            hipLaunchKernelGGL(stream_scatter_kernel<3>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
+        const auto kernel = out->P <= 8 ? stream_scatter_kernel<3>
+                                        : (out->P <= 32 ? stream_scatter_kernel<5> : stream_scatter_kernel<6>);
+        e = in_launches(n_units, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>((n + kXcds - 1) / kXcds * kXcds)),
+                               dim3(kScatterThreads), lds, s, offsets, ids, N, out->P, out->G, out->NG, per, first, n,
                                d_res, out->part_base, out->gstart, out->gend, out->ids);
-        else if (out->P <= 32)
-            hipLaunchKernelGGL(stream_scatter_kernel<5>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
-                               d_res, out->part_base, out->gstart, out->gend, out->ids);
-        else
-            hipLaunchKernelGGL(stream_scatter_kernel<6>, grid, b, lds, s, offsets, ids, N, out->P, out->G, out->NG, per,
-                               d_res, out->part_base, out->gstart, out->gend, out->ids);
-        e = hipGetLastError();
+        });
     }
     if (e != hipSuccess) {
         free_stream_layout(out, s);

@@ -133,10 +133,23 @@ __device__ __forceinline__ void scatter_trial_direct(const uint32_t* __restrict_
     }
 }
 
-// consecutive units to one XCD, whose L2 then merges the lines they share
+// consecutive units of a launch to one XCD, whose L2 then merges the lines they share
 __device__ __forceinline__ int64_t scatter_unit_index(int64_t n_units) {
     const int64_t per = (n_units + kXcds - 1) / kXcds;
     return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+}
+
+// f(first, count) over `n` workgroups in launches of at most 2^22: a launch may have
+// no 2^32 threads, which a workgroup per few trials reaches at 5e8 trials
+template <typename F>
+inline hipError_t in_launches(int64_t n, F f) {
+    constexpr int64_t kMost = int64_t(1) << 22;
+    hipError_t e = hipSuccess;
+    for (int64_t at = 0; at < n && e == hipSuccess; at += kMost) {
+        f(at, n - at < kMost ? n - at : kMost);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // most trials of mean `lam` events that fit a stage of `cap` (six standard
