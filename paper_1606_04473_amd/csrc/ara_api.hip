@@ -965,17 +965,19 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         if (bins > 0) shift = ara::kStreamShift;
         else bins = ara::part_layout_parts(n_trials, catalogue_size);
     }
-    if (bins > 0) {
+    while (bins > 0) {
         const size_t cnt_bytes = sizeof(int32_t) * static_cast<size_t>(n_trials) * bins;
         e = counts.alloc(cnt_bytes, s);
         if (e == hipSuccess) {
             if ((e = hipMemsetAsync(counts.p, 0, cnt_bytes, s)) != hipSuccess) return cleanup(hip_fail(e, "memset"));
-        } else if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-            (void)hipGetLastError();
-            bins = 0;                          // not enough memory for the copies: plain layout only
-        } else {
-            return cleanup(hip_fail(e, "scratch"));
+            break;
         }
+        if (e != hipErrorOutOfMemory && e != hipErrorMemoryAllocation) return cleanup(hip_fail(e, "scratch"));
+        (void)hipGetLastError();
+        // no memory for the finer counts: the 32-bit copy alone, whose parts are a
+        // quarter as many; none for those either: the plain layout
+        bins = shift == ara::kStreamShift ? ara::part_layout_parts(n_trials, catalogue_size) : 0;
+        shift = ara::kImgShift;
     }
     int32_t* cnt = static_cast<int32_t*>(counts.p);
     if ((e = ara::launch_yet_count(t->offsets, n_trials, ids_in, t->ids, n_events, catalogue_size, shift, bins, cnt,
