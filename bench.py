@@ -332,39 +332,44 @@ def main() -> None:
     achieved = tp_bytes / (tp_avg / 1e3) / 1e9
     lay = tables.layout()
     streaming = lay["stream_parts"] > 0
+    by_losses = tables.loss_copy([spec])
+    if by_losses["streamed"]:
+        # the pass streams the copy of the events with a loss in some table.  What it
+        # cannot do without is 2 B for each of those, a year loss per trial and a value
+        # per event of the pool
+        with_loss = np.any(pool.losses > 0.0, axis=0)
+        kept = sum(int(np.count_nonzero(with_loss[yet.ids[i:i + (1 << 25)]])) for i in range(0, n_ev, 1 << 25))
+        tp_bytes = step_bytes = 2.0 * kept + 8.0 * N + 8.0 * by_losses["events"]
+        achieved = tp_bytes / (tp_avg / 1e3) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
-                "traffic": measured_traffic() if streaming else None,
-                "kernel": "stream_pass_kernel" if streaming else "xcd_pass_kernel",
+                "traffic": measured_traffic() if streaming and not by_losses["streamed"] else None,
+                "kernel": "loss_pass_kernel" if by_losses["streamed"] else
+                          ("stream_pass_kernel" if streaming else "xcd_pass_kernel"),
                 "algorithmic_bytes_per_launch": tp_bytes, "avg_launch_ms": round(tp_avg, 5)}
-    if streaming:
+    if by_losses["streamed"]:
+        # the copy's own bytes: its IDs (2 B each, padding included), each group's start
+        # (4 B), and the per-(column, trial) partial sums written (8 + 4 B)
+        sums = by_losses["columns"]
+        lay_bytes = 2.0 * by_losses["ids"] + 4.0 * sums * by_losses["groups"] + 12.0 * sums * N
+        roofline["layout"] = dict(by_losses, events_with_a_loss=kept)
+    elif streaming:
         # the 16-bit layout's own bytes: its IDs (2 B each, padding included),
         # each group's 32 trial ends (2 B) and start (4 B) per part, and the
         # per-(part, trial) partial sums written (8 + 4 B)
-        P16, NG = lay["stream_parts"], lay["stream_groups"]
-        lay_bytes = 2.0 * lay["stream_ids"] + P16 * NG * (64.0 + 4.0) + 12.0 * P16 * N
+        sums, NG = lay["stream_parts"], lay["stream_groups"]
+        lay_bytes = 2.0 * lay["stream_ids"] + sums * NG * (64.0 + 4.0) + 12.0 * sums * N
+        roofline["layout"] = {"stream_parts": sums, "group_trials": lay["stream_group_trials"],
+                              "groups_per_part": NG, "stream_ids": lay["stream_ids"]}
+    if streaming:
         roofline["layout_bytes_per_launch"] = lay_bytes
         roofline["layout_achieved"] = round(lay_bytes / (tp_avg / 1e3) / 1e9, 1)
         roofline["layout_frac"] = round(lay_bytes / (tp_avg / 1e3) / 1e9 / HBM_PEAK_GBS, 4)
-        roofline["layout"] = {"stream_parts": P16, "group_trials": lay["stream_group_trials"],
-                              "groups_per_part": NG, "stream_ids": lay["stream_ids"]}
-    if streaming and roofline["layout_frac"] > 1.0:
-        # faster than the whole copy's bytes allow: the pass streamed the copy of the
-        # events with a loss in some table.  What it cannot do without is 2 B for each
-        # of those, a year loss per trial and a value per event of the pool
-        with_loss = np.any(pool.losses > 0.0, axis=0)
-        kept = sum(int(np.count_nonzero(with_loss[yet.ids[i:i + (1 << 25)]])) for i in range(0, n_ev, 1 << 25))
-        tp_bytes = step_bytes = 2.0 * kept + 8.0 * N + 8.0 * int(np.count_nonzero(with_loss))
-        achieved = tp_bytes / (tp_avg / 1e3) / 1e9
-        roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                    "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "loss_pass_kernel",
-                    "algorithmic_bytes_per_launch": tp_bytes, "avg_launch_ms": round(tp_avg, 5),
-                    "events_with_a_loss": kept}
 
     extra = {"pct_hbm_step": round(step_bytes / (ms_step / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
              "step_algorithmic_bytes": step_bytes, "fold_ms": round(fold_avg, 5),
              "combine_ms": round(comb_avg, 5),
-             "combine_bytes": 12.0 * lay["stream_parts"] * N + 16.0 * N if streaming else 16.0 * lay["image_parts"] * N + 16.0 * N,
+             "combine_bytes": 12.0 * sums * N + 16.0 * N if streaming else 16.0 * lay["image_parts"] * N + 16.0 * N,
              "ms_per_step_with_kernel_events": round(ms_step_profiled, 5),
              "ms_per_step_eager": round(ms_step_eager, 5),
              "ms_per_step_layer_graph_metrics_eager": round(ms_step_layer_graph, 5),

@@ -568,6 +568,29 @@ typedef struct ara_layout_info {
 } ara_layout_info;
 ara_status ara_layout_info_get(const ara_tables* tables, ara_layout_info* info);
 
+/*
+ * ara_loss_copy_get -- the 16-bit copy that holds only the events with a loss
+ * in some table of the pool (see ara_create_tables), all sizes 0 where the
+ * tables hold none, and whether a call of these layers with `flags` streams
+ * it.  `streamed` is 1 where ara_run_layers, ara_run_portfolio, ara_analyze
+ * and (of the one layer) ara_backward read it under the current tuning; 0
+ * where they read another copy, as they also do where they find no memory for
+ * its scratch.  layers may be NULL with n_layers = 0 (streamed 0).  Errors as
+ * ara_run_layers.
+ */
+typedef struct ara_loss_copy_info {
+    int32_t streamed;
+    int32_t parts;                  /* of the events, at most 20479 each */
+    int32_t columns;                /* parts times the splits of each trial: partial sums per trial */
+    int32_t group_trials;           /* 64, or 128 where a lane sums two trials */
+    int64_t events;                 /* of the catalogue with a loss */
+    int64_t groups;                 /* per column */
+    int64_t ids;                    /* stored, padding included (16-bit) */
+    int64_t bytes;
+} ara_loss_copy_info;
+ara_status ara_loss_copy_get(const ara_tables* tables, const ara_layer* layers, int32_t n_layers, uint32_t flags,
+                             ara_loss_copy_info* info);
+
 /* Number of compute units and the device index of the tables' device. */
 ara_status ara_device_info(int32_t* n_cu, int32_t* device);
 

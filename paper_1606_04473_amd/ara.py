@@ -52,6 +52,7 @@ EXPORTED = (
     "ara_event_nets", "ara_run_portfolio",
     "ara_read_checkpoints", "ara_set_tuning", "ara_get_tuning", "ara_device_info",
     "ara_kernel_stats", "ara_create_yet", "ara_tail_count", "ara_layout_info_get",
+    "ara_loss_copy_get",
 )
 
 
@@ -107,7 +108,6 @@ class CTuning(ctypes.Structure):
     ]
 
 
-
 class CLayoutInfo(ctypes.Structure):
     _fields_ = [
         ("image_parts", ctypes.c_int32),
@@ -120,6 +120,20 @@ class CLayoutInfo(ctypes.Structure):
         ("stream_ids", ctypes.c_int64),
         ("stream_bytes", ctypes.c_int64),
     ]
+
+
+class CLossCopyInfo(ctypes.Structure):
+    _fields_ = [
+        ("streamed", ctypes.c_int32),
+        ("parts", ctypes.c_int32),
+        ("columns", ctypes.c_int32),
+        ("group_trials", ctypes.c_int32),
+        ("events", ctypes.c_int64),
+        ("groups", ctypes.c_int64),
+        ("ids", ctypes.c_int64),
+        ("bytes", ctypes.c_int64),
+    ]
+
 
 _LIB = None
 
@@ -186,6 +200,8 @@ def lib():
     L.ara_kernel_stats.restype = i32
     L.ara_layout_info_get.argtypes = [P, ctypes.POINTER(CLayoutInfo)]
     L.ara_layout_info_get.restype = i32
+    L.ara_loss_copy_get.argtypes = [P, ctypes.POINTER(CLayer), i32, u32, ctypes.POINTER(CLossCopyInfo)]
+    L.ara_loss_copy_get.restype = i32
     L.ara_device_info.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i32)]
     L.ara_device_info.restype = i32
     L.ara_tail_count.argtypes = [i64, f64, ctypes.POINTER(i64)]
@@ -338,6 +354,15 @@ class Tables:
         v = CLayoutInfo()
         _check(lib().ara_layout_info_get(self.handle, ctypes.byref(v)))
         return {name: int(getattr(v, name)) for name, _ in CLayoutInfo._fields_ if name != "reserved"}
+
+
+    def loss_copy(self, layers: Sequence["LayerSpec"] = (), flags: int = 0) -> dict:
+        """ara_loss_copy_get: the copy of the events with a loss, and whether a
+        call of `layers` streams it."""
+        v = CLossCopyInfo()
+        arr, keep = _c_layers(layers) if len(layers) else (None, [])
+        _check(lib().ara_loss_copy_get(self.handle, arr, len(layers), int(flags), ctypes.byref(v)))
+        return {name: int(getattr(v, name)) for name, _ in CLossCopyInfo._fields_}
 
 
 def create_tables(offsets, ids, elt_losses, catalogue_size: Optional[int] = None,

@@ -1115,6 +1115,34 @@ ara_status ara_layout_info_get(const ara_tables* t, ara_layout_info* info) {
     return ARA_OK;
 }
 
+ara_status ara_loss_copy_get(const ara_tables* t, const ara_layer* layers, int32_t n_layers, uint32_t flags,
+                             ara_loss_copy_info* info) {
+    if (!t || !info || n_layers < 0 || (n_layers > 0 && !layers))
+        return fail(ARA_ERR_INVALID_ARG, "NULL argument or negative layer count");
+    std::vector<ara::LayerArgs> L(n_layers);
+    for (int i = 0; i < n_layers; ++i) {
+        const ara_status st = build_layer_args(t, layers[i], L[i]);
+        if (st != ARA_OK) return st;
+    }
+    ara_tuning tu;
+    {
+        std::lock_guard<std::mutex> g(const_cast<ara_tables*>(t)->mu);
+        tu = t->tuning;
+    }
+    const bool other_pass = t->parts.P == 0 || (flags & (ARA_LITERAL | ARA_CHECKPOINT_STRIDE)) != 0;
+    ara_loss_copy_info v{};
+    v.streamed = n_layers > 0 && !other_pass && SplitPass(t, tu, losses_faster(t, L.data(), n_layers)).losses;
+    v.parts = t->loss_index.P;
+    v.columns = t->losses.P;
+    v.group_trials = t->losses.G;
+    v.events = t->loss_index.n_events;
+    v.groups = t->losses.NG;
+    v.ids = t->losses.length;
+    v.bytes = t->losses.bytes + t->loss_index.bytes;
+    *info = v;
+    return ARA_OK;
+}
+
 ara_status ara_kernel_stats(ara_tables* t, int32_t kernel, int64_t* launches, double* total_ms, int32_t reset) {
     if (!t || kernel < 0 || kernel > ARA_KERNEL_AGGREGATE) return fail(ARA_ERR_INVALID_ARG, "bad argument");
     DeviceScope ds(t->device);
