@@ -75,7 +75,8 @@ typedef int32_t ara_status;
                                        launch) or 2 (one sequence per layer). */
 #define ARA_GRAPH        (1u << 4)  /* ara_run_layers: replay a HIP graph of the whole call, captured
                                        on first use for this shape (layer count, trial ranges,
-                                       output pointer; with pass_variant 1 also the ELT counts) --
+                                       output pointer, the copy the layers are estimated faster
+                                       over; with pass_variant 1 also the ELT counts) --
                                        the launches of pass_variant 0 or 2, or with pass_variant 1
                                        and several layers the batched launch.  Terms and ELT choices may change
                                        between replays (they are copied to the device only when
@@ -295,9 +296,9 @@ ara_status ara_risk_metrics(const double* ylt, int64_t n_trials, const double* p
  *   flags       ARA_DEVICE_PTR (ylt and metrics are device memory),
  *               ARA_GRAPH (with ARA_DEVICE_PTR and a non-null stream: the
  *               fold, the pass, the combine and the metrics kernels are
- *               captured as one HIP graph per output addresses, trial range
- *               and tail counts, with scratch of its own, and replayed; new
- *               terms and ELT choices reuse it), ARA_PROFILE.
+ *               captured as one HIP graph per output addresses, trial range,
+ *               tail counts and copy streamed, with scratch of its own, and
+ *               replayed; new terms and ELT choices reuse it), ARA_PROFILE.
  *
  * Errors as ara_run_layers and ara_risk_metrics; ARA_ERR_INVALID_ARG for
  * other flags.  Asynchronous on `stream` with device outputs.

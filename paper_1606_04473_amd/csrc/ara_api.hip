@@ -669,6 +669,8 @@ struct SplitPass {
     SplitPass(const ara_tables* tt, const ara_tuning& tu, bool by_losses)
         : t(tt), stream(tu.pass_variant == 0 && tt->stream.P > 0), losses(stream && tt->losses.P > 0 && by_losses) {}
     const ara::StreamLayout& lay() const { return losses ? t->losses : t->stream; }
+    // which pass and copy, as a part of a graph's key
+    int64_t kind() const { return losses ? 2 : (stream ? 1 : 0); }
     // the fold, its outputs in part_scratch (terms from L_dev where given)
     hipError_t fold(const ara::LayerArgs& L, const ara::LayerArgs* L_dev, void* part_scratch, uint64_t* probe,
                     hipStream_t s) const {
@@ -1388,9 +1390,10 @@ static ara_status run_layers(ara_tables* t, const ara_layer* layers, int32_t n_l
     if ((flags & ARA_GRAPH) && (batched || xgraph) && (!dev_out || s == nullptr))
         return fail(ARA_ERR_INVALID_ARG, "ARA_GRAPH needs a device output and a non-null stream");
     if (xgraph) {
-        // key: the pass captured, layer count, output, trial ranges (terms and
-        // ELT choices may change); -1: not a batched plan
-        std::vector<int64_t> key{-1, split.stream ? 1 : 0, static_cast<int64_t>(n_layers),
+        // key: the pass captured and the copy it streams (the ELT choices tell which is
+        // the faster), layer count, output, trial ranges (terms and ELT choices may
+        // change); -1: not a batched plan
+        std::vector<int64_t> key{-1, split.kind(), static_cast<int64_t>(n_layers),
                                  reinterpret_cast<int64_t>(out)};
         int64_t most = 0;
         for (int i = 0; i < n_layers; ++i) {
@@ -1894,9 +1897,9 @@ static ara_status analyze(ara_tables* t, const ara_layer* layer, const double* p
     const size_t p_bytes = up(static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P)));
     const size_t xg_bytes = up(split.partial_bytes(L.trial_count));
     const size_t m_bytes = up(static_cast<size_t>(ara::metrics_scratch_bytes(n_probs, L.trial_count)));
-    // what the graph bakes in: the outputs, the trial range, the pass and the tail counts
+    // what the graph bakes in: the outputs, the trial range, the pass with its copy and the tail counts
     std::vector<int64_t> key{-2, reinterpret_cast<int64_t>(ylt), reinterpret_cast<int64_t>(metrics), L.trial_begin,
-                             L.trial_count, split.stream ? 1 : 0, n_probs};
+                             L.trial_count, split.kind(), n_probs};
     for (int q = 0; q < n_probs; ++q) key.push_back(m[q]);
     const bool prof = (flags & ARA_PROFILE) != 0;
     std::lock_guard<std::mutex> g(t->stage_mu);
