@@ -122,6 +122,7 @@ hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s) {
     e = hipMalloc(&q, cls);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
         (void)hipGetLastError();
+        (void)hipStreamSynchronize(s);              // what this stream freed is then idle
         release_idle(c);
         e = hipMalloc(&q, cls);
     }
@@ -226,6 +227,10 @@ struct PoolBuffer {
         s = stream;
         if (bytes == 0) bytes = 256;
         return ara::dev_alloc(&p, bytes, stream);
+    }
+    void free() {
+        ara::dev_free(p, s);
+        p = nullptr;
     }
 };
 
@@ -967,6 +972,16 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         if (bins > 0) shift = ara::kStreamShift;
         else bins = ara::part_layout_parts(n_trials, catalogue_size);
     }
+    // a copy that does not fit in memory is left out: the passes over the others remain
+    auto left_out = [](hipError_t err) {
+        if (err != hipErrorOutOfMemory && err != hipErrorMemoryAllocation) return false;
+        (void)hipGetLastError();
+        return true;
+    };
+    if (bins > 0) {                 // before the counts, which can be fewer
+        e = ara::begin_part_layout(n_trials, catalogue_size, s, &t->parts);
+        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
+    }
     while (bins > 0) {
         const size_t cnt_bytes = sizeof(int32_t) * static_cast<size_t>(n_trials) * bins;
         e = counts.alloc(cnt_bytes, s);
@@ -974,26 +989,20 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
             if ((e = hipMemsetAsync(counts.p, 0, cnt_bytes, s)) != hipSuccess) return cleanup(hip_fail(e, "memset"));
             break;
         }
-        if (e != hipErrorOutOfMemory && e != hipErrorMemoryAllocation) return cleanup(hip_fail(e, "scratch"));
-        (void)hipGetLastError();
+        if (!left_out(e)) return cleanup(hip_fail(e, "scratch"));
         // no memory for the finer counts: the 32-bit copy alone, whose parts are a
         // quarter as many; none for those either: the plain layout
-        bins = shift == ara::kStreamShift ? ara::part_layout_parts(n_trials, catalogue_size) : 0;
+        bins = shift == ara::kStreamShift ? t->parts.P : 0;
         shift = ara::kImgShift;
     }
+    if (bins == 0) ara::free_part_layout(&t->parts, s);
     int32_t* cnt = static_cast<int32_t*>(counts.p);
     if ((e = ara::launch_yet_count(t->offsets, n_trials, ids_in, t->ids, n_events, catalogue_size, shift, bins, cnt,
                                    d_res, t->n_cu, s)) != hipSuccess)
         return cleanup(hip_fail(e, "pass over the event ids"));
-    // a copy that does not fit in memory is left out: the passes over the others remain
-    auto left_out = [](hipError_t err) {
-        if (err != hipErrorOutOfMemory && err != hipErrorMemoryAllocation) return false;
-        (void)hipGetLastError();
-        return true;
-    };
     if (bins > 0) {
-        e = ara::plan_part_layout(cnt, shift, bins, n_trials, catalogue_size, d_res, s, &t->parts);
-        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
+        if ((e = ara::plan_part_layout(cnt, shift, bins, n_trials, d_res, s, t->parts)) != hipSuccess)
+            return cleanup(hip_fail(e, "partitioned layout"));
         if (shift == ara::kStreamShift) {
             e = ara::plan_stream_layout(cnt, n_trials, n_events, catalogue_size, d_res, s, &t->stream);
             if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));
@@ -1003,6 +1012,7 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     if ((e = hipMemcpyAsync(&res, d_res, sizeof(res), hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return cleanup(hip_fail(e, "read checks and sizes"));
+    counts.free();                  // the copies take memory next
     if (res.flags & ara::kCreateBadId)
         return cleanup(fail(ARA_ERR_OUT_OF_RANGE, "an event ID is >= catalogue size %lld", (long long)catalogue_size));
     if (res.flags & ara::kCreateBadOffsets)
@@ -1017,7 +1027,14 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     }
     if (bins > 0) {
         e = ara::fill_part_layout(t->offsets, t->ids, n_trials, n_events, res, s, &t->parts);
-        if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
+        if (e != hipSuccess && t->stream.P > 0 && left_out(e)) {       // rather the 32-bit copy alone than neither
+            ara::free_stream_layout(&t->stream, s);
+            e = ara::fill_part_layout(t->offsets, t->ids, n_trials, n_events, res, s, &t->parts);
+        }
+        if (e != hipSuccess) {
+            ara::free_part_layout(&t->parts, s);
+            if (!left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
+        }
         t->bytes += t->parts.bytes;
         e = ara::fill_stream_layout(t->offsets, t->ids, n_trials, n_events, res, d_res, s, &t->stream);
         if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "16-bit stream layout"));

@@ -581,8 +581,11 @@ hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* s
 int part_layout_parts(int64_t N, int64_t C);        // 0: not used
 // exclusive prefix sums of v[0..n) in place, the total to v[n]
 hipError_t launch_scan_i64(int64_t* v, int64_t n, hipStream_t s);
-hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
-                            hipStream_t s, PartLayout* out);
+// begin: memory for the segment and tile starts; plan: those from the trials' counts;
+// fill: the copy, of the length read back (an error leaves the plan as it was)
+hipError_t begin_part_layout(int64_t N, int64_t C, hipStream_t s, PartLayout* out);
+hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, CreateResult* res, hipStream_t s,
+                            const PartLayout& lay);
 hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
                             const CreateResult& res, hipStream_t s, PartLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)

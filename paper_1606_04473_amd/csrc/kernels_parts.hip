@@ -1773,8 +1773,7 @@ int part_layout_parts(int64_t N, int64_t C) {
     return N < 1 || P < 1 || P > kMaxParts ? 0 : static_cast<int>(P);
 }
 
-hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, int64_t C, CreateResult* res,
-                            hipStream_t s, PartLayout* out) {
+hipError_t begin_part_layout(int64_t N, int64_t C, hipStream_t s, PartLayout* out) {
     *out = PartLayout{};
     const int P = part_layout_parts(N, C);
     if (P == 0) return hipSuccess;                                     // layout not used
@@ -1784,16 +1783,6 @@ hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, 
                              sizeof(uint32_t) * (n_tiles * (static_cast<int64_t>(T) * P + 1)), s);
     if (e == hipSuccess)
         e = dev_alloc(reinterpret_cast<void**>(&out->tile_start), sizeof(int64_t) * (n_tiles + 1), s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(tile_scan_kernel, dim3(static_cast<uint32_t>(n_tiles)), dim3(256),
-                           sizeof(int32_t) * static_cast<size_t>(T) * P, s, cnt, bins,
-                           kPartShift - shift, N, P, T, out->seg_rel, out->tile_start);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(tile_starts_kernel, dim3(1), dim3(1024), 0, s, out->tile_start, n_tiles, res);
-        e = hipGetLastError();
-    }
     if (e != hipSuccess) {
         free_part_layout(out, s);
         return e;
@@ -1802,6 +1791,18 @@ hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, 
     out->T = T;
     out->n_tiles = n_tiles;
     return hipSuccess;
+}
+
+hipError_t plan_part_layout(const int32_t* cnt, int shift, int bins, int64_t N, CreateResult* res, hipStream_t s,
+                            const PartLayout& lay) {
+    if (lay.P == 0) return hipSuccess;
+    hipLaunchKernelGGL(tile_scan_kernel, dim3(static_cast<uint32_t>(lay.n_tiles)), dim3(256),
+                       sizeof(int32_t) * static_cast<size_t>(lay.T) * lay.P, s, cnt, bins, kPartShift - shift, N, lay.P,
+                       lay.T, lay.seg_rel, lay.tile_start);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(tile_starts_kernel, dim3(1), dim3(1024), 0, s, lay.tile_start, lay.n_tiles, res);
+    return hipGetLastError();
 }
 
 hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
@@ -1826,10 +1827,7 @@ hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t
                                out->seg_rel, out->tile_start, out->pids);
         });
     }
-    if (e != hipSuccess) {
-        free_part_layout(out, s);
-        return e;
-    }
+    if (e != hipSuccess) return e;
     out->length = total;
     out->bytes = static_cast<int64_t>(sizeof(uint32_t)) * (total + kIdPad) +
                  static_cast<int64_t>(sizeof(uint32_t)) * (out->n_tiles * (int64_t(out->T) * out->P + 1)) +

@@ -9,7 +9,9 @@ from workloads import make_elt_pool
 pytestmark = pytest.mark.gpu
 
 
-def test_counts_of_one_copy_fit():
+# no room for the finer counts; room for them but not beside the 32-bit copy's starts
+@pytest.mark.parametrize("left_mb", [900, 1_200])
+def test_counts_of_one_copy_fit(left_mb):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -29,13 +31,14 @@ def test_counts_of_one_copy_fit():
     torch.cuda.synchronize()
     ara.release_cached_memory()
     torch.cuda.empty_cache()
-    # offsets and IDs 48 MB, the copy and its starts 450, counts 268: 1000 MB leave
-    # no room for the 1073 of the finer counts' size class
-    hog = torch.empty(torch.cuda.mem_get_info()[0] - (1_000 << 20), dtype=torch.uint8, device="cuda")
+    # offsets and IDs 50 MB, the copy's starts 268, its counts 268 or the copy 75; the
+    # finer counts 1074
+    first = torch.empty(torch.cuda.mem_get_info()[0] - (4 << 30), dtype=torch.uint8, device="cuda")
+    hog = torch.empty(torch.cuda.mem_get_info()[0] - (left_mb << 20), dtype=torch.uint8, device="cuda")
     try:
         little = ara.create_yet(base, offsets, ids)
     finally:
-        del hog
+        del first, hog
         torch.cuda.empty_cache()
     assert little.layout()["image_parts"] == 16 and little.layout()["stream_parts"] == 0
     assert np.array_equal(ara.run_layers(little, [spec]), want)
