@@ -3,13 +3,15 @@
 // Year losses are >= 0, so their IEEE-754 bit patterns (keys) order like their
 // values when read as uint64.  PML_p is the m-th largest.  It is found in one
 // histogram over all values and a selection among the few that share its bin:
-//  * the largest key gives the top bin; every octave below it is cut into 64
-//    bins (six mantissa bits), 4096 bins in all, the lowest one holding
-//    everything further down (zeros among it).  The map is monotone, so the
-//    histogram's counts from the top give each probability's bin, the rank left
-//    to find inside it and the count above it.  Values spread over many bins:
-//    a histogram of plain top bits (sign and exponent) crowds them into a
-//    few, where LDS and device atomics queue up on each other;
+//  * the largest finite key gives the top bin; the 32 octaves below it are cut
+//    into 64 bins each (six mantissa bits), every octave further down is a bin of
+//    its own, 4096 bins in all (infinities share the top one, zeros the lowest).
+//    The map is monotone, so the histogram's counts from the top give each
+//    probability's bin, the rank left to find inside it and the count above it.
+//    Values spread over many bins: a histogram of plain top bits (sign and
+//    exponent) crowds them into a few, where LDS and device atomics queue up on
+//    each other; one bin for all below 64 octaves leaves a million losses over
+//    2000 octaves, or below one infinity, to one workgroup: 1340 and 1720 us, now 37 and 39;
 //  * values above the bin are summed, the keys inside it collected;
 //  * one workgroup narrows those by further 4096-bin steps between their smallest
 //    and largest key (one step as a rule; none when all are equal, as at a
@@ -40,12 +42,15 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kPer = 8;                // values per thread of the multi-workgroup launches
 constexpr int kSumBlocks = 512;
 constexpr int kBins = 4096;
-constexpr int kBinShift = 46;          // a key's bits below its bin: 64 bins per octave
+constexpr int kFinePerOctave = 6;      // log2 of the bins per octave below the largest key
+constexpr int kBinShift = 52 - kFinePerOctave;
+constexpr int kFineBins = 2048;        // of them; the other 2048 are one per exponent
 constexpr int kMaxProbs = 4;
 constexpr int kDirect = 256;           // candidates ranked directly (all pairs)
 // One workgroup up to here: 16 values per thread in registers.
 constexpr int kSmallPer = 16;
 constexpr int64_t kSmallMax = int64_t(kThreads) * kSmallPer;
+constexpr uint64_t kInfKey = uint64_t(0x7FF) << 52;
 constexpr uint64_t kBadKey = ~uint64_t(0);
 
 // one probability's state after the histogram
@@ -59,7 +64,7 @@ struct Pick {
 struct Scratch {
     double* part_hi;      // [kMaxProbs + 1][kSumBlocks]: mean partials, then the tails'
     double* part_lo;
-    uint64_t* part_max;   // [kSumBlocks] largest key; kBadKey when a value is NaN or < 0
+    uint64_t* part_max;   // [kSumBlocks] largest finite key; kBadKey when a value is NaN or < 0
     uint32_t* hist;       // [kBins]
     Pick* pick;           // [kMaxProbs] each probability's bin
     uint32_t* ccount;     // [kMaxProbs] candidates collected per probability
@@ -108,10 +113,27 @@ __device__ __forceinline__ uint64_t key_of(double x) {
     return __double_as_longlong(x + 0.0);
 }
 
-// a key's bin below `top`, the largest key's bin number
-__device__ __forceinline__ uint32_t bin_of(uint64_t key, uint64_t top) {
-    const uint64_t below = top - (key >> kBinShift);
-    return below < kBins ? kBins - 1 - static_cast<uint32_t>(below) : 0u;
+// a key's bin; `top`: the largest finite key's top bits (a key above it is infinite)
+__device__ __forceinline__ uint32_t top_bits(uint64_t key) { return static_cast<uint32_t>(key >> kBinShift); }
+__device__ __forceinline__ uint32_t bin_of(uint64_t key, uint32_t top) {
+    const uint32_t bits = top_bits(key);
+    const int below = static_cast<int>(top) - static_cast<int>(bits);
+    return below < kFineBins ? kBins - 1 - max(below, 0) : bits >> kFinePerOctave;     // below: the exponent
+}
+
+// the top bits of a bin's keys: lo .. lo + span
+struct BinBits {
+    uint32_t lo, span;
+};
+__device__ __forceinline__ BinBits bits_of(uint32_t bin, uint32_t top) {
+    if (bin >= kFineBins) return BinBits{top - (kBins - 1 - bin), bin == kBins - 1 ? ~0u - top : 0u};
+    const uint32_t lo = bin << kFinePerOctave, hi = min(lo + (1u << kFinePerOctave) - 1, top - kFineBins);
+    return BinBits{lo, hi - lo};
+}
+
+// the largest finite key so far
+__device__ __forceinline__ uint64_t max_finite(uint64_t mx, uint64_t key) {
+    return key > mx && key < kInfKey ? key : mx;
 }
 
 __device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
@@ -365,7 +387,9 @@ __device__ __forceinline__ Chosen select_candidate(FinishLds& sh, Each each, All
     return r;
 }
 
-// a probability's candidates in memory: up to kPer per thread are loaded once
+// A probability's candidates in memory: up to kPer per thread are loaded once, more
+// are read again for each step, kPer in flight (one in flight: a million losses within
+// 0.1 % of each other 1720 us, now 690).
 __device__ __forceinline__ Chosen select_in_memory(FinishLds& sh, const uint64_t* cand, uint32_t c, int64_t k) {
     if (c <= kThreads * kPer) {
         uint64_t key[kPer];
@@ -382,7 +406,14 @@ __device__ __forceinline__ Chosen select_in_memory(FinishLds& sh, const uint64_t
         return select_candidate(sh, each, each, c, k);
     }
     auto each = [&](auto f) {
-        for (uint32_t i = threadIdx.x; i < c; i += kThreads) f(cand[i]);
+        for (int64_t i0 = threadIdx.x; i0 < c; i0 += kThreads * kPer) {
+            uint64_t key[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) key[u] = cand[i0 + u * kThreads < c ? i0 + u * kThreads : i0];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (i0 + u * kThreads < c) f(key[u]);
+        }
     };
     return select_candidate(sh, each, each, c, k);
 }
@@ -457,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void combine_sum_max_kernel(const double*
         ylt[k] = y;
         bad |= !(y >= 0.0);
         dd_add(sum_hi, sum_lo, y);
-        mx = max_u64(mx, key_of(y));
+        mx = max_finite(mx, key_of(y));
     }
     store_partials(sh, s, sum_hi, sum_lo, bad ? kBadKey : mx);
 }
@@ -477,7 +508,7 @@ __global__ __launch_bounds__(kThreads) void sum_max_kernel(const double* __restr
         for (int u = 0; u < kPer; ++u) {
             bad |= !(v[u] >= 0.0);
             dd_add(hi, lo, v[u]);
-            mx = max_u64(mx, key_of(v[u]));
+            mx = max_finite(mx, key_of(v[u]));
         }
     }
     store_partials(sh, s, hi, lo, bad ? kBadKey : mx);
@@ -500,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void bin_kernel(const double* __restrict_
     for (int u = 0; u < kPer; ++u) v[u] = first + u * stride < n ? x[first + u * stride] : 0.0;
     const uint64_t mk = top_key(sh, s, n_part);
     if (mk == kBadKey) return;
-    const uint64_t top = mk >> kBinShift;
+    const uint32_t top = top_bits(mk);
     for (int64_t i = first; i < n; i += kPer * stride) {
         if (i != first) {
 #pragma unroll
@@ -535,7 +566,7 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const double* __restr
     const u32x4 counts = own_bins(s.hist);
     const uint64_t mk = top_key(red, s, n_part);
     if (mk == kBadKey) return;
-    const uint64_t top = mk >> kBinShift;
+    const uint32_t top = top_bits(mk);
     pick_bins(sel, counts, ma.m, n_probs);
     if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n_probs) s.pick[threadIdx.x] = sel.pick[threadIdx.x];
     uint32_t bins[kMaxProbs];
@@ -667,7 +698,13 @@ __global__ __launch_bounds__(kThreads) void small_metrics_kernel(const double* _
         write_bad(n_probs, out, tail, ma);
         return;
     }
-    const uint64_t top = mx >> kBinShift;
+    if (mx == kInfKey) {
+        mx = 0;
+#pragma unroll
+        for (int u = 0; u < kV; ++u) mx = max_finite(mx, key_of(v[u]));
+        mx = block_max(sh.red, mx);
+    }
+    const uint32_t top = top_bits(mx);
 #pragma unroll
     for (int u = 0; u < kV; ++u)
         if (u * kThreads + static_cast<int>(threadIdx.x) < n) atomicAdd(&sh.hist[bin_of(key_of(v[u]), top)], 1u);
@@ -688,9 +725,10 @@ __global__ __launch_bounds__(kThreads) void small_metrics_kernel(const double* _
 #pragma unroll 1
     for (int q = 0; q < n_probs; ++q) {
         const Pick p = picks[q];
+        const BinBits in = bits_of(p.bin, top);
         auto each = [&](auto f) {
             all([&](uint64_t key) {
-                if (bin_of(key, top) == p.bin) f(key);
+                if (top_bits(key) - in.lo <= in.span) f(key);
             });
         };
         const Chosen r = select_candidate(sh, each, all, p.count, p.k);
