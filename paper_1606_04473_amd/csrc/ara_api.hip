@@ -160,18 +160,21 @@ void dev_drop(void* p, hipStream_t s) {
     int device = 0;
     if (!p || hipGetDevice(&device) != hipSuccess) return;
     DeviceCache& c = device_cache(device);
+    bool large = false;
     {
         std::lock_guard<std::mutex> g(c.mu);
         auto it = c.blocks.find(p);
-        if (it == c.blocks.end()) return;
-        if (it->second.size > kKept) {
-            if (it->second.ready) (void)hipEventDestroy(it->second.ready);
-            c.blocks.erase(it);
-            (void)hipFree(p);
-            return;
-        }
+        large = it != c.blocks.end() && it->second.size > kKept;
     }
-    dev_free(p, s);
+    if (!large || hipStreamSynchronize(s) != hipSuccess) {
+        dev_free(p, s);
+        return;
+    }
+    std::lock_guard<std::mutex> g(c.mu);
+    auto it = c.blocks.find(p);
+    if (it->second.ready) (void)hipEventDestroy(it->second.ready);
+    c.blocks.erase(it);
+    (void)hipFree(p);
 }
 
 }  // namespace ara
@@ -944,8 +947,6 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         return cleanup(hip_fail(e, "copy offsets"));
     if (elt_bytes && (e = hipMemcpyAsync(t->elts, elt_losses, elt_bytes, kind, s)) != hipSuccess)
         return cleanup(hip_fail(e, "copy ELT pool"));
-    if ((e = hipMemsetAsync(t->ids + n_events, 0, sizeof(uint32_t) * ara::kIdPad, s)) != hipSuccess)
-        return cleanup(hip_fail(e, "clear id padding"));
     // IDs in this device's memory that lie on 16 bytes are copied by the pass that
     // checks and counts them
     const uint32_t* ids_in = t->ids;
@@ -959,12 +960,6 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     PoolBuffer result, counts;
     if ((e = result.alloc(sizeof(ara::CreateResult), s)) != hipSuccess) return cleanup(hip_fail(e, "scratch"));
     ara::CreateResult* d_res = static_cast<ara::CreateResult*>(result.p);
-    if ((e = hipMemsetAsync(d_res, 0, sizeof(ara::CreateResult), s)) != hipSuccess)
-        return cleanup(hip_fail(e, "memset"));
-    if ((e = ara::launch_validate(t->offsets, n_trials, n_events, t->elts,
-                                  base ? 0 : static_cast<int64_t>(n_elts) * catalogue_size, d_res, t->n_cu, s)) !=
-        hipSuccess)
-        return cleanup(hip_fail(e, "validate kernel"));
     // counted in the finer parts where the 16-bit copy can be built
     int shift = ara::kImgShift, bins = 0;
     if (!(flags & ARA_PLAIN_LAYOUT) && n_trials > 0) {
@@ -983,12 +978,8 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
         if (e != hipSuccess && !left_out(e)) return cleanup(hip_fail(e, "partitioned layout"));
     }
     while (bins > 0) {
-        const size_t cnt_bytes = sizeof(int32_t) * static_cast<size_t>(n_trials) * bins;
-        e = counts.alloc(cnt_bytes, s);
-        if (e == hipSuccess) {
-            if ((e = hipMemsetAsync(counts.p, 0, cnt_bytes, s)) != hipSuccess) return cleanup(hip_fail(e, "memset"));
-            break;
-        }
+        e = counts.alloc(sizeof(int32_t) * static_cast<size_t>(n_trials) * bins, s);
+        if (e == hipSuccess) break;
         if (!left_out(e)) return cleanup(hip_fail(e, "scratch"));
         // no memory for the finer counts: the 32-bit copy alone, whose parts are a
         // quarter as many; none for those either: the plain layout
@@ -997,6 +988,11 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     }
     if (bins == 0) ara::free_part_layout(&t->parts, s);
     int32_t* cnt = static_cast<int32_t*>(counts.p);
+    if ((e = ara::launch_create_clear(t->ids + n_events, d_res, cnt, n_trials * bins, t->n_cu, s)) != hipSuccess ||
+        (e = ara::launch_validate(t->offsets, n_trials, n_events, t->elts,
+                                  base ? 0 : static_cast<int64_t>(n_elts) * catalogue_size, d_res, t->n_cu, s)) !=
+            hipSuccess)
+        return cleanup(hip_fail(e, "validate kernel"));
     if ((e = ara::launch_yet_count(t->offsets, n_trials, ids_in, t->ids, n_events, catalogue_size, shift, bins, cnt,
                                    d_res, t->n_cu, s)) != hipSuccess)
         return cleanup(hip_fail(e, "pass over the event ids"));
@@ -1020,8 +1016,7 @@ static ara_status create_impl(const int64_t* trial_offsets, int64_t n_trials, co
     if (res.flags & ara::kCreateBadLoss) return cleanup(fail(ARA_ERR_INVALID_ARG, "ELT losses must be finite and >= 0"));
     if (!base) {
         // the pool's nonzero entries, which the per-request fold reads
-        if ((e = ara::build_sparse_pool(t->elts, n_elts, catalogue_size, s, &t->sparse)) != hipSuccess ||
-            (e = hipStreamSynchronize(s)) != hipSuccess)
+        if ((e = ara::build_sparse_pool(t->elts, n_elts, catalogue_size, s, &t->sparse)) != hipSuccess)
             return cleanup(hip_fail(e, "sparse ELT pool"));
         t->bytes += t->sparse.bytes;
     }

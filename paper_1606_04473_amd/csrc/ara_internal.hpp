@@ -22,8 +22,8 @@ constexpr int kWave = 64;
 // once s has reached the free.  Blocks are kept, not returned to the runtime.
 hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s);
 void dev_free(void* p, hipStream_t s);
-// dev_free for a temporary whose work has completed: a large one goes back to the
-// runtime (hipFree), so that it does not stay with the process
+// dev_free for a temporary: a large one goes back to the runtime once s has reached
+// this point (the call waits), so that it does not stay with the process
 void dev_drop(void* p, hipStream_t s);
 // bytes the cache of `device` holds, and of those not in use
 void cache_stats(int device, int64_t* held, int64_t* idle);
@@ -239,6 +239,10 @@ hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, i
                               hipStream_t s, StreamLayout* out);
 hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
                               const CreateResult& res, const CreateResult* d_res, hipStream_t s, StreamLayout* out);
+// the same before the lengths are read back, with room for the most there can be: empty
+// where d_res flags the layout as one not to use
+hipError_t fill_stream_layout_unread(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                                     const CreateResult* d_res, hipStream_t s, StreamLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_stream_layout(StreamLayout* L, hipStream_t s);
 // bytes of the per-(part, trial) partial sums of the streaming pass
@@ -295,7 +299,7 @@ struct LossIndex {
     int P = 0;                      // parts; 0 = not used
     int64_t n_events = 0;
     int64_t bytes = 0;
-    uint64_t* probe = nullptr;      // [(C + 31) / 32]
+    uint64_t* probe = nullptr;      // [(C + 31) / 32], the block that holds the others too
     uint32_t* events = nullptr;     // [P][kLossSlots] the slots' events
     uint32_t* part_n = nullptr;     // [P] slots in use
 };
@@ -573,6 +577,8 @@ hipError_t launch_debug_lookups(const int64_t* offsets, const uint32_t* ids, con
                                 double* losses_out, hipStream_t s);
 
 // catalogue-partitioned path
+// before create's passes: the IDs' padding, the results and n_cnt counts to zero
+hipError_t launch_create_clear(uint32_t* pad, CreateResult* res, int32_t* cnt, int64_t n_cnt, int n_cu, hipStream_t s);
 // create's pass over the IDs: copied from src (unless src == ids), checked, and
 // each trial's events counted in `bins` parts of 2^shift catalogue events
 // (cnt[trial][bin], zero before); src and ids 16-byte aligned

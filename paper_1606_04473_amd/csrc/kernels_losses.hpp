@@ -33,6 +33,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
+#include <type_traits>
 #include <vector>
 
 #include "ara_internal.hpp"
@@ -53,8 +55,11 @@ constexpr int kMetaRows = 4;                    // least rows of a group whose l
 // ---------------------------------------------------------------------------
 
 // per superblock: the bits of its events with a loss in some table (low halves of
-// the probe words) and their number
-__global__ __launch_bounds__(256) void loss_bits_kernel(SparsePool sp, int n_rows, int64_t C,
+// the probe words) and their number.  A wave takes a table; a lane joins the bits of four
+// consecutive events, as the entries are in order and dense tables queue up on a word
+// (16 tables of 3700 events per superblock: an event per lane and load 41 us, and 69 in
+// four waves, now 12)
+__global__ __launch_bounds__(1024) void loss_bits_kernel(SparsePool sp, int n_rows, int64_t C,
                                                         uint64_t* __restrict__ probe, uint32_t* __restrict__ count) {
     __shared__ uint32_t bits[kSuperEvents / 32];
     __shared__ uint32_t total;
@@ -63,9 +68,20 @@ __global__ __launch_bounds__(256) void loss_bits_kernel(SparsePool sp, int n_row
     if (threadIdx.x == 0) total = 0;
     __syncthreads();
     for (int r = threadIdx.x >> 6; r < n_rows; r += static_cast<int>(blockDim.x >> 6)) {
-        const int64_t key = static_cast<int64_t>(r) * sp.n_chunks + sb;
-        for (int64_t k = sp.chunk_off[key] + (threadIdx.x & 63); k < sp.chunk_off[key + 1]; k += 64)
-            atomicOr(&bits[sp.ev[k] >> 5], 1u << (sp.ev[k] & 31u));
+        const int64_t key = static_cast<int64_t>(r) * sp.n_chunks + sb, end = sp.chunk_off[key + 1];
+        for (int64_t k = sp.chunk_off[key] + 4 * (threadIdx.x & 63); k < end; k += 256) {
+            uint32_t ev[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ev[u] = sp.ev[min(k + u, end - 1)];
+            uint32_t own = 0;                       // of ev[u]'s word
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                own |= 1u << (ev[u] & 31u);
+                if (u < 3 && ev[u + 1] >> 5 == ev[u] >> 5) continue;
+                atomicOr(&bits[ev[u] >> 5], own);
+                own = 0;
+            }
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kSuperEvents / 32; i += blockDim.x) {
@@ -79,17 +95,24 @@ __global__ __launch_bounds__(256) void loss_bits_kernel(SparsePool sp, int n_row
 
 // what the host asks of the plan
 struct LossPlan {
+    int64_t kept;                   // occurrences in the YET of events with a loss (the scan's total)
     int64_t events;                 // with a loss in some table
-    int64_t kept;                   // their occurrences in the YET
     int32_t parts;                  // past `most_parts`: more than there may be
     int32_t pad_;
+};
+// and of the intermediate copy and the rows: findings, the rows of each column
+struct LossRows {
+    CreateResult res;
+    int64_t rows[kMaxStreamParts * 64];
 };
 
 // the superblocks' counts in place[] to the places of their first events, part << 16 |
 // slot: whole superblocks to a part, its last slot kept free (one wave)
 __global__ __launch_bounds__(64) void loss_plan_kernel(int64_t n_sb, int most_parts, uint32_t* __restrict__ place,
-                                                       uint32_t* __restrict__ part_n, LossPlan* __restrict__ plan) {
+                                                       uint32_t* __restrict__ part_n, LossPlan* __restrict__ plan,
+                                                       CreateResult* __restrict__ res) {
     const int lane = threadIdx.x;
+    if (lane == 0) res->flags = 0;
     int part = 0;
     uint32_t at = 0;
     int64_t events = 0;
@@ -147,10 +170,14 @@ __global__ __launch_bounds__(64) void loss_place_kernel(int64_t C, int most_part
 // L2, 64 lines an instruction: 5.2 ms per 1e9 events with a gather each.  So a
 // workgroup holds a map with a bit per 2^shift events in LDS and gathers the words of
 // the events whose bit is set (the other lanes share the first word's line): 2.1 ms
-// at 15 % of the events.  shift < 0: no map (a catalogue past kMapShift bits).
+// at 15 % of the events.  kExact, a bit per event: the map is the words' low halves,
+// and the count gathers nothing; the high halves lie in LDS too where they fit
+// (5e7 events, 84 % of them with a loss: count 183 -> 68 us, fill 208 -> 110).
 constexpr int kMapWords = 39936;                // 156 KB
 constexpr int kMapShift = 2;
-template <bool kFill, int kAhead>
+static_assert(int64_t(kMaxStreamParts) << kStreamShift <= int64_t(kMapWords) * 32 << kMapShift,
+              "a map for every catalogue with a 16-bit copy");
+template <bool kFill, int kAhead, bool kExact>
 __global__ __launch_bounds__(1024) void loss_filter_kernel(const int64_t* __restrict__ offsets,
                                                            const uint32_t* __restrict__ ids, int64_t N,
                                                            const uint64_t* __restrict__ probe, int64_t n_words,
@@ -159,7 +186,14 @@ __global__ __launch_bounds__(1024) void loss_filter_kernel(const int64_t* __rest
                                                            int32_t* __restrict__ cnt) {
     __shared__ uint32_t map[kMapWords];
     __shared__ uint32_t counts[16][kMaxStreamParts];
-    if (shift >= 0) {
+    const bool whole = kExact && kFill && 2 * n_words <= kMapWords;
+    if constexpr (kExact) {
+        for (int64_t w = threadIdx.x; w < n_words; w += blockDim.x) {
+            const uint64_t v = probe[w];
+            map[w] = static_cast<uint32_t>(v);
+            if (whole) map[n_words + w] = static_cast<uint32_t>(v >> 32);
+        }
+    } else {
         for (int i = threadIdx.x; i < kMapWords; i += blockDim.x) map[i] = 0;
         __syncthreads();
         for (int64_t w = threadIdx.x; w < n_words; w += blockDim.x) {
@@ -180,8 +214,8 @@ __global__ __launch_bounds__(1024) void loss_filter_kernel(const int64_t* __rest
             const int per = 32 >> shift;            // bits of the map a word gives
             if (b) atomicOr(&map[w * per >> 5], b << (static_cast<int>(w * per) & 31));
         }
-        __syncthreads();
     }
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     uint32_t* count = counts[threadIdx.x >> 6];     // this wave's
     if (kFill && lane < P) count[lane] = 0;
@@ -191,28 +225,32 @@ __global__ __launch_bounds__(1024) void loss_filter_kernel(const int64_t* __rest
         const int64_t b = uniform_i64(offsets[t]), e = uniform_i64(offsets[t + 1]);
         int64_t to = kFill ? uniform_i64(start[t]) : 0;
         for (int64_t c = b; c < e; c += 64 * kAhead) {
-            uint32_t id[kAhead];
-            uint64_t w[kAhead];
+            uint32_t id[kAhead], bits[kAhead], first[kAhead];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) id[k] = ids[min(c + k * 64 + lane, e - 1)];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
-                uint32_t at = id[k] >> 5;
-                if (shift >= 0) {
+                const uint32_t at = id[k] >> 5;
+                if constexpr (kExact) {
+                    bits[k] = map[at];
+                    if constexpr (kFill) {
+                        if (whole) first[k] = map[n_words + at];
+                        else first[k] = static_cast<uint32_t>(probe[bits[k] >> (id[k] & 31u) & 1u ? at : 0u] >> 32);
+                    }
+                } else {
                     const uint32_t m = id[k] >> shift;
-                    at = map[m >> 5] >> (m & 31u) & 1u ? at : 0u;
+                    const bool may = map[m >> 5] >> (m & 31u) & 1u;
+                    const uint64_t w = probe[may ? at : 0u];
+                    bits[k] = may ? static_cast<uint32_t>(w) : 0u;
+                    first[k] = static_cast<uint32_t>(w >> 32);
                 }
-                w[k] = probe[at];
-                if (at != id[k] >> 5) w[k] = 0;
             }
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
-                const uint32_t bits = static_cast<uint32_t>(w[k]);
-                const bool keep = c + k * 64 + lane < e && (bits >> (id[k] & 31u) & 1u);
+                const bool keep = c + k * 64 + lane < e && (bits[k] >> (id[k] & 31u) & 1u);
                 const uint64_t kept = __ballot(keep);
                 if (kFill && keep) {
-                    const uint32_t slot =
-                        static_cast<uint32_t>(w[k] >> 32) + __popc(bits & ((1u << (id[k] & 31u)) - 1u));
+                    const uint32_t slot = first[k] + __popc(bits[k] & ((1u << (id[k] & 31u)) - 1u));
                     out[to + __popcll(kept & ((1ull << lane) - 1))] = slot;
                     if (P > 1) atomicAdd(&count[slot >> 16], 1u);
                 }
@@ -340,6 +378,23 @@ __global__ __launch_bounds__(1024) void loss_scan_kernel(int64_t NG, uint32_t* _
         v[NG] = static_cast<uint32_t>(tsum[1023]);
         rows[blockIdx.x] = tsum[1023];
     }
+}
+
+// the columns' first slots from their rows (one wave)
+__global__ __launch_bounds__(64) void loss_bases_kernel(int Q, const int64_t* __restrict__ rows,
+                                                        int64_t* __restrict__ base) {
+    const int lane = threadIdx.x;
+    int64_t carry = 0;
+    for (int q0 = 0; q0 < Q; q0 += 64) {
+        int64_t inc = q0 + lane < Q ? rows[q0 + lane] * 64 * kRowIds : 0;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        if (q0 + lane < Q) base[q0 + lane + 1] = carry + inc;
+        carry += __shfl(inc, 63, 64);
+    }
+    if (lane == 0) base[0] = 0;
 }
 
 // One wave per (column, group): the rows.  A lane's 16 slots of four rows are two
@@ -780,53 +835,44 @@ int splits_of(int P, int64_t N, int64_t kept, int n_cu) {
 // trials 160 / 183 (a wave's last group is a larger part of its share).
 constexpr double kPairLeast = 3.0, kPairMost = 64.0;
 
-// the copy from the intermediate one, unless it takes more than `most` bytes
-hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t most, int n_cu, hipStream_t s,
-                      StreamLayout* out) {
+// the copy from the intermediate one, unless that is not to be used or the copy takes
+// more than `most` bytes
+hipError_t build_rows(const StreamLayout& in, int64_t N, int64_t kept, int64_t most, int n_cu, LossRows* d_rows,
+                      hipStream_t s, StreamLayout* out) {
     const int S = splits_of(in.P, N, kept, n_cu), Q = in.P * S;
     const double lam = static_cast<double>(kept) / (static_cast<double>(N) * Q);
     const bool pair = lam >= kPairLeast && lam <= kPairMost && Q * (N / 128) >= 32 * int64_t(n_cu);
     const int G = pair ? 128 : 64;
     const int64_t NG = (N + G - 1) / G;
-    std::vector<int64_t> base(Q + 1);
-    int64_t* rows = nullptr;
     hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->gstart), sizeof(uint32_t) * Q * (NG + 1), s);
     if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&out->part_base), sizeof(int64_t) * (Q + 1), s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&rows), sizeof(int64_t) * Q, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL((pair ? loss_group_kernel<true> : loss_group_kernel<false>), dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(in.P)),
-                           dim3(256), 0, s, in, N, S, NG, out->gstart);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(loss_scan_kernel, dim3(static_cast<uint32_t>(Q)), dim3(1024), 0, s, NG, out->gstart, rows);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(base.data() + 1, rows, sizeof(int64_t) * Q, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (rows) dev_free(rows, s);
     if (e != hipSuccess) return e;
-    base[0] = 0;
-    for (int q = 0; q < Q; ++q) {
-        if (base[q + 1] >= (int64_t(1) << 32) - 4096) return hipErrorOutOfMemory;      // past 32-bit rows
-        base[q + 1] = base[q] + base[q + 1] * 64 * kRowIds;
+    hipLaunchKernelGGL((pair ? loss_group_kernel<true> : loss_group_kernel<false>), dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(in.P)),
+                       dim3(256), 0, s, in, N, S, NG, out->gstart);
+    hipLaunchKernelGGL(loss_scan_kernel, dim3(static_cast<uint32_t>(Q)), dim3(1024), 0, s, NG, out->gstart, d_rows->rows);
+    hipLaunchKernelGGL(loss_bases_kernel, dim3(1), dim3(64), 0, s, Q, d_rows->rows, out->part_base);
+    std::vector<char> host(offsetof(LossRows, rows) + sizeof(int64_t) * Q);
+    LossRows* rows = reinterpret_cast<LossRows*>(host.data());
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(host.data(), d_rows, host.size(), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    bool used = !(rows->res.flags & (kCreateWideGroup | kCreateWidePart));
+    for (int q = 0; used && q < Q; ++q) {
+        if (rows->rows[q] >= (int64_t(1) << 32) - 4096) return hipErrorOutOfMemory;    // past 32-bit rows
+        out->length += rows->rows[q] * 64 * kRowIds;
     }
-    if (static_cast<int64_t>(sizeof(uint16_t)) * base[Q] > most) {        // not used
+    if (!used || static_cast<int64_t>(sizeof(uint16_t)) * out->length > most) {
         free_stream_layout(out, s);
         return hipSuccess;
     }
-    out->length = base[Q];
-    e = hipMemcpyAsync(out->part_base, base.data(), sizeof(int64_t) * (Q + 1), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (out->length + 64 * kRowIds), s);
+    e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (out->length + 64 * kRowIds), s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL((pair ? loss_rows_kernel<true> : loss_rows_kernel<false>), dim3(static_cast<uint32_t>((NG + 3) / 4), static_cast<uint32_t>(Q)),
                            dim3(256), 0, s, in, N, S, NG, out->gstart, out->part_base,
                            reinterpret_cast<uint64_t*>(out->ids));
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     out->P = Q;
     out->G = G;
@@ -864,9 +910,7 @@ hipError_t launch_loss_adjoint(const StreamLayout& lay, const LossIndex& ix, con
 }
 
 void free_loss_index(LossIndex* ix, hipStream_t s) {
-    if (ix->probe) dev_free(ix->probe, s);
-    if (ix->events) dev_free(ix->events, s);
-    if (ix->part_n) dev_free(ix->part_n, s);
+    dev_free(ix->probe, s);
     *ix = LossIndex{};
 }
 
@@ -874,47 +918,54 @@ hipError_t build_losses(const SparsePool& sp, int n_rows, int64_t C, const int64
                         int64_t N, int64_t n_events, int n_cu, hipStream_t s, LossIndex* ix, StreamLayout* out) {
     *ix = LossIndex{};
     *out = StreamLayout{};
-    if (n_rows < 1 || sp.n_chunks < 1 || N < 1) return hipSuccess;
+    if (n_rows < 1 || sp.n_chunks < 1 || N < 1 || C > int64_t(kMaxStreamParts) << kStreamShift) return hipSuccess;
     const int64_t n_sb = sp.n_chunks, n_words = (C + 31) / 32;
     // two neighbouring parts hold more than kSlots - 1 events
     const int most_parts = static_cast<int>(std::min<int64_t>(kMaxStreamParts, 2 * (C / (kSlots - 1)) + 1));
-    uint32_t* place = nullptr;
-    int64_t* start = nullptr;
+    LossRows* d_rows = nullptr;                 // the temporaries' block: the results,
+    int64_t* start = nullptr;                   // [N], then the plan,
+    uint32_t* place = nullptr;                  // [n_sb]
     uint32_t* kept_ids = nullptr;
     int32_t* cnt = nullptr;
-    CreateResult* d_res = nullptr;
-    CreateResult res{};
     StreamLayout by_part{};
     LossPlan plan{};
     int shift = 0;
-    while (shift <= kMapShift && C > (int64_t(kMapWords) * 32 << shift)) ++shift;
-    if (shift > kMapShift) shift = -1;
+    while (C > (int64_t(kMapWords) * 32 << shift)) ++shift;
     const dim3 g(static_cast<uint32_t>(std::min((N + 15) / 16, int64_t(n_cu)))), b(1024);
     const bool long_trials = n_events / N > 256;
+    auto filter = [&](auto fill, int P) {
+        constexpr bool kFill = decltype(fill)::value;
+        const auto kernel = shift == 0 ? (long_trials ? loss_filter_kernel<kFill, 16, true> : loss_filter_kernel<kFill, 4, true>)
+                                       : (long_trials ? loss_filter_kernel<kFill, 16, false> : loss_filter_kernel<kFill, 4, false>);
+        hipLaunchKernelGGL(kernel, g, b, 0, s, offsets, ids, N, ix->probe, n_words, shift, start, kept_ids, P, cnt);
+    };
 
     // the events' slots, and how many events the trials keep
-    LossPlan* d_plan = nullptr;
-    hipError_t e = dev_alloc(reinterpret_cast<void**>(&ix->probe), sizeof(uint64_t) * n_words, s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&ix->events), sizeof(uint32_t) * kSlots * most_parts, s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&ix->part_n), sizeof(uint32_t) * kMaxStreamParts, s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&place), sizeof(uint32_t) * n_sb, s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&start), sizeof(int64_t) * (N + 1), s);
-    if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&d_plan), sizeof(LossPlan), s);
+    ix->bytes = static_cast<int64_t>(sizeof(uint64_t)) * n_words +
+                static_cast<int64_t>(sizeof(uint32_t)) * (static_cast<int64_t>(kSlots) * most_parts + kMaxStreamParts);
+    hipError_t e = dev_alloc(reinterpret_cast<void**>(&ix->probe), static_cast<size_t>(ix->bytes), s);
+    if (e == hipSuccess)
+        e = dev_alloc(reinterpret_cast<void**>(&d_rows),
+                      sizeof(LossRows) + sizeof(int64_t) * N + sizeof(LossPlan) + sizeof(uint32_t) * n_sb, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(loss_bits_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(256), 0, s, sp, n_rows, C,
+        static_assert(offsetof(LossPlan, kept) == 0, "the scan's total after the starts");
+        ix->events = reinterpret_cast<uint32_t*>(ix->probe + n_words);
+        ix->part_n = ix->events + static_cast<int64_t>(kSlots) * most_parts;
+        start = reinterpret_cast<int64_t*>(d_rows + 1);
+        LossPlan* d_plan = reinterpret_cast<LossPlan*>(start + N);
+        place = reinterpret_cast<uint32_t*>(d_plan + 1);
+        hipLaunchKernelGGL(loss_bits_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(1024), 0, s, sp, n_rows, C,
                            ix->probe, place);
-        hipLaunchKernelGGL(loss_plan_kernel, dim3(1), dim3(64), 0, s, n_sb, most_parts, place, ix->part_n, d_plan);
+        hipLaunchKernelGGL(loss_plan_kernel, dim3(1), dim3(64), 0, s, n_sb, most_parts, place, ix->part_n, d_plan,
+                           &d_rows->res);
         hipLaunchKernelGGL(loss_place_kernel, dim3(static_cast<uint32_t>(n_sb)), dim3(64), 0, s, C, most_parts, place,
                            ix->probe, ix->events);
-        hipLaunchKernelGGL((long_trials ? loss_filter_kernel<false, 16> : loss_filter_kernel<false, 4>), g, b, 0, s,
-                           offsets, ids, N, ix->probe, n_words, shift, start, kept_ids, 0, cnt);
+        filter(std::false_type{}, 0);
         e = hipGetLastError();
+        if (e == hipSuccess) e = launch_scan_i64(start, N, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&plan, d_plan, sizeof(plan), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
-    if (e == hipSuccess) e = launch_scan_i64(start, N, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&d_plan->kept, start + N, sizeof(int64_t), hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&plan, d_plan, sizeof(plan), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
 
     // Not used without a kept event, past the parts a copy can have, where trials are so
     // short that most of the copy would be padding (a row takes 8 bytes of each trial),
@@ -927,33 +978,24 @@ hipError_t build_losses(const SparsePool& sp, int n_rows, int64_t C, const int64
         12 * kept + 16 * N * P + most <= static_cast<int64_t>(mem_free / 4)) {
         e = dev_alloc(reinterpret_cast<void**>(&kept_ids), sizeof(uint32_t) * (kept + kIdPad), s);
         if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&cnt), sizeof(int32_t) * N * P, s);
-        if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&d_res), sizeof(CreateResult), s);
-        if (e == hipSuccess) e = hipMemsetAsync(d_res, 0, sizeof(CreateResult), s);
         if (e == hipSuccess) {
-            hipLaunchKernelGGL((long_trials ? loss_filter_kernel<true, 16> : loss_filter_kernel<true, 4>), g, b, 0, s,
-                               offsets, ids, N, ix->probe, n_words, shift, start, kept_ids, P, cnt);
+            filter(std::true_type{}, P);
             e = hipGetLastError();
         }
         // a part's slots as 2^16 catalogue events
         if (e == hipSuccess)
-            e = plan_stream_layout(cnt, N, kept, static_cast<int64_t>(P) << kStreamShift, d_res, s, &by_part);
-        if (e == hipSuccess) e = hipMemcpyAsync(&res, d_res, sizeof(res), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e == hipSuccess) e = fill_stream_layout(start, kept_ids, N, kept, res, d_res, s, &by_part);
-        if (e == hipSuccess && by_part.P > 0) e = build_rows(by_part, N, kept, most, n_cu, s, out);
-        (void)hipStreamSynchronize(s);
+            e = plan_stream_layout(cnt, N, kept, static_cast<int64_t>(P) << kStreamShift, &d_rows->res, s, &by_part);
+        if (e == hipSuccess) e = fill_stream_layout_unread(start, kept_ids, N, kept, &d_rows->res, s, &by_part);
+        if (e == hipSuccess && by_part.P > 0) e = build_rows(by_part, N, kept, most, n_cu, d_rows, s, out);
     }
     dev_drop(by_part.ids, s);
     by_part.ids = nullptr;
     free_stream_layout(&by_part, s);
     dev_drop(kept_ids, s);
-    for (void* p : {static_cast<void*>(place), static_cast<void*>(start), static_cast<void*>(cnt),
-                    static_cast<void*>(d_res), static_cast<void*>(d_plan)})
-        if (p) dev_free(p, s);
+    dev_free(cnt, s);
+    dev_free(d_rows, s);
     ix->P = P;
     ix->n_events = plan.events;
-    ix->bytes = static_cast<int64_t>(sizeof(uint64_t)) * n_words +
-                static_cast<int64_t>(sizeof(uint32_t)) * (static_cast<int64_t>(kSlots) * most_parts + kMaxStreamParts);
     if (e != hipSuccess || out->P == 0) {
         free_stream_layout(out, s);
         free_loss_index(ix, s);

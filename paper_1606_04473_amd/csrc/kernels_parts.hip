@@ -65,6 +65,18 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 // create-time layout
 // ---------------------------------------------------------------------------
 
+// what creating tables starts from zero: the IDs' padding, the results and the counts,
+// in one launch
+__global__ __launch_bounds__(256) void create_clear_kernel(uint32_t* __restrict__ pad, CreateResult* __restrict__ res,
+                                                           u32x4* __restrict__ cnt, int64_t n16) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < n16; i += stride) cnt[i] = u32x4{0, 0, 0, 0};
+    for (int64_t i = first; i < kIdPad; i += stride) pad[i] = 0;
+    for (int64_t i = first; i < static_cast<int64_t>(sizeof(CreateResult) / 4); i += stride)
+        reinterpret_cast<uint32_t*>(res)[i] = 0;
+}
+
 // smallest t in [lo, hi] with offsets[t] >= target, given offsets[hi] >=
 // target; a 64-way search, all arguments uniform over the wave
 __device__ int64_t first_trial_at(const int64_t* __restrict__ offsets, int64_t lo, int64_t hi, int64_t target,
@@ -789,11 +801,21 @@ __global__ __launch_bounds__(1024) void sparse_scan_kernel(int64_t* __restrict__
     for (int64_t c0 = first; c0 < last; c0 += kScanChunk) {
         const int64_t i0 = c0 + static_cast<int64_t>(threadIdx.x) * kPer;
         int64_t x[kPer], own = 0;
+        // two entries a load, as the arrays start on 16 bytes (10000 entries 13 -> 7.6 us)
+        const bool whole = i0 + kPer <= n;
+        if (whole) {
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            x[k] = i0 + k < n ? v[i0 + k] : 0;
-            own += x[k];
+            for (int k = 0; k < kPer / 2; ++k) {
+                const u64x2 two = reinterpret_cast<const u64x2*>(v + i0)[k];
+                x[2 * k] = static_cast<int64_t>(two.x);
+                x[2 * k + 1] = static_cast<int64_t>(two.y);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) x[k] = i0 + k < n ? v[i0 + k] : 0;
         }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) own += x[k];
         int64_t inc = own;                          // inclusive over the wave
         for (int off = 1; off < 64; off <<= 1) {
             const int64_t add = __shfl_up(inc, off, 64);
@@ -807,9 +829,15 @@ __global__ __launch_bounds__(1024) void sparse_scan_kernel(int64_t* __restrict__
             carry += wsum[w];
         }
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            if (i0 + k < n) v[i0 + k] = at;
-            at += x[k];
+        for (int k = 0; k < kPer; k += 2) {
+            const u64x2 two{static_cast<uint64_t>(at), static_cast<uint64_t>(at + x[k])};
+            if (whole) {
+                *reinterpret_cast<u64x2*>(v + i0 + k) = two;
+            } else {
+                if (i0 + k < n) v[i0 + k] = static_cast<int64_t>(two.x);
+                if (i0 + k + 1 < n) v[i0 + k + 1] = static_cast<int64_t>(two.y);
+            }
+            at += x[k] + x[k + 1];
         }
         __syncthreads();
     }
@@ -1731,8 +1759,8 @@ hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipS
         return e;
     out->nnz = nnz;
     const int64_t cap = nnz > 0 ? nnz : 1;
-    if ((e = hipMalloc(&out->ev, sizeof(uint16_t) * cap)) != hipSuccess) return e;
-    if ((e = hipMalloc(&out->val, sizeof(double) * cap)) != hipSuccess) return e;
+    if ((e = hipMalloc(&out->val, (sizeof(double) + sizeof(uint16_t)) * cap)) != hipSuccess) return e;
+    out->ev = reinterpret_cast<uint16_t*>(out->val + cap);
     out->bytes += static_cast<int64_t>(sizeof(uint16_t) + sizeof(double)) * cap;
     hipLaunchKernelGGL(sparse_fill_kernel, grid, dim3(256), 0, s, elts, C, n_chunks, out->chunk_off, out->ev,
                        out->val);
@@ -1740,7 +1768,6 @@ hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipS
 }
 
 void free_sparse_pool(SparsePool* sp) {
-    if (sp->ev) (void)hipFree(sp->ev);
     if (sp->val) (void)hipFree(sp->val);
     if (sp->chunk_off) (void)hipFree(sp->chunk_off);
     *sp = SparsePool{};
@@ -1748,14 +1775,23 @@ void free_sparse_pool(SparsePool* sp) {
 int64_t part_size() { return kPartSize; }
 int part_tile_trials() { return kTileMax; }
 
+hipError_t launch_create_clear(uint32_t* pad, CreateResult* res, int32_t* cnt, int64_t n_cnt, int n_cu, hipStream_t s) {
+    const int64_t n16 = (n_cnt + 3) / 4;            // the cache's blocks are whole multiples of 16 bytes
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n16 + 1023) / 1024, int64_t(n_cu) * 8));
+    hipLaunchKernelGGL(create_clear_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, pad, res,
+                       reinterpret_cast<u32x4*>(cnt), n16);
+    return hipGetLastError();
+}
+
 hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* src, uint32_t* ids, int64_t n_events,
                             int64_t C, int shift, int bins, int32_t* cnt, CreateResult* res, int n_cu, hipStream_t s) {
     if (n_events <= 0) return hipSuccess;
     if (bins < 0 || bins > 64) return hipErrorInvalidValue;
     const bool copy = src != ids;
     if (reinterpret_cast<uintptr_t>(src) % 16 || reinterpret_cast<uintptr_t>(ids) % 16) return hipErrorInvalidValue;
-    // 32 waves per CU, at least four loads of 1024 IDs each
-    int64_t waves = (n_events + 4095) / 4096;
+    // 32 waves per CU, at least a row of 256 IDs each (16 rows: 10000 trials of 30 events
+    // 107 -> 14 us, of 100 40 -> 11: a wave's time goes by its trials)
+    int64_t waves = (n_events + 255) / 256;
     waves = std::min(waves, int64_t(n_cu) * 32);
     const dim3 g(static_cast<uint32_t>((waves + 3) / 4)), b(256);
     const uint32_t c32 = static_cast<uint32_t>(std::min<int64_t>(C, 0xFFFFFFFFll));

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kScatterThreads) void stream_scatter_kernel(
     const int lane = threadIdx.x & 63;
     const int units = (G + per - 1) / per;
     const int64_t of_launch = scatter_unit_index(n_units);
-    if (of_launch >= n_units) return;
+    if (of_launch >= n_units || (res->flags & (kCreateWideGroup | kCreateWidePart))) return;   // no ends to go by
     const int64_t unit = first_unit + of_launch;
     const int64_t g = unit / units;
     const int i0 = static_cast<int>(unit - g * units) * per;
@@ -1174,15 +1174,10 @@ hipError_t plan_stream_layout(const int32_t* cnt, int64_t N, int64_t n_events, i
     return hipSuccess;
 }
 
-hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
-                              const CreateResult& res, const CreateResult* d_res, hipStream_t s, StreamLayout* out) {
-    if (out->P == 0) return hipSuccess;
-    if (res.flags & (kCreateWideGroup | kCreateWidePart)) {     // too large for 16/32-bit offsets: not used
-        free_stream_layout(out, s);
-        return hipSuccess;
-    }
-    int64_t length = 0;
-    for (int q = 0; q < out->P; ++q) length += res.stream_ids[q];
+namespace {
+// the scatter into a copy of `length` IDs (or of room for as many)
+hipError_t scatter_stream(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events, int64_t length,
+                          const CreateResult* d_res, hipStream_t s, StreamLayout* out) {
     hipError_t e = dev_alloc(reinterpret_cast<void**>(&out->ids), sizeof(uint16_t) * (length + kStreamPad), s);
     if (e == hipSuccess) {
         // units of even size within a group, each part's run up to 14 IDs from whole chunks
@@ -1199,16 +1194,35 @@ hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64
                                d_res, out->part_base, out->gstart, out->gend, out->ids);
         });
     }
-    if (e != hipSuccess) {
+    if (e != hipSuccess) free_stream_layout(out, s);
+    return e;
+}
+}  // namespace
+
+hipError_t fill_stream_layout(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                              const CreateResult& res, const CreateResult* d_res, hipStream_t s, StreamLayout* out) {
+    if (out->P == 0) return hipSuccess;
+    if (res.flags & (kCreateWideGroup | kCreateWidePart)) {     // too large for 16/32-bit offsets: not used
         free_stream_layout(out, s);
-        return e;
+        return hipSuccess;
     }
+    int64_t length = 0;
+    for (int q = 0; q < out->P; ++q) length += res.stream_ids[q];
+    const hipError_t e = scatter_stream(offsets, ids, N, n_events, length, d_res, s, out);
+    if (e != hipSuccess) return e;
     out->length = length;
     out->bytes = static_cast<int64_t>(sizeof(uint16_t)) * (length + kStreamPad) +
                  static_cast<int64_t>(sizeof(uint16_t)) * out->P * out->NG * kStreamGroupSlots +
                  static_cast<int64_t>(sizeof(uint32_t)) * out->P * (out->NG + 1) +
                  static_cast<int64_t>(sizeof(int64_t)) * (out->P + 1);
     return hipSuccess;
+}
+
+hipError_t fill_stream_layout_unread(const int64_t* offsets, const uint32_t* ids, int64_t N, int64_t n_events,
+                                     const CreateResult* d_res, hipStream_t s, StreamLayout* out) {
+    if (out->P == 0) return hipSuccess;
+    // every group of a part starts on a whole chunk
+    return scatter_stream(offsets, ids, N, n_events, n_events + (kChunkIds - 1) * out->P * out->NG, d_res, s, out);
 }
 
 void free_stream_layout(StreamLayout* L, hipStream_t s) {
