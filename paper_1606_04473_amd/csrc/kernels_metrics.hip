@@ -454,11 +454,21 @@ __device__ __forceinline__ void write_bad(int n_probs, const MetricsOut& out, Ta
 
 // A workgroup's part of the first launch: its sum and largest key, and its share
 // of the histogram and the counts cleared for the next ones, so the scratch may
-// hold anything before a call (a launch of its own for the counts took 4.5 us).
-__device__ __forceinline__ void store_partials(ReduceLds& sh, const Scratch& s, double hi, double lo, uint64_t mx) {
+// hold anything before a call (a launch of its own for the counts took 4.5 us).  A
+// workgroup with an infinite value reads its values (x, strided by the grid) again for
+// the largest finite one.
+__device__ __forceinline__ void store_partials(ReduceLds& sh, const Scratch& s, double hi, double lo, uint64_t mx,
+                                               const double* x, int64_t n) {
     double h[1] = {hi}, l[1] = {lo};
     block_sums(sh, h, l, 1);
     mx = block_max(sh, mx);
+    if (mx == kInfKey) {
+        mx = 0;
+        const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+        for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n; i += stride)
+            mx = max_finite(mx, key_of(x[i]));
+        mx = block_max(sh, mx);
+    }
     if (threadIdx.x == 0) {
         s.part_hi[blockIdx.x] = h[0];
         s.part_lo[blockIdx.x] = l[0];
@@ -488,9 +498,9 @@ __global__ __launch_bounds__(kThreads) void combine_sum_max_kernel(const double*
         ylt[k] = y;
         bad |= !(y >= 0.0);
         dd_add(sum_hi, sum_lo, y);
-        mx = max_finite(mx, key_of(y));
+        mx = max_u64(mx, key_of(y));
     }
-    store_partials(sh, s, sum_hi, sum_lo, bad ? kBadKey : mx);
+    store_partials(sh, s, sum_hi, sum_lo, bad ? kBadKey : mx, ylt, n);
 }
 
 // launch 1: sums and largest keys
@@ -508,10 +518,10 @@ __global__ __launch_bounds__(kThreads) void sum_max_kernel(const double* __restr
         for (int u = 0; u < kPer; ++u) {
             bad |= !(v[u] >= 0.0);
             dd_add(hi, lo, v[u]);
-            mx = max_finite(mx, key_of(v[u]));
+            mx = max_u64(mx, key_of(v[u]));
         }
     }
-    store_partials(sh, s, hi, lo, bad ? kBadKey : mx);
+    store_partials(sh, s, hi, lo, bad ? kBadKey : mx, x, n);
 }
 
 // the largest key over the first launch's workgroups
