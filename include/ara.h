@@ -78,12 +78,16 @@ typedef int32_t ara_status;
                                        output pointer, the copy the layers are estimated faster
                                        over; with pass_variant 1 also the ELT counts) --
                                        the launches of pass_variant 0 or 2, or with pass_variant 1
-                                       and several layers the batched launch.  Terms and ELT choices may change
-                                       between replays (they are copied to the device only when
-                                       they differ from the last replay's, so repeated replays
-                                       queue without host waits).  Requires a
-                                       device output and a non-null stream (ARA_ERR_INVALID_ARG
-                                       otherwise). */
+                                       and several layers the batched launch.  Terms and ELT choices
+                                       may change between replays (they are copied to the device
+                                       only when they differ from the last replay's, so repeated
+                                       replays queue without host waits).  A graph keeps its device
+                                       memory (what the folds write and the passes' partial sums;
+                                       for several layers with pass_variant 0 up to 384 MiB, or
+                                       what the largest one needs) until the tables are destroyed
+                                       or it is the oldest of eight and another is captured.
+                                       Requires a device output and a non-null stream
+                                       (ARA_ERR_INVALID_ARG otherwise). */
 #define ARA_PROFILE      (1u << 5)  /* ara_run_layers: bracket each kernel with HIP events on the
                                        call's stream; read the totals with ara_kernel_stats */
 

@@ -687,6 +687,10 @@ struct SplitPass {
                                            static_cast<double*>(part_scratch), s);
         return ara::launch_fold_parts(t->sparse, t->C, L, L_dev, nullptr, t->parts.P, part_scratch, !stream, probe, s);
     }
+    // fold's outputs
+    int64_t fold_bytes() const {
+        return losses ? ara::loss_table_bytes(t->loss_index) : ara::part_scratch_bytes(t->C, t->parts.P, !stream);
+    }
     size_t partial_bytes(int64_t trials) const {
         const int64_t n = trials > 0 ? trials : 1;
         return stream ? static_cast<size_t>(ara::stream_partials_bytes(lay(), n))
@@ -1225,7 +1229,7 @@ ara_status ara_footprint(const ara_tables* t, const ara_layer* layers, int32_t n
         int64_t need = 0;
         for (const bool by_losses : {false, true}) {                   // whichever copy the call streams
             const SplitPass split(t, tu, by_losses);
-            need = std::max(need, ara::part_scratch_bytes(t->C, t->parts.P) +
+            need = std::max(need, ara::part_scratch_bytes(t->C, t->parts.P, true) +
                                       static_cast<int64_t>(split.partial_bytes(most)));
             if (split.stream && n_layers > 1 && !(flags & (ARA_CHECKPOINT_S | ARA_CHECKPOINT_STRIDE))) {
                 std::vector<ara::StreamUnit> units;
@@ -1341,11 +1345,12 @@ static ara_status run_layers(ara_tables* t, const ara_layer* layers, int32_t n_l
         for (int i = 0; i < n_layers; ++i)
             units.push_back({i, L[i].trial_begin, L[i].trial_count, L[i].out_offset, layer_density(t, L[i])});
     const StreamBatches joint(split, units);
-    // one kept scratch buffer for the per-layer path: occurrence losses, part
-    // images, partial sums (the batched path and graphs keep their own)
+    // one kept scratch buffer for the per-layer path: what the fold leaves for the
+    // pass, partial sums (the batched path and graphs keep their own)
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
-    const size_t o_bytes = literal ? 0 : up(sizeof(double) * t->C);
-    const size_t p_bytes = use_parts ? up(static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P))) : 0;
+    const size_t o_bytes = literal || use_parts ? 0 : up(sizeof(double) * t->C);
+    const size_t p_bytes = !use_parts ? 0 : up(static_cast<size_t>(
+        use_xcd ? split.fold_bytes() : ara::part_scratch_bytes(t->C, t->parts.P, true)));
     size_t x_bytes = 0;
     if (use_xcd) {
         int64_t most = 0;
@@ -1430,7 +1435,7 @@ static ara_status run_layers(ara_tables* t, const ara_layer* layers, int32_t n_l
             joined = joined && e == hipSuccess;     // no memory for batches: layer by layer
             if (!joined) {
                 if (n_layers > 1) (void)hipGetLastError();
-                e = hipMalloc(&ge->scratch, la_bytes + o_bytes + p_bytes + xg_bytes);
+                e = hipMalloc(&ge->scratch, la_bytes + p_bytes + xg_bytes);
             }
             if (e != hipSuccess) {
                 free_graph(ge);
@@ -1438,9 +1443,8 @@ static ara_status run_layers(ara_tables* t, const ara_layer* layers, int32_t n_l
             }
             char* gb = static_cast<char*>(ge->scratch);
             const ara::LayerArgs* dL = reinterpret_cast<const ara::LayerArgs*>(gb);
-            double* go = reinterpret_cast<double*>(gb + la_bytes);
-            void* gp = gb + la_bytes + o_bytes;
-            void* gx = gb + la_bytes + o_bytes + p_bytes;
+            void* gp = gb + la_bytes;
+            void* gx = gb + la_bytes + p_bytes;
             if ((e = upload(ge)) != hipSuccess || (e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal)) !=
                                                       hipSuccess) {
                 free_graph(ge);
@@ -1670,11 +1674,12 @@ static ara_status run_portfolio(ara_tables* t, const ara_program* programs, int3
     auto split_at = [&](int64_t i) { return begin + (n * i) / splits; };
     int64_t most = 0;
     for (int64_t i = 0; i < splits; ++i) most = std::max(most, split_at(i + 1) - split_at(i));
-    // one kept scratch buffer: occurrence losses, part images, partial sums of
+    // one kept scratch buffer: what the fold leaves for the passes, partial sums of
     // the largest split, and whatever output the caller keeps on the host
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
-    const size_t o_bytes = literal ? 0 : up(sizeof(double) * t->C);
-    const size_t p_bytes = use_parts ? up(static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P))) : 0;
+    const size_t o_bytes = literal || use_parts ? 0 : up(sizeof(double) * t->C);
+    const size_t p_bytes = !use_parts ? 0 : up(static_cast<size_t>(
+        use_xcd ? split.fold_bytes() : ara::part_scratch_bytes(t->C, t->parts.P, true)));
     // over the streaming pass the layers and splits share launches
     bool joined = use_xcd && split.stream;
     std::vector<ara::StreamUnit> units;
@@ -1905,8 +1910,7 @@ static ara_status analyze(ara_tables* t, const ara_layer* layer, const double* p
     const SplitPass split(t, tu, by_losses && losses_faster(t, &L, 1));
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     const size_t la_bytes = up(sizeof(ara::LayerArgs));
-    const size_t o_bytes = up(sizeof(double) * t->C);
-    const size_t p_bytes = up(static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P)));
+    const size_t p_bytes = up(static_cast<size_t>(split.fold_bytes()));
     const size_t xg_bytes = up(split.partial_bytes(L.trial_count));
     const size_t m_bytes = up(static_cast<size_t>(ara::metrics_scratch_bytes(n_probs, L.trial_count)));
     // what the graph bakes in: the outputs, the trial range, the pass with its copy and the tail counts
@@ -1922,17 +1926,16 @@ static ara_status analyze(ara_tables* t, const ara_layer* layer, const double* p
     if (!ge) {
         ge = new ara::GraphEntry();
         ge->key = key;
-        hipError_t e = hipMalloc(&ge->scratch, la_bytes + o_bytes + p_bytes + xg_bytes + m_bytes);
+        hipError_t e = hipMalloc(&ge->scratch, la_bytes + p_bytes + xg_bytes + m_bytes);
         if (e != hipSuccess) {
             free_graph(ge);
             return hip_fail(e, "graph scratch");
         }
         char* gb = static_cast<char*>(ge->scratch);
         const ara::LayerArgs* dL = reinterpret_cast<const ara::LayerArgs*>(gb);
-        double* go = reinterpret_cast<double*>(gb + la_bytes);
-        void* gp = gb + la_bytes + o_bytes;
-        void* gx = gb + la_bytes + o_bytes + p_bytes;
-        void* gm = gb + la_bytes + o_bytes + p_bytes + xg_bytes;
+        void* gp = gb + la_bytes;
+        void* gx = gb + la_bytes + p_bytes;
+        void* gm = gb + la_bytes + p_bytes + xg_bytes;
         if ((e = upload(ge)) != hipSuccess ||
             (e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
             free_graph(ge);
@@ -2043,7 +2046,7 @@ static ara_status backward(ara_tables* t, const ara_layer* layer, double tvar_p,
         if (use_losses)                 // that copy's histogram needs no images
             HIP_TRY(pbuf.alloc(ara::loss_adjoint_bytes(t->loss_index, t->n_cu), s), "scratch for counts");
         else
-            HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P), s), "scratch for part images");
+            HIP_TRY(pbuf.alloc(ara::part_scratch_bytes(t->C, t->parts.P, !use_stream), s), "scratch for part images");
         if (!t->sparse.chunk_off) {
             HIP_TRY(obuf.alloc(sizeof(double) * t->C, s), "scratch for occurrence losses");
             HIP_TRY(ara::launch_fold(t->elts, t->C, L, static_cast<double*>(obuf.p), tu, s), "fold");
@@ -2144,7 +2147,7 @@ ara_status ara_debug_read(ara_tables* t, const ara_layer* layer, int32_t what, v
         ara_status st = build_layer_args(t, probe, L);
         if (st != ARA_OK) return st;
         const size_t o_bytes = (sizeof(double) * t->C + 255) & ~size_t(255);
-        const size_t p_bytes = static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P));
+        const size_t p_bytes = static_cast<size_t>(ara::part_scratch_bytes(t->C, t->parts.P, true));
         HIP_TRY(buf.alloc(o_bytes + p_bytes, s), "scratch for the fold");
         double* o = static_cast<double*>(buf.p);
         void* pbuf = static_cast<char*>(buf.p) + o_bytes;
@@ -2212,21 +2215,20 @@ ara_status ara_event_nets(ara_tables* t, const ara_layer* layer, double* nets, i
     // words, staged output
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
     const int P = ara::part_count(t->C);
-    const size_t o_bytes = up(sizeof(double) * t->C);
-    const size_t p_bytes = up(static_cast<size_t>(ara::part_scratch_bytes(t->C, P)));
+    const size_t p_bytes = up(static_cast<size_t>(ara::part_scratch_bytes(t->C, P, false)));
     const size_t w_bytes = up(static_cast<size_t>(ara::probe_table_bytes(t->C)));
     const size_t n_bytes = dev ? 0 : up(sizeof(double) * n);
     ScratchLease lease(t->scratch_mu);
     lease.s = s;
-    HIP_TRY(scratch_acquire(t->scratch_mu, t->scratch, o_bytes + p_bytes + w_bytes + n_bytes + 256, s, &lease.b),
-            "scratch for occurrence losses, part images, probe words and net losses");
+    HIP_TRY(scratch_acquire(t->scratch_mu, t->scratch, p_bytes + w_bytes + n_bytes + 256, s, &lease.b),
+            "scratch for part images, probe words and net losses");
     use_fence.hand_over();
     char* base = static_cast<char*>(lease.b->p);
-    uint64_t* probe = reinterpret_cast<uint64_t*>(base + o_bytes + p_bytes);
-    double* out = dev ? nets : reinterpret_cast<double*>(base + o_bytes + p_bytes + w_bytes);
-    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base + o_bytes, false, probe, s),
+    uint64_t* probe = reinterpret_cast<uint64_t*>(base + p_bytes);
+    double* out = dev ? nets : reinterpret_cast<double*>(base + p_bytes + w_bytes);
+    HIP_TRY(ara::launch_fold_parts(t->sparse, t->C, L, nullptr, nullptr, P, base, false, probe, s),
             "fold and part images");
-    HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base + o_bytes, P, t->C, probe, layer_density(t, L),
+    HIP_TRY(ara::launch_event_nets(t->offsets, t->ids, base, P, t->C, probe, layer_density(t, L),
                                    static_cast<double>(n), L, out, t->n_cu, s),
             "net-loss kernel");
     if (!dev) {

@@ -596,7 +596,8 @@ hipError_t fill_part_layout(const int64_t* offsets, const uint32_t* ids, int64_t
                             const CreateResult& res, hipStream_t s, PartLayout* out);
 // frees in stream order on s (the layout's memory comes from dev_alloc)
 void free_part_layout(PartLayout* L, hipStream_t s);
-int64_t part_scratch_bytes(int64_t C, int P);
+// what launch_fold_parts writes for a layer, with the compact array or without
+int64_t part_scratch_bytes(int64_t C, int P, bool compact);
 int part_count(int64_t C);   // catalogue parts of the part images
 hipError_t launch_part_fold(const double* o, int64_t C, int P, void* scratch, hipStream_t s, bool with_ranks);
 // the fold fused with the part images and the superblocks' packed values; with

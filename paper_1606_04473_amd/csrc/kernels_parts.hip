@@ -1772,8 +1772,6 @@ void free_sparse_pool(SparsePool* sp) {
     if (sp->chunk_off) (void)hipFree(sp->chunk_off);
     *sp = SparsePool{};
 }
-int64_t part_size() { return kPartSize; }
-int part_tile_trials() { return kTileMax; }
 
 hipError_t launch_create_clear(uint32_t* pad, CreateResult* res, int32_t* cnt, int64_t n_cnt, int n_cu, hipStream_t s) {
     const int64_t n16 = (n_cnt + 3) / 4;            // the cache's blocks are whole multiples of 16 bytes
@@ -1878,9 +1876,10 @@ void free_part_layout(PartLayout* L, hipStream_t s) {
     *L = PartLayout{};
 }
 
-int64_t part_scratch_bytes(int64_t C, int P) {
+int64_t part_scratch_bytes(int64_t C, int P, bool compact) {
     const int64_t n_sb = static_cast<int64_t>(P) * kBase32;
-    return part_image_bytes(P) + sizeof(uint32_t) * n_sb + sizeof(double) * C + sizeof(double) * n_sb * kSuper + 256;
+    return part_image_bytes(P) + sizeof(uint32_t) * n_sb + (compact ? sizeof(double) * C : 0) +
+           sizeof(double) * n_sb * kSuper + 256;
 }
 
 namespace {
