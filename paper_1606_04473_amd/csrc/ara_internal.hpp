@@ -185,6 +185,7 @@ struct SparsePool {
     int64_t n_chunks = 0;
     int64_t nnz = 0;
     int64_t bytes = 0;
+    bool joint = false;             // ev lies in val's block
 };
 hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipStream_t s, SparsePool* out);
 void free_sparse_pool(SparsePool* sp);

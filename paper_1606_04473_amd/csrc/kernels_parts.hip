@@ -223,6 +223,38 @@ __global__ __launch_bounds__(256) void yet_count_kernel(const int64_t* __restric
     if (bad) atomicOr(flags, kCreateBadId);
 }
 
+// The counts of tables whose trials are short (fewer than 16 events on average), a
+// thread per trial, after a pass above has copied and checked the IDs: there the flush
+// at each trial's end is what takes the time (200000 trials of 2 events: 102 us there,
+// 8 in both).  A workgroup's counters lie in LDS (dynamic, [256][bins | 1]); a wave
+// counts a trial past 64 events together.
+constexpr int kShortTrial = 16;
+__global__ __launch_bounds__(256) void short_count_kernel(const int64_t* __restrict__ offsets, int64_t N,
+                                                          const uint32_t* __restrict__ ids, int shift, int bins,
+                                                          int32_t* __restrict__ cnt, const uint32_t* __restrict__ flags) {
+    extern __shared__ int32_t own[];
+    if (*flags & kCreateBadOffsets) return;         // the trials' ranges can't be trusted
+    const int row = bins | 1;                       // odd: the threads' rows in different banks
+    for (int i = threadIdx.x; i < 256 * row; i += 256) own[i] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const uint32_t last_bin = static_cast<uint32_t>(bins - 1);
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 256, t = t0 + threadIdx.x;
+    const int64_t b = t < N ? offsets[t] : 0, e = t < N ? offsets[t + 1] : 0;
+    if (e - b <= 64)
+        for (int64_t i = b; i < e; ++i) own[threadIdx.x * row + min(ids[i] >> shift, last_bin)] += 1;
+    for (uint64_t many = __ballot(e - b > 64); many; many &= many - 1) {
+        const int l = __builtin_ctzll(many);
+        const int64_t lb = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(b), l));
+        const int64_t le = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(e), l));
+        int32_t* of = own + ((threadIdx.x & ~63u) + l) * row;
+        for (int64_t i = lb + lane; i < le; i += 64) atomicAdd(of + min(ids[i] >> shift, last_bin), 1);
+    }
+    __syncthreads();
+    const int n = static_cast<int>(N - t0 < 256 ? N - t0 : 256) * bins;
+    for (int i = threadIdx.x; i < n; i += 256) cnt[t0 * bins + i] = own[i / bins * row + i % bins];
+}
+
 // Per tile: layout-order exclusive scan of the padded segment sizes, from counts
 // in `bins` parts, 2^fine of them to a part here.  The tile's counts, one
 // contiguous piece of cnt, are summed per (part, trial) in LDS (dynamic, [P][Tk])
@@ -1759,8 +1791,12 @@ hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipS
         return e;
     out->nnz = nnz;
     const int64_t cap = nnz > 0 ? nnz : 1;
-    if ((e = hipMalloc(&out->val, (sizeof(double) + sizeof(uint16_t)) * cap)) != hipSuccess) return e;
-    out->ev = reinterpret_cast<uint16_t*>(out->val + cap);
+    // one block where it stays below the 2 MB from which the runtime's free takes 300 us
+    const size_t both = (sizeof(double) + sizeof(uint16_t)) * cap;
+    out->joint = both < (size_t(2) << 20);
+    if ((e = hipMalloc(&out->val, out->joint ? both : sizeof(double) * cap)) != hipSuccess) return e;
+    if (out->joint) out->ev = reinterpret_cast<uint16_t*>(out->val + cap);
+    else if ((e = hipMalloc(&out->ev, sizeof(uint16_t) * cap)) != hipSuccess) return e;
     out->bytes += static_cast<int64_t>(sizeof(uint16_t) + sizeof(double)) * cap;
     hipLaunchKernelGGL(sparse_fill_kernel, grid, dim3(256), 0, s, elts, C, n_chunks, out->chunk_off, out->ev,
                        out->val);
@@ -1768,6 +1804,7 @@ hipError_t build_sparse_pool(const double* elts, int32_t n_rows, int64_t C, hipS
 }
 
 void free_sparse_pool(SparsePool* sp) {
+    if (sp->ev && !sp->joint) (void)hipFree(sp->ev);
     if (sp->val) (void)hipFree(sp->val);
     if (sp->chunk_off) (void)hipFree(sp->chunk_off);
     *sp = SparsePool{};
@@ -1787,18 +1824,19 @@ hipError_t launch_yet_count(const int64_t* offsets, int64_t N, const uint32_t* s
     if (bins < 0 || bins > 64) return hipErrorInvalidValue;
     const bool copy = src != ids;
     if (reinterpret_cast<uintptr_t>(src) % 16 || reinterpret_cast<uintptr_t>(ids) % 16) return hipErrorInvalidValue;
+    const bool apart = bins > 0 && n_events / kShortTrial < N;         // short trials: counted afterwards
     // 32 waves per CU, at least a row of 256 IDs each (16 rows: 10000 trials of 30 events
     // 107 -> 14 us, of 100 40 -> 11: a wave's time goes by its trials)
     int64_t waves = (n_events + 255) / 256;
     waves = std::min(waves, int64_t(n_cu) * 32);
     const dim3 g(static_cast<uint32_t>((waves + 3) / 4)), b(256);
     const uint32_t c32 = static_cast<uint32_t>(std::min<int64_t>(C, 0xFFFFFFFFll));
-    if (copy)
-        hipLaunchKernelGGL(yet_count_kernel<true>, g, b, 0, s, offsets, N, src, ids, n_events, c32, shift, bins, cnt,
-                           &res->flags);
-    else
-        hipLaunchKernelGGL(yet_count_kernel<false>, g, b, 0, s, offsets, N, src, ids, n_events, c32, shift, bins, cnt,
-                           &res->flags);
+    hipLaunchKernelGGL((copy ? yet_count_kernel<true> : yet_count_kernel<false>), g, b, 0, s, offsets, N, src, ids,
+                       n_events, c32, shift, apart ? 0 : bins, cnt, &res->flags);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !apart) return e;
+    hipLaunchKernelGGL(short_count_kernel, dim3(static_cast<uint32_t>((N + 255) / 256)), dim3(256),
+                       sizeof(int32_t) * 256 * (bins | 1), s, offsets, N, ids, shift, bins, cnt, &res->flags);
     return hipGetLastError();
 }
 
