@@ -727,7 +727,7 @@ struct SplitPass {
 // unit the three launches, the pass's start and end and its LDS images; the
 // partial sums of a batch can stay in the 256 MB last-level cache.  Measured, a
 // sequence per layer or split against batches: 12 layers of up to 250000 trials of an
-// event-loss library 1385 -> 1290 us, a portfolio of 9 layers in 4 splits
+// event-loss library 1385 -> 1290 us, a portfolio of 9 layers in 2 splits
 // (50000 trials) 720 -> 500 us.
 struct StreamBatches {
     static constexpr int64_t kBatchBytes = int64_t(384) << 20;
@@ -741,8 +741,6 @@ struct StreamBatches {
     int64_t scratch_bytes = 0;              // fold outputs and partial sums of the largest batch
 
     static int64_t up(int64_t n) { return (n + 255) & ~int64_t(255); }
-    // units in order of their layers; those of no trials are dropped, and
-    // neighbours that continue one layer's range and output are joined
     int64_t fold_bytes(int n_layers) const {
         return up(split.losses ? n_layers * ara::loss_table_bytes(split.t->loss_index)
                                : ara::fold_batch_bytes(n_layers, split.t->parts.P));
@@ -763,6 +761,8 @@ struct StreamBatches {
         }
         return lo;
     }
+    // units in order of their layers; those of no trials are dropped, and
+    // neighbours that continue one layer's range and output are joined
     StreamBatches(const SplitPass& sp, const std::vector<ara::StreamUnit>& in) : split(sp) {
         int64_t most = kBatchBytes;
         for (const auto& u : in) most = std::max(most, bytes_of(1, u.count));
